@@ -428,6 +428,125 @@ __global__ __launch_bounds__(KRON_THREADS) void kron_split_kernel(const void* __
     }
 }
 
+// Form for several tokens (n = 64 * R, R = 1 or 2): Z = X Q^T on the binary32 matrix instruction.  A workgroup owns
+// sixteen columns j' of Y for one token; its four wavefronts own four row tiles each and split the sum over j KS = 4 / R
+// ways.  v_mfma_f32_16x16x4_f32 adds exact binary32 products into binary32 sums, so nothing is lost against the vector
+// form; only the order of the sum over j differs.
+// What it saves is memory requests: kron_split_kernel reads the whole token with row-strided loads (64 cache lines per
+// instruction) once per column, i.e. m times per token; here sixteen columns share one pass over the token, and a lane
+// fetches four consecutive j for four matrix steps at once (k slot kb = lane / 16 of step s stands for j = 16 S + 4 kb + s
+// on both operands).  Bound by the latency of one round of loads and of the chain behind it, not by the matrix cores
+// (44 instructions per wavefront at m = 172).  Launch to launch, 64 x 172: 16 tokens fp16 10.8 -> 4.4 us, fp32
+// 23.0 -> 4.0 us; 4 tokens fp16 4.6 -> 4.2 us.  (Also tried with n = 512 and 1024: the binary32 matrix rate and the
+// transform of 32 or 64 rows per lane then weigh on few workgroups, 512 x 28 at 16 tokens 5.5 -> 8.4 us.)
+template <int DT, int R>
+__global__ __launch_bounds__(KRON_THREADS) void kron_mfma_kernel(const void* __restrict__ x, int m, const float* __restrict__ Q,
+                                                                 float norm, float* __restrict__ y)
+{
+    constexpr int KS = 4 / R;   // parts of the sum over j
+    constexpr int WT = 4;       // row tiles of sixteen per wavefront
+    constexpr int DEPTH = 3;    // groups of sixteen j in flight per wavefront
+    __shared__ float z[KS][64 * R * 16];
+    using XT = typename XStore<DT>::type;
+    const int token = blockIdx.y, j0 = blockIdx.x * 16;
+    const int lane = threadIdx.x & 63, i = lane & 15, kb = lane >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int ks = wave % KS, t0 = (wave / KS) * WT;
+    const int K = 64 * R * m, groups = (m + 15) / 16;
+    const XT* xr = static_cast<const XT*>(x) + static_cast<size_t>(token) * K + static_cast<size_t>(16 * t0 + i) * m;
+    const float* qr = Q + static_cast<size_t>(min(j0 + i, m - 1)) * m;  // columns past the end repeat the last one and are not stored
+
+    v4f acc[WT];
+#pragma unroll
+    for (int t = 0; t < WT; ++t) acc[t] = v4f{0.0f, 0.0f, 0.0f, 0.0f};
+    for (int S0 = ks; S0 < groups; S0 += DEPTH * KS) {
+        float4 q[DEPTH];
+        uint4 raw[DEPTH][WT];
+#pragma unroll
+        for (int d = 0; d < DEPTH; ++d) {  // all loads of the round first
+            const int j = 16 * (S0 + d * KS) + 4 * kb;
+            const bool have = j < m;  // m is a multiple of four: a piece is whole or absent
+            q[d] = have ? *reinterpret_cast<const float4*>(qr + j) : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+#pragma unroll
+            for (int t = 0; t < WT; ++t) {
+                raw[d][t] = make_uint4(0u, 0u, 0u, 0u);
+                if (have) {
+                    const XT* p = xr + static_cast<size_t>(16 * t) * m + j;
+                    if constexpr (sizeof(XT) == 4) raw[d][t] = *reinterpret_cast<const uint4*>(p);
+                    else {
+                        const uint2 two = *reinterpret_cast<const uint2*>(p);
+                        raw[d][t].x = two.x;
+                        raw[d][t].y = two.y;
+                    }
+                }
+            }
+        }
+#pragma unroll
+        for (int d = 0; d < DEPTH; ++d) {
+            const float qs[4] = {q[d].x, q[d].y, q[d].z, q[d].w};
+#pragma unroll
+            for (int s = 0; s < 4; ++s)
+#pragma unroll
+                for (int t = 0; t < WT; ++t) {
+                    float a;
+                    if constexpr (sizeof(XT) == 4) {
+                        const uint32_t w[4] = {raw[d][t].x, raw[d][t].y, raw[d][t].z, raw[d][t].w};
+                        a = __uint_as_float(w[s]);
+                    } else {
+                        const uint32_t w = s < 2 ? raw[d][t].x : raw[d][t].y;
+                        a = XStore<DT>::widen(static_cast<uint16_t>((s & 1) ? w >> 16 : w & 0xffffu));
+                    }
+                    acc[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(a, qs[s], acc[t], 0, 0, 0);
+                }
+        }
+    }
+    // acc[t][v] = Z[16 (t0 + t) + 4 kb + v][j0 + i].  The tile goes through LDS so that a lane ends up with 4 R
+    // consecutive rows of one column; groups of four rows are spread over the banks for both access patterns.
+    auto at = [](int row, int col) {
+        const int f = R == 1 ? (row >> 2) & 3 : ((row >> 2) ^ (row / (4 * R))) & 3;
+        const int g = (row / (16 * R)) & 3;
+        return (row * 16 + col) ^ (f << 4) ^ (g << 2);
+    };
+#pragma unroll
+    for (int t = 0; t < WT; ++t)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) z[ks][at(16 * (t0 + t) + 4 * kb + v, i)] = acc[t][v];
+    __syncthreads();
+    constexpr int E = 4 * R;
+    const int col = 4 * wave + (lane & 3), row0 = (lane >> 2) * E;
+    float c[E];
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+        const int w = at(row0 + e, col);
+        c[e] = z[0][w];
+#pragma unroll
+        for (int k = 1; k < KS; ++k) c[e] += z[k][w];
+    }
+    // Hadamard transform down the column in ascending stride order: inside the lane, then lanes 4, 8, 16, 32 apart
+#pragma unroll
+    for (int st = 1; st < E; st <<= 1)
+#pragma unroll
+        for (int e = 0; e < E; ++e)
+            if ((e & st) == 0) {
+                const float a = c[e], b = c[e + st];
+                c[e] = a + b;
+                c[e + st] = a - b;
+            }
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+        float v = c[e];
+        const float p4 = __shfl_xor(v, 4, 64);
+        v = (lane & 4) ? p4 - v : v + p4;
+        const float p8 = __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x128, 0xf, 0xf, false));  // lane ^ 8
+        v = (lane & 8) ? p8 - v : v + p8;
+        auto r16 = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+        v = (lane & 16) ? __uint_as_float(r16[0]) - __uint_as_float(r16[1]) : __uint_as_float(r16[0]) + __uint_as_float(r16[1]);
+        auto r32 = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+        v = (lane & 32) ? __uint_as_float(r32[0]) - __uint_as_float(r32[1]) : __uint_as_float(r32[0]) + __uint_as_float(r32[1]);
+        if (j0 + col < m) y[static_cast<size_t>(token) * K + static_cast<size_t>(row0 + e) * m + j0 + col] = v * norm;
+    }
+}
+
 template <int DT, int RPL>
 static int launch_kron_split(const void* x, int M, const rcp_rotation* rot, float* y, float norm, hipStream_t st)
 {
@@ -582,6 +701,16 @@ static int launch_kron(const void* x, int M, int K, const rcp_rotation* rot, flo
     const int n = rot->n_wht, m = rot->m;
     const float norm = static_cast<float>(1.0 / sqrt(static_cast<double>(n)));
     const size_t xbytes = static_cast<size_t>(K) * sizeof(typename XStore<DT>::type);
+    // sixteen columns per workgroup on the matrix cores once the row-strided requests of the one-column form add up
+    // (its workgroups together read the tokens m times: the two forms meet at 8 to 15 MB, sweeps over 64 x 160, 64 x 172,
+    // 64 x 256 and 128 x 88 at 1 to 16 tokens, 16- and 32-bit inputs).  One token keeps the order of the sum that the
+    // sequence kernel reproduces.
+    if (M > 1 && m % 4 == 0 && (n == 64 || n == 128) && static_cast<size_t>(M) * m * xbytes >= (12u << 20)) {
+        const dim3 grid((m + 15) / 16, M);
+        if (n == 64) kron_mfma_kernel<DT, 1><<<grid, KRON_THREADS, 0, st>>>(x, m, rot->Q, norm, y);
+        else kron_mfma_kernel<DT, 2><<<grid, KRON_THREADS, 0, st>>>(x, m, rot->Q, norm, y);
+        return check_launch("rcp_rotate_quant_act(kron)");
+    }
     // one workgroup per output column when a wavefront's share of the columns fits in registers:
     // (n/64) rows per lane x ceil(m/16) groups of four columns <= KRON_SPLIT_MAXQ
     if (m % 4 == 0 && m >= 8 && n >= 64 && n <= 1024 && (n / 64) * ((m / 4 + 3) / 4) <= KRON_SPLIT_MAXQ) {
