@@ -149,8 +149,7 @@ __global__ __launch_bounds__(256) void kv4_append_kv_kernel(const void* __restri
 constexpr int KV_THREADS = 256;
 constexpr int KV_MAX_L = 256;          // tokens per workgroup at most: four per lane group, all loads in flight at once
 constexpr int KV_PART = KV_D + 4;      // floats per partial result: acc[128], m, l, 2 unused
-constexpr float KV_LAZY = 30.0f;       // how far a score may exceed the streaming kernel's reference before it is raised
-constexpr int KV_STREAM_L = 1024;      // tokens per workgroup of the streaming kernel unless the option says otherwise
+constexpr int KV_STREAM_L = 1024;      // tokens per workgroup of the matrix-core kernel for large calls
 
 // The four low nibbles and the four high nibbles of a dword as bytes.  The empty asm keeps the
 // compiler from folding the mask into each later byte extraction (a 4-bit field extract plus a
@@ -228,6 +227,36 @@ __device__ __forceinline__ void kv_rotate_query(float (&t)[32], int piece)
     for (int e = 0; e < 32; ++e) t[e] = t[e] * norm;
 }
 
+// The same with the four pieces of a head in lanes 16 apart (piece = lane / 16) instead of neighbouring ones.
+__device__ __forceinline__ void kv_rotate_query_rows(float (&t)[32], int piece)
+{
+#pragma clang fp contract(off)
+#pragma unroll
+    for (int st = 1; st < 32; st <<= 1)
+#pragma unroll
+        for (int e = 0; e < 32; ++e)
+            if ((e & st) == 0) {
+                const float a = t[e], b = t[e + st];
+                t[e] = a + b;
+                t[e + st] = a - b;
+            }
+#pragma unroll
+    for (int e = 0; e < 32; ++e) {  // stride 32; the swap leaves (value of the even row, value of the odd row) in every lane
+        auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(t[e]), __float_as_uint(t[e]), false, false);
+        const float a = __uint_as_float(r[0]), b = __uint_as_float(r[1]);
+        t[e] = (piece & 1) ? a - b : a + b;
+    }
+#pragma unroll
+    for (int e = 0; e < 32; ++e) {  // stride 64
+        auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(t[e]), __float_as_uint(t[e]), false, false);
+        const float a = __uint_as_float(r[0]), b = __uint_as_float(r[1]);
+        t[e] = (piece & 2) ? a - b : a + b;
+    }
+    const float norm = 0.088388347648318440550f;  // (float)(1 / sqrt(128))
+#pragma unroll
+    for (int e = 0; e < 32; ++e) t[e] = t[e] * norm;
+}
+
 // This lane's 32 query values in register order (r = 8 d + 4 e + b <-> element 8 d + 2 b + e) and their sum.
 template <int QDT>
 __device__ __forceinline__ float kv_query_registers(const Raw8<QDT> (&qraw)[4], bool rotate, int piece, float (&qr)[32])
@@ -264,9 +293,11 @@ struct KvMergeLds {
     float dred[KV_CT / KV_D], mred[KV_CT / KV_D];
 };
 
-__device__ __forceinline__ void kv_merge_head(const float* __restrict__ src, int splits, int groups, void* __restrict__ out,
+// unit: log2(e) when the m_i are in units of e, 1 when they are powers of two.
+__device__ __forceinline__ void kv_merge_head(const float* __restrict__ src, int splits, int groups, float unit, void* __restrict__ out,
                                               bool out_f16, int h, KvMergeLds& lds, int nthreads)
 {
+    auto power = [unit](float x) { return __builtin_amdgcn_exp2f(x * unit); };
     for (int vt = threadIdx.x; vt < groups * KV_D; vt += nthreads) {
         const int j = vt & (KV_D - 1), g = vt >> 7;
         float M = -INFINITY, num = 0.0f, den = 0.0f;
@@ -283,13 +314,13 @@ __device__ __forceinline__ void kv_merge_head(const float* __restrict__ src, int
 #pragma unroll
             for (int u = 0; u < 4; ++u)
                 if (i0 + groups * u < splits) mb = fmaxf(mb, mi[u]);
-            const float r = __expf(M - mb);  // 0 on the first round (M = -inf, mb finite)
+            const float r = power(M - mb);  // 0 on the first round (M = -inf, mb finite)
             num *= r;
             den *= r;
             M = mb;
 #pragma unroll
             for (int u = 0; u < 4; ++u) {
-                const float e = (i0 + groups * u < splits) ? __expf(mi[u] - M) : 0.0f;
+                const float e = (i0 + groups * u < splits) ? power(mi[u] - M) : 0.0f;
                 num = fmaf(e, ai[u], num);
                 den = fmaf(e, li[u], den);
             }
@@ -307,7 +338,7 @@ __device__ __forceinline__ void kv_merge_head(const float* __restrict__ src, int
         for (int w = 1; w < groups; ++w) Mt = fmaxf(Mt, lds.mred[w]);
         float n = 0.0f, d = 0.0f;
         for (int w = 0; w < groups; ++w) {
-            const float e = __expf(lds.mred[w] - Mt);
+            const float e = power(lds.mred[w] - Mt);
             n = fmaf(e, lds.red[w][tid], n);
             d = fmaf(e, lds.dred[w], d);
         }
@@ -497,182 +528,417 @@ __global__ __launch_bounds__(KV_THREADS) void kv4_attn_kernel(const void* __rest
 }
 
 // ---------------------------------------------------------------------------------------
-// The streaming form for long contexts and batches, where the device is refilled many times and
-// a workgroup that loads, waits, computes and leaves keeps too few bytes in flight.  Workgroup =
-// (split of L tokens, head [, sequence]), L = 512 ... 2048.  The split is cut into chunks of 16
-// tokens; wavefront w takes chunks w, w + 4, ... and walks them on its own: no workgroup barrier
-// inside the loop, the loads of its next two chunks in flight while it computes one.  Each
-// wavefront keeps a reference m (uniform over the wavefront; the running maximum, raised lazily)
-// and rescales its sums when a chunk raises it:  acc <- acc * e^(m_old - m_new);  p_t = e^(score_t - m_new).
-// At the end the four wavefronts merge in LDS with the same rule and (m, l, acc) of the split
-// goes to the workspace for kv4_combine_kernel.
+// The matrix-core form for long contexts, batches and grouped query heads.  Workgroup = (split of L tokens, cache head
+// [, sixteen of its query heads] [, sequence]); all query heads that read the cache head are rows of one matrix
+// product, so the codes are fetched and unpacked once for all of them.  Wavefront w of the four walks the chunks
+// w, w + 4, ... of 64 tokens on its own (no workgroup barrier inside the loop).
+//
+// Operands.  A code in a byte of its own is c * 2^-9 as an E4M3 number, and one instruction turns two of those into
+// binary16 numbers (7 operations for the eight codes of a dword).  Left as binary16 subnormals c * 2^-24 they would take
+// five, but the matrix unit aligns products by their nominal exponents: outputs were off by 4e-5 instead of 3e-7.
+// The other operand (query, softmax weights) is a sum of two binary16 numbers, hi + lo, 22 bits and more of each value,
+// in two instructions; products are exact and the sums binary32.  The (s, z) of a token stay outside the products:
+//   score = s_t (q . c_t - z_t sum q),   out = sum_t (p_t s_t) c_t - sum_t p_t s_t z_t.
+//   scores   rows = query heads, columns = 16 tokens, k = the 128 elements: the codes go from memory to registers in
+//            operand order (lane = token l % 16, 16 bytes l / 16 of it)
+//   values   rows = query heads, columns = 16 elements, k = 32 tokens: the codes go to LDS as they lie in memory and
+//            come back transposed by ds_read_b64_tr_b4 (16 tokens of one element per lane); the 16-byte pieces of a
+//            token are permuted by the token's position so that sixteen rows fall into different banks
+// Between the two a lane holds the scores of its token(s) for up to four heads; the weights pass through LDS.
+// Bound by HBM for up to about eight query heads per cache head (16 matrix cycles and about as many vector cycles per
+// token and cache head on a SIMD, against 60 at 5.5 TB/s over 1024 SIMDs).
+// RP: query heads per cache head, rounded up to a power of two.
 // ---------------------------------------------------------------------------------------
-struct KvChunk {
-    u32x4 kw, vw;
-    uint32_t kp, vp;
-    bool valid;
+typedef _Float16 v8h __attribute__((ext_vector_type(8)));
+typedef _Float16 v2h __attribute__((ext_vector_type(2)));
+typedef int v2i __attribute__((ext_vector_type(2)));
+constexpr float KV_LAZY2 = 5.0f;       // how far (in powers of two) a score may exceed the reference before it is raised
+constexpr int KV_WSTRIDE = 68;         // dwords per head of the weights in LDS: 64 tokens, padded off the bank period
+
+union KvHalves {
+    uint32_t w[4];
+    v8h h;
 };
 
-template <int QDT, bool BATCHED, bool QROT = false>
-__global__ __launch_bounds__(KV_THREADS) void kv4_attn_stream_kernel(const void* __restrict__ q, int S, int S_max, int rep,
-                                                                     int splits, float softmax_scale,
-                                                                     const u32x4* __restrict__ k_codes,
-                                                                     const uint32_t* __restrict__ k_params,
-                                                                     const u32x4* __restrict__ v_codes,
-                                                                     const uint32_t* __restrict__ v_params, int L,
-                                                                     float* __restrict__ part, KvBatch batch)
+// eight codes of a dword as binary16 numbers, elements 0,2 | 4,6 | 1,3 | 5,7
+__device__ __forceinline__ v8h kv_code_halves(uint32_t w)
 {
-    __shared__ float red[4][KV_D];
-    __shared__ float wm[4], lrow[4][4], zrow[4][4];
-    int split, h, hk;
-    if (!kv_place(blockIdx.x, splits, rep, batch.H_kv, split, h, hk)) return;  // padding of the grid
-    const int tid = threadIdx.x, lane = tid & 63, slot = lane >> 2, piece = tid & 3;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int lo = static_cast<int>(w & 0x0f0f0f0fu), hi = static_cast<int>((w >> 4) & 0x0f0f0f0fu);
+    const v2h a = __builtin_amdgcn_cvt_scalef32_pk_f16_fp8(lo, 512.0f, false), b = __builtin_amdgcn_cvt_scalef32_pk_f16_fp8(lo, 512.0f, true);
+    const v2h c = __builtin_amdgcn_cvt_scalef32_pk_f16_fp8(hi, 512.0f, false), d = __builtin_amdgcn_cvt_scalef32_pk_f16_fp8(hi, 512.0f, true);
+    return v8h{a[0], a[1], b[0], b[1], c[0], c[1], d[0], d[1]};
+}
+// which element of the dword stands in half e of register r of that operand
+__device__ __forceinline__ constexpr int kv_half_element(int r, int e) { return ((r & 2) >> 1) + 4 * (r & 1) + 2 * e; }
+
+__device__ __forceinline__ uint32_t half_bits(float v) { return __half_as_ushort(__float2half_rn(v)); }
+
+// v as hi + lo, two binary16 numbers: hi in the low 16 bits
+__device__ __forceinline__ uint32_t kv_split_half(float v)
+{
+    const uint32_t hi = half_bits(v);
+    return hi | (half_bits(v - half_bits_to_float(static_cast<uint16_t>(hi))) << 16);
+}
+
+// maximum / sum over the lanes that hold values of the same head in the score layout
+template <int RP>
+__device__ __forceinline__ float kv_head_max(float v)
+{
+#define RCP_ROW_MAX(ctrl) v = fmaxf(v, __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), ctrl, 0xf, 0xf, false)))
+    RCP_ROW_MAX(0x128);
+    RCP_ROW_MAX(0x124);
+    RCP_ROW_MAX(0x122);
+    RCP_ROW_MAX(0x121);
+#undef RCP_ROW_MAX
+    if constexpr (RP <= 4) {
+        auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+        v = fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
+    }
+    if constexpr (RP <= 8) {
+        auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+        v = fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
+    }
+    return v;
+}
+
+template <int RP>
+__device__ __forceinline__ float kv_head_sum(float v)
+{
+    v = row_sum16f(v);
+    if constexpr (RP <= 4) v = fold16f(v, v);
+    if constexpr (RP <= 8) v = fold32f(v, v);
+    return v;
+}
+
+template <int RP>
+struct KvMfmaLds {
+    union {
+        struct {
+            u32x4 v[4][256];                       // a chunk's value codes of each wavefront
+            uint32_t w[4][RP * KV_WSTRIDE];        // its softmax weights, hi | lo << 16; first the sums of q
+        } run;
+        struct {
+            float red[4][RP][KV_D];
+            float m[4][RP], l[4][RP];
+        } end;
+    };
+};
+
+template <int RP>
+__global__ __launch_bounds__(KV_THREADS, RP <= 4 ? 3 : 2) void kv4_attn_mfma_kernel(const void* __restrict__ q, int q_dt, int rotate, int S_max, int rep,
+                                                                   int splits, float softmax_scale, const u32x4* __restrict__ k_codes,
+                                                                   const uint32_t* __restrict__ k_params,
+                                                                   const u32x4* __restrict__ v_codes,
+                                                                   const uint32_t* __restrict__ v_params, int L,
+                                                                   float* __restrict__ part, KvBatch batch)
+{
+    constexpr int HV = RP < 4 ? RP : 4;                       // heads a lane holds scores of
+    constexpr int SETS = RP <= 4 ? 1 : RP == 8 ? 2 : 4;       // tokens a lane holds scores of
+    __shared__ KvMfmaLds<RP> lds;
+    const int seq = blockIdx.z;
+    const int S = batch.v[seq];
+    const int split = static_cast<int>(blockIdx.x) % splits, hk0 = static_cast<int>(blockIdx.x) / splits;
     const int t0 = split * L;
-    if constexpr (BATCHED) {
-        const int seq = blockIdx.z;
-        S = batch.v[seq];
-        if (t0 >= S) return;  // the whole workgroup: this sequence has fewer splits
-        h += seq * batch.H_q;
-        hk += seq * batch.H_kv;
-    }
+    if (t0 >= S) return;  // the whole workgroup: this sequence has fewer splits
     const int t_end = min(S, t0 + L);
+    const int hk = hk0 + seq * batch.H_kv;
+    const int R = min(RP, rep - static_cast<int>(blockIdx.y) * RP);  // query heads of this workgroup
+    const int h0 = seq * batch.H_q + hk0 * rep + static_cast<int>(blockIdx.y) * RP;
+    const int tid = threadIdx.x, lane = tid & 63, i = lane & 15, g = lane >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int first = t0 + 64 * wave;
+    const int nchunks = t_end > first ? (t_end - first + 255) >> 8 : 0;  // of this wavefront; uniform
+
+    // One resource per tensor and cache head that ends with this workgroup's last token: what lies beyond reads as
+    // zero (code 0 of weight 0), so no address is clamped.  The cache is read once per call: non-temporal loads.
     const size_t head_base = static_cast<size_t>(hk) * S_max;
-    // chunks of this wavefront that hold at least one cached token
-    const int span = t_end - t0 - 16 * wave;
-    const int nchunks = span > 0 ? (span + 63) >> 6 : 0;
-
-    auto load = [&](int c, KvChunk& r) {  // chunk c of this wavefront: tokens t0 + 16 (4 c + wave) ...; past the end: the last token, weight 0
-        const int t = t0 + 16 * (4 * c + wave) + slot;
-        r.valid = t < t_end;
-        const size_t at = head_base + (r.valid ? t : t_end - 1);
-        // read once per call: non-temporal loads, as in kv4_attn_kernel
-        r.kw = __builtin_nontemporal_load(k_codes + (at * 4 + piece));
-        r.kp = __builtin_nontemporal_load(k_params + at);
-        r.vw = __builtin_nontemporal_load(v_codes + (at * 4 + piece));
-        r.vp = __builtin_nontemporal_load(v_params + at);
+    auto resource = [&](const void* p, int bytes) {
+        return __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(static_cast<const char*>(p)) + head_base * bytes, 0, t_end * bytes, 0x00020000);
     };
-
-    Raw8<QDT> qraw[4];
+    const __amdgpu_buffer_rsrc_t kc = resource(k_codes, 64), vc = resource(v_codes, 64), kr = resource(k_params, 4), vr = resource(v_params, 4);
+    constexpr int NT = 2;
+    u32x4 kw[4];
+    uint32_t kp[SETS], vp[SETS];
+    auto set_token = [&](int s) { return RP <= 4 ? lane : RP == 8 ? 32 * s + 16 * (g >> 1) + i : 16 * s + i; };
+    const int k_lane = i * 64 + g * 16, v_lane = (lane >> 2) * 64 + ((lane & 3) ^ g) * 16, p_lane = set_token(0) * 4;
+    constexpr int P_SET = RP == 8 ? 128 : 64;  // bytes of parameters from one set to the next
+    auto load_keys = [&](int base) {
 #pragma unroll
-    for (int d = 0; d < 4; ++d) qraw[d] = load8_raw<QDT>(q, static_cast<size_t>(h) * KV_D + 32 * piece + 8 * d);
-    KvChunk cA, cB;
-    load(0, cA);
-    load(1, cB);
-
-    float qr[32];
-    const float qsum = kv_query_registers<QDT>(qraw, QROT, piece, qr);
-    const float unit = kv_fp8_unit(), inv_unit = 1.0f / unit;
-    const float scale_by_unit = softmax_scale * inv_unit, qsum_unit = qsum * unit;
-
-    float acc[32];
+        for (int n = 0; n < 4; ++n) kw[n] = __builtin_amdgcn_raw_buffer_load_b128(kc, k_lane + base * 64 + 1024 * n, 0, NT);
 #pragma unroll
-    for (int r = 0; r < 32; ++r) acc[r] = 0.0f;
-    float lsum = 0.0f, zacc = 0.0f;
-    float m = -INFINITY;  // uniform over the wavefront
-    int chunk = 0;
-
-    auto step = [&](KvChunk& cur) {
-        float dot[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+        for (int s = 0; s < SETS; ++s) {
+            kp[s] = __builtin_amdgcn_raw_buffer_load_b32(kr, p_lane + base * 4 + P_SET * s, 0, NT);
+            vp[s] = __builtin_amdgcn_raw_buffer_load_b32(vr, p_lane + base * 4 + P_SET * s, 0, NT);
+        }
+    };
+    auto load_values = [&](int base) {  // lane -> (token lane / 4, piece lane % 4 of it after the permutation)
 #pragma unroll
-        for (int d = 0; d < 4; ++d) {
-            uint32_t lo, hi;
-            nibble_bytes(cur.kw[d], lo, hi);
-            float fl[4], fh[4];
-            bytes_to_floats(lo, fl);
-            bytes_to_floats(hi, fh);
+        for (int n = 0; n < 4; ++n)
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(vc, (__attribute__((address_space(3))) void*)(&lds.run.v[wave][64 * n]), 16,
+                                                     v_lane + base * 64 + 1024 * n, 0, 0, NT);
+    };
+    // ---- the query: lane = (head i, elements 32 g ...) ----
+    v8h qhi[4], qlo[4];
+    float qs[HV];     // sum of the query in the units of the products
+    float cs = 0.0f;  // products -> score in powers of two
+    if (nchunks > 0) {
+        // the query is requested first: memory answers in order and it is needed first
+        float t[32];
+        const size_t qat = static_cast<size_t>(h0 + min(i, R - 1)) * KV_D + 32 * g;
+        if (q_dt == RCP_F32) {  // uniform
 #pragma unroll
-            for (int b = 0; b < 4; ++b) {
-                dot[d] = fmaf(qr[8 * d + b], fl[b], dot[d]);
-                dot[d] = fmaf(qr[8 * d + 4 + b], fh[b], dot[d]);
+            for (int d = 0; d < 8; ++d) {
+                const float4 x = reinterpret_cast<const float4*>(static_cast<const float*>(q) + qat)[d];
+                t[4 * d] = x.x;
+                t[4 * d + 1] = x.y;
+                t[4 * d + 2] = x.z;
+                t[4 * d + 3] = x.w;
+            }
+            __builtin_amdgcn_sched_barrier(0);
+            load_keys(first);
+            load_values(first);
+            __builtin_amdgcn_sched_barrier(0);
+        } else {
+            Raw8<RCP_F16> raw[4];
+#pragma unroll
+            for (int d = 0; d < 4; ++d) raw[d] = load8_raw<RCP_F16>(q, qat + 8 * d);
+            __builtin_amdgcn_sched_barrier(0);
+            load_keys(first);
+            load_values(first);
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int d = 0; d < 4; ++d) {
+                const uint32_t w[4] = {raw[d].a.x, raw[d].a.y, raw[d].a.z, raw[d].a.w};
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const uint16_t x = static_cast<uint16_t>(w[e] & 0xffffu), y = static_cast<uint16_t>(w[e] >> 16);
+                    t[8 * d + 2 * e] = q_dt == RCP_F16 ? half_bits_to_float(x) : bf16_bits_to_float(x);
+                    t[8 * d + 2 * e + 1] = q_dt == RCP_F16 ? half_bits_to_float(y) : bf16_bits_to_float(y);
+                }
             }
         }
-        const float s = half_bits_to_float(static_cast<uint16_t>(cur.kp & 0xffffu)) * scale_by_unit;
-        const float z = static_cast<float>(static_cast<int>(cur.kp) >> 16);
-        float sc = quad_sum(s * (((dot[0] + dot[1]) + (dot[2] + dot[3])) - z * qsum_unit));
-        sc = cur.valid ? sc : -INFINITY;
-        // The reference m only has to keep the exponentials in range, so it is raised lazily: when some score
-        // of the chunk exceeds it by more than KV_LAZY (always on the first chunk, where m = -inf; every chunk
-        // that is stepped holds a cached token, so the new maximum is finite).  Weights then stay below
-        // e^KV_LAZY and the sums of a split far inside the binary32 range.
-        if (__builtin_amdgcn_ballot_w64(sc > m + KV_LAZY) != 0) {  // uniform
-            const float m_new = fmaxf(m, wave_max(sc));
-            const float alpha = __expf(m - m_new);  // 0 on the first chunk
+        if (rotate) kv_rotate_query_rows(t, g);  // uniform
+        float top = 0.0f, sum = 0.0f;
 #pragma unroll
-            for (int r = 0; r < 32; ++r) acc[r] *= alpha;
-            lsum *= alpha;
-            zacc *= alpha;
-            m = m_new;
+        for (int e = 0; e < 32; ++e) {
+            if (i >= R) t[e] = 0.0f;
+            top = fmaxf(top, fabsf(t[e]));
         }
-        const float p = __expf(sc - m);
-        const float w0 = p * half_bits_to_float(static_cast<uint16_t>(cur.vp & 0xffffu));
-        const float w = w0 * inv_unit;
-        lsum += p;
-        zacc = fmaf(w0, static_cast<float>(static_cast<int>(cur.vp) >> 16), zacc);
+        const int E = __builtin_amdgcn_frexp_expf(wave_max(top));  // the largest element becomes 2^13 .. 2^14
+#pragma unroll
+        for (int e = 0; e < 32; ++e) {
+            t[e] = ldexpf(t[e], 14 - E);
+            sum += t[e];
+        }
+        sum = fold32f(fold16f(sum, sum), fold16f(sum, sum));
+        uint32_t* const slot = lds.run.w[wave];
+        if (g == 0 && i < RP) slot[i] = __float_as_uint(sum);
+        __builtin_amdgcn_wave_barrier();
+#pragma unroll
+        for (int v = 0; v < HV; ++v) qs[v] = __uint_as_float(slot[RP <= 4 ? v : RP == 8 ? 4 * (g & 1) + v : 4 * g + v]);
+        __builtin_amdgcn_wave_barrier();
+        cs = ldexpf(softmax_scale * 1.44269504088896340736f, E - 14);
 #pragma unroll
         for (int d = 0; d < 4; ++d) {
-            uint32_t lo, hi;
-            nibble_bytes(cur.vw[d], lo, hi);
-            float fl[4], fh[4];
-            bytes_to_floats(lo, fl);
-            bytes_to_floats(hi, fh);
+            KvHalves hi, lo;
 #pragma unroll
-            for (int b = 0; b < 4; ++b) {
-                acc[8 * d + b] = fmaf(w, fl[b], acc[8 * d + b]);
-                acc[8 * d + 4 + b] = fmaf(w, fh[b], acc[8 * d + 4 + b]);
+            for (int r = 0; r < 4; ++r) {
+                const uint32_t x = kv_split_half(t[8 * d + kv_half_element(r, 0)]), y = kv_split_half(t[8 * d + kv_half_element(r, 1)]);
+                hi.w[r] = __builtin_amdgcn_perm(y, x, 0x05040100u);
+                lo.w[r] = __builtin_amdgcn_perm(y, x, 0x07060302u);
+            }
+            qhi[d] = hi.h;
+            qlo[d] = lo.h;
+        }
+    }
+
+    v4f acc[8];
+#pragma unroll
+    for (int b = 0; b < 8; ++b) acc[b] = v4f{0.0f, 0.0f, 0.0f, 0.0f};
+    float m[HV], lsum[HV], zacc[HV];
+#pragma unroll
+    for (int v = 0; v < HV; ++v) {
+        m[v] = -INFINITY;
+        lsum[v] = zacc[v] = 0.0f;
+    }
+    float vs = 0.0f, vlim = -1.0f;  // power of two on the weights that keeps them inside binary16, and the step it holds for
+
+    for (int c = 0; c < nchunks; ++c) {
+        const int base = first + 256 * c;
+        v4f D[4];
+#pragma unroll
+        for (int n = 0; n < 4; ++n) {
+            D[n] = v4f{0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+            for (int d = 0; d < 4; ++d) {
+                const v8h b = kv_code_halves(kw[n][d]);
+                D[n] = __builtin_amdgcn_mfma_f32_16x16x32_f16(qlo[d], b, D[n], 0, 0, 0);
+                D[n] = __builtin_amdgcn_mfma_f32_16x16x32_f16(qhi[d], b, D[n], 0, 0, 0);
             }
         }
-        __builtin_amdgcn_sched_barrier(0);
-        load(chunk + 2, cur);  // refill with the chunk two steps ahead (past the end: a harmless repeat of the last token)
-        __builtin_amdgcn_sched_barrier(0);
-        ++chunk;
-    };
-    // steps counted up front and run in pairs: one loop body, one exit (four chunks in flight instead of
-    // two: 130 registers and no gain)
-    for (int i = 0; i < nchunks / 2; ++i) {
-        step(cA);
-        step(cB);
-    }
-    if (nchunks & 1) step(cA);
-
-    // ---- the 16 tokens of a wavefront's chunks are summed as in kv4_attn_kernel; the four wavefronts
-    // merge through LDS, each weighted by e^(its m - the largest m) ----
+        float ks[SETS], kz[SETS], sv[SETS], zv[SETS];
+        bool valid[SETS];
 #pragma unroll
-    for (int r = 0; r < 32; ++r) acc[r] = row_tokens_sum(acc[r]);
-    lsum = row_tokens_sum(lsum);
-    zacc = row_tokens_sum(zacc);
-    float f16v[16], f32v[8];
-#pragma unroll
-    for (int k = 0; k < 16; ++k) f16v[k] = fold16f(acc[2 * k], acc[2 * k + 1]);
-#pragma unroll
-    for (int k = 0; k < 8; ++k) f32v[k] = fold32f(f16v[2 * k], f16v[2 * k + 1]);
-    const int rw = (tid >> 4) & 3;
-    if ((tid & 12) == 0) {
-#pragma unroll
-        for (int k = 0; k < 8; ++k) red[wave][32 * piece + kv_elem_of_reg(4 * k + rw)] = f32v[k];
-        if (piece == 0) {
-            lrow[wave][rw] = lsum;
-            zrow[wave][rw] = zacc;
+        for (int s = 0; s < SETS; ++s) {
+            ks[s] = half_bits_to_float(static_cast<uint16_t>(kp[s] & 0xffffu)) * cs;
+            kz[s] = static_cast<float>(static_cast<int>(kp[s]) >> 16);
+            sv[s] = half_bits_to_float(static_cast<uint16_t>(vp[s] & 0xffffu));
+            zv[s] = static_cast<float>(static_cast<int>(vp[s]) >> 16);
+            valid[s] = base + set_token(s) < t_end;
+            // computed before the next parameters arrive in the same registers
+            asm volatile("" : "+v"(ks[s]), "+v"(kz[s]), "+v"(sv[s]), "+v"(zv[s]));
         }
+        __builtin_amdgcn_sched_barrier(0);
+        load_keys(base + 256);  // past the end: zeros
+        __builtin_amdgcn_sched_barrier(0);
+
+        // rows of sixteen lanes without a head are filled with the other tokens' scores
+        float sc[SETS][HV];
+#pragma unroll
+        for (int v = 0; v < HV; ++v) {
+            if constexpr (RP <= 4) {
+                auto a = __builtin_amdgcn_permlane16_swap(__float_as_uint(D[0][v]), __float_as_uint(D[1][v]), false, false);
+                auto b = __builtin_amdgcn_permlane16_swap(__float_as_uint(D[2][v]), __float_as_uint(D[3][v]), false, false);
+                auto r = __builtin_amdgcn_permlane32_swap(a[0], b[0], false, false);
+                sc[0][v] = __uint_as_float(r[0]);
+            } else if constexpr (RP == 8) {
+#pragma unroll
+                for (int s = 0; s < 2; ++s) {
+                    auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(D[2 * s][v]), __float_as_uint(D[2 * s + 1][v]), false, false);
+                    sc[s][v] = __uint_as_float(r[0]);
+                }
+            } else {
+#pragma unroll
+                for (int s = 0; s < SETS; ++s) sc[s][v] = D[s][v];
+            }
+        }
+        bool raise = false;
+#pragma unroll
+        for (int s = 0; s < SETS; ++s) {
+            raise |= sv[s] > vlim;
+#pragma unroll
+            for (int v = 0; v < HV; ++v) {
+                sc[s][v] = valid[s] ? fmaf(-kz[s], qs[v], sc[s][v]) * ks[s] : -INFINITY;
+                raise |= sc[s][v] > m[v] + KV_LAZY2;
+            }
+        }
+        // The reference m (one per head) and the power of two vs only have to keep the weights in range: they move when
+        // a score or a value step of the chunk leaves it (always on the first chunk, whose first token is valid).
+        if (__builtin_amdgcn_ballot_w64(raise) != 0) {  // uniform
+            float top = sv[0];
+#pragma unroll
+            for (int s = 1; s < SETS; ++s) top = fmaxf(top, sv[s]);
+            top = fmaxf(wave_max(top), 0.5f * vlim);
+            const int ev = __builtin_amdgcn_frexp_expf(top);
+            const float vs_new = ldexpf(1.0f, 9 - ev);
+            vlim = ldexpf(1.0f, ev + 1);  // steps below 2^10 after scaling, weights below 2^15
+            const float f = vs == 0.0f ? 0.0f : vs_new / vs;
+            vs = vs_new;
+#pragma unroll
+            for (int v = 0; v < HV; ++v) {
+                float mt = sc[0][v];
+#pragma unroll
+                for (int s = 1; s < SETS; ++s) mt = fmaxf(mt, sc[s][v]);
+                const float m_new = fmaxf(m[v], kv_head_max<RP>(mt));
+                const float alpha = __builtin_amdgcn_exp2f(m[v] - m_new);  // 0 on the first chunk
+                m[v] = m_new;
+                lsum[v] *= alpha;
+                zacc[v] *= alpha;
+#pragma unroll
+                for (int b = 0; b < 8; ++b) acc[b][v] *= alpha * f;
+            }
+        }
+        uint32_t* const ww = lds.run.w[wave];
+#pragma unroll
+        for (int s = 0; s < SETS; ++s)
+#pragma unroll
+            for (int v = 0; v < HV; ++v) {
+                const float p = __builtin_amdgcn_exp2f(sc[s][v] - m[v]);  // 0 for the surplus tokens
+                const float w0 = p * sv[s];
+                lsum[v] += p;
+                zacc[v] = fmaf(w0, zv[s], zacc[v]);
+                const int head = RP <= 4 ? v : RP == 8 ? 4 * (g & 1) + v : 4 * g + v;
+                ww[head * KV_WSTRIDE + set_token(s)] = kv_split_half(w0 * vs);
+            }
+        // weights back as operands: lane = (head i, tokens 16 g + 8 h ...)
+        v8h phi[2], plo[2];
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const u32x4* const src = reinterpret_cast<const u32x4*>(ww + min(i, RP - 1) * KV_WSTRIDE + 16 * g + 8 * h);
+            const u32x4 w03 = src[0], w47 = src[1];
+            const uint32_t ws[8] = {w03.x, w03.y, w03.z, w03.w, w47.x, w47.y, w47.z, w47.w};
+            KvHalves hi, lo;
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const uint32_t x = ws[kv_half_element(r, 0)], y = ws[kv_half_element(r, 1)];
+                hi.w[r] = __builtin_amdgcn_perm(y, x, 0x05040100u);
+                lo.w[r] = __builtin_amdgcn_perm(y, x, 0x07060302u);
+            }
+            phi[h] = hi.h;
+            plo[h] = lo.h;
+        }
+        // the values of this chunk are in LDS once no more loads than the keys requested above are outstanding
+        constexpr int AFTER = 4 + 2 * SETS;
+        __builtin_amdgcn_sched_barrier(0);
+        __builtin_amdgcn_s_waitcnt((AFTER & 15) | (7 << 4) | (15 << 8));
+        __builtin_amdgcn_sched_barrier(0);
+        const int tok = 16 * g + i;
+        const char* const row = reinterpret_cast<const char*>(&lds.run.v[wave][0]) + tok * 64;
+        const int f = (tok >> 2) & 3;
+#pragma unroll
+        for (int b = 0; b < 8; ++b) {
+            const v2i r = __builtin_amdgcn_ds_read_tr4_b64_v2i32(
+                (__attribute__((address_space(3))) v2i*)(row + (((b >> 1) ^ f) * 16 + (b & 1) * 8)));
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                const v8h x = kv_code_halves(static_cast<uint32_t>(r[h]));
+                acc[b] = __builtin_amdgcn_mfma_f32_16x16x32_f16(plo[h], x, acc[b], 0, 0, 0);
+                acc[b] = __builtin_amdgcn_mfma_f32_16x16x32_f16(phi[h], x, acc[b], 0, 0, 0);
+            }
+        }
+        // every read of the chunk has returned before the next one overwrites it
+        __builtin_amdgcn_sched_barrier(0);
+        __builtin_amdgcn_s_waitcnt(15 | (7 << 4) | (0 << 8) | (3 << 14));
+        load_values(base + 256);
+        __builtin_amdgcn_sched_barrier(0);
     }
-    if (lane == 0) wm[wave] = m;
+#pragma unroll
+    for (int v = 0; v < HV; ++v) {
+        lsum[v] = kv_head_sum<RP>(lsum[v]);
+        zacc[v] = kv_head_sum<RP>(zacc[v]);
+    }
+    __builtin_amdgcn_s_waitcnt(0);  // the surplus values have landed: LDS changes hands
     __syncthreads();
-    float* dst = part + (static_cast<size_t>(h) * splits + split) * KV_PART;
-    if (tid <= KV_D) {
-        const float M = fmaxf(fmaxf(wm[0], wm[1]), fmaxf(wm[2], wm[3]));  // wavefront 0 always has a token: finite
-        float total = 0.0f;
+    const float back = vs == 0.0f ? 0.0f : 1.0f / vs;
+    if (4 * g < RP) {
+#pragma unroll
+        for (int v = 0; v < HV; ++v) {
+#pragma unroll
+            for (int b = 0; b < 8; ++b) lds.end.red[wave][4 * g + v][16 * b + i] = acc[b][v] * back - zacc[v];
+            if (i == 0) {
+                lds.end.m[wave][4 * g + v] = m[v];
+                lds.end.l[wave][4 * g + v] = lsum[v];
+            }
+        }
+    }
+    __syncthreads();
+    for (int idx = tid; idx < R * KV_D; idx += KV_THREADS) {
+        const int h = idx >> 7, j = idx & (KV_D - 1);
+        float M = lds.end.m[0][h];  // wavefront 0 always has a token: finite
+#pragma unroll
+        for (int w = 1; w < 4; ++w) M = fmaxf(M, lds.end.m[w][h]);
+        float total = 0.0f, ls = 0.0f;
 #pragma unroll
         for (int w = 0; w < 4; ++w) {
-            const float e = __expf(wm[w] - M);  // 0 for a wavefront without tokens
-            float v;
-            if (tid < KV_D) v = red[w][tid] - ((zrow[w][0] + zrow[w][1]) + (zrow[w][2] + zrow[w][3]));
-            else v = (lrow[w][0] + lrow[w][1]) + (lrow[w][2] + lrow[w][3]);
-            total = fmaf(e, v, total);
+            const float e = __builtin_amdgcn_exp2f(lds.end.m[w][h] - M);  // 0 for a wavefront without tokens
+            total = fmaf(e, lds.end.red[w][h][j], total);
+            ls = fmaf(e, lds.end.l[w][h], ls);
         }
-        if (tid < KV_D) dst[tid] = total;
-        else {
+        float* const dst = part + (static_cast<size_t>(h0 + h) * splits + split) * KV_PART;
+        dst[j] = total;
+        if (j == 0) {
             dst[KV_D] = M;
-            dst[KV_D + 1] = total;
+            dst[KV_D + 1] = ls;
         }
     }
 }
@@ -682,7 +948,7 @@ __global__ __launch_bounds__(KV_THREADS) void kv4_attn_stream_kernel(const void*
 // first ceil(length / L) of the `splits` slots of each head.
 template <bool OUT_F16, bool BATCHED>
 __global__ __launch_bounds__(KV_CT) void kv4_combine_kernel(const float* __restrict__ part, int splits, int groups,
-                                                            void* __restrict__ out, int L, KvBatch batch)
+                                                            void* __restrict__ out, int L, float unit, KvBatch batch)
 {
     __shared__ KvMergeLds lds;
     const int h = blockIdx.x;
@@ -693,7 +959,7 @@ __global__ __launch_bounds__(KV_CT) void kv4_combine_kernel(const float* __restr
         splits = (batch.v[h / batch.H_q] + L - 1) / L;
         groups = min(groups, (splits + 3) / 4);
     }
-    kv_merge_head(src, splits, groups, out, OUT_F16, h, lds, groups * KV_D);
+    kv_merge_head(src, splits, groups, unit, out, OUT_F16, h, lds, groups * KV_D);
 }
 
 // ---------------------------------------------------------------------------------------
@@ -777,57 +1043,74 @@ int launch_kv4_attn(const void* q, rcp_dtype q_dt, int B, int H_q, int H_kv, int
         batch.H_q = H_q;
         batch.H_kv = H_kv;
     }
-    // 128 tokens per workgroup below 2048 x 32 (token, head) pairs, 256 below 4096 x 32, then the streaming kernel: on
-    // splits of 512 tokens up to 8192 x 32 pairs, of 1024 tokens beyond (sweeps at 32 heads, one to sixteen sequences:
-    // 4096 tokens 9.2 -> 8.9 us, 8192 tokens 12.4 -> 11.5, 8 x 1024 tokens 12.5 -> 11.4 against 256 per workgroup)
-    int L = options().kv_tokens;
-    if (L == 0) L = total * H_q < 65536 ? 128 : total * H_q < 131072 ? KV_MAX_L : total * H_q <= 262144 ? 512 : KV_STREAM_L;
-    const bool stream = L > KV_MAX_L;
-    const int splits = (S + L - 1) / L;
+    // Below 4096 x 32 (token, query head) pairs the form that issues all loads at once: 128 tokens per workgroup, 256 from
+    // 2048 x 32 pairs on.  Beyond, the matrix-core form, whose work is counted in (token, cache head) pairs: splits of 256
+    // tokens while that gives fewer than 256 workgroups, 512 up to 8192 x 32, 1024 above (sweeps of all three lengths and
+    // the other form; launches of both kernels, cold caches).  One query head per cache head: level with the vector form
+    // it replaces, 50.7 -> 49.0 us at 16 x 4096 tokens of 32 heads.  Grouped heads, 32 over 8: 16 sequences of 300 to 6000
+    // tokens 43.6 -> 20.7 us, 65536 tokens 44.2 -> 21.1, 16384 tokens 16.4 -> 11.6; 64 over 4 heads at 8192 tokens
+    // 16.0 -> 10.6 us; level at 4001 tokens of 32 over 8.
     const int rep = H_q / H_kv;
+    const long long pairs = total * H_kv;
+    int L = options().kv_tokens;
+    const bool matrix = L == 0 ? total * H_q >= 131072 : L > KV_MAX_L;
+    if (L == 0) {
+        if (matrix) L = pairs < 90000 ? 256 : pairs <= 262144 ? 512 : KV_STREAM_L;
+        else L = total * H_q < 65536 ? 128 : KV_MAX_L;
+    }
+    const int splits = (S + L - 1) / L;
     batch.H_q = H_q;
     batch.H_kv = H_kv;
-    // one index per (split, query head), padded to whole groups of 8 * rep (see kv_place)
-    const unsigned units = static_cast<unsigned>(splits) * static_cast<unsigned>(H_kv);
-    const dim3 grid(8u * static_cast<unsigned>(rep) * ((units + 7u) / 8u), 1u, static_cast<unsigned>(batched ? B : 1));
+    if (!batched) batch.v[0] = S;
+    const unsigned nseq = static_cast<unsigned>(batched ? B : 1);
     auto* kc = static_cast<const u32x4*>(k_codes);
     auto* vc = static_cast<const u32x4*>(v_codes);
     auto* kp = static_cast<const uint32_t*>(k_params);
     auto* vp = static_cast<const uint32_t*>(v_params);
     auto* part = static_cast<float*>(workspace);
-    auto launch = [&](auto kernel) {
-        kernel<<<grid, KV_THREADS, 0, st>>>(q, S, S_max, rep, splits, softmax_scale, kc, kp, vc, vp, part, batch);
-    };
+    if (matrix) {
+        const unsigned per = rep < 16 ? 1u : static_cast<unsigned>((rep + 15) / 16);  // sixteen query heads at most per workgroup
+        const dim3 grid(static_cast<unsigned>(splits) * static_cast<unsigned>(H_kv), per, nseq);
+        auto launch = [&](auto kernel) {
+            kernel<<<grid, KV_THREADS, 0, st>>>(q, static_cast<int>(q_dt), fused ? 1 : 0, S_max, rep, splits, softmax_scale, kc, kp, vc, vp, L,
+                                                part, batch);
+        };
+        if (rep == 1) launch(&kv4_attn_mfma_kernel<1>);
+        else if (rep == 2) launch(&kv4_attn_mfma_kernel<2>);
+        else if (rep <= 4) launch(&kv4_attn_mfma_kernel<4>);
+        else if (rep <= 8) launch(&kv4_attn_mfma_kernel<8>);
+        else launch(&kv4_attn_mfma_kernel<16>);
+    } else {
+        // one index per (split, query head), padded to whole groups of 8 * rep (see kv_place)
+        const unsigned units = static_cast<unsigned>(splits) * static_cast<unsigned>(H_kv);
+        const dim3 grid(8u * static_cast<unsigned>(rep) * ((units + 7u) / 8u), 1u, nseq);
+        auto launch = [&](auto kernel) {
+            kernel<<<grid, KV_THREADS, 0, st>>>(q, S, S_max, rep, splits, softmax_scale, kc, kp, vc, vp, part, batch);
+        };
 #define RCP_KV_LAUNCH(QDT, ITERS)                                        \
     do {                                                                 \
         if (batched) launch(&kv4_attn_kernel<QDT, ITERS, true>);         \
         else if (fused) launch(&kv4_attn_kernel<QDT, ITERS, false, true>); \
         else launch(&kv4_attn_kernel<QDT, ITERS, false>);                \
     } while (0)
-    auto launch_stream = [&](auto kernel) {
-        kernel<<<grid, KV_THREADS, 0, st>>>(q, S, S_max, rep, splits, softmax_scale, kc, kp, vc, vp, L, part, batch);
-    };
-#define RCP_KV_DISPATCH(QDT)                                                   \
-    do {                                                                       \
-        if (stream) {                                                          \
-            if (batched) launch_stream(&kv4_attn_stream_kernel<QDT, true>);    \
-            else if (fused) launch_stream(&kv4_attn_stream_kernel<QDT, false, true>); \
-            else launch_stream(&kv4_attn_stream_kernel<QDT, false>);           \
-        } else if (L == 64) RCP_KV_LAUNCH(QDT, 1);                             \
-        else if (L == 128) RCP_KV_LAUNCH(QDT, 2);                              \
-        else RCP_KV_LAUNCH(QDT, 4);                                            \
+#define RCP_KV_DISPATCH(QDT)                       \
+    do {                                           \
+        if (L == 64) RCP_KV_LAUNCH(QDT, 1);        \
+        else if (L == 128) RCP_KV_LAUNCH(QDT, 2);  \
+        else RCP_KV_LAUNCH(QDT, 4);                \
     } while (0)
-    if (q_dt == RCP_F32) RCP_KV_DISPATCH(RCP_F32);
-    else if (q_dt == RCP_F16) RCP_KV_DISPATCH(RCP_F16);
-    else RCP_KV_DISPATCH(RCP_BF16);
+        if (q_dt == RCP_F32) RCP_KV_DISPATCH(RCP_F32);
+        else if (q_dt == RCP_F16) RCP_KV_DISPATCH(RCP_F16);
+        else RCP_KV_DISPATCH(RCP_BF16);
 #undef RCP_KV_DISPATCH
 #undef RCP_KV_LAUNCH
+    }
     int rc = check_launch("rcp_kv4_attn_decode");
     if (rc != RCP_OK) return rc;
     int groups = (splits + 3) / 4;
     if (groups > KV_CT / KV_D) groups = KV_CT / KV_D;
     const unsigned cgrid = static_cast<unsigned>(H_q) * (batched ? B : 1);
-    auto combine = [&](auto kernel) { kernel<<<cgrid, groups * KV_D, 0, st>>>(part, splits, groups, out, L, batch); };
+    auto combine = [&](auto kernel) { kernel<<<cgrid, groups * KV_D, 0, st>>>(part, splits, groups, out, L, matrix ? 1.0f : 1.44269504088896340736f, batch); };
     if (batched) {
         if (out_dt == RCP_F16) combine(&kv4_combine_kernel<true, true>);
         else combine(&kv4_combine_kernel<false, true>);

@@ -29,3 +29,41 @@ def test_kronecker_rotation_of_several_tokens_on_the_matrix_cores(M, n, m, dtype
     # binary32 sums of m products, then log2(n) butterfly levels and the norm: each rounds relative to the token's norm
     bound = (m + np.log2(n) + 2) * 2.0 ** -24 * np.linalg.norm(x64, axis=1, keepdims=True)
     assert np.all(np.abs(y - ref) <= bound)
+
+
+@pytest.mark.parametrize("H_q,H_kv,S,tokens", [
+    (2, 2, 1, 512),        # one token: three wavefronts without work
+    (4, 2, 63, 512), (6, 2, 64, 512), (8, 2, 65, 512),   # 2, 3 and 4 query heads per cache head around one chunk
+    (10, 2, 255, 512), (16, 2, 257, 512),                # 5 and 8 heads, around one chunk of each wavefront
+    (12, 1, 513, 512), (16, 1, 1100, 512),               # 9 to 16 heads, several splits
+    (20, 1, 300, 1024), (36, 2, 700, 2048),              # more than sixteen query heads: several workgroups per cache head
+    (64, 4, 2100, 0), (32, 8, 5000, 0), (8, 8, 20000, 0),  # automatic split length: 256, 512, 512
+])
+@pytest.mark.parametrize("q_dtype", [torch.float16, torch.float32, torch.bfloat16])
+def test_attention_of_grouped_heads_on_the_matrix_cores(H_q, H_kv, S, tokens, q_dtype):
+    """Codes, query and weights enter the matrix cores as exact binary16 pieces: the result is held to a few binary32
+    roundings of the terms (2^-20 of what a row of the sum holds), far inside the stated 1e-3."""
+    print(f"kv4 mfma H_q={H_q} H_kv={H_kv} S={S} tokens={tokens} {q_dtype}", flush=True)
+    cache = []
+    for name, rotate in (("k", True), ("v", False)):
+        c, p = rcp.kv4_new_cache(H_kv, S + 3, DEV)
+        x = rcp_synth.kv_vectors(31, name, S, H_kv)
+        if name == "v":  # value steps over twelve powers of two, growing and shrinking along the sequence
+            x = (x * np.exp2(6 * np.sin(np.arange(S) / 40.0))[:, None, None]).astype(np.float16)
+        rcp.kv4_append(torch.from_numpy(x).to(DEV), 0, c, p, rotate=rotate)
+        cache += [c, p]
+    q = torch.from_numpy(rcp_synth.query_vectors(31, f"q{H_q}", H_q)).to(DEV).to(q_dtype)
+    rcp.set_option("kv_tokens", tokens)
+    try:
+        out = rcp.kv4_attn_decode(q, S, *cache, 0.3)   # sharp scores: the reference of the exponentials moves
+    finally:
+        rcp.set_option("reset", 0)
+    host = [a.cpu().numpy() for a in cache]
+    q64 = q.double().cpu().numpy()
+    ref = oracle.kv4_attn_decode(q64, S, *host, 0.3)
+    K, V = (np.abs(oracle.kv4_dequant(host[i], host[i + 1], 0, S)) for i in (0, 2))
+    rep = H_q // H_kv
+    for h in range(H_q):
+        score = 0.3 * np.abs(q64[h]) @ (np.abs(K[:, h // rep]).max(axis=0))   # bound of |score|: relative error of a weight
+        bound = (2.0 ** -20 * (1 + score)) * V[:, h // rep].max()
+        assert np.abs(out[h].double().cpu().numpy() - ref[h]).max() <= bound, h
