@@ -158,7 +158,8 @@ int rcp_version(void);
  *                  per wavefront on)
  *   "gemm_rows"    output rows per workgroup of the matrix-core kernel: 16 (four lanes per group of four rows), or
  *                  20, 24 .. 64 (one lane per group); automatic = 16 up to 8192 rows, else the smallest count that
- *                  gives every compute unit the same number of workgroups
+ *                  gives every compute unit the same number of workgroups.  With group-wise tables: rounded up to blocks
+ *                  of sixteen rows; automatic = as many blocks as one workgroup per compute unit takes, at most eight
  *   "kv_tokens"    cached tokens per workgroup of rcp_kv4_attn_decode: 64, 128, 256 (all loads of a workgroup
  *                  issued at once), 512, 1024, 2048 (the matrix-core kernel for long contexts, batches and grouped heads)
  *   "gemv_waves"   wavefronts per workgroup of the fused one-token GEMV (rcp_quant_w2a4_gemv): 4, 8

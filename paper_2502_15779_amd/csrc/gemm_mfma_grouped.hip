@@ -7,258 +7,228 @@
 //     O[m][h]       = S[m] * sum_g sum_l LUT[h][g][l] * P[m][h][g][l]        (fp32)
 //
 // One 128-column step of the matrix instruction is exactly one quantisation group, so the
-// accumulators are not carried from step to step: after the 24 instructions of a step (three
-// bit planes x four rows of a nibble x lo / hi part of the int4 activation, hi weighted 2^2 and
-// the 0.5 / 1 / 2 of the masks undone by the instruction's E8M0 scales) a lane holds the exact
-// plane sums F_p of 16 rows for one token and adds their products with the group's levels to 16
-// running fp32 outputs.  The per-group sum of q that level 0 needs comes from two more
-// instructions with an all-ones A operand.
+// accumulators are not carried from step to step: after three instructions (one per bit plane; the
+// 16 rows of the A operand are (row group, row in the nibble) pairs as in gemm_mfma.hip, the mask
+// and the E8M0 scale that undoes its 0.5 / 1 / 2 per-lane values, the int4 activations FP8 bytes)
+// a lane holds the exact plane sums F_p of four rows for one token and adds their products with
+// the group's levels to four running fp32 outputs.  The per-group sum T of q that level 0 needs comes
+// from one more instruction with an all-ones A operand.  The fourth row of a nibble is the FP4 sign
+// bit: instead of shifting it down, its lanes set 1.0 beside it, so the operand is 1 - 2 b, the sum
+// T - 2 F_p, and the row's coefficients absorb the difference.
 //
-// Work decomposition: a workgroup owns 64 output rows, its 8 wavefronts take the groups of K in
-// turn.  Lane l supplies row group l%16 and the two 16-byte units 2*(l/16), 2*(l/16)+1 of the
-// group (the grouped packed layout keeps the same unit of neighbouring groups side by side, so
-// the wavefronts of a workgroup, which work on neighbouring groups, share cache lines), and
-// token l%16 for the B operand.  The 512 bytes of levels a step needs are fetched once per
-// wavefront (16 bytes = two rows per lane); the fetching lane turns the four levels of a row
-// into the coefficients of (sum of q, F_b0, F_b1, F_b0&b1),
+// Work decomposition.  A wavefront takes a batch of four neighbouring groups, converts the
+// activations of the batch once, and walks the sixteen-row blocks of its workgroup with the next
+// block's weights and levels in flight: small loads that arrive one after the other, so that the
+// products overlap the stream.  (With 64 rows at a time in registers all wavefronts waited for the
+// end of the stream and computed after it; and the conversion weighs as much as the products of
+// sixteen rows.)  The four lanes of a quad share a row group: each fetches one group of the batch,
+// 64 consecutive bytes together -- in memory the same unit of neighbouring groups lies side by side,
+// while row groups are K/16 units apart -- and a step takes its group from one of the four lanes.
+// (Fetched in operand order, every lane is a request of its own and every cache line is asked for by
+// four wavefronts at different times: the loads alone took 13.6 of 16.1 us on 28672 x 4096.)
+// Token l%16 feeds the B operand; up to 8 (4) tokens, lanes 8 (4) apart convert different groups of
+// the batch and the operand of each is rotated into place.
+// The levels of the 64 (row, group) pairs of a block and batch come one pair to a lane, which turns
+// the four levels into the coefficients of (sum of q, F_b0, F_b1, F_b0&b1),
 //     O += L0*T + (L1-L0)*F0 + (L2-L0)*F1 + (L3-L2-L1+L0)*F3      (= sum_l L_l * P_l),
-// once for all 16 token lanes, and passes them through a wavefront-private LDS buffer from which
-// they are read back as broadcasts: four FMAs per (row, token) and group.  At the end every
-// wavefront parks its 16 x 64 partial outputs in LDS and the workgroup adds them in a fixed
-// order (deterministic), scales and stores.
+// once for all token lanes; they are read back from a wavefront-private LDS buffer as broadcasts.
+// Every wavefront parks its partial outputs in LDS and the workgroup adds them in a fixed order
+// (deterministic), scales and stores.
+#include <type_traits>
+
 #include "rcp_internal.hpp"
 
 namespace rcp {
 
-constexpr int MG_THREADS = 512;
-constexpr int MG_WAVES = MG_THREADS / 64;
-constexpr int MG_STRIDE = 65;  // LDS row stride in floats: conflict-free writes and reads
+constexpr int MG_WAVES = 16;   // wavefronts per workgroup at most
+constexpr int MG_MAX_BLOCKS = 8;   // sixteen-row blocks per workgroup at most (partial outputs in LDS)
 
-struct MgStage {
-    u32x4 wa, wb;  // units 2*kb and 2*kb+1 of the group: 4 rows x 32 columns, planes interleaved per cell
-    u32x4 xq;      // 32 int4 activations of this lane's token
-    u32x4 lut;     // lanes 0..31: 16 bytes of the levels of (row group lane/2, this group)
+// every lane of a quad gets what lane s of it holds
+template <int S>
+__device__ __forceinline__ uint32_t quad_broadcast(uint32_t v)
+{
+    return static_cast<uint32_t>(__builtin_amdgcn_mov_dpp(static_cast<int>(v), S * 0x55, 0xf, 0xf, true));
+}
+
+struct MgBlock {
+    u32x4 wa, wb;  // two units of (row group quad % 4, group quad lane): 4 rows x 16 columns each, planes interleaved per cell
+    uint2 lut;     // the levels of one (row, group)
 };
 
-// NARROW: the workgroup owns 4 row groups (16 output rows): the 16 rows of the A operand are (row group,
-// row in the nibble) pairs as in gemm_mfma.hip, the mask and its E8M0 scale are per-lane values, and
-// one instruction per plane and activation part covers all four rows of a nibble.
-// WANTP: the per-group sums are written to Pout as well (a verification output: with its stores and branches in the
-// loop the wide form needs 221 registers instead of 102, which leaves room for a single workgroup on a compute unit).
-template <bool OUT_F16, bool NARROW, bool WANTP>
-__global__ __launch_bounds__(MG_THREADS) void gemm_mfma_grouped_kernel(const uint4* __restrict__ packed,
+// BATCH: groups a wavefront takes at a time: four (one 64-byte piece per row group and unit), or one (short K, where four
+// would leave most wavefronts without work).
+// TK: tokens a B operand holds (16, 8 or 4): the smallest of them that is not below M.
+// WANTP: the per-group sums are written to Pout as well (a verification output).
+template <bool OUT_F16, bool WANTP, int BATCH, int TK>
+__global__ __launch_bounds__(64 * MG_WAVES) void gemm_mfma_grouped_kernel(const uint4* __restrict__ packed,
                                                                        const uint4* __restrict__ codebook, int N, int K,
                                                                        const uint4* __restrict__ xq,
-                                                                       const uint16_t* __restrict__ scale, int M, int W,
+                                                                       const uint16_t* __restrict__ scale, int M, int W, int NB,
                                                                        void* __restrict__ out, int32_t* __restrict__ Pout)
 {
-    __shared__ float slab[MG_WAVES * 16 * MG_STRIDE];  // [wavefront][token][row of the block]
-    __shared__ float4 coef_lds[MG_WAVES][64];          // [wavefront][row of the block]: coefficients of (T, F0, F1, F3)
+    extern __shared__ float4 mg_lds[];
+    // (W wavefronts and NB blocks of the workgroup are arguments: the launch dimensions would have to be fetched from memory)
     const int tid = threadIdx.x;
     const int lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    // (W, the wavefronts of the workgroup, is an argument: the launch dimensions would have to be fetched from memory)
-    const int i = lane & 15, kb = lane >> 4;
+    float4* const coef = mg_lds + wave * (BATCH * 16);                    // [group][row]: of (T, F0, F1, F3)
+    const int stride = 16 * NB + 1;                                          // floats per token: conflict-free
+    float* const slab = reinterpret_cast<float*>(mg_lds + W * (BATCH * 16));  // [wavefront][token][row]
+    const int i = lane & 15, kb = lane >> 4, t = lane & 3;
     const int U = K / 16, G = N / 4, NG = K / RCP_GROUP;
-    constexpr int RB = NARROW ? 16 : 64;   // output rows of the workgroup
-    constexpr int RGB = RB / 4;            // its row groups
-    const int rg = NARROW ? static_cast<int>(blockIdx.x) * 4 + (i >> 2) : static_cast<int>(blockIdx.x) * 16 + i;
-    // NARROW: this lane's row of the nibble as a mask, the shift that brings the fourth row (the FP4 sign
-    // bit) down, and the scale that undoes the mask's 0.5 / 1 / 2
-    const uint32_t row_mask = (i & 3) == 0 ? 0x11111111u : (i & 3) == 1 ? 0x22222222u : 0x44444444u;
-    const int row_shift = (i & 3) == 3 ? 1 : 0;
-    const int row_scale = (i & 3) == 0 ? 0x80 : (i & 3) == 1 ? 0x7f : 0x7e;
+    const int rg0 = static_cast<int>(blockIdx.x) * 4 * NB;
+    // this lane's row of the nibble as a mask, what stands beside the fourth row (the FP4 sign bit), and the scale that
+    // undoes the mask's 0.5 / 1 / 2
+    const uint32_t row_mask = 0x11111111u << t, row_one = t == 3 ? 0x22222222u : 0u;
+    const int row_scale = t == 0 ? 0x80 : t == 2 ? 0x7e : 0x7f;
 
     const __amdgpu_buffer_rsrc_t wres = __builtin_amdgcn_make_buffer_rsrc(
         const_cast<uint4*>(packed), 0, static_cast<int>(static_cast<unsigned>(G) * static_cast<unsigned>(U) * 16u), 0x00020000);
     const __amdgpu_buffer_rsrc_t cres = __builtin_amdgcn_make_buffer_rsrc(
         const_cast<uint4*>(codebook), 0, static_cast<int>(static_cast<unsigned>(G) * static_cast<unsigned>(NG) * 32u), 0x00020000);
-    // tokens beyond M start beyond the end of the resource and read as zero
     const __amdgpu_buffer_rsrc_t xres =
         __builtin_amdgcn_make_buffer_rsrc(const_cast<uint4*>(xq), 0, M * (K / 2), 0x00020000);
-    const unsigned row_base = rg < G ? static_cast<unsigned>(rg) * U * 16u : 0x80000000u;
-    const unsigned xbase = static_cast<unsigned>(i) * (K / 2) + kb * 16u;
-    // the piece of the levels this lane fetches: row group lane/2 of the block, half lane&1
-    const int lut_rg = blockIdx.x * RGB + (lane >> 1);
-    const unsigned lut_base = (lane < 2 * RGB && lut_rg < G) ? static_cast<unsigned>(lut_rg) * NG * 32u + (lane & 1) * 16u : 0x80000000u;
+    constexpr unsigned OUTSIDE = 0x80000000u;            // beyond every resource: reads as zero
+    constexpr int PER = 16 / TK, NX = BATCH / PER;
+    static_assert(BATCH == 4 || (BATCH == 1 && TK == 16), "");    // groups per converted operand, conversions per batch
+    constexpr int SC_ONE = 0x7f;
 
-    auto load = [&](int group_index, MgStage& st) {
-        const int g = __builtin_amdgcn_readfirstlane(group_index);  // uniform: scalar offsets
-        const bool ok = g < NG;
-        const int round = g >> 5;
+    const int batches = (NG + BATCH - 1) / BATCH;
+    const int lg = BATCH == 1 ? 0 : (lane >> 2) & 3;  // the group of this lane's levels; row group lane / 16, row lane % 4
+    const int wg = BATCH == 1 ? 0 : t;                // the group of this lane's weights
+    // Groups past the end of K and row groups past the end of N lie outside the resources: they read zeros and add zeros.
+    auto load = [&](int b, int block, MgBlock& st) {
+        const int g0 = BATCH * b, round = g0 >> 5;
         const int R = min(32, NG - 32 * round);
-        const unsigned pos = 256u * round + 2u * kb * R + (g & 31);  // unit 2*kb of group g; unit 2*kb+1 is R further
-        const unsigned wo = (ok && row_base != 0x80000000u) ? row_base + pos * 16u : 0x80000000u;
+        const unsigned unit = 256u * round + static_cast<unsigned>(a4b8_unit(kb)) * R + (g0 & 31) + wg;  // the second unit is 2 R further
+        const unsigned wo = g0 + wg < NG ? static_cast<unsigned>(rg0 + 4 * block + (i >> 2)) * U * 16u + unit * 16u : OUTSIDE;
+        const unsigned lo = g0 + lg < NG ? (static_cast<unsigned>(rg0 + 4 * block + kb) * NG + g0 + lg) * 32u + t * 8u : OUTSIDE;
         st.wa = __builtin_amdgcn_raw_buffer_load_b128(wres, static_cast<int>(wo), 0, 0);
-        st.wb = __builtin_amdgcn_raw_buffer_load_b128(wres, static_cast<int>(wo), ok ? R * 16 : 0, 0);
-        st.xq = __builtin_amdgcn_raw_buffer_load_b128(xres, static_cast<int>(ok ? xbase : 0x80000000u), ok ? g * 64 : 0, 0);
-        st.lut = __builtin_amdgcn_raw_buffer_load_b128(cres, static_cast<int>((ok && lut_base != 0x80000000u) ? lut_base : 0x80000000u),
-                                                       ok ? g * 32 : 0, 0);
+        st.wb = __builtin_amdgcn_raw_buffer_load_b128(wres, static_cast<int>(wo), g0 < NG ? R * 32 : 0, 0);
+        const auto l = __builtin_amdgcn_raw_buffer_load_b64(cres, static_cast<int>(lo), 0, 0);
+        st.lut = make_uint2(l[0], l[1]);
     };
-
-    MgStage sA, sB;
-    int g = wave;  // this wavefront's current group
-    load(g, sA);
-
-    // [v][r]: output of row 4*(4*kb + v) + r of the block for token i; NARROW: [v][0], row 4*kb + v
-    float o[4][4];
+    u32x4 xv[NX];
+    auto load_tokens = [&](int b) {
 #pragma unroll
-    for (int v = 0; v < 4; ++v)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) o[v][r] = 0.0f;
-
-    // E8M0 scales (byte 0 is used): 2^1, 2^0, 2^-1 undo the 0.5 / 1 / 2 of the masked nibbles;
-    // 2^2 weighs the high part of the activation
-    constexpr int SC_A[4] = {0x80, 0x7f, 0x7e, 0x7e};
-    constexpr int SC_ONE = 0x7f, SC_HI = 0x81;
-
-    auto compute = [&](const MgStage& cur, int gcur) {
-        if (lane < 2 * RGB) {
-            // two rows: 4 * (lane / 2) + 2 * (lane & 1) and the next one
-            const uint32_t lw[4] = {cur.lut.x, cur.lut.y, cur.lut.z, cur.lut.w};
-#pragma unroll
-            for (int rr = 0; rr < 2; ++rr) {
-                const float c0 = half_bits_to_float(static_cast<uint16_t>(lw[2 * rr] & 0xffffu));
-                const float c1 = half_bits_to_float(static_cast<uint16_t>(lw[2 * rr] >> 16));
-                const float c2 = half_bits_to_float(static_cast<uint16_t>(lw[2 * rr + 1] & 0xffffu));
-                const float c3 = half_bits_to_float(static_cast<uint16_t>(lw[2 * rr + 1] >> 16));
-                coef_lds[wave][2 * lane + rr] = make_float4(c0, c1 - c0, c2 - c0, ((c3 - c2) - c1) + c0);
-            }
-        }
-        const uint32_t xw[4] = {cur.xq.x, cur.xq.y, cur.xq.z, cur.xq.w};
-        v8i blo = {0, 0, 0, 0, 0, 0, 0, 0}, bhi = {0, 0, 0, 0, 0, 0, 0, 0};
-#pragma unroll
-        for (int d = 0; d < 4; ++d) {
-            blo[d] = static_cast<int>(fp4_lo(xw[d]));
-            bhi[d] = static_cast<int>(fp4_hi(xw[d]));
-        }
-        const v4f zero = {0.0f, 0.0f, 0.0f, 0.0f};
-        // sum of q over the group, for this lane's token (the same in all four registers)
-        const v8i ones = {0x22222222, 0x22222222, 0x22222222, 0x22222222, 0, 0, 0, 0};
-        v4f tq = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(ones, blo, zero, 4, 4, 0, SC_ONE, 0, SC_ONE);
-        tq = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(ones, bhi, tq, 4, 4, 0, SC_ONE, 0, SC_HI);
-
-        const uint32_t p0[4] = {cur.wa.x, cur.wa.z, cur.wb.x, cur.wb.z};
-        const uint32_t p1[4] = {cur.wa.y, cur.wa.w, cur.wb.y, cur.wb.w};
-        if constexpr (NARROW) {
-            v4f acc[3][1];
-            v8i an[3];
-#pragma unroll
-            for (int p = 0; p < 3; ++p) an[p] = v8i{0, 0, 0, 0, 0, 0, 0, 0};
-#pragma unroll
-            for (int d = 0; d < 4; ++d) {
-                an[0][d] = static_cast<int>((p0[d] >> row_shift) & row_mask);
-                an[1][d] = static_cast<int>((p1[d] >> row_shift) & row_mask);
-                an[2][d] = an[0][d] & an[1][d];
-            }
-#pragma unroll
-            for (int p = 0; p < 3; ++p) {
-                acc[p][0] = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(an[p], blo, zero, 4, 4, 0, row_scale, 0, SC_ONE);
-                acc[p][0] = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(an[p], bhi, acc[p][0], 4, 4, 0, row_scale, 0, SC_HI);
-            }
-            const bool store_pn = WANTP && i < M && gcur < NG;
-#pragma unroll
-            for (int v = 0; v < 4; ++v) {
-                const float4 c = coef_lds[wave][4 * kb + v];
-                const float F0 = acc[0][0][v], F1 = acc[1][0][v], F3 = acc[2][0][v];
-                float val = o[v][0];
-                val = fmaf(c.x, tq[v], val);
-                val = fmaf(c.y, F0, val);
-                val = fmaf(c.z, F1, val);
-                val = fmaf(c.w, F3, val);
-                o[v][0] = val;
-                if constexpr (WANTP) if (store_pn) {
-                    const int h = 4 * (static_cast<int>(blockIdx.x) * 4 + kb) + v;
-                    if (h < N)
-                        reinterpret_cast<int4*>(Pout)[(static_cast<size_t>(i) * N + h) * NG + gcur] =
-                            make_int4(static_cast<int>(tq[v] - F0 - F1 + F3), static_cast<int>(F0 - F3),
-                                      static_cast<int>(F1 - F3), static_cast<int>(F3));
-                }
-            }
-            return;
-        }
-        // one row of the nibble at a time: its three plane operands, six instructions, and the products with the
-        // coefficients of its 16 rows of the block
-        const bool store_p = WANTP && i < M && gcur < NG;
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            v8i a[3];
-#pragma unroll
-            for (int p = 0; p < 3; ++p) a[p] = v8i{0, 0, 0, 0, 0, 0, 0, 0};
-#pragma unroll
-            for (int d = 0; d < 4; ++d) {
-                const uint32_t m = r == 0 ? 0x11111111u : r == 1 ? 0x22222222u : 0x44444444u;
-                a[0][d] = static_cast<int>((p0[d] >> (r == 3 ? 1 : 0)) & m);
-                a[1][d] = static_cast<int>((p1[d] >> (r == 3 ? 1 : 0)) & m);
-                a[2][d] = a[0][d] & a[1][d];  // the mask of b0 & b1
-            }
-            v4f ar[3];
-#pragma unroll
-            for (int p = 0; p < 3; ++p) {
-                ar[p] = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(a[p], blo, zero, 4, 4, 0, SC_A[r], 0, SC_ONE);
-                ar[p] = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(a[p], bhi, ar[p], 4, 4, 0, SC_A[r], 0, SC_HI);
-            }
-            // plane sums (exact small integers in binary32) times the coefficients of (row, group)
-#pragma unroll
-            for (int v = 0; v < 4; ++v) {
-                const float4 c = coef_lds[wave][4 * (4 * kb + v) + r];
-                const float F0 = ar[0][v], F1 = ar[1][v], F3 = ar[2][v];
-                float val = o[v][r];
-                val = fmaf(c.x, tq[v], val);
-                val = fmaf(c.y, F0, val);
-                val = fmaf(c.z, F1, val);
-                val = fmaf(c.w, F3, val);
-                o[v][r] = val;
-                if constexpr (WANTP) if (store_p) {
-                    const int h = 4 * (blockIdx.x * 16 + 4 * kb + v) + r;
-                    if (h < N)
-                        reinterpret_cast<int4*>(Pout)[(static_cast<size_t>(i) * N + h) * NG + gcur] =
-                            make_int4(static_cast<int>(tq[v] - F0 - F1 + F3), static_cast<int>(F0 - F3),
-                                      static_cast<int>(F1 - F3), static_cast<int>(F3));
-                }
-            }
-            __builtin_amdgcn_sched_barrier(0);  // rows are not interleaved: one row's operands and sums live at a time
+        for (int n = 0; n < NX; ++n) {
+            const int g = BATCH * b + PER * n + i / TK;  // tokens beyond M lie outside the resource
+            xv[n] = __builtin_amdgcn_raw_buffer_load_b128(
+                xres, static_cast<int>(((g < NG) & (i % TK < M)) ? static_cast<unsigned>(i % TK) * (K / 2) + kb * 16u + 64u * g : OUTSIDE), 0, 0);
         }
     };
-    // Two register sets alternate: the next group's loads are in flight while the current one is
-    // computed.  Groups past the end of K read zeros and add zeros.
-    auto stage = [&](const MgStage& cur, MgStage& next) {
-        load(g + W, next);
-        // nothing that needs `cur` may move above the loads just issued
+    MgBlock cur;
+    load_tokens(wave);
+    load(wave, 0, cur);
+    for (int b = wave; b < batches; b += W) {  // uniform
         __builtin_amdgcn_sched_barrier(0);
-        compute(cur, g);
-        g += W;
-    };
-    while (true) {
-        stage(sA, sB);
-        if (g >= NG) break;
-        stage(sB, sA);
-        if (g >= NG) break;
-    }
-    // The last stage loaded (zeros) is "used" here on purpose: without a use on the exit path the
-    // optimiser sinks each stage's loads below the exit test and the loop is no longer pipelined.
-    const uint32_t keep = sA.wa.x | sA.wb.x | sA.xq.x | sA.lut.x | sB.wa.x | sB.wb.x | sB.xq.x | sB.lut.x;
-    if (__builtin_expect(K < 0, 0)) slab[0] = __uint_as_float(keep);  // never true
+        const int g0 = BATCH * b;
+        // the B operands of the four groups and the sums of q for this lane's token
+        v8i bop[BATCH];
+        float tq[BATCH];
+        const v4f zero = {0.0f, 0.0f, 0.0f, 0.0f};
+        const v8i ones = {0x22222222, 0x22222222, 0x22222222, 0x22222222, 0, 0, 0, 0};
+#pragma unroll
+        for (int s = 0; s < BATCH; ++s) {
+            if (s % PER == 0) {
+#pragma unroll
+                for (int d = 0; d < 4; ++d) {
+                    int first, second;
+                    int4_to_fp8(xv[s / PER][d], first, second);
+                    bop[s][2 * d] = first;
+                    bop[s][2 * d + 1] = second;
+                }
+            } else {  // this group was converted by the lanes TK further up: rotate them down
+#pragma unroll
+                for (int d = 0; d < 8; ++d) bop[s][d] = __builtin_amdgcn_mov_dpp(bop[s - 1][d], 0x120 + 16 - TK, 0xf, 0xf, true);
+            }
+            tq[s] = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(ones, bop[s], zero, 4, 0, 0, SC_ONE, 0, FP8_INT_SCALE)[0];
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        // the activations of the next batch (sixteen tokens leave no registers for that: 128 keep sixteen wavefronts on a
+        // compute unit)
+        if constexpr (TK < 16) load_tokens(b + W);
 
-    if constexpr (NARROW) {
-        float* dst = slab + (wave * 16 + i) * MG_STRIDE + 4 * kb;
+        auto compute = [&](const MgBlock& cur, int block) {
+            {
+                const float c0 = half_bits_to_float(static_cast<uint16_t>(cur.lut.x & 0xffffu));
+                const float c1 = half_bits_to_float(static_cast<uint16_t>(cur.lut.x >> 16));
+                const float c2 = half_bits_to_float(static_cast<uint16_t>(cur.lut.y & 0xffffu));
+                const float c3 = half_bits_to_float(static_cast<uint16_t>(cur.lut.y >> 16));
+                float4 c = make_float4(c0, c1 - c0, c2 - c0, ((c3 - c2) - c1) + c0);
+                if (t == 3) c = make_float4(fmaf(0.5f, (c.y + c.z) + c.w, c0), -0.5f * c.y, -0.5f * c.z, -0.5f * c.w);
+                coef[16 * lg + 4 * kb + t] = c;
+            }
+            float o[4] = {0.0f, 0.0f, 0.0f, 0.0f};  // rows 4 * kb + v of the block, this lane's token
+            auto step = [&](auto index) {
+                constexpr int s = decltype(index)::value;
+                const uint32_t p0[4] = {cur.wa.x, cur.wa.z, cur.wb.x, cur.wb.z};
+                const uint32_t p1[4] = {cur.wa.y, cur.wa.w, cur.wb.y, cur.wb.w};
+                v8i an[3];
 #pragma unroll
-        for (int v = 0; v < 4; ++v) dst[v] = o[v][0];
-    } else {
-        float* dst = slab + (wave * 16 + i) * MG_STRIDE + 16 * kb;
+                for (int p = 0; p < 3; ++p) an[p] = v8i{0, 0, 0, 0, 0, 0, 0, 0};
 #pragma unroll
-        for (int v = 0; v < 4; ++v)
+                for (int d = 0; d < 4; ++d) {
+                    an[0][d] = static_cast<int>(((BATCH == 1 ? p0[d] : quad_broadcast<s>(p0[d])) & row_mask) | row_one);
+                    an[1][d] = static_cast<int>(((BATCH == 1 ? p1[d] : quad_broadcast<s>(p1[d])) & row_mask) | row_one);
+                    an[2][d] = an[0][d] & an[1][d];
+                }
+                v4f F[3];
 #pragma unroll
-            for (int r = 0; r < 4; ++r) dst[4 * v + r] = o[v][r];
+                for (int p = 0; p < 3; ++p)
+                    F[p] = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(an[p], bop[s], zero, 4, 0, 0, row_scale, 0, FP8_INT_SCALE);
+#pragma unroll
+                for (int v = 0; v < 4; ++v) {
+                    const float4 c = coef[16 * s + 4 * kb + v];
+                    float val = fmaf(c.x, tq[s], o[v]);
+                    val = fmaf(c.y, F[0][v], val);
+                    val = fmaf(c.z, F[1][v], val);
+                    o[v] = fmaf(c.w, F[2][v], val);
+                    if constexpr (WANTP) {
+                        float f[3];
+#pragma unroll
+                        for (int p = 0; p < 3; ++p) f[p] = v == 3 ? 0.5f * (tq[s] - F[p][v]) : F[p][v];
+                        const int h = 4 * (rg0 + 4 * block + kb) + v;
+                        if (i < M && g0 + s < NG && h < N)
+                            reinterpret_cast<int4*>(Pout)[(static_cast<size_t>(i) * N + h) * NG + g0 + s] =
+                                make_int4(static_cast<int>(tq[s] - f[0] - f[1] + f[2]), static_cast<int>(f[0] - f[2]),
+                                          static_cast<int>(f[1] - f[2]), static_cast<int>(f[2]));
+                    }
+                }
+                __builtin_amdgcn_sched_barrier(0);  // one step's operands and sums live at a time
+            };
+            step(std::integral_constant<int, 0>{});
+            if constexpr (BATCH == 4) {
+                step(std::integral_constant<int, 1>{});
+                step(std::integral_constant<int, 2>{});
+                step(std::integral_constant<int, 3>{});
+            }
+            // (the products run in all lanes: the compiler would move them into the branch, which switches rows off)
+            asm volatile("" : "+v"(o[0]), "+v"(o[1]), "+v"(o[2]), "+v"(o[3]));
+            if (i < TK) {
+                float* const dst = slab + (wave * TK + i) * stride + 16 * block + 4 * kb;
+#pragma unroll
+                for (int v = 0; v < 4; ++v) dst[v] = b == wave ? o[v] : dst[v] + o[v];
+            }
+        };
+        for (int block = 0; block < NB; ++block) {
+            MgBlock next;  // the next block, or the first one of the next batch, is in flight while this one is computed
+            const bool last = block + 1 == NB;
+            load(last ? b + W : b, last ? 0 : block + 1, next);
+            __builtin_amdgcn_sched_barrier(0);
+            compute(cur, block);
+            cur = next;
+        }
+        if constexpr (TK == 16) load_tokens(b + W);
     }
     __syncthreads();
 
-    for (int idx = tid; idx < M * RB; idx += 64 * W) {
-        const int n = idx / RB, hh = idx % RB;
-        const int h = blockIdx.x * RB + hh;
+    for (int idx = tid; idx < M * 16 * NB; idx += 64 * W) {
+        const int n = idx / (16 * NB), hh = idx - n * (16 * NB);
+        const int h = 4 * rg0 + hh;
         if (h >= N) continue;
         float val = 0.0f;
-        for (int w = 0; w < W; ++w) val += slab[(w * 16 + n) * MG_STRIDE + hh];  // fixed order
+        for (int w = 0; w < W; ++w) val += slab[(w * TK + n) * stride + hh];  // fixed order
         val *= half_bits_to_float(scale[n]);
         const size_t oi = static_cast<size_t>(n) * N + h;
         if constexpr (OUT_F16) static_cast<__half*>(out)[oi] = __float2half_rn(val);
@@ -272,30 +242,53 @@ int launch_gemm_mfma_grouped(const void* packed, const void* codebook, int N, in
     if (static_cast<long long>(N) * K / 4 >= (1LL << 31))
         return fail(RCP_ERR_SHAPE, "rcp_w2a4_gemm_grouped: packed matrix of %lld bytes exceeds 2 GiB",
                     static_cast<long long>(N) * K / 4);
-    // 16-row workgroups when 64-row ones would leave most compute units idle ("gemm_rows" = 16 / 64 forces a form)
-    bool narrow = (N + 63) / 64 < num_compute_units() / 2;
-    if (options().gemm_rows != 0) narrow = options().gemm_rows == 16;
-    const int blocks = narrow ? (N + 15) / 16 : (N + 63) / 64;
     const int NG = K / RCP_GROUP;
-    int waves = MG_WAVES;
-    if (options().gemm_waves != 0) waves = options().gemm_waves;
-    while (waves > 1 && waves > NG) waves /= 2;
+    // One workgroup per compute unit, of as many sixteen-row blocks as that takes ("gemm_rows" sets the rows): the converted
+    // activations serve all of them, and no unit carries more than its share.  At 6 tokens, blocks per workgroup 1 / 2 / 3 /
+    // 4 / 7 / 8: 12288 x 4096 8.3 / 7.3 / 6.6 / 7.3 / 10.1 / 11.0 us, 28672 x 4096 15.3 / 12.5 / 12.7 / 11.1 / 10.6 / 11.3;
+    // the first form of this kernel (64 or 16 rows, one group at a time): 9.2 and 15.0.
+    const int total = (N + 15) / 16, cus = num_compute_units();
+    int nb = (total + cus - 1) / cus;
+    if (nb > MG_MAX_BLOCKS) nb = MG_MAX_BLOCKS;
+    if (options().gemm_rows != 0) nb = (options().gemm_rows + 15) / 16;
+    // One group at a time up to K = 2048, where batches of four would leave most of the wavefronts without work (256 x 512 at
+    // 16 tokens 3.8 against 2.5 us, 8192 x 2048 4.8 against 4.3; at K = 4096 4.65 against 4.8), else four.
+    const int batch = NG <= 16 ? 1 : 4;
+    // As few wavefronts as take the batches in the same number of rounds as the most would: sixteen (4096 x 14336, 6 tokens:
+    // 10.1 us with at most eight, 9.1 with fourteen).
+    const int batches = (NG + batch - 1) / batch;
+    int waves = options().gemm_waves != 0 ? options().gemm_waves : MG_WAVES;
+    const int rounds = (batches + waves - 1) / waves;
+    waves = (batches + rounds - 1) / rounds;
+    const int blocks = (total + nb - 1) / nb;
     auto* pk = static_cast<const uint4*>(packed);
     auto* cb = static_cast<const uint4*>(codebook);
     auto* x4 = static_cast<const uint4*>(xq);
     auto* sc = static_cast<const uint16_t*>(scale);
-#define RCP_MG(F16, NA)                                                                                                  \
-    do {                                                                                                                 \
-        if (P != nullptr) gemm_mfma_grouped_kernel<F16, NA, true><<<blocks, waves * 64, 0, st>>>(pk, cb, N, K, x4, sc, M, waves, out, P); \
-        else gemm_mfma_grouped_kernel<F16, NA, false><<<blocks, waves * 64, 0, st>>>(pk, cb, N, K, x4, sc, M, waves, out, P);             \
+    const int tk = P != nullptr || batch == 1 || M > 8 ? 16 : M > 4 ? 8 : 4;
+    const size_t lds = static_cast<size_t>(waves) * (batch * 16 * sizeof(float4) + tk * (16 * nb + 1) * sizeof(float));
+#define RCP_MG(F16, P_, B_, TK)                                                                                                 \
+    do {                                                                                                                        \
+        if (lds > 64 * 1024) {                                                                                                  \
+            const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_mfma_grouped_kernel<F16, P_, B_, TK>), \
+                                                     hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(lds));        \
+            if (e != hipSuccess) return fail(RCP_ERR_HIP, "rcp_w2a4_gemm_grouped: LDS opt-in failed: %s", hipGetErrorString(e)); \
+        }                                                                                                                       \
+        gemm_mfma_grouped_kernel<F16, P_, B_, TK><<<blocks, waves * 64, lds, st>>>(pk, cb, N, K, x4, sc, M, waves, nb, out, P); \
     } while (0)
-    if (narrow) {
-        if (out_dt == RCP_F16) RCP_MG(true, true);
-        else RCP_MG(false, true);
-    } else {
-        if (out_dt == RCP_F16) RCP_MG(true, false);
-        else RCP_MG(false, false);
-    }
+#define RCP_MG_TK(F16)                               \
+    do {                                             \
+        if (batch == 1) {                            \
+            if (P != nullptr) RCP_MG(F16, true, 1, 16);  \
+            else RCP_MG(F16, false, 1, 16);          \
+        } else if (P != nullptr) RCP_MG(F16, true, 4, 16);  \
+        else if (tk == 4) RCP_MG(F16, false, 4, 4);  \
+        else if (tk == 8) RCP_MG(F16, false, 4, 8);  \
+        else RCP_MG(F16, false, 4, 16);              \
+    } while (0)
+    if (out_dt == RCP_F16) RCP_MG_TK(true);
+    else RCP_MG_TK(false);
+#undef RCP_MG_TK
 #undef RCP_MG
     return check_launch("rcp_w2a4_gemm_grouped");
 }

@@ -448,6 +448,24 @@ __device__ __forceinline__ uint32_t fp4_hi(uint32_t x)
     return n3 | ((n3 >> 1) & ~n2) | (n2 >> 1);
 }
 
+// eight int4 -> eight FP8 (E4M3) bytes in order, each q * 2^-9: 0..8 with that unit are E4M3 codes of their own value
+// (subnormals and the first binade), so only the sign has to be split off
+__device__ __forceinline__ void int4_to_fp8(uint32_t x, int& first, int& second)
+{
+    const uint32_t sign = x & 0x88888888u, one = sign >> 3;
+    const uint32_t mag = ((x & 0x77777777u) ^ (sign - one)) + one;  // per nibble: |q|
+    const uint32_t even = (mag & 0x0f0f0f0fu) | ((sign << 4) & 0x80808080u);
+    const uint32_t odd = ((mag >> 4) & 0x0f0f0f0fu) | (sign & 0x80808080u);
+    first = static_cast<int>(__builtin_amdgcn_perm(odd, even, 0x05010400u));
+    second = static_cast<int>(__builtin_amdgcn_perm(odd, even, 0x07030602u));
+}
+// The k order of a 16x16x128 product with a four-bit A and an eight-bit B operand: nibble j of an A lane in block kb is
+// k = 32 kb + j, byte j of a B lane is k = 16 kb + j below 16 and 64 + 16 kb + (j - 16) from there on.  A B lane that
+// takes 32 consecutive columns (16-column units 2 kb and 2 kb + 1) therefore meets A lanes that take the units
+// a4b8_unit(kb) and a4b8_unit(kb) + 2.
+__device__ __forceinline__ int a4b8_unit(int kb) { return 4 * (kb & 1) + (kb >> 1); }
+constexpr int FP8_INT_SCALE = 0x88;  // E8M0 scale that takes the 2^-9 out again
+
 // ---- the int4 quantiser (shared by the activation kernels and the fused GEMV prologue) ----
 // S = fp16((ratio * a) / 7); 1 when that is zero, capped at the largest finite half.
 __device__ __forceinline__ uint16_t scale_bits_from_amax(float a, float clip_ratio)

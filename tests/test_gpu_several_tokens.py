@@ -67,3 +67,34 @@ def test_attention_of_grouped_heads_on_the_matrix_cores(H_q, H_kv, S, tokens, q_
         score = 0.3 * np.abs(q64[h]) @ (np.abs(K[:, h // rep]).max(axis=0))   # bound of |score|: relative error of a weight
         bound = (2.0 ** -20 * (1 + score)) * V[:, h // rep].max()
         assert np.abs(out[h].double().cpu().numpy() - ref[h]).max() <= bound, h
+
+
+@pytest.mark.parametrize("N,K", [
+    (8204, 512),     # groups one at a time; three blocks of rows per workgroup, the last workgroup ragged
+    (4100, 2048),    # the most groups of that form, two blocks
+    (4100, 2176),    # batches of four groups from here on: 17 groups, the last batch with one
+    (8204, 4096),
+    (1028, 8320),    # 65 groups: seventeen batches in two rounds, the third round of units one group wide
+])
+@pytest.mark.parametrize("M", [2, 4, 7, 9, 16])
+def test_grouped_products_of_several_row_blocks(N, K, M):
+    print(f"grouped gemm N={N} K={K} M={M}", flush=True)
+    NG = K // 128
+    idx = rcp_synth.random_indices(41, f"gb{N}x{K}", N, K)
+    q = rcp_synth.random_int4(41 + M, f"gb{K}", M, K)
+    rng = np.random.default_rng(41)
+    cb = np.sort(rng.standard_normal((N // 4, NG, 4, 4)) * 0.03, axis=3).astype(np.float16)
+    sc = (np.abs(rng.standard_normal(M)) * 0.2 + 0.05).astype(np.float16)
+    xq = ((q[:, 0::2].astype(np.uint8) & 0xF) | ((q[:, 1::2].astype(np.uint8) & 0xF) << 4)).astype(np.uint8)
+    packed = oracle.pack_indices_grouped(idx)
+    ref, P = oracle.w2a4_gemv_grouped(packed, cb.view(np.uint16).ravel(), N, K, xq, sc.view(np.uint16), M=M)
+    dev = [torch.from_numpy(np.ascontiguousarray(a)).to(DEV) for a in (packed, cb, xq, sc)]
+    out = rcp.w2a4_gemm_grouped(dev[0], dev[1], N, K, dev[2], dev[3], M, out_dtype=torch.float32).cpu().numpy()
+    lut = np.abs(cb.astype(np.float64)).transpose(0, 2, 1, 3).reshape(N, NG, 4)
+    terms = np.abs(P.reshape(M, N, NG, 4).astype(np.float64))
+    # binary32 multiply-adds on exact sums: at most 4 NG + 20 roundings, each relative to the magnitudes met so far, and the
+    # coefficients of the row in the sign bit double those
+    cond = sc.astype(np.float64)[:, None] * np.einsum("mngl,ngl->mn", terms, lut)
+    spread = sc.astype(np.float64)[:, None] * (8 * 128 * lut.max(axis=2).sum(axis=1))[None]
+    assert np.all(np.abs(out - ref.reshape(M, N)) <= (4 * NG + 20) * 2.0 ** -24 * (2 * cond + spread))
+    assert np.linalg.norm(out - ref.reshape(M, N)) <= 1e-5 * np.linalg.norm(ref)
