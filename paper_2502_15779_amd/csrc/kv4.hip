@@ -9,6 +9,8 @@
 // (16 tokens) per load instruction.
 #include <math.h>
 
+#include <type_traits>
+
 #include "rcp_internal.hpp"
 
 namespace rcp {
@@ -27,43 +29,58 @@ struct KvBatch {
 // ROT: the vector first goes through the normalised order-128 Hadamard transform: butterflies in
 // ascending stride order (1, 2, 4 in registers, 8 .. 64 between the sixteen lanes), each output
 // one IEEE add or subtract, then one multiplication by (float)(1/sqrt(128)).
+//
+// A prompt of thousands of tokens was bound by instruction issue, not by memory (2000 tokens of 8 heads, bf16 keys and
+// values, are 10 MB: 2 us at the rate of a copy), so the quantiser runs without divisions and the exchanges between lanes
+// are operands of the additions.  That launch: 6.7 -> 4.7 us; 2000 tokens of 32 heads 18.4 -> 13.1 us; one token of 32
+// heads 2.8 -> 2.4 us.
 // ---------------------------------------------------------------------------------------
-// BATCHED: row i of x belongs to sequence i (one new token each), whose cache starts at head
-// i * H of the pooled cache and whose position is batch.v[i].
-template <int DT, bool ROT, bool BATCHED>
-__device__ __forceinline__ void kv4_append_rows(const void* __restrict__ x, int rows, int H, int S_max, int pos, float clip_ratio,
-                                                uint32_t* __restrict__ codes, uint32_t* __restrict__ params, const KvBatch& batch,
-                                                int block)
+// a / s, correctly rounded, for s with at most eleven significant bits and rs = 1 / s up to a unit in the last place: the
+// residual a - q0 s of q0 = a rs is exact, so that q0 + (a - q0 s) rs misses the quotient by less than 2^-20 units in the
+// last place before its rounding, while a quotient by an eleven-bit divisor is 2^-12 units away from every midpoint of
+// two floats (it cannot be one: midpoint times divisor needs more than 24 bits).  Holds while q0 is finite; where the
+// quotient underflows both round to the integer 0.
+__device__ __forceinline__ float kv_quotient(float a, float s, float rs)
+{
+    const float q0 = __fmul_rn(a, rs);
+    return __fmaf_rn(__fmaf_rn(-q0, s, a), rs, q0);
+}
+
+template <int CTRL>
+__device__ __forceinline__ float kv_dpp(float v)
+{
+    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xf, 0xf, true));
+}
+
+struct KvCode {
+    uint32_t word;   // eight codes of this lane
+    uint32_t param;  // step and zero point of the vector
+};
+
+// Quantises the vector of a lane row from its eight elements per lane.  EXACT: divides; otherwise `far` is set where a
+// quotient may overflow, and the caller starts again with the divisions.
+template <int DT, bool ROT, bool EXACT>
+__device__ __forceinline__ KvCode kv4_quantise_vector(const Raw8<DT>& raw, int l, float clip_ratio, bool& far)
 {
     // every product and difference below is rounded on its own (hi_c - lo_c must not become a
     // fused multiply-add: for a constant vector it has to be exactly zero).  The pragma covers
     // the operators written in this body, hence plain * and - rather than the __f*_rn wrappers.
 #pragma clang fp contract(off)
-    const int row = block * 16 + (threadIdx.x >> 4);
-    const int l = threadIdx.x & 15;
-    const bool have = row < rows;
-    const int rr = have ? row : rows - 1;  // surplus lanes repeat the last vector and store nothing
     float v[8];
-    load8_as_float<DT>(x, static_cast<size_t>(rr) * KV_D + 8 * l, v);
+    widen8<DT>(raw, v);
     if constexpr (ROT) {
+        register_stages<3>(v, 0);
+        // element stride 8 * m: the partner is lane l ^ m of the row.  partner - v in the upper lane of a pair is written
+        // partner + (-v): one sign flip and one addition that reads the partner's lane
+        auto stage = [&](int m, auto partner) {
+            const uint32_t sign = (l & m) != 0 ? 0x80000000u : 0u;
 #pragma unroll
-        for (int st = 1; st < 8; st <<= 1)
-#pragma unroll
-            for (int e = 0; e < 8; ++e)
-                if ((e & st) == 0) {
-                    const float a = v[e], b = v[e + st];
-                    v[e] = a + b;
-                    v[e + st] = a - b;
-                }
-#pragma unroll
-        for (int m = 1; m < 16; m <<= 1) {  // element stride 8 * m: the partner is lane l ^ m of the row
-            const bool upper = (l & m) != 0;
-#pragma unroll
-            for (int e = 0; e < 8; ++e) {
-                const float other = __shfl_xor(v[e], m, 16);
-                v[e] = upper ? other - v[e] : v[e] + other;
-            }
-        }
+            for (int e = 0; e < 8; ++e) v[e] = partner(v[e]) + __uint_as_float(__float_as_uint(v[e]) ^ sign);
+        };
+        stage(1, [](float z) { return kv_dpp<0xB1>(z); });                 // quad 1,0,3,2
+        stage(2, [](float z) { return kv_dpp<0x4E>(z); });                 // quad 2,3,0,1
+        stage(4, [](float z) { return kv_dpp<0x1B>(kv_dpp<0x141>(z)); });  // half row mirrored, quads mirrored back
+        stage(8, [](float z) { return kv_dpp<0x128>(z); });                // row rotated by eight
         const float norm = 0.088388347648318440550f;  // (float)(1 / sqrt(128))
 #pragma unroll
         for (int e = 0; e < 8; ++e) v[e] = v[e] * norm;
@@ -74,9 +91,9 @@ __device__ __forceinline__ void kv4_append_rows(const void* __restrict__ x, int 
         lo = fminf(lo, v[j]);
         hi = fmaxf(hi, v[j]);
     }
-#define RCP_ROW_MINMAX(ctrl)                                                                                        \
-    lo = fminf(lo, __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(lo), ctrl, 0xf, 0xf, false)));    \
-    hi = fmaxf(hi, __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(hi), ctrl, 0xf, 0xf, false)))
+#define RCP_ROW_MINMAX(ctrl)          \
+    lo = fminf(lo, kv_dpp<ctrl>(lo)); \
+    hi = fmaxf(hi, kv_dpp<ctrl>(hi))
     RCP_ROW_MINMAX(0x128);
     RCP_ROW_MINMAX(0x124);
     RCP_ROW_MINMAX(0x122);
@@ -84,53 +101,105 @@ __device__ __forceinline__ void kv4_append_rows(const void* __restrict__ x, int 
 #undef RCP_ROW_MINMAX
     const float lo_c = clip_ratio * lo, hi_c = clip_ratio * hi;
     const float range = hi_c - lo_c;
-    const float raw = __fdiv_rn(range, 15.0f);
-    uint16_t sb = __half_as_ushort(__float2half_rn(raw));
+    // (an infinite range ends at the largest step either way)
+    uint16_t sb = __half_as_ushort(round_to_half(EXACT ? __fdiv_rn(range, 15.0f) : kv_quotient(range, 15.0f, 0.066666670143604279f)));
     if ((sb & 0x7fffu) == 0) sb = 0x3c00u;
     if ((sb & 0x7fffu) >= 0x7c00u) sb = 0x7bffu;
     const float s = half_bits_to_float(sb);
-    float zf = -rintf(__fdiv_rn(lo_c, s));
+    const float rs = __builtin_amdgcn_rcpf(s);
+    far = !(fmaxf(fabsf(lo), fabsf(hi)) * rs < 1.0e38f);
+    float zf = -rintf(EXACT ? __fdiv_rn(lo_c, s) : kv_quotient(lo_c, s, rs));
     zf = fminf(fmaxf(zf, -32768.0f), 32767.0f);
     const int z = static_cast<int>(zf);
     zf = static_cast<float>(z);
-    uint32_t word = 0;
+    float q[8];
 #pragma unroll
-    for (int j = 0; j < 8; ++j) {
-        const float r = __builtin_amdgcn_fmed3f(rintf(__fdiv_rn(v[j], s)) + zf, 0.0f, 15.0f);
-        word |= static_cast<uint32_t>(r) << (4 * j);
-    }
-    if (have) {
-        const int i = row / H, h = row - i * H;
-        const size_t slot = BATCHED ? static_cast<size_t>(row) * S_max + batch.v[i]
-                                    : static_cast<size_t>(h) * S_max + (pos + i);
-        codes[slot * 16 + l] = word;
-        if (l == 0) params[slot] = static_cast<uint32_t>(sb) | (static_cast<uint32_t>(z & 0xffff) << 16);
+    for (int j = 0; j < 8; ++j)
+        q[j] = __builtin_amdgcn_fmed3f(rintf(EXACT ? __fdiv_rn(v[j], s) : kv_quotient(v[j], s, rs)) + zf, 0.0f, 15.0f);
+    // four codes as one exact integer below 2^16
+    const float w0 = fmaf(q[3], 4096.0f, fmaf(q[2], 256.0f, fmaf(q[1], 16.0f, q[0])));
+    const float w1 = fmaf(q[7], 4096.0f, fmaf(q[6], 256.0f, fmaf(q[5], 16.0f, q[4])));
+    return {static_cast<uint32_t>(w0) | (static_cast<uint32_t>(w1) << 16),
+            static_cast<uint32_t>(sb) | (static_cast<uint32_t>(z & 0xffff) << 16)};
+}
+
+template <int DT, bool ROT>
+__device__ __forceinline__ KvCode kv4_quantise(const Raw8<DT>& raw, int l, float clip_ratio)
+{
+    bool far;
+    KvCode c = kv4_quantise_vector<DT, ROT, false>(raw, l, clip_ratio, far);
+    // uniform: the lanes of a row exchange values in there
+    if (__builtin_expect(__any(far), 0)) c = kv4_quantise_vector<DT, ROT, true>(raw, l, clip_ratio, far);
+    return c;
+}
+
+// Few tokens: sixteen consecutive (token, head) vectors per workgroup.
+// BATCHED: row i of x belongs to sequence i (one new token each), whose cache starts at head
+// i * H of the pooled cache and whose position is batch.v[i].
+template <int DT, bool ROT, bool BATCHED>
+__device__ __forceinline__ void kv4_append_rows(const void* __restrict__ x, int rows, int H, int S_max, int pos, float clip_ratio,
+                                                uint32_t* __restrict__ codes, uint32_t* __restrict__ params, const KvBatch& batch,
+                                                int block)
+{
+    const int row = block * 16 + (threadIdx.x >> 4);
+    const int l = threadIdx.x & 15;
+    const int rr = min(row, rows - 1);  // surplus lanes repeat the last vector and store nothing
+    const Raw8<DT> raw = load8_raw<DT>(x, static_cast<size_t>(rr) * KV_D + 8 * l);
+    const int i = rr / H, h = rr - i * H;
+    const size_t slot = BATCHED ? static_cast<size_t>(rr) * S_max + batch.v[i]
+                                : static_cast<size_t>(h) * S_max + (pos + i);
+    const KvCode c = kv4_quantise<DT, ROT>(raw, l, clip_ratio);
+    if (row < rows) {
+        codes[slot * 16 + l] = c.word;
+        if (l == 0) params[slot] = c.param;
     }
 }
 
-template <int DT, bool ROT, bool BATCHED>
+// Many tokens: sixteen consecutive tokens of one head per workgroup, so that its codes and parameters are contiguous in
+// the cache (consecutive rows of x leave a parameter by itself in each 128-byte line).  Two or four vectors per lane with
+// their loads side by side are slower throughout: there are enough wavefronts, and fewer of them hide less.
+template <int DT, bool ROT>
+__device__ __forceinline__ void kv4_append_tokens(const void* __restrict__ x, int n_tokens, int H, int S_max, int pos, float clip_ratio,
+                                                  uint32_t* __restrict__ codes, uint32_t* __restrict__ params, int block, int h)
+{
+    const int i = block * 16 + (threadIdx.x >> 4);
+    const int l = threadIdx.x & 15;
+    const Raw8<DT> raw = load8_raw<DT>(x, (static_cast<size_t>(min(i, n_tokens - 1)) * H + h) * KV_D + 8 * l);
+    const KvCode c = kv4_quantise<DT, ROT>(raw, l, clip_ratio);
+    if (i < n_tokens) {
+        const size_t slot = static_cast<size_t>(h) * S_max + (pos + i);
+        codes[slot * 16 + l] = c.word;
+        if (l == 0) params[slot] = c.param;
+    }
+}
+
+// TOKENS: blockIdx = (block of tokens, head) instead of blocks of rows
+template <int DT, bool ROT, bool BATCHED, bool TOKENS = false>
 __global__ __launch_bounds__(256) void kv4_append_kernel(const void* __restrict__ x, int rows, int H, int S_max, int pos,
                                                          float clip_ratio, uint32_t* __restrict__ codes,
                                                          uint32_t* __restrict__ params, KvBatch batch)
 {
-    kv4_append_rows<DT, ROT, BATCHED>(x, rows, H, S_max, pos, clip_ratio, codes, params, batch, blockIdx.x);
+    if constexpr (TOKENS) kv4_append_tokens<DT, ROT>(x, rows, H, S_max, pos, clip_ratio, codes, params, blockIdx.x, blockIdx.y);
+    else kv4_append_rows<DT, ROT, BATCHED>(x, rows, H, S_max, pos, clip_ratio, codes, params, batch, blockIdx.x);
 }
 
-// The new keys and the new values of the same tokens in one launch: blockIdx.y = 0 quantises the keys (rotated when
-// rotate_k is set), blockIdx.y = 1 the values (never rotated) -- the arithmetic of kv4_append_kernel on each.
-template <int DT>
+// The new keys and the new values of the same tokens in one launch: blockIdx.z = 0 quantises the keys (rotated when
+// rotate_k is set), blockIdx.z = 1 the values (never rotated) -- the arithmetic of kv4_append_kernel on each.
+template <int DT, bool TOKENS>
 __global__ __launch_bounds__(256) void kv4_append_kv_kernel(const void* __restrict__ k, const void* __restrict__ v, int rows, int H,
                                                             int S_max, int pos, int rotate_k, float clip_ratio,
                                                             uint32_t* __restrict__ k_codes, uint32_t* __restrict__ k_params,
                                                             uint32_t* __restrict__ v_codes, uint32_t* __restrict__ v_params)
 {
-    const KvBatch none = {};
-    if (blockIdx.y == 0) {
-        if (rotate_k) kv4_append_rows<DT, true, false>(k, rows, H, S_max, pos, clip_ratio, k_codes, k_params, none, blockIdx.x);
-        else kv4_append_rows<DT, false, false>(k, rows, H, S_max, pos, clip_ratio, k_codes, k_params, none, blockIdx.x);
-    } else {
-        kv4_append_rows<DT, false, false>(v, rows, H, S_max, pos, clip_ratio, v_codes, v_params, none, blockIdx.x);
-    }
+    auto append = [&](auto rot, const void* x, uint32_t* codes, uint32_t* params) {
+        constexpr bool ROT = decltype(rot)::value;
+        const KvBatch none = {};
+        if constexpr (TOKENS) kv4_append_tokens<DT, ROT>(x, rows, H, S_max, pos, clip_ratio, codes, params, blockIdx.x, blockIdx.y);
+        else kv4_append_rows<DT, ROT, false>(x, rows, H, S_max, pos, clip_ratio, codes, params, none, blockIdx.x);
+    };
+    if (blockIdx.z == 0 && rotate_k) append(std::true_type{}, k, k_codes, k_params);
+    else if (blockIdx.z == 0) append(std::false_type{}, k, k_codes, k_params);
+    else append(std::false_type{}, v, v_codes, v_params);
 }
 
 // ---------------------------------------------------------------------------------------
@@ -973,30 +1042,45 @@ size_t kv4_workspace_bytes(int H_q, int S)
     return static_cast<size_t>(H_q) * splits * KV_PART * sizeof(float);
 }
 
+// From sixteen tokens on (a lane row of a workgroup each) a workgroup takes tokens of one head; below, where lane rows
+// would be left without work, vectors in the order of x.
+static bool kv4_by_tokens(int n_tokens) { return n_tokens >= 16; }
+
+static dim3 kv4_append_grid(int n_tokens, int H, bool by_tokens, unsigned tensors)
+{
+    if (by_tokens) return dim3(static_cast<unsigned>((n_tokens + 15) / 16), static_cast<unsigned>(H), tensors);
+    return dim3(static_cast<unsigned>((n_tokens * H + 15) / 16), 1u, tensors);
+}
+
 // positions == nullptr: n_tokens tokens of one sequence from `pos` on; otherwise one token for each of
 // n_tokens sequences of a pooled cache, at positions[i]
 int launch_kv4_append(const void* x, rcp_dtype dt, int n_tokens, int H, int S_max, int pos, const int* positions, bool rotate,
                       float clip_ratio, void* codes, void* params, hipStream_t st)
 {
-    const int rows = n_tokens * H;
-    if (rows == 0) return RCP_OK;
-    const unsigned grid = static_cast<unsigned>((rows + 15) / 16);
+    if (n_tokens * H == 0) return RCP_OK;
     auto* c = static_cast<uint32_t*>(codes);
     auto* p = static_cast<uint32_t*>(params);
     KvBatch batch = {};
     const bool batched = positions != nullptr;
     if (batched)
         for (int i = 0; i < n_tokens; ++i) batch.v[i] = positions[i];
-    auto launch = [&](auto kernel) { kernel<<<grid, 256, 0, st>>>(x, rows, H, S_max, pos, clip_ratio, c, p, batch); };
-#define RCP_KV_APPEND(DT)                                                   \
-    do {                                                                    \
-        if (batched) {                                                      \
-            if (rotate) launch(&kv4_append_kernel<DT, true, true>);         \
-            else launch(&kv4_append_kernel<DT, false, true>);               \
-        } else {                                                            \
-            if (rotate) launch(&kv4_append_kernel<DT, true, false>);        \
-            else launch(&kv4_append_kernel<DT, false, false>);              \
-        }                                                                   \
+    const bool by_tokens = !batched && kv4_by_tokens(n_tokens) && H <= 65535;
+    const dim3 grid = kv4_append_grid(n_tokens, H, by_tokens, 1u);
+    auto launch = [&](auto kernel) {
+        kernel<<<grid, 256, 0, st>>>(x, by_tokens ? n_tokens : n_tokens * H, H, S_max, pos, clip_ratio, c, p, batch);
+    };
+#define RCP_KV_APPEND(DT)                                                          \
+    do {                                                                           \
+        if (batched) {                                                             \
+            if (rotate) launch(&kv4_append_kernel<DT, true, true>);                \
+            else launch(&kv4_append_kernel<DT, false, true>);                      \
+        } else if (by_tokens) {                                                    \
+            if (rotate) launch(&kv4_append_kernel<DT, true, false, true>);         \
+            else launch(&kv4_append_kernel<DT, false, false, true>);               \
+        } else {                                                                   \
+            if (rotate) launch(&kv4_append_kernel<DT, true, false>);               \
+            else launch(&kv4_append_kernel<DT, false, false>);                     \
+        }                                                                          \
     } while (0)
     if (dt == RCP_F32) RCP_KV_APPEND(RCP_F32);
     else if (dt == RCP_F16) RCP_KV_APPEND(RCP_F16);
@@ -1009,16 +1093,20 @@ int launch_kv4_append(const void* x, rcp_dtype dt, int n_tokens, int H, int S_ma
 int launch_kv4_append_kv(const void* k, const void* v, rcp_dtype dt, int n_tokens, int H, int S_max, int pos, bool rotate_k,
                          float clip_ratio, void* k_codes, void* k_params, void* v_codes, void* v_params, hipStream_t st)
 {
-    const int rows = n_tokens * H;
-    if (rows == 0) return RCP_OK;
-    const dim3 grid(static_cast<unsigned>((rows + 15) / 16), 2u);
+    if (n_tokens * H == 0) return RCP_OK;
+    const bool by_tokens = kv4_by_tokens(n_tokens) && H <= 65535;
+    const dim3 grid = kv4_append_grid(n_tokens, H, by_tokens, 2u);
     auto launch = [&](auto kernel) {
-        kernel<<<grid, 256, 0, st>>>(k, v, rows, H, S_max, pos, rotate_k ? 1 : 0, clip_ratio, static_cast<uint32_t*>(k_codes),
-                                     static_cast<uint32_t*>(k_params), static_cast<uint32_t*>(v_codes), static_cast<uint32_t*>(v_params));
+        kernel<<<grid, 256, 0, st>>>(k, v, by_tokens ? n_tokens : n_tokens * H, H, S_max, pos, rotate_k ? 1 : 0, clip_ratio,
+                                     static_cast<uint32_t*>(k_codes), static_cast<uint32_t*>(k_params),
+                                     static_cast<uint32_t*>(v_codes), static_cast<uint32_t*>(v_params));
     };
-    if (dt == RCP_F32) launch(&kv4_append_kv_kernel<RCP_F32>);
-    else if (dt == RCP_F16) launch(&kv4_append_kv_kernel<RCP_F16>);
-    else launch(&kv4_append_kv_kernel<RCP_BF16>);
+#define RCP_KV_APPEND(DT)                                                              \
+    by_tokens ? launch(&kv4_append_kv_kernel<DT, true>) : launch(&kv4_append_kv_kernel<DT, false>)
+    if (dt == RCP_F32) RCP_KV_APPEND(RCP_F32);
+    else if (dt == RCP_F16) RCP_KV_APPEND(RCP_F16);
+    else RCP_KV_APPEND(RCP_BF16);
+#undef RCP_KV_APPEND
     return check_launch("rcp_kv4_append_kv");
 }
 

@@ -98,3 +98,25 @@ def test_grouped_products_of_several_row_blocks(N, K, M):
     spread = sc.astype(np.float64)[:, None] * (8 * 128 * lut.max(axis=2).sum(axis=1))[None]
     assert np.all(np.abs(out - ref.reshape(M, N)) <= (4 * NG + 20) * 2.0 ** -24 * (2 * cond + spread))
     assert np.linalg.norm(out - ref.reshape(M, N)) <= 1e-5 * np.linalg.norm(ref)
+
+
+@pytest.mark.parametrize("n", [15, 16, 17, 32, 47])   # a workgroup takes sixteen vectors of any heads, then sixteen tokens of one
+@pytest.mark.parametrize("rotate", [False, True])
+@pytest.mark.parametrize("dtype", [torch.float16, torch.bfloat16, torch.float32])
+def test_appended_prompts_are_exact(n, rotate, dtype):
+    """Codes, steps and zero points byte for byte, at magnitudes from steps below the smallest binary16 number to quotients
+    beyond binary32 (there the quantiser divides)."""
+    print(f"kv4 append n={n} rotate={rotate} {dtype}", flush=True)
+    H, pos = 5, 3
+    x = rcp_synth.kv_vectors(51, f"prompt{n}", n, H).astype(np.float32)
+    x *= np.exp2(np.linspace(-30, 8 if dtype == torch.float16 else 30, n)).astype(np.float32)[:, None, None]
+    if not rotate:
+        x[1, 1], x[2, 2] = (6e4, -6e4) if dtype == torch.float16 else (3e38, -3e38)   # constant vectors: step 1
+        x[3, 3, ::2] = x[1, 1, 0]
+    xd = torch.from_numpy(x).to(DEV).to(dtype)
+    codes, params = rcp.kv4_new_cache(H, n + 5, DEV)
+    rcp.kv4_append(xd, pos, codes, params, rotate=rotate)
+    rc, rp = oracle.kv4_new_cache(H, n + 5)
+    oracle.kv4_append(xd.float().cpu().numpy(), pos, 0.95, rc, rp, rotate=rotate)
+    assert np.array_equal(params.cpu().numpy(), rp)
+    assert np.array_equal(codes.cpu().numpy(), rc)
