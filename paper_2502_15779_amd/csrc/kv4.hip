@@ -684,7 +684,8 @@ struct KvMfmaLds {
     union {
         struct {
             u32x4 v[4][256];                       // a chunk's value codes of each wavefront
-            uint32_t w[4][RP * KV_WSTRIDE];        // its softmax weights, hi | lo << 16; first the sums of q
+            float2 qc[4][RP];                      // sum of q in the units of the products, products -> score in powers of two
+            uint32_t w[4][RP * KV_WSTRIDE];        // its softmax weights, hi | lo << 16
         } run;
         struct {
             float red[4][RP][KV_D];
@@ -694,7 +695,7 @@ struct KvMfmaLds {
 };
 
 template <int RP>
-__global__ __launch_bounds__(KV_THREADS, RP <= 4 ? 3 : 2) void kv4_attn_mfma_kernel(const void* __restrict__ q, int q_dt, int rotate, int S_max, int rep,
+__global__ __launch_bounds__(KV_THREADS, RP == 8 ? 2 : 3) void kv4_attn_mfma_kernel(const void* __restrict__ q, int q_dt, int rotate, int S_max, int rep,
                                                                    int splits, float softmax_scale, const u32x4* __restrict__ k_codes,
                                                                    const uint32_t* __restrict__ k_params,
                                                                    const u32x4* __restrict__ v_codes,
@@ -748,8 +749,6 @@ __global__ __launch_bounds__(KV_THREADS, RP <= 4 ? 3 : 2) void kv4_attn_mfma_ker
     };
     // ---- the query: lane = (head i, elements 32 g ...) ----
     v8h qhi[4], qlo[4];
-    float qs[HV];     // sum of the query in the units of the products
-    float cs = 0.0f;  // products -> score in powers of two
     if (nchunks > 0) {
         // the query is requested first: memory answers in order and it is needed first
         float t[32];
@@ -793,20 +792,23 @@ __global__ __launch_bounds__(KV_THREADS, RP <= 4 ? 3 : 2) void kv4_attn_mfma_ker
             if (i >= R) t[e] = 0.0f;
             top = fmaxf(top, fabsf(t[e]));
         }
-        const int E = __builtin_amdgcn_frexp_expf(wave_max(top));  // the largest element becomes 2^13 .. 2^14
+        // The head's largest element becomes 2^13 .. 2^14.  One power of two per head and not one for the sixteen: an
+        // infinite element must not push the other heads out of binary16, nor a large head the small ones below it.
+        {
+            auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(top), __float_as_uint(top), false, false);
+            top = fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
+            r = __builtin_amdgcn_permlane32_swap(__float_as_uint(top), __float_as_uint(top), false, false);
+            top = fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
+        }
+        const int E = __builtin_amdgcn_frexp_expf(top);
 #pragma unroll
         for (int e = 0; e < 32; ++e) {
             t[e] = ldexpf(t[e], 14 - E);
             sum += t[e];
         }
         sum = fold32f(fold16f(sum, sum), fold16f(sum, sum));
-        uint32_t* const slot = lds.run.w[wave];
-        if (g == 0 && i < RP) slot[i] = __float_as_uint(sum);
+        if (g == 0 && i < RP) lds.run.qc[wave][i] = make_float2(sum, ldexpf(softmax_scale * 1.44269504088896340736f, E - 14));
         __builtin_amdgcn_wave_barrier();
-#pragma unroll
-        for (int v = 0; v < HV; ++v) qs[v] = __uint_as_float(slot[RP <= 4 ? v : RP == 8 ? 4 * (g & 1) + v : 4 * g + v]);
-        __builtin_amdgcn_wave_barrier();
-        cs = ldexpf(softmax_scale * 1.44269504088896340736f, E - 14);
 #pragma unroll
         for (int d = 0; d < 4; ++d) {
             KvHalves hi, lo;
@@ -849,7 +851,7 @@ __global__ __launch_bounds__(KV_THREADS, RP <= 4 ? 3 : 2) void kv4_attn_mfma_ker
         bool valid[SETS];
 #pragma unroll
         for (int s = 0; s < SETS; ++s) {
-            ks[s] = half_bits_to_float(static_cast<uint16_t>(kp[s] & 0xffffu)) * cs;
+            ks[s] = half_bits_to_float(static_cast<uint16_t>(kp[s] & 0xffffu));
             kz[s] = static_cast<float>(static_cast<int>(kp[s]) >> 16);
             sv[s] = half_bits_to_float(static_cast<uint16_t>(vp[s] & 0xffffu));
             zv[s] = static_cast<float>(static_cast<int>(vp[s]) >> 16);
@@ -881,13 +883,20 @@ __global__ __launch_bounds__(KV_THREADS, RP <= 4 ? 3 : 2) void kv4_attn_mfma_ker
                 for (int s = 0; s < SETS; ++s) sc[s][v] = D[s][v];
             }
         }
+        float2 qc[HV];  // fetched anew for each chunk: held, they would cost the third wavefront of a SIMD
+        {
+            int at = RP <= 4 ? 0 : RP == 8 ? 4 * (g & 1) : 4 * g;
+            asm("" : "+v"(at) : "s"(c));
+#pragma unroll
+            for (int v = 0; v < HV; ++v) qc[v] = lds.run.qc[wave][at + v];
+        }
         bool raise = false;
 #pragma unroll
         for (int s = 0; s < SETS; ++s) {
             raise |= sv[s] > vlim;
 #pragma unroll
             for (int v = 0; v < HV; ++v) {
-                sc[s][v] = valid[s] ? fmaf(-kz[s], qs[v], sc[s][v]) * ks[s] : -INFINITY;
+                sc[s][v] = valid[s] ? fmaf(-kz[s], qc[v].x, sc[s][v]) * (ks[s] * qc[v].y) : -INFINITY;
                 raise |= sc[s][v] > m[v] + KV_LAZY2;
             }
         }

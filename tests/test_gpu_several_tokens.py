@@ -69,6 +69,39 @@ def test_attention_of_grouped_heads_on_the_matrix_cores(H_q, H_kv, S, tokens, q_
         assert np.abs(out[h].double().cpu().numpy() - ref[h]).max() <= bound, h
 
 
+@pytest.mark.parametrize("rep", [2, 4, 8, 16])
+def test_query_heads_of_a_cache_head_do_not_touch_each_other(rep):
+    """One head with an infinite element, one with a NaN and one 2^30 times as large as the rest leave the other heads of
+    their cache head what they are without them."""
+    print(f"kv4 mfma independent heads rep={rep}", flush=True)
+    S, H_kv = 700, 4
+    cache = []
+    for name in ("k", "v"):
+        c, p = rcp.kv4_new_cache(H_kv, S, DEV)
+        rcp.kv4_append(torch.from_numpy(rcp_synth.kv_vectors(61, name, S, H_kv)).to(DEV), 0, c, p)
+        cache += [c, p]
+    q = torch.from_numpy(rcp_synth.query_vectors(61, f"q{rep}", rep * H_kv)).float().to(DEV)
+    bad = q.clone()
+    bad[0, 5], bad[rep, 7] = float("inf"), float("nan")
+    bad[2 * rep] *= 2.0 ** 30
+    rcp.set_option("kv_tokens", 512)
+    try:
+        want, got = (rcp.kv4_attn_decode(x, S, *cache, 0.1).cpu() for x in (q, bad))
+    finally:
+        rcp.set_option("reset", 0)
+    changed = {0, rep, 2 * rep}
+    K, V = (np.abs(oracle.kv4_dequant(cache[i].cpu().numpy(), cache[i + 1].cpu().numpy(), 0, S)) for i in (0, 2))
+    for h in range(rep * H_kv):
+        if h in changed:
+            continue
+        # not bit for bit: the references of the exponentials move for all heads of a wavefront at once, which rounds the
+        # weights anew -- both sides within the bound of test_attention_of_grouped_heads_on_the_matrix_cores
+        score = 0.1 * np.abs(q[h].cpu().numpy().astype(np.float64)) @ K[:, h // rep].max(axis=0)
+        bound = 2 * 2.0 ** -20 * (1 + score) * V[:, h // rep].max()
+        assert (got[h].double() - want[h].double()).abs().max().item() <= bound, h
+    assert not torch.isfinite(got[0]).any() and not torch.isfinite(got[rep]).any()
+
+
 @pytest.mark.parametrize("N,K", [
     (8204, 512),     # groups one at a time; three blocks of rows per workgroup, the last workgroup ragged
     (4100, 2048),    # the most groups of that form, two blocks
