@@ -80,6 +80,27 @@ def test_pack_grid_edge_values():
     assert np.array_equal(packed.cpu().numpy(), ref_packed)
 
 
+@pytest.mark.parametrize("K", [128, 2048, 2176])   # less than one workgroup of cells, one, one and a rest
+@pytest.mark.parametrize("dtype", [torch.float16, torch.bfloat16, torch.float32])
+@pytest.mark.parametrize("grouped", [False, True])
+def test_pack_of_values_that_are_no_numbers(K, dtype, grouped):
+    """The index counts the thresholds that are not above a value: 3 for +inf, 0 for -inf and NaN, in any column."""
+    _say(f"pack inf/nan K={K} {dtype} grouped={grouped}")
+    N = 8
+    units = (N, K // 128) if grouped else (N,)
+    rng = np.random.default_rng(7)
+    W = torch.from_numpy(rng.uniform(-1, 1, size=(N, K)).astype(np.float32)).to(dtype)
+    for at, value in ((0, np.inf), (3, -np.inf), (5, np.nan)):
+        W[:, at::13] = value
+    lo, hi = np.full(units, -0.75, np.float32), np.full(units, 0.8125, np.float32)
+    part = np.broadcast_to(np.array([0.25, 0.5, 0.25], np.float32), units + (3,)).copy()
+    T, _ = oracle.ldp_grid(lo.flat[0], hi.flat[0], *part.reshape(-1, 3)[0])
+    want = (W.float().numpy()[..., None] >= np.asarray(T, np.float32)).sum(axis=2)
+    pack, unpack = (rcp.pack_weights_grouped, rcp.unpack_indices_grouped) if grouped else (rcp.pack_weights, rcp.unpack_indices)
+    packed, _ = pack(W.to(DEV), _t(lo), _t(hi), _t(part))
+    assert np.array_equal(unpack(packed, N, K).cpu().numpy(), want)
+
+
 # ------------------------------------------------------------------------------------------
 # weight-only GEMV (16- / 32-bit activations)
 # ------------------------------------------------------------------------------------------
