@@ -605,8 +605,11 @@ __global__ __launch_bounds__(KV_THREADS) void kv4_attn_kernel(const void* __rest
 // Operands.  A code in a byte of its own is c * 2^-9 as an E4M3 number, and one instruction turns two of those into
 // binary16 numbers (7 operations for the eight codes of a dword).  Left as binary16 subnormals c * 2^-24 they would take
 // five, but the matrix unit aligns products by their nominal exponents: outputs were off by 4e-5 instead of 3e-7.
-// The other operand (query, softmax weights) is a sum of two binary16 numbers, hi + lo, 22 bits and more of each value,
-// in two instructions; products are exact and the sums binary32.  The (s, z) of a token stay outside the products:
+// The other operand (query, softmax weights) is a sum of two binary16 numbers, hi + lo, in two instructions; products are
+// exact and the sums binary32.  A piece keeps 11 bits down to 2^-14 and an absolute 2^-25 below, so the operands are scaled:
+// the query by a power of two per head (largest element 2^13 .. 2^14), the weights through their reference (below).  Both
+// then hold 22 bits and more of every value down to 2^-12 of the largest, and 2^-34 of the largest below that.
+// The (s, z) of a token stay outside the products:
 //   score = s_t (q . c_t - z_t sum q),   out = sum_t (p_t s_t) c_t - sum_t p_t s_t z_t.
 //   scores   rows = query heads, columns = 16 tokens, k = the 128 elements: the codes go from memory to registers in
 //            operand order (lane = token l % 16, 16 bytes l / 16 of it)
@@ -621,7 +624,8 @@ __global__ __launch_bounds__(KV_THREADS) void kv4_attn_kernel(const void* __rest
 typedef _Float16 v8h __attribute__((ext_vector_type(8)));
 typedef _Float16 v2h __attribute__((ext_vector_type(2)));
 typedef int v2i __attribute__((ext_vector_type(2)));
-constexpr float KV_LAZY2 = 5.0f;       // how far (in powers of two) a score may exceed the reference before it is raised
+constexpr float KV_W_TOP = 14.0f;      // the weights of a head stay below 2^14 (binary16 ends at 2^16) ...
+constexpr float KV_W_REF = 9.0f;       // ... and a raised reference puts the largest so far at 2^9
 constexpr int KV_WSTRIDE = 68;         // dwords per head of the weights in LDS: 64 tokens, padded off the bank period
 
 union KvHalves {
@@ -832,7 +836,6 @@ __global__ __launch_bounds__(KV_THREADS, RP == 8 ? 2 : 3) void kv4_attn_mfma_ker
         m[v] = -INFINITY;
         lsum[v] = zacc[v] = 0.0f;
     }
-    float vs = 0.0f, vlim = -1.0f;  // power of two on the weights that keeps them inside binary16, and the step it holds for
 
     for (int c = 0; c < nchunks; ++c) {
         const int base = first + 256 * c;
@@ -890,40 +893,35 @@ __global__ __launch_bounds__(KV_THREADS, RP == 8 ? 2 : 3) void kv4_attn_mfma_ker
 #pragma unroll
             for (int v = 0; v < HV; ++v) qc[v] = lds.run.qc[wave][at + v];
         }
-        bool raise = false;
+        // A weight of the product is p s = 2^(score - m) s, so the reference m of a head is held against score + log2 s: with
+        // the largest score alone, or the largest step of the chunk, one token of a large step and no attention would push
+        // the weights that matter below the binary16 pieces.  p itself stays below 2^(14 + 24) (the smallest step), as does
+        // a step of zero (a slot that was never written) with the same bound in its place.
+        float top[HV];  // the largest of score + log2 s of this lane's tokens
 #pragma unroll
         for (int s = 0; s < SETS; ++s) {
-            raise |= sv[s] > vlim;
+            const float ls = __builtin_amdgcn_logf(__builtin_amdgcn_fmed3f(fabsf(sv[s]), 0x1p-24f, 65504.0f));
 #pragma unroll
             for (int v = 0; v < HV; ++v) {
                 sc[s][v] = valid[s] ? fmaf(-kz[s], qc[v].x, sc[s][v]) * (ks[s] * qc[v].y) : -INFINITY;
-                raise |= sc[s][v] > m[v] + KV_LAZY2;
+                top[v] = s == 0 ? sc[s][v] + ls : fmaxf(top[v], sc[s][v] + ls);
             }
         }
-        // The reference m (one per head) and the power of two vs only have to keep the weights in range: they move when
-        // a score or a value step of the chunk leaves it (always on the first chunk, whose first token is valid).
-        if (__builtin_amdgcn_ballot_w64(raise) != 0) {  // uniform
-            float top = sv[0];
+        bool raise = false;
 #pragma unroll
-            for (int s = 1; s < SETS; ++s) top = fmaxf(top, sv[s]);
-            top = fmaxf(wave_max(top), 0.5f * vlim);
-            const int ev = __builtin_amdgcn_frexp_expf(top);
-            const float vs_new = ldexpf(1.0f, 9 - ev);
-            vlim = ldexpf(1.0f, ev + 1);  // steps below 2^10 after scaling, weights below 2^15
-            const float f = vs == 0.0f ? 0.0f : vs_new / vs;
-            vs = vs_new;
+        for (int v = 0; v < HV; ++v) raise |= top[v] > m[v] + KV_W_TOP;
+        // It only has to keep the weights in range and moves when one would leave it (always on the first chunk, whose
+        // first token is valid).
+        if (__builtin_amdgcn_ballot_w64(raise) != 0) {  // uniform
 #pragma unroll
             for (int v = 0; v < HV; ++v) {
-                float mt = sc[0][v];
-#pragma unroll
-                for (int s = 1; s < SETS; ++s) mt = fmaxf(mt, sc[s][v]);
-                const float m_new = fmaxf(m[v], kv_head_max<RP>(mt));
+                const float m_new = fmaxf(m[v], kv_head_max<RP>(top[v]) - KV_W_REF);
                 const float alpha = __builtin_amdgcn_exp2f(m[v] - m_new);  // 0 on the first chunk
                 m[v] = m_new;
                 lsum[v] *= alpha;
                 zacc[v] *= alpha;
 #pragma unroll
-                for (int b = 0; b < 8; ++b) acc[b][v] *= alpha * f;
+                for (int b = 0; b < 8; ++b) acc[b][v] *= alpha;
             }
         }
         uint32_t* const ww = lds.run.w[wave];
@@ -936,7 +934,7 @@ __global__ __launch_bounds__(KV_THREADS, RP == 8 ? 2 : 3) void kv4_attn_mfma_ker
                 lsum[v] += p;
                 zacc[v] = fmaf(w0, zv[s], zacc[v]);
                 const int head = RP <= 4 ? v : RP == 8 ? 4 * (g & 1) + v : 4 * g + v;
-                ww[head * KV_WSTRIDE + set_token(s)] = kv_split_half(w0 * vs);
+                ww[head * KV_WSTRIDE + set_token(s)] = kv_split_half(w0);
             }
         // weights back as operands: lane = (head i, tokens 16 g + 8 h ...)
         v8h phi[2], plo[2];
@@ -987,12 +985,11 @@ __global__ __launch_bounds__(KV_THREADS, RP == 8 ? 2 : 3) void kv4_attn_mfma_ker
     }
     __builtin_amdgcn_s_waitcnt(0);  // the surplus values have landed: LDS changes hands
     __syncthreads();
-    const float back = vs == 0.0f ? 0.0f : 1.0f / vs;
     if (4 * g < RP) {
 #pragma unroll
         for (int v = 0; v < HV; ++v) {
 #pragma unroll
-            for (int b = 0; b < 8; ++b) lds.end.red[wave][4 * g + v][16 * b + i] = acc[b][v] * back - zacc[v];
+            for (int b = 0; b < 8; ++b) lds.end.red[wave][4 * g + v][16 * b + i] = acc[b][v] - zacc[v];
             if (i == 0) {
                 lds.end.m[wave][4 * g + v] = m[v];
                 lds.end.l[wave][4 * g + v] = lsum[v];

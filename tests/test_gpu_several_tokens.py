@@ -69,6 +69,40 @@ def test_attention_of_grouped_heads_on_the_matrix_cores(H_q, H_kv, S, tokens, q_
         assert np.abs(out[h].double().cpu().numpy() - ref[h]).max() <= bound, h
 
 
+@pytest.mark.parametrize("H_q,H_kv", [(2, 2), (8, 2), (16, 2), (16, 1)])
+@pytest.mark.parametrize("loud", [5, 900])
+@pytest.mark.parametrize("ramp", [0.0, 40.0])   # scores that rise by about 32 along the sequence: the references move in every chunk
+def test_a_large_value_without_attention_leaves_the_rest_precise(H_q, H_kv, loud, ramp):
+    """One cached value 2^24 times as large as the others, at a token whose weight is below 1e-22: the error stays within a few
+    binary32 roundings of the values that are attended to."""
+    print(f"kv4 loud value H_q={H_q} H_kv={H_kv} loud={loud} ramp={ramp}", flush=True)
+    S, scale = 2048, 0.05
+    K, V = (rcp_synth.kv_vectors(71, n, S, H_kv).astype(np.float32) for n in "kv")
+    K[..., 0], V = 0.0, V * 2.0 ** -10
+    K[..., 1] += np.linspace(0, ramp, S)[:, None]
+    K[loud], K[loud, :, 0], V[loud] = 0.0, -20.0, 3e4 * np.sign(V[loud])
+    q = rcp_synth.query_vectors(71, f"q{H_q}", H_q).astype(np.float32)
+    q[:, 0], q[:, 1] = 64.0, 16.0
+    cache = []
+    for x in (K, V):
+        c, p = rcp.kv4_new_cache(H_kv, S, DEV)
+        rcp.kv4_append(torch.from_numpy(x).to(DEV), 0, c, p)
+        cache += [c, p]
+    rcp.set_option("kv_tokens", 2048)
+    try:
+        out = rcp.kv4_attn_decode(torch.from_numpy(q).to(DEV), S, *cache, scale)
+    finally:
+        rcp.set_option("reset", 0)
+    host = [a.cpu().numpy() for a in cache]
+    ref = oracle.kv4_attn_decode(q.astype(np.float64), S, *host, scale)
+    rest = np.arange(S) != loud
+    K, V = (np.abs(oracle.kv4_dequant(host[i], host[i + 1], 0, S))[rest] for i in (0, 2))
+    for h in range(H_q):
+        score = scale * np.abs(q[h].astype(np.float64)) @ K[:, h * H_kv // H_q].max(axis=0)
+        bound = 2.0 ** -20 * (1 + score) * V[:, h * H_kv // H_q].max()
+        assert np.abs(out[h].double().cpu().numpy() - ref[h]).max() <= bound, h
+
+
 @pytest.mark.parametrize("rep", [2, 4, 8, 16])
 def test_query_heads_of_a_cache_head_do_not_touch_each_other(rep):
     """One head with an infinite element, one with a NaN and one 2^30 times as large as the rest leave the other heads of
