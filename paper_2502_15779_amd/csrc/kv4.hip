@@ -911,11 +911,12 @@ __global__ __launch_bounds__(KV_THREADS, RP == 8 ? 2 : 3) void kv4_attn_mfma_ker
 #pragma unroll
         for (int v = 0; v < HV; ++v) raise |= top[v] > m[v] + KV_W_TOP;
         // It only has to keep the weights in range and moves when one would leave it (always on the first chunk, whose
-        // first token is valid).
+        // first token is valid), for that head alone: what a head returns does not depend on its neighbours.
         if (__builtin_amdgcn_ballot_w64(raise) != 0) {  // uniform
 #pragma unroll
             for (int v = 0; v < HV; ++v) {
-                const float m_new = fmaxf(m[v], kv_head_max<RP>(top[v]) - KV_W_REF);
+                const float t = kv_head_max<RP>(top[v]);
+                const float m_new = t > m[v] + KV_W_TOP ? t - KV_W_REF : m[v];
                 const float alpha = __builtin_amdgcn_exp2f(m[v] - m_new);  // 0 on the first chunk
                 m[v] = m_new;
                 lsum[v] *= alpha;
