@@ -610,7 +610,12 @@ __global__ __launch_bounds__(KV_THREADS) void kv4_attn_kernel(const void* __rest
 // the query by a power of two per head (largest element 2^13 .. 2^14), the weights through their reference (below).  Both
 // then hold 22 bits and more of every value down to 2^-12 of the largest, and 2^-34 of the largest below that.
 // The (s, z) of a token stay outside the products:
-//   score = s_t (q . c_t - z_t sum q),   out = sum_t (p_t s_t) c_t - sum_t p_t s_t z_t.
+//   score = s_t (q . c_t - z_t sum q),   out = sum_t (p_t s_t) (c_t - 8) - sum_t p_t s_t (z_t - 8).
+// Value codes enter less 8: the two sums of `out` grow with the tokens and cancel, and their binary32 roundings with them
+// (60000 tokens of 32 heads, error against 64 bits: 4.6e-7 with 0 .. 15, 1.2e-7 with -8 .. 7; the vector form 2.5e-7).  That
+// costs nine operations for the eight codes of a dword instead of seven: 16 sequences of up to 6000 tokens 23.1 -> 23.9 us,
+// otherwise within the noise.  (The same for the keys costs as much again and gains only
+// where the elements of a query share an offset.)
 //   scores   rows = query heads, columns = 16 tokens, k = the 128 elements: the codes go from memory to registers in
 //            operand order (lane = token l % 16, 16 bytes l / 16 of it)
 //   values   rows = query heads, columns = 16 elements, k = 32 tokens: the codes go to LDS as they lie in memory and
@@ -643,6 +648,22 @@ __device__ __forceinline__ v8h kv_code_halves(uint32_t w)
 }
 // which element of the dword stands in half e of register r of that operand
 __device__ __forceinline__ constexpr int kv_half_element(int r, int e) { return ((r & 2) >> 1) + 4 * (r & 1) + 2 * e; }
+
+// The eight codes of a dword less 8, elements 0,4 | 1,5 | 2,6 | 3,7: a code under the exponent of 1024 reads as 1024 + c, in
+// the next four bits up as 1024 + 16 c.
+__device__ __forceinline__ v8h kv_centred_halves(uint32_t w)
+{
+    uint32_t base = 0x64006400u;
+    asm("" : "+v"(base));
+    auto pair = [&](uint32_t x, uint32_t mask) { return __builtin_bit_cast(v2h, (x & mask) | base); };
+    const v2h by = {0.0625f, 0.0625f}, less = {-1032, -1032}, less16 = {-72, -72};
+    const uint32_t u = w >> 8;
+    const v2h a = pair(w, 0x000f000fu) + less, b = __builtin_elementwise_fma(pair(w, 0x00f000f0u), by, less16);
+    const v2h c = pair(u, 0x000f000fu) + less, d = __builtin_elementwise_fma(pair(u, 0x00f000f0u), by, less16);
+    return v8h{a[0], a[1], b[0], b[1], c[0], c[1], d[0], d[1]};
+}
+// which token stands in half e of register r of that operand
+__device__ __forceinline__ constexpr int kv_centred_element(int r, int e) { return r + 4 * e; }
 
 __device__ __forceinline__ uint32_t half_bits(float v) { return __half_as_ushort(__float2half_rn(v)); }
 
@@ -857,7 +878,7 @@ __global__ __launch_bounds__(KV_THREADS, RP == 8 ? 2 : 3) void kv4_attn_mfma_ker
             ks[s] = half_bits_to_float(static_cast<uint16_t>(kp[s] & 0xffffu));
             kz[s] = static_cast<float>(static_cast<int>(kp[s]) >> 16);
             sv[s] = half_bits_to_float(static_cast<uint16_t>(vp[s] & 0xffffu));
-            zv[s] = static_cast<float>(static_cast<int>(vp[s]) >> 16);
+            zv[s] = static_cast<float>((static_cast<int>(vp[s]) >> 16) - 8);
             valid[s] = base + set_token(s) < t_end;
             // computed before the next parameters arrive in the same registers
             asm volatile("" : "+v"(ks[s]), "+v"(kz[s]), "+v"(sv[s]), "+v"(zv[s]));
@@ -947,7 +968,7 @@ __global__ __launch_bounds__(KV_THREADS, RP == 8 ? 2 : 3) void kv4_attn_mfma_ker
             KvHalves hi, lo;
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
-                const uint32_t x = ws[kv_half_element(r, 0)], y = ws[kv_half_element(r, 1)];
+                const uint32_t x = ws[kv_centred_element(r, 0)], y = ws[kv_centred_element(r, 1)];
                 hi.w[r] = __builtin_amdgcn_perm(y, x, 0x05040100u);
                 lo.w[r] = __builtin_amdgcn_perm(y, x, 0x07060302u);
             }
@@ -968,7 +989,7 @@ __global__ __launch_bounds__(KV_THREADS, RP == 8 ? 2 : 3) void kv4_attn_mfma_ker
                 (__attribute__((address_space(3))) v2i*)(row + (((b >> 1) ^ f) * 16 + (b & 1) * 8)));
 #pragma unroll
             for (int h = 0; h < 2; ++h) {
-                const v8h x = kv_code_halves(static_cast<uint32_t>(r[h]));
+                const v8h x = kv_centred_halves(static_cast<uint32_t>(r[h]));
                 acc[b] = __builtin_amdgcn_mfma_f32_16x16x32_f16(plo[h], x, acc[b], 0, 0, 0);
                 acc[b] = __builtin_amdgcn_mfma_f32_16x16x32_f16(phi[h], x, acc[b], 0, 0, 0);
             }

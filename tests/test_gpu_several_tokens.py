@@ -103,6 +103,32 @@ def test_a_large_value_without_attention_leaves_the_rest_precise(H_q, H_kv, loud
         assert np.abs(out[h].double().cpu().numpy() - ref[h]).max() <= bound, h
 
 
+@pytest.mark.parametrize("H_q,H_kv", [(8, 8), (8, 4), (16, 4), (16, 2)])
+def test_sums_over_long_contexts_keep_their_precision(H_q, H_kv):
+    """The average of 30000 values that nearly cancel.  A sum of centred codes walks about zero: its partial sums stay below
+    sqrt(512) codes in a wavefront, so that roundings of 2^-24 of them and of the output (0.3 of a value's standard deviation)
+    leave less than 2^-24 of the deviation: 0.2 to 0.4 of it here, 0.4 to 0.5 with sums over few tokens a lane on the vector
+    unit.  Sums of the codes 0 .. 15 grow with every token: 0.9."""
+    print(f"kv4 long context H_q={H_q} H_kv={H_kv}", flush=True)
+    S, scale = 30000, 128 ** -0.5
+    cache = []
+    for name in ("k", "v"):
+        c, p = rcp.kv4_new_cache(H_kv, S, DEV)
+        rcp.kv4_append(torch.from_numpy(rcp_synth.kv_vectors(81, name, S, H_kv)).to(DEV), 0, c, p)
+        cache += [c, p]
+    q = torch.from_numpy(rcp_synth.query_vectors(81, f"q{H_q}", H_q)).to(DEV)
+    rcp.set_option("kv_tokens", 2048)
+    try:
+        out = rcp.kv4_attn_decode(q, S, *cache, scale)
+    finally:
+        rcp.set_option("reset", 0)
+    host = [a.cpu().numpy() for a in cache]
+    ref = oracle.kv4_attn_decode(q.double().cpu().numpy(), S, *host, scale)
+    V = oracle.kv4_dequant(host[2], host[3], 0, S).std(axis=0).repeat(H_q // H_kv, axis=0)
+    err = (out.double().cpu().numpy() - ref) / V
+    assert np.sqrt((err ** 2).mean()) <= 0.6 * 2.0 ** -24
+
+
 @pytest.mark.parametrize("rep", [2, 4, 8, 16])
 def test_query_heads_of_a_cache_head_do_not_touch_each_other(rep):
     """One head with an infinite element, one with a NaN and one 2^30 times as large as the rest leave the other heads of
