@@ -613,8 +613,8 @@ __global__ __launch_bounds__(KV_THREADS) void kv4_attn_kernel(const void* __rest
 //   score = s_t (q . c_t - z_t sum q),   out = sum_t (p_t s_t) (c_t - 8) - sum_t p_t s_t (z_t - 8).
 // Value codes enter less 8: the two sums of `out` grow with the tokens and cancel, and their binary32 roundings with them
 // (60000 tokens of 32 heads, error against 64 bits: 4.6e-7 with 0 .. 15, 1.2e-7 with -8 .. 7; the vector form 2.5e-7).  That
-// costs nine operations for the eight codes of a dword instead of seven: 16 sequences of up to 6000 tokens 23.1 -> 23.9 us,
-// otherwise within the noise.  (The same for the keys costs as much again and gains only
+// costs nine operations for the eight codes of a dword instead of seven: 1 to 4 % of the call where several query heads share
+// a cache head (16 sequences of up to 6000 tokens 23.1 -> 23.9 us, 40000 tokens of 32 over 16 heads 24.1 -> 25.0).  (The same for the keys costs as much again and gains only
 // where the elements of a query share an offset.)
 //   scores   rows = query heads, columns = 16 tokens, k = the 128 elements: the codes go from memory to registers in
 //            operand order (lane = token l % 16, 16 bytes l / 16 of it)
@@ -625,6 +625,8 @@ __global__ __launch_bounds__(KV_THREADS) void kv4_attn_kernel(const void* __rest
 // Bound by HBM for up to about eight query heads per cache head (16 matrix cycles and about as many vector cycles per
 // token and cache head on a SIMD, against 60 at 5.5 TB/s over 1024 SIMDs).
 // RP: query heads per cache head, rounded up to a power of two.
+// Registers: four wavefronts a SIMD for one and two heads (124 and 128 registers; left at 130, 120000 tokens of 16 over 8
+// heads take 34.3 us instead of 31.6), three for the others.
 // ---------------------------------------------------------------------------------------
 typedef _Float16 v8h __attribute__((ext_vector_type(8)));
 typedef _Float16 v2h __attribute__((ext_vector_type(2)));
@@ -720,7 +722,7 @@ struct KvMfmaLds {
 };
 
 template <int RP>
-__global__ __launch_bounds__(KV_THREADS, RP == 8 ? 2 : 3) void kv4_attn_mfma_kernel(const void* __restrict__ q, int q_dt, int rotate, int S_max, int rep,
+__global__ __launch_bounds__(KV_THREADS, RP <= 2 ? 4 : 3) void kv4_attn_mfma_kernel(const void* __restrict__ q, int q_dt, int rotate, int S_max, int rep,
                                                                    int splits, float softmax_scale, const u32x4* __restrict__ k_codes,
                                                                    const uint32_t* __restrict__ k_params,
                                                                    const u32x4* __restrict__ v_codes,
