@@ -129,6 +129,46 @@ def test_sums_over_long_contexts_keep_their_precision(H_q, H_kv):
     assert np.sqrt((err ** 2).mean()) <= 0.6 * 2.0 ** -24
 
 
+def _attention_of_heads(q64, lengths, host, scale, heads, B, H_kv):
+    """The oracle for some heads of every sequence, one query head per cache head."""
+    for b in range(B):
+        for h in heads:
+            at = slice(b * H_kv + h, b * H_kv + h + 1)
+            yield b, h, oracle.kv4_attn_decode(q64[b, h:h + 1], lengths[b], *[np.ascontiguousarray(a[at]) for a in host], scale)[0]
+
+
+@pytest.mark.parametrize("H,lengths", [
+    (32, [4095]), (32, [4097]),      # all loads at once up to here, the streaming form from here on
+    (32, [8192]), (5, [52500]),      # splits of 512 and of 1024 tokens
+    (8, [81900]), (8, [81920]),      # the last of the streaming form and the first of the matrix-core form
+    (16, [600, 4000, 1, 2900, 1500]),
+])
+@pytest.mark.parametrize("q_dtype", [torch.float16, torch.float32, torch.bfloat16])
+def test_attention_with_one_query_head_per_cache_head(H, lengths, q_dtype):
+    print(f"kv4 one query head per cache head H={H} {lengths} {q_dtype}", flush=True)
+    B, S, scale = len(lengths), max(lengths), 0.2
+    cache = []
+    for name in ("k", "v"):
+        c, p = rcp.kv4_new_cache(B * H, S + 2, DEV)
+        for b, n in enumerate(lengths):
+            rcp.kv4_append(torch.from_numpy(rcp_synth.kv_vectors(91 + b, name, n, H)).to(DEV), 0, c[b * H:(b + 1) * H], p[b * H:(b + 1) * H])
+        cache += [c, p]
+    q = torch.from_numpy(np.stack([rcp_synth.query_vectors(91 + b, f"q{H}", H) for b in range(B)])).to(DEV).to(q_dtype)
+    if B == 1:
+        out = rcp.kv4_attn_decode(q[0], S, *cache, scale)[None]
+        rotated = rcp.kv4_rotate_attn_decode(q[0], S, *cache, scale)
+        apart = rcp.kv4_attn_decode(rcp.rotate_act(q[0], rcp.Rotation.wht(128)), S, *cache, scale)
+        assert torch.equal(rotated, apart)
+    else:
+        out = rcp.kv4_attn_decode_batched(q, lengths, *cache, scale)
+    host, q64 = [a.cpu().numpy() for a in cache], q.double().cpu().numpy()
+    for b, h, ref in _attention_of_heads(q64, lengths, host, scale, (0, H // 2, H - 1), B, H):
+        K, V = (np.abs(oracle.kv4_dequant(host[i][b * H + h:b * H + h + 1], host[i + 1][b * H + h:b * H + h + 1], 0, lengths[b])) for i in (0, 2))
+        score = scale * np.abs(q64[b, h]) @ K[:, 0].max(axis=0)
+        # as in test_attention_of_grouped_heads_on_the_matrix_cores
+        assert np.abs(out[b, h].double().cpu().numpy() - ref).max() <= 2.0 ** -20 * (1 + score) * V.max(), (b, h)
+
+
 @pytest.mark.parametrize("rep", [2, 4, 8, 16])
 def test_query_heads_of_a_cache_head_do_not_touch_each_other(rep):
     """One head with an infinite element, one with a NaN and one 2^30 times as large as the rest leave the other heads of
