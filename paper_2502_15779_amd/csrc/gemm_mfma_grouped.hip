@@ -13,8 +13,7 @@
 // a lane holds the exact plane sums F_p of four rows for one token and adds their products with
 // the group's levels to four running fp32 outputs.  The per-group sum T of q that level 0 needs comes
 // from one more instruction with an all-ones A operand.  The fourth row of a nibble is the FP4 sign
-// bit: instead of shifting it down, its lanes set 1.0 beside it, so the operand is 1 - 2 b, the sum
-// T - 2 F_p, and the row's coefficients absorb the difference.
+// bit; its lanes shift it down by one.
 //
 // Work decomposition.  A wavefront takes a batch of four neighbouring groups, converts the
 // activations of the batch once, and walks the sixteen-row blocks of its workgroup with the next
@@ -77,10 +76,10 @@ __global__ __launch_bounds__(64 * MG_WAVES) void gemm_mfma_grouped_kernel(const 
     const int i = lane & 15, kb = lane >> 4, t = lane & 3;
     const int U = K / 16, G = N / 4, NG = K / RCP_GROUP;
     const int rg0 = static_cast<int>(blockIdx.x) * 4 * NB;
-    // this lane's row of the nibble as a mask, what stands beside the fourth row (the FP4 sign bit), and the scale that
-    // undoes the mask's 0.5 / 1 / 2
-    const uint32_t row_mask = 0x11111111u << t, row_one = t == 3 ? 0x22222222u : 0u;
-    const int row_scale = t == 0 ? 0x80 : t == 2 ? 0x7e : 0x7f;
+    // this lane's row of the nibble as a mask, how far it is shifted down (the fourth row is the FP4 sign bit), and the
+    // scale that undoes the 0.5 / 1 / 2 / 2 it then stands for
+    const uint32_t row_mask = 0x11111111u << t, row_shift = t == 3 ? 1u : 0u;
+    const int row_scale = t == 0 ? 0x80 : t == 1 ? 0x7f : 0x7e;
 
     const __amdgpu_buffer_rsrc_t wres = __builtin_amdgcn_make_buffer_rsrc(
         const_cast<uint4*>(packed), 0, static_cast<int>(static_cast<unsigned>(G) * static_cast<unsigned>(U) * 16u), 0x00020000);
@@ -155,8 +154,7 @@ __global__ __launch_bounds__(64 * MG_WAVES) void gemm_mfma_grouped_kernel(const 
                 const float c1 = half_bits_to_float(static_cast<uint16_t>(cur.lut.x >> 16));
                 const float c2 = half_bits_to_float(static_cast<uint16_t>(cur.lut.y & 0xffffu));
                 const float c3 = half_bits_to_float(static_cast<uint16_t>(cur.lut.y >> 16));
-                float4 c = make_float4(c0, c1 - c0, c2 - c0, ((c3 - c2) - c1) + c0);
-                if (t == 3) c = make_float4(fmaf(0.5f, (c.y + c.z) + c.w, c0), -0.5f * c.y, -0.5f * c.z, -0.5f * c.w);
+                const float4 c = make_float4(c0, c1 - c0, c2 - c0, ((c3 - c2) - c1) + c0);
                 coef[16 * lg + 4 * kb + t] = c;
             }
             float o[4] = {0.0f, 0.0f, 0.0f, 0.0f};  // rows 4 * kb + v of the block, this lane's token
@@ -169,8 +167,8 @@ __global__ __launch_bounds__(64 * MG_WAVES) void gemm_mfma_grouped_kernel(const 
                 for (int p = 0; p < 3; ++p) an[p] = v8i{0, 0, 0, 0, 0, 0, 0, 0};
 #pragma unroll
                 for (int d = 0; d < 4; ++d) {
-                    an[0][d] = static_cast<int>(((BATCH == 1 ? p0[d] : quad_broadcast<s>(p0[d])) & row_mask) | row_one);
-                    an[1][d] = static_cast<int>(((BATCH == 1 ? p1[d] : quad_broadcast<s>(p1[d])) & row_mask) | row_one);
+                    an[0][d] = static_cast<int>(((BATCH == 1 ? p0[d] : quad_broadcast<s>(p0[d])) & row_mask) >> row_shift);
+                    an[1][d] = static_cast<int>(((BATCH == 1 ? p1[d] : quad_broadcast<s>(p1[d])) & row_mask) >> row_shift);
                     an[2][d] = an[0][d] & an[1][d];
                 }
                 v4f F[3];
@@ -185,14 +183,11 @@ __global__ __launch_bounds__(64 * MG_WAVES) void gemm_mfma_grouped_kernel(const 
                     val = fmaf(c.z, F[1][v], val);
                     o[v] = fmaf(c.w, F[2][v], val);
                     if constexpr (WANTP) {
-                        float f[3];
-#pragma unroll
-                        for (int p = 0; p < 3; ++p) f[p] = v == 3 ? 0.5f * (tq[s] - F[p][v]) : F[p][v];
                         const int h = 4 * (rg0 + 4 * block + kb) + v;
                         if (i < M && g0 + s < NG && h < N)
                             reinterpret_cast<int4*>(Pout)[(static_cast<size_t>(i) * N + h) * NG + g0 + s] =
-                                make_int4(static_cast<int>(tq[s] - f[0] - f[1] + f[2]), static_cast<int>(f[0] - f[2]),
-                                          static_cast<int>(f[1] - f[2]), static_cast<int>(f[2]));
+                                make_int4(static_cast<int>(tq[s] - F[0][v] - F[1][v] + F[2][v]), static_cast<int>(F[0][v] - F[2][v]),
+                                          static_cast<int>(F[1][v] - F[2][v]), static_cast<int>(F[2][v]));
                     }
                 }
                 __builtin_amdgcn_sched_barrier(0);  // one step's operands and sums live at a time

@@ -218,12 +218,31 @@ def test_grouped_products_of_several_row_blocks(N, K, M):
     out = rcp.w2a4_gemm_grouped(dev[0], dev[1], N, K, dev[2], dev[3], M, out_dtype=torch.float32).cpu().numpy()
     lut = np.abs(cb.astype(np.float64)).transpose(0, 2, 1, 3).reshape(N, NG, 4)
     terms = np.abs(P.reshape(M, N, NG, 4).astype(np.float64))
-    # binary32 multiply-adds on exact sums: at most 4 NG + 20 roundings, each relative to the magnitudes met so far, and the
-    # coefficients of the row in the sign bit double those
+    # binary32 multiply-adds on exact sums: at most 4 NG + 20 roundings, each relative to the magnitudes met so far (the
+    # sums of the bit planes times differences of levels: up to twice the levels' own, and `spread`)
     cond = sc.astype(np.float64)[:, None] * np.einsum("mngl,ngl->mn", terms, lut)
     spread = sc.astype(np.float64)[:, None] * (8 * 128 * lut.max(axis=2).sum(axis=1))[None]
     assert np.all(np.abs(out - ref.reshape(M, N)) <= (4 * NG + 20) * 2.0 ** -24 * (2 * cond + spread))
     assert np.linalg.norm(out - ref.reshape(M, N)) <= 1e-5 * np.linalg.norm(ref)
+
+
+@pytest.mark.parametrize("K", [512, 2176, 4096])   # groups one at a time, batches of four with a rest, whole batches
+@pytest.mark.parametrize("M", [3, 8, 16])
+def test_the_four_rows_of_a_nibble_are_computed_alike(K, M):
+    """Rows of equal weights and levels give equal bits, whichever bit of the nibble holds them, at levels far apart (sums of
+    levels that need more than 24 bits)."""
+    print(f"grouped gemm equal rows K={K} M={M}", flush=True)
+    N, NG = 48, K // 128
+    idx = np.repeat(rcp_synth.random_indices(43, f"er{K}", N // 4, K), 4, axis=0)
+    q = rcp_synth.random_int4(43 + M, f"er{K}", M, K)
+    rng = np.random.default_rng(43)
+    levels = (rng.standard_normal((N // 4, NG, 1, 4)) * np.exp2(rng.integers(-12, 8, (N // 4, NG, 1, 4)))).astype(np.float16)
+    cb = np.ascontiguousarray(np.repeat(levels, 4, axis=2))
+    sc = np.ones(M, np.float16)
+    xq = ((q[:, 0::2].astype(np.uint8) & 0xF) | ((q[:, 1::2].astype(np.uint8) & 0xF) << 4)).astype(np.uint8)
+    dev = [torch.from_numpy(a).to(DEV) for a in (oracle.pack_indices_grouped(idx), cb, xq, sc)]
+    out = rcp.w2a4_gemm_grouped(dev[0], dev[1], N, K, dev[2], dev[3], M, out_dtype=torch.float32).view(M, N // 4, 4)
+    assert torch.equal(out, out[:, :, :1].expand_as(out))
 
 
 @pytest.mark.parametrize("n", [15, 16, 17, 32, 47])   # a workgroup takes sixteen vectors of any heads, then sixteen tokens of one
