@@ -40,6 +40,7 @@
 namespace rcp {
 
 constexpr int MG_WAVES = 16;   // wavefronts per workgroup at most
+constexpr int MG_P_WAVES = 8;  // with batches of four and the per-group sums
 constexpr int MG_MAX_BLOCKS = 8;   // sixteen-row blocks per workgroup at most (partial outputs in LDS)
 
 // every lane of a quad gets what lane s of it holds
@@ -57,9 +58,13 @@ struct MgBlock {
 // BATCH: groups a wavefront takes at a time: four (one 64-byte piece per row group and unit), or one (short K, where four
 // would leave most wavefronts without work).
 // TK: tokens a B operand holds (16, 8 or 4): the smallest of them that is not below M.
-// WANTP: the per-group sums are written to Pout as well (a verification output).
+// WANTP: the per-group sums are written to Pout as well (a verification output), the four groups of a batch together, so that
+// a cache line is not left half written while the other wavefronts' lines push it out.  With batches of four that takes 144
+// registers and leaves eight wavefronts, each of which stands for one or two of the W that the partial outputs are counted
+// in, so that the outputs have the same bits.  (Sixteen wavefronts with 101 registers spilled: 28672 x 4096 at 2 / 16 tokens
+// 100 / 247 us; now 24 / 95.)
 template <bool OUT_F16, bool WANTP, int BATCH, int TK>
-__global__ __launch_bounds__(64 * MG_WAVES) void gemm_mfma_grouped_kernel(const uint4* __restrict__ packed,
+__global__ __launch_bounds__(64 * (WANTP && BATCH == 4 ? MG_P_WAVES : MG_WAVES)) void gemm_mfma_grouped_kernel(const uint4* __restrict__ packed,
                                                                        const uint4* __restrict__ codebook, int N, int K,
                                                                        const uint4* __restrict__ xq,
                                                                        const uint16_t* __restrict__ scale, int M, int W, int NB,
@@ -116,16 +121,11 @@ __global__ __launch_bounds__(64 * MG_WAVES) void gemm_mfma_grouped_kernel(const 
                 xres, static_cast<int>(((g < NG) & (i % TK < M)) ? static_cast<unsigned>(i % TK) * (K / 2) + kb * 16u + 64u * g : OUTSIDE), 0, 0);
         }
     };
-    MgBlock cur;
-    load_tokens(wave);
-    load(wave, 0, cur);
-    for (int b = wave; b < batches; b += W) {  // uniform
-        __builtin_amdgcn_sched_barrier(0);
-        const int g0 = BATCH * b;
-        // the B operands of the four groups and the sums of q for this lane's token
-        v8i bop[BATCH];
-        float tq[BATCH];
-        const v4f zero = {0.0f, 0.0f, 0.0f, 0.0f};
+    // the B operands of a batch's groups and the sums of q for this lane's token
+    v8i bop[BATCH];
+    float tq[BATCH];
+    const v4f zero = {0.0f, 0.0f, 0.0f, 0.0f};
+    auto convert = [&]() {
         const v8i ones = {0x22222222, 0x22222222, 0x22222222, 0x22222222, 0, 0, 0, 0};
 #pragma unroll
         for (int s = 0; s < BATCH; ++s) {
@@ -143,82 +143,104 @@ __global__ __launch_bounds__(64 * MG_WAVES) void gemm_mfma_grouped_kernel(const 
             }
             tq[s] = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(ones, bop[s], zero, 4, 0, 0, SC_ONE, 0, FP8_INT_SCALE)[0];
         }
-        __builtin_amdgcn_sched_barrier(0);
-        // the activations of the next batch (sixteen tokens leave no registers for that: 128 keep sixteen wavefronts on a
-        // compute unit)
-        if constexpr (TK < 16) load_tokens(b + W);
-
-        auto compute = [&](const MgBlock& cur, int block) {
-            {
-                const float c0 = half_bits_to_float(static_cast<uint16_t>(cur.lut.x & 0xffffu));
-                const float c1 = half_bits_to_float(static_cast<uint16_t>(cur.lut.x >> 16));
-                const float c2 = half_bits_to_float(static_cast<uint16_t>(cur.lut.y & 0xffffu));
-                const float c3 = half_bits_to_float(static_cast<uint16_t>(cur.lut.y >> 16));
-                const float4 c = make_float4(c0, c1 - c0, c2 - c0, ((c3 - c2) - c1) + c0);
-                coef[16 * lg + 4 * kb + t] = c;
-            }
-            float o[4] = {0.0f, 0.0f, 0.0f, 0.0f};  // rows 4 * kb + v of the block, this lane's token
-            auto step = [&](auto index) {
-                constexpr int s = decltype(index)::value;
-                const uint32_t p0[4] = {cur.wa.x, cur.wa.z, cur.wb.x, cur.wb.z};
-                const uint32_t p1[4] = {cur.wa.y, cur.wa.w, cur.wb.y, cur.wb.w};
-                v8i an[3];
-#pragma unroll
-                for (int p = 0; p < 3; ++p) an[p] = v8i{0, 0, 0, 0, 0, 0, 0, 0};
-#pragma unroll
-                for (int d = 0; d < 4; ++d) {
-                    an[0][d] = static_cast<int>(((BATCH == 1 ? p0[d] : quad_broadcast<s>(p0[d])) & row_mask) >> row_shift);
-                    an[1][d] = static_cast<int>(((BATCH == 1 ? p1[d] : quad_broadcast<s>(p1[d])) & row_mask) >> row_shift);
-                    an[2][d] = an[0][d] & an[1][d];
-                }
-                v4f F[3];
-#pragma unroll
-                for (int p = 0; p < 3; ++p)
-                    F[p] = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(an[p], bop[s], zero, 4, 0, 0, row_scale, 0, FP8_INT_SCALE);
-#pragma unroll
-                for (int v = 0; v < 4; ++v) {
-                    const float4 c = coef[16 * s + 4 * kb + v];
-                    float val = fmaf(c.x, tq[s], o[v]);
-                    val = fmaf(c.y, F[0][v], val);
-                    val = fmaf(c.z, F[1][v], val);
-                    o[v] = fmaf(c.w, F[2][v], val);
-                    if constexpr (WANTP) {
-                        const int h = 4 * (rg0 + 4 * block + kb) + v;
-                        if (i < M && g0 + s < NG && h < N)
-                            reinterpret_cast<int4*>(Pout)[(static_cast<size_t>(i) * N + h) * NG + g0 + s] =
-                                make_int4(static_cast<int>(tq[s] - F[0][v] - F[1][v] + F[2][v]), static_cast<int>(F[0][v] - F[2][v]),
-                                          static_cast<int>(F[1][v] - F[2][v]), static_cast<int>(F[2][v]));
-                    }
-                }
-                __builtin_amdgcn_sched_barrier(0);  // one step's operands and sums live at a time
-            };
-            step(std::integral_constant<int, 0>{});
-            if constexpr (BATCH == 4) {
-                step(std::integral_constant<int, 1>{});
-                step(std::integral_constant<int, 2>{});
-                step(std::integral_constant<int, 3>{});
-            }
-            // (the products run in all lanes: the compiler would move them into the branch, which switches rows off)
-            asm volatile("" : "+v"(o[0]), "+v"(o[1]), "+v"(o[2]), "+v"(o[3]));
-            if (i < TK) {
-                float* const dst = slab + (wave * TK + i) * stride + 16 * block + 4 * kb;
-#pragma unroll
-                for (int v = 0; v < 4; ++v) dst[v] = b == wave ? o[v] : dst[v] + o[v];
-            }
-        };
-        for (int block = 0; block < NB; ++block) {
-            MgBlock next;  // the next block, or the first one of the next batch, is in flight while this one is computed
-            const bool last = block + 1 == NB;
-            load(last ? b + W : b, last ? 0 : block + 1, next);
-            __builtin_amdgcn_sched_barrier(0);
-            compute(cur, block);
-            cur = next;
+    };
+    // rows 4 * kb + v of the block, this lane's token
+    auto products = [&](const MgBlock& cur, int block, int g0, float (&o)[4]) {
+        {
+            const float c0 = half_bits_to_float(static_cast<uint16_t>(cur.lut.x & 0xffffu));
+            const float c1 = half_bits_to_float(static_cast<uint16_t>(cur.lut.x >> 16));
+            const float c2 = half_bits_to_float(static_cast<uint16_t>(cur.lut.y & 0xffffu));
+            const float c3 = half_bits_to_float(static_cast<uint16_t>(cur.lut.y >> 16));
+            const float4 c = make_float4(c0, c1 - c0, c2 - c0, ((c3 - c2) - c1) + c0);
+            coef[16 * lg + 4 * kb + t] = c;
         }
-        if constexpr (TK == 16) load_tokens(b + W);
-    }
+        int4 sums[4][BATCH];
+        auto step = [&](auto index) {
+            constexpr int s = decltype(index)::value;
+            const uint32_t p0[4] = {cur.wa.x, cur.wa.z, cur.wb.x, cur.wb.z};
+            const uint32_t p1[4] = {cur.wa.y, cur.wa.w, cur.wb.y, cur.wb.w};
+            v8i an[3];
+#pragma unroll
+            for (int p = 0; p < 3; ++p) an[p] = v8i{0, 0, 0, 0, 0, 0, 0, 0};
+#pragma unroll
+            for (int d = 0; d < 4; ++d) {
+                an[0][d] = static_cast<int>(((BATCH == 1 ? p0[d] : quad_broadcast<s>(p0[d])) & row_mask) >> row_shift);
+                an[1][d] = static_cast<int>(((BATCH == 1 ? p1[d] : quad_broadcast<s>(p1[d])) & row_mask) >> row_shift);
+                an[2][d] = an[0][d] & an[1][d];
+            }
+            v4f F[3];
+#pragma unroll
+            for (int p = 0; p < 3; ++p)
+                F[p] = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(an[p], bop[s], zero, 4, 0, 0, row_scale, 0, FP8_INT_SCALE);
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                const float4 c = coef[16 * s + 4 * kb + v];
+                float val = fmaf(c.x, tq[s], o[v]);
+                val = fmaf(c.y, F[0][v], val);
+                val = fmaf(c.z, F[1][v], val);
+                o[v] = fmaf(c.w, F[2][v], val);
+                if constexpr (WANTP)
+                    sums[v][s] = make_int4(static_cast<int>(tq[s] - F[0][v] - F[1][v] + F[2][v]), static_cast<int>(F[0][v] - F[2][v]),
+                                           static_cast<int>(F[1][v] - F[2][v]), static_cast<int>(F[2][v]));
+            }
+            __builtin_amdgcn_sched_barrier(0);  // one step's operands and sums live at a time
+        };
+        step(std::integral_constant<int, 0>{});
+        if constexpr (BATCH == 4) {
+            step(std::integral_constant<int, 1>{});
+            step(std::integral_constant<int, 2>{});
+            step(std::integral_constant<int, 3>{});
+        }
+        // (the products run in all lanes: the compiler would move them into the branch, which switches rows off)
+        asm volatile("" : "+v"(o[0]), "+v"(o[1]), "+v"(o[2]), "+v"(o[3]));
+        if constexpr (WANTP) {
+            const int group = rg0 + 4 * block + kb;
+            if (i < M && group < G)
+#pragma unroll
+                for (int v = 0; v < 4; ++v)
+#pragma unroll
+                    for (int s = 0; s < BATCH; ++s)
+                        if (g0 + s < NG) reinterpret_cast<int4*>(Pout)[(static_cast<size_t>(i) * N + 4 * group + v) * NG + g0 + s] = sums[v][s];
+        }
+    };
+    auto park = [&](int part, int block, bool first, const float (&o)[4]) {
+        if (i < TK) {
+            float* const dst = slab + (part * TK + i) * stride + 16 * block + 4 * kb;
+#pragma unroll
+            for (int v = 0; v < 4; ++v) dst[v] = first ? o[v] : dst[v] + o[v];
+        }
+    };
+    auto stream = [&](int part) {
+        MgBlock cur;
+        load_tokens(part);
+        load(part, 0, cur);
+        for (int b = part; b < batches; b += W) {  // uniform
+            __builtin_amdgcn_sched_barrier(0);
+            convert();
+            __builtin_amdgcn_sched_barrier(0);
+            // the activations of the next batch (sixteen tokens leave no registers for that: 128 keep sixteen wavefronts on a
+            // compute unit)
+            if constexpr (TK < 16) load_tokens(b + W);
+            for (int block = 0; block < NB; ++block) {
+                MgBlock next;  // the next block, or the first one of the next batch, is in flight while this one is computed
+                const bool last = block + 1 == NB;
+                load(last ? b + W : b, last ? 0 : block + 1, next);
+                __builtin_amdgcn_sched_barrier(0);
+                float o[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+                products(cur, block, BATCH * b, o);
+                park(part, block, b == part, o);
+                cur = next;
+            }
+            if constexpr (TK == 16) load_tokens(b + W);
+        }
+    };
+    constexpr bool SHARED = WANTP && BATCH == 4;
+    if constexpr (SHARED)
+        for (int part = wave; part < W; part += MG_P_WAVES) stream(part);
+    else stream(wave);
     __syncthreads();
 
-    for (int idx = tid; idx < M * 16 * NB; idx += 64 * W) {
+    for (int idx = tid; idx < M * 16 * NB; idx += 64 * (SHARED ? min(W, MG_P_WAVES) : W)) {
         const int n = idx / (16 * NB), hh = idx - n * (16 * NB);
         const int h = 4 * rg0 + hh;
         if (h >= N) continue;
@@ -261,6 +283,7 @@ int launch_gemm_mfma_grouped(const void* packed, const void* codebook, int N, in
     auto* x4 = static_cast<const uint4*>(xq);
     auto* sc = static_cast<const uint16_t*>(scale);
     const int tk = P != nullptr || batch == 1 || M > 8 ? 16 : M > 4 ? 8 : 4;
+    const int resident = P != nullptr && batch == 4 && waves > MG_P_WAVES ? MG_P_WAVES : waves;
     const size_t lds = static_cast<size_t>(waves) * (batch * 16 * sizeof(float4) + tk * (16 * nb + 1) * sizeof(float));
 #define RCP_MG(F16, P_, B_, TK)                                                                                                 \
     do {                                                                                                                        \
@@ -269,7 +292,7 @@ int launch_gemm_mfma_grouped(const void* packed, const void* codebook, int N, in
                                                      hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(lds));        \
             if (e != hipSuccess) return fail(RCP_ERR_HIP, "rcp_w2a4_gemm_grouped: LDS opt-in failed: %s", hipGetErrorString(e)); \
         }                                                                                                                       \
-        gemm_mfma_grouped_kernel<F16, P_, B_, TK><<<blocks, waves * 64, lds, st>>>(pk, cb, N, K, x4, sc, M, waves, nb, out, P); \
+        gemm_mfma_grouped_kernel<F16, P_, B_, TK><<<blocks, resident * 64, lds, st>>>(pk, cb, N, K, x4, sc, M, waves, nb, out, P); \
     } while (0)
 #define RCP_MG_TK(F16)                               \
     do {                                             \

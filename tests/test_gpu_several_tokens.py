@@ -245,6 +245,27 @@ def test_the_four_rows_of_a_nibble_are_computed_alike(K, M):
     assert torch.equal(out, out[:, :, :1].expand_as(out))
 
 
+@pytest.mark.parametrize("N,K", [(4100, 2176), (16420, 2304), (40, 8320)])   # two blocks of rows, five, one; ragged N and K
+@pytest.mark.parametrize("M", [2, 8, 9, 16])
+def test_per_group_sums_of_several_tokens_are_exact(N, K, M):
+    print(f"grouped gemm sums N={N} K={K} M={M}", flush=True)
+    NG, rows = K // 128, np.r_[0:8, N // 2:N // 2 + 8, N - 8:N]
+    idx = rcp_synth.random_indices(45, f"ps{N}x{K}", N, K)
+    q = rcp_synth.random_int4(45 + M, f"ps{K}", M, K)
+    cb = np.sort(np.random.default_rng(45).standard_normal((N // 4, NG, 4, 4)) * 0.03, axis=3).astype(np.float16)
+    xq = ((q[:, 0::2].astype(np.uint8) & 0xF) | ((q[:, 1::2].astype(np.uint8) & 0xF) << 4)).astype(np.uint8)
+    dev = [torch.from_numpy(a).to(DEV) for a in (oracle.pack_indices_grouped(idx), cb, xq, np.ones(M, np.float16))]
+    out, P = rcp.w2a4_gemm_grouped(dev[0], dev[1], N, K, dev[2], dev[3], M, out_dtype=torch.float32, want_partial_sums=True)
+    onehot = (idx[rows].reshape(-1, NG, 128)[None, ..., None] == np.arange(4))
+    want = (q.reshape(M, 1, NG, 128, 1).astype(np.int32) * onehot).sum(axis=3)
+    assert np.array_equal(P.view(M, N, NG, 4)[:, rows].cpu().numpy(), want)
+    lut = cb.astype(np.float64).transpose(0, 2, 1, 3).reshape(N, NG, 4)[rows]
+    ref = (want * lut).sum(axis=(2, 3))
+    assert np.linalg.norm(out[:, rows].cpu().numpy() - ref) <= 1e-5 * np.linalg.norm(ref)
+    # eight wavefronts stand for up to sixteen here: the same bits as without the sums
+    assert torch.equal(out, rcp.w2a4_gemm_grouped(dev[0], dev[1], N, K, dev[2], dev[3], M, out_dtype=torch.float32))
+
+
 @pytest.mark.parametrize("n", [15, 16, 17, 32, 47])   # a workgroup takes sixteen vectors of any heads, then sixteen tokens of one
 @pytest.mark.parametrize("rotate", [False, True])
 @pytest.mark.parametrize("dtype", [torch.float16, torch.bfloat16, torch.float32])
