@@ -430,14 +430,15 @@ __global__ __launch_bounds__(KRON_THREADS) void kron_split_kernel(const void* __
 
 // Form for several tokens (n = 64 * R, R = 1 or 2): Z = X Q^T on the binary32 matrix instruction.  A workgroup owns
 // sixteen columns j' of Y for one token; its four wavefronts own four row tiles each and split the sum over j KS = 4 / R
-// ways.  v_mfma_f32_16x16x4_f32 adds exact binary32 products into binary32 sums, so nothing is lost against the vector
-// form; only the order of the sum over j differs.
+// ways.  v_mfma_f32_16x16x4_f32 adds exact binary32 products into binary32 sums; what is lost against 64 bits grows with
+// the length of a sum, so every element has four of them, added in pairs, as long as the vector form's (error at 64 x 172
+// 1.43e-7 against its 1.42e-7, 128 x 88 1.23e-7 both; with two sums at n = 128 1.46e-7).
 // What it saves is memory requests: kron_split_kernel reads the whole token with row-strided loads (64 cache lines per
 // instruction) once per column, i.e. m times per token; here sixteen columns share one pass over the token, and a lane
 // fetches four consecutive j for four matrix steps at once (k slot kb = lane / 16 of step s stands for j = 16 S + 4 kb + s
 // on both operands).  Bound by the latency of one round of loads and of the chain behind it, not by the matrix cores
 // (44 instructions per wavefront at m = 172).  Launch to launch, 64 x 172: 16 tokens fp16 10.8 -> 4.4 us, fp32
-// 23.0 -> 4.0 us; 4 tokens fp16 4.6 -> 4.2 us.  (Also tried with n = 512 and 1024: the binary32 matrix rate and the
+// 23.0 -> 4.1 us; 4 tokens fp16 4.8 -> 4.4 us; 128 x 88, 16 tokens fp16 8.2 -> 4.9 us.  (Also tried with n = 512 and 1024: the binary32 matrix rate and the
 // transform of 32 or 64 rows per lane then weigh on few workgroups, 512 x 28 at 16 tokens 5.5 -> 8.4 us.)
 template <int DT, int R>
 __global__ __launch_bounds__(KRON_THREADS) void kron_mfma_kernel(const void* __restrict__ x, int m, const float* __restrict__ Q,
@@ -446,6 +447,7 @@ __global__ __launch_bounds__(KRON_THREADS) void kron_mfma_kernel(const void* __r
     constexpr int KS = 4 / R;   // parts of the sum over j
     constexpr int WT = 4;       // row tiles of sixteen per wavefront
     constexpr int DEPTH = 3;    // groups of sixteen j in flight per wavefront
+    constexpr int CHAINS = R;   // sums per element and wavefront: 4 in all
     __shared__ float z[KS][64 * R * 16];
     using XT = typename XStore<DT>::type;
     const int token = blockIdx.y, j0 = blockIdx.x * 16;
@@ -456,9 +458,11 @@ __global__ __launch_bounds__(KRON_THREADS) void kron_mfma_kernel(const void* __r
     const XT* xr = static_cast<const XT*>(x) + static_cast<size_t>(token) * K + static_cast<size_t>(16 * t0 + i) * m;
     const float* qr = Q + static_cast<size_t>(min(j0 + i, m - 1)) * m;  // columns past the end repeat the last one and are not stored
 
-    v4f acc[WT];
+    v4f acc[CHAINS][WT];
 #pragma unroll
-    for (int t = 0; t < WT; ++t) acc[t] = v4f{0.0f, 0.0f, 0.0f, 0.0f};
+    for (int c = 0; c < CHAINS; ++c)
+#pragma unroll
+        for (int t = 0; t < WT; ++t) acc[c][t] = v4f{0.0f, 0.0f, 0.0f, 0.0f};
     for (int S0 = ks; S0 < groups; S0 += DEPTH * KS) {
         float4 q[DEPTH];
         uint4 raw[DEPTH][WT];
@@ -496,11 +500,16 @@ __global__ __launch_bounds__(KRON_THREADS) void kron_mfma_kernel(const void* __r
                         const uint32_t w = s < 2 ? raw[d][t].x : raw[d][t].y;
                         a = XStore<DT>::widen(static_cast<uint16_t>((s & 1) ? w >> 16 : w & 0xffffu));
                     }
-                    acc[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(a, qs[s], acc[t], 0, 0, 0);
+                    acc[s % CHAINS][t] = __builtin_amdgcn_mfma_f32_16x16x4f32(a, qs[s], acc[s % CHAINS][t], 0, 0, 0);
                 }
         }
     }
-    // acc[t][v] = Z[16 (t0 + t) + 4 kb + v][j0 + i].  The tile goes through LDS so that a lane ends up with 4 R
+    if constexpr (CHAINS == 2)
+#pragma unroll
+        for (int t = 0; t < WT; ++t)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) acc[0][t][v] += acc[1][t][v];
+    // acc[0][t][v] = Z[16 (t0 + t) + 4 kb + v][j0 + i].  The tile goes through LDS so that a lane ends up with 4 R
     // consecutive rows of one column; groups of four rows are spread over the banks for both access patterns.
     auto at = [](int row, int col) {
         const int f = R == 1 ? (row >> 2) & 3 : ((row >> 2) ^ (row / (4 * R))) & 3;
@@ -510,7 +519,7 @@ __global__ __launch_bounds__(KRON_THREADS) void kron_mfma_kernel(const void* __r
 #pragma unroll
     for (int t = 0; t < WT; ++t)
 #pragma unroll
-        for (int v = 0; v < 4; ++v) z[ks][at(16 * (t0 + t) + 4 * kb + v, i)] = acc[t][v];
+        for (int v = 0; v < 4; ++v) z[ks][at(16 * (t0 + t) + 4 * kb + v, i)] = acc[0][t][v];
     __syncthreads();
     constexpr int E = 4 * R;
     const int col = 4 * wave + (lane & 3), row0 = (lane >> 2) * E;
@@ -518,9 +527,8 @@ __global__ __launch_bounds__(KRON_THREADS) void kron_mfma_kernel(const void* __r
 #pragma unroll
     for (int e = 0; e < E; ++e) {
         const int w = at(row0 + e, col);
-        c[e] = z[0][w];
-#pragma unroll
-        for (int k = 1; k < KS; ++k) c[e] += z[k][w];
+        c[e] = z[0][w] + z[1][w];
+        if constexpr (KS == 4) c[e] += z[2][w] + z[3][w];
     }
     // Hadamard transform down the column in ascending stride order: inside the lane, then lanes 4, 8, 16, 32 apart
 #pragma unroll

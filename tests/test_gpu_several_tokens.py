@@ -31,6 +31,20 @@ def test_kronecker_rotation_of_several_tokens_on_the_matrix_cores(M, n, m, dtype
     assert np.all(np.abs(y - ref) <= bound)
 
 
+@pytest.mark.parametrize("M,n,m", [(16, 128, 88), (16, 128, 100), (16, 64, 172)])
+def test_kronecker_rotation_of_several_tokens_is_as_precise_as_of_one(M, n, m):
+    """Sums as long as the one-token kernel's leave the same rounding error (5 % for the order of the additions; with half
+    as many sums, twice as long, it is 20 % larger)."""
+    print(f"kron mfma precision M={M} {n}x{m}", flush=True)
+    x = torch.from_numpy(rcp_synth.activation(25, f"kp{M}x{n}x{m}", M, n * m)).to(DEV).float()
+    Q = rcp_synth.orthogonal(5, m)
+    rot = rcp.Rotation.kron(n, torch.from_numpy(Q).to(DEV))
+    ref = oracle.rotate(x.double().cpu().numpy(), oracle.ROT_KRON, n, m, Q.astype(np.float64))
+    together = rcp.rotate_act(x, rot).double().cpu().numpy()
+    apart = np.stack([rcp.rotate_act(x[i], rot)[0].double().cpu().numpy() for i in range(M)])
+    assert np.linalg.norm(together - ref) <= 1.05 * np.linalg.norm(apart - ref)
+
+
 @pytest.mark.parametrize("H_q,H_kv,S,tokens", [
     (2, 2, 1, 512),        # one token: three wavefronts without work
     (4, 2, 63, 512), (6, 2, 64, 512), (8, 2, 65, 512),   # 2, 3 and 4 query heads per cache head around one chunk
