@@ -66,23 +66,23 @@ __device__ static LdpGrid ldp_grid(float lo_f, float hi_f, float p1_f, float p2_
 // (4 rows x 8 columns -> two 32-bit bit planes).  Thresholds of the four rows sit in LDS.
 // Bound by the read of W once its loads are under way while the first threads derive the thresholds in 64 bits: behind the
 // barrier, every workgroup began its stream with the whole of that chain.  The four matrices of a 7B-shaped layer in fp16:
-// 104.8 -> 83.7 us (4.4 -> 5.5 TB/s; a plain read gives 6.1).
+// 104.8 -> 83.7 us (4.4 -> 5.5 TB/s; a plain read gives 6.1); 28672 x 4096 with one table per group 54.1 -> 47.1 us.
 constexpr int PACK_THREADS = 256;
 
-// the eight values of row r of a cell, read once: past the caches
+// The eight values of row r of a cell, read once: past the caches, except for binary32, where a lane's two loads take half
+// of each cache line and the second one finds the line that the first one brought (4096 x 11008: 37.2 us with loads behind
+// the barrier, 39.8 past the caches, 36.7 through them; one table per group 38.7, 42.4 and 38.4).
 template <int DT>
 __device__ __forceinline__ Raw8<DT> load8_raw_once(const void* p, size_t i)
 {
     Raw8<DT> r;
-    const u32x4* q = reinterpret_cast<const u32x4*>(static_cast<const char*>(p) + i * (DT == RCP_F32 ? 4 : 2));
-    const u32x4 a = __builtin_nontemporal_load(q);
-    r.a = make_uint4(a.x, a.y, a.z, a.w);
-    r.b = make_uint4(0u, 0u, 0u, 0u);
-    if constexpr (DT == RCP_F32) {
-        const u32x4 b = __builtin_nontemporal_load(q + 1);
-        r.b = make_uint4(b.x, b.y, b.z, b.w);
+    if constexpr (DT == RCP_F32) return load8_raw<DT>(p, i);
+    else {
+        const u32x4 a = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(static_cast<const char*>(p) + i * 2));
+        r.a = make_uint4(a.x, a.y, a.z, a.w);
+        r.b = make_uint4(0u, 0u, 0u, 0u);
+        return r;
     }
-    return r;
 }
 
 // Index = how many thresholds are not above the value: the comparisons of a row are added into one nibble per column (a
