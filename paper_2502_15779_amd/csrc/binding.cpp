@@ -13,6 +13,7 @@
 #include <torch/csrc/Dtype.h>
 #include <torch/csrc/autograd/python_variable.h>
 
+#include <climits>
 #include <cstdint>
 #include <string>
 #include <vector>
@@ -57,11 +58,19 @@ inline bool none(PyObject* o) { return o == Py_None; }
 
 inline void* opt(PyObject* o, const char* what) { return none(o) ? nullptr : dev(o, what); }
 
+// The library counts in 32 bits: what does not fit is refused here, before a check could pass on its low half.
+inline int narrow(int64_t v)
+{
+    require(v >= INT_MIN && v <= INT_MAX, "sizes, counts and positions must fit a 32-bit integer");
+    return static_cast<int>(v);
+}
+
 inline int integer(PyObject* o)
 {
-    const unsigned long v = PyLong_AsUnsignedLongMask(o);
-    if (v == static_cast<unsigned long>(-1) && PyErr_Occurred()) throw Raised{};
-    return static_cast<int>(v);
+    int overflow = 0;
+    const long long v = PyLong_AsLongLongAndOverflow(o, &overflow);
+    if (v == -1 && overflow == 0 && PyErr_Occurred()) throw Raised{};
+    return narrow(overflow != 0 ? INT64_MAX : v);
 }
 
 inline float real(PyObject* o)
@@ -392,8 +401,8 @@ PyObject* quant_w3a4_gemv(Args a)
 inline void rows_of(const Tensor& x, int& M, int& K)
 {
     require(x.dim() == 1 || x.dim() == 2, "x must be [M, K] or [K]");
-    M = x.dim() == 1 ? 1 : static_cast<int>(x.size(0));
-    K = static_cast<int>(x.size(-1));
+    M = x.dim() == 1 ? 1 : narrow(x.size(0));
+    K = narrow(x.size(-1));
 }
 
 // x, rotation, clip_ratio, xq_out, scale_out, workspace
@@ -464,8 +473,8 @@ inline const float* learnt(PyObject* o, const char* name)
 inline void matrix_of(const Tensor& W, int& N, int& K, rcp_dtype& dt)
 {
     require(W.dim() == 2, "W must be [N, K]");
-    N = static_cast<int>(W.size(0));
-    K = static_cast<int>(W.size(1));
+    N = narrow(W.size(0));
+    K = narrow(W.size(1));
     dt = in_dtype(W, "W must be float16, bfloat16 or float32");
 }
 
@@ -558,7 +567,7 @@ constexpr int64_t D = RCP_KV_HEAD_DIM;
 
 struct Cache {
     void *codes, *params;
-    int64_t heads, S_max;
+    int heads, S_max;
 };
 
 // codes uint8 [heads, S_max, 64] and params uint8 [heads, S_max, 4]; heads / S_max < 0: not known beforehand
@@ -571,7 +580,7 @@ inline Cache cache(PyObject* codes, PyObject* params, int64_t heads, int64_t S_m
     require(c.size(0) == heads && c.size(1) == S_max && c.size(2) == D / 2 && p.size(0) == heads && p.size(1) == S_max &&
                 p.size(2) == 4 && c.is_contiguous() && p.is_contiguous(),
             message);
-    return {dev(c, cname), dev(p, pname), heads, S_max};
+    return {dev(c, cname), dev(p, pname), narrow(heads), narrow(S_max)};
 }
 
 inline void heads_of(const Tensor& x, const char* message) { require(x.dim() == 3 && x.size(2) == D && x.is_contiguous(), message); }
@@ -586,13 +595,13 @@ PyObject* kv4_append(Args a)
     const Tensor& x = tensor(a[0], "x");
     heads_of(x, "x must be contiguous [n_tokens, H, 128]");
     const Cache c = cache(a[2], a[3], x.size(1), -1, "codes", "params", kCodes);
-    const int n = static_cast<int>(x.size(0)), H = static_cast<int>(x.size(1)), pos = integer(a[1]);
+    const int n = narrow(x.size(0)), H = narrow(x.size(1)), pos = integer(a[1]);
     const float ratio = real(a[4]);
     const int rotate = truth(a[5]);
     if (n == 0) return nothing();  // an empty tensor has no device pointer to hand over
     const rcp_dtype xd = in_dtype(x, kXType);
     void* const xp = dev(x, "x");
-    call([&](void* st) { return rcp_kv4_append(xp, xd, n, H, static_cast<int>(c.S_max), pos, rotate, ratio, c.codes, c.params, st); });
+    call([&](void* st) { return rcp_kv4_append(xp, xd, n, H, c.S_max, pos, rotate, ratio, c.codes, c.params, st); });
     return nothing();
 }
 
@@ -606,14 +615,14 @@ PyObject* kv4_append_kv(Args a)
     const char* const one = "codes must be uint8 [H, S_max, 64] and params uint8 [H, S_max, 4], contiguous, one S_max";
     const Cache kc = cache(a[3], a[4], k.size(1), -1, "k_codes", "k_params", one);
     const Cache vc = cache(a[5], a[6], k.size(1), kc.S_max, "v_codes", "v_params", one);
-    const int n = static_cast<int>(k.size(0)), H = static_cast<int>(k.size(1)), pos = integer(a[2]);
+    const int n = narrow(k.size(0)), H = narrow(k.size(1)), pos = integer(a[2]);
     const float ratio = real(a[7]);
     const int rotate = truth(a[8]);
     if (n == 0) return nothing();
     const rcp_dtype xd = in_dtype(k, "k and v must be float16, bfloat16 or float32");
     void *const kp = dev(k, "k"), *const vp = dev(v, "v");
     call([&](void* st) {
-        return rcp_kv4_append_kv(kp, vp, xd, n, H, static_cast<int>(kc.S_max), pos, rotate, ratio, kc.codes, kc.params, vc.codes, vc.params, st);
+        return rcp_kv4_append_kv(kp, vp, xd, n, H, kc.S_max, pos, rotate, ratio, kc.codes, kc.params, vc.codes, vc.params, st);
     });
     return nothing();
 }
@@ -625,7 +634,7 @@ PyObject* kv4_attn_decode(Args a)
     require(q.dim() == 2 && q.size(1) == D && q.is_contiguous(), "q must be contiguous [H_q, 128]");
     const Cache k = cache(a[2], a[3], -1, -1, "k_codes", "k_params", kCaches);
     const Cache v = cache(a[4], a[5], k.heads, k.S_max, "v_codes", "v_params", kCaches);
-    const int H_q = static_cast<int>(q.size(0)), S = integer(a[1]);
+    const int H_q = narrow(q.size(0)), S = integer(a[1]);
     const float scale = real(a[6]);
     const Result out = output(a[7], a[8], {H_q, D}, q);
     const rcp_dtype od = out_code(out.t, "out must be float16 or float32 [H_q, 128]");
@@ -641,7 +650,7 @@ PyObject* kv4_attn_decode(Args a)
     void *const qp = dev(q, "q"), *const o = dev(out.t, "out"), *const ws = dev(work, "workspace");
     const auto f = rotate ? rcp_kv4_rotate_attn_decode : rcp_kv4_attn_decode;
     call([&](void* st) {
-        return f(qp, qd, H_q, static_cast<int>(k.heads), static_cast<int>(k.S_max), S, k.codes, k.params, v.codes, v.params, scale, o, od, ws,
+        return f(qp, qd, H_q, k.heads, k.S_max, S, k.codes, k.params, v.codes, v.params, scale, o, od, ws,
                  work.nbytes(), st);
     });
     return out.give();
@@ -656,14 +665,21 @@ inline std::vector<int> integers(PyObject* o)
     for (Py_ssize_t i = 0; i < n; ++i) {
         PyObject* item = PySequence_Fast_GET_ITEM(s, i);
         PyObject* whole = PyLong_Check(item) ? (Py_INCREF(item), item) : PyNumber_Long(item);
+        int overflow = 0;
+        long long v = 0;
         if (whole != nullptr) {
-            r[static_cast<size_t>(i)] = static_cast<int>(PyLong_AsUnsignedLongMask(whole));
+            v = PyLong_AsLongLongAndOverflow(whole, &overflow);
             Py_DECREF(whole);
         }
         if (PyErr_Occurred()) {
             Py_DECREF(s);
             throw Raised{};
         }
+        if (overflow != 0 || v < INT_MIN || v > INT_MAX) {
+            Py_DECREF(s);
+            narrow(INT64_MAX);
+        }
+        r[static_cast<size_t>(i)] = static_cast<int>(v);
     }
     Py_DECREF(s);
     return r;
@@ -674,7 +690,7 @@ PyObject* kv4_append_batched(Args a)
 {
     const Tensor& x = tensor(a[0], "x");
     heads_of(x, "x must be contiguous [B, H, 128]");
-    const int B = static_cast<int>(x.size(0)), H = static_cast<int>(x.size(1));
+    const int B = narrow(x.size(0)), H = narrow(x.size(1));
     const std::vector<int> pos = integers(a[1]);
     require(static_cast<int>(pos.size()) == B, "one position per sequence");
     const Cache c = cache(a[2], a[3], x.size(0) * x.size(1), -1, "codes", "params",
@@ -683,7 +699,7 @@ PyObject* kv4_append_batched(Args a)
     const int rotate = truth(a[5]);
     const rcp_dtype xd = in_dtype(x, kXType);
     void* const xp = dev(x, "x");
-    call([&](void* st) { return rcp_kv4_append_batched(xp, xd, B, H, static_cast<int>(c.S_max), pos.data(), rotate, ratio, c.codes, c.params, st); });
+    call([&](void* st) { return rcp_kv4_append_batched(xp, xd, B, H, c.S_max, pos.data(), rotate, ratio, c.codes, c.params, st); });
     return nothing();
 }
 
@@ -692,7 +708,7 @@ PyObject* kv4_attn_decode_batched(Args a)
 {
     const Tensor& q = tensor(a[0], "q");
     heads_of(q, "q must be contiguous [B, H_q, 128]");
-    const int B = static_cast<int>(q.size(0)), H_q = static_cast<int>(q.size(1));
+    const int B = narrow(q.size(0)), H_q = narrow(q.size(1));
     const std::vector<int> lens = integers(a[1]);
     const Cache k = cache(a[2], a[3], -1, -1, "k_codes", "k_params", kPool);
     require(static_cast<int>(lens.size()) == B && B > 0 && k.heads % B == 0, "one length per sequence, and a pooled cache of B * H_kv heads");
@@ -712,9 +728,9 @@ PyObject* kv4_attn_decode_batched(Args a)
         work = tensor(a[9], "workspace");
     const rcp_dtype qd = in_dtype(q, "q must be float16, bfloat16 or float32");
     void *const qp = dev(q, "q"), *const o = dev(out.t, "out"), *const ws = dev(work, "workspace");
-    const int H_kv = static_cast<int>(k.heads / B);
+    const int H_kv = k.heads / B;
     call([&](void* st) {
-        return rcp_kv4_attn_decode_batched(qp, qd, B, H_q, H_kv, static_cast<int>(k.S_max), lens.data(), k.codes, k.params, v.codes, v.params, scale,
+        return rcp_kv4_attn_decode_batched(qp, qd, B, H_q, H_kv, k.S_max, lens.data(), k.codes, k.params, v.codes, v.params, scale,
                                            o, od, ws, work.nbytes(), st);
     });
     return out.give();

@@ -35,6 +35,27 @@ def test_arguments_that_do_not_fit_are_value_errors(call, message):
         call()
 
 
+BIG = 2 ** 32   # a multiple of what 32 bits hold: the low half of BIG + n is n
+Q, CODES, PARAMS = torch.zeros((1, 1, K)), torch.zeros((1, 4, 64), dtype=torch.uint8), torch.zeros((1, 4, 4), dtype=torch.uint8)
+
+
+@pytest.mark.parametrize("call", [
+    lambda: rcp.w2a4_gemv(P, C, BIG + N, K, XQ, S, out=OUT),
+    lambda: rcp.w2a4_gemv(P, C, N, BIG + K, XQ, S, out=OUT),
+    lambda: rcp.w2a4_gemv(P, C, N, K, XQ, S, BIG + 1, out=OUT),
+    lambda: rcp.w2a4_gemv(P, C, N - BIG, K, XQ, S, out=OUT),
+    lambda: rcp.w2a4_gemv(P, C, 2 ** 70 + N, K, XQ, S, out=OUT),
+    lambda: rcp.w2a4_gemm_grouped(P, C, N, K, XQ, S, 1, group=BIG + 128, out=OUT),
+    lambda: rcp.pack_weights_grouped(torch.zeros(N, K), X[:N], X[:N], X[:3 * N], group=BIG + 128),
+    lambda: rcp.kv4_append_batched(Q, [BIG], CODES, PARAMS),
+    lambda: rcp.kv4_attn_decode_batched(Q, [-BIG + 1], CODES, PARAMS, CODES, PARAMS, 1.0),
+    lambda: rcp.kv4_attn_decode_batched(Q, [2 ** 70], CODES, PARAMS, CODES, PARAMS, 1.0),
+])
+def test_numbers_beyond_32_bits_are_not_cut(call):
+    with pytest.raises(ValueError, match="32-bit"):
+        call()
+
+
 def test_public_signatures_keep_their_defaults():
     p = inspect.signature(rcp.quant_w2a4_gemv).parameters
     assert list(p)[:6] == ["packed", "codebook", "N", "K", "x", "clip_ratio"] and p["out_dtype"].default is torch.float16
