@@ -73,6 +73,18 @@ inline int integer(PyObject* o)
     return narrow(overflow != 0 ? INT64_MAX : v);
 }
 
+// A position or length: anything that int() takes.
+inline int position(PyObject* o)
+{
+    if (__builtin_expect(PyLong_Check(o), 1)) return integer(o);
+    PyObject* const whole = PyNumber_Long(o);
+    if (whole == nullptr) throw Raised{};
+    int overflow = 0;
+    const long long v = PyLong_AsLongLongAndOverflow(whole, &overflow);
+    Py_DECREF(whole);
+    return narrow(overflow != 0 ? INT64_MAX : v);
+}
+
 inline float real(PyObject* o)
 {
     const double v = PyFloat_AsDouble(o);
@@ -595,7 +607,7 @@ PyObject* kv4_append(Args a)
     const Tensor& x = tensor(a[0], "x");
     heads_of(x, "x must be contiguous [n_tokens, H, 128]");
     const Cache c = cache(a[2], a[3], x.size(1), -1, "codes", "params", kCodes);
-    const int n = narrow(x.size(0)), H = narrow(x.size(1)), pos = integer(a[1]);
+    const int n = narrow(x.size(0)), H = narrow(x.size(1)), pos = position(a[1]);
     const float ratio = real(a[4]);
     const int rotate = truth(a[5]);
     if (n == 0) return nothing();  // an empty tensor has no device pointer to hand over
@@ -615,7 +627,7 @@ PyObject* kv4_append_kv(Args a)
     const char* const one = "codes must be uint8 [H, S_max, 64] and params uint8 [H, S_max, 4], contiguous, one S_max";
     const Cache kc = cache(a[3], a[4], k.size(1), -1, "k_codes", "k_params", one);
     const Cache vc = cache(a[5], a[6], k.size(1), kc.S_max, "v_codes", "v_params", one);
-    const int n = narrow(k.size(0)), H = narrow(k.size(1)), pos = integer(a[2]);
+    const int n = narrow(k.size(0)), H = narrow(k.size(1)), pos = position(a[2]);
     const float ratio = real(a[7]);
     const int rotate = truth(a[8]);
     if (n == 0) return nothing();
@@ -634,7 +646,7 @@ PyObject* kv4_attn_decode(Args a)
     require(q.dim() == 2 && q.size(1) == D && q.is_contiguous(), "q must be contiguous [H_q, 128]");
     const Cache k = cache(a[2], a[3], -1, -1, "k_codes", "k_params", kCaches);
     const Cache v = cache(a[4], a[5], k.heads, k.S_max, "v_codes", "v_params", kCaches);
-    const int H_q = narrow(q.size(0)), S = integer(a[1]);
+    const int H_q = narrow(q.size(0)), S = position(a[1]);
     const float scale = real(a[6]);
     const Result out = output(a[7], a[8], {H_q, D}, q);
     const rcp_dtype od = out_code(out.t, "out must be float16 or float32 [H_q, 128]");
@@ -663,23 +675,12 @@ inline std::vector<int> integers(PyObject* o)
     const Py_ssize_t n = PySequence_Fast_GET_SIZE(s);
     std::vector<int> r(static_cast<size_t>(n));
     for (Py_ssize_t i = 0; i < n; ++i) {
-        PyObject* item = PySequence_Fast_GET_ITEM(s, i);
-        PyObject* whole = PyLong_Check(item) ? (Py_INCREF(item), item) : PyNumber_Long(item);
-        int overflow = 0;
-        long long v = 0;
-        if (whole != nullptr) {
-            v = PyLong_AsLongLongAndOverflow(whole, &overflow);
-            Py_DECREF(whole);
-        }
-        if (PyErr_Occurred()) {
+        try {
+            r[static_cast<size_t>(i)] = position(PySequence_Fast_GET_ITEM(s, i));
+        } catch (...) {
             Py_DECREF(s);
-            throw Raised{};
+            throw;
         }
-        if (overflow != 0 || v < INT_MIN || v > INT_MAX) {
-            Py_DECREF(s);
-            narrow(INT64_MAX);
-        }
-        r[static_cast<size_t>(i)] = static_cast<int>(v);
     }
     Py_DECREF(s);
     return r;

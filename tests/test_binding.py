@@ -2,6 +2,7 @@
 ValueError before any call into the library, and the public signatures keep their defaults."""
 import inspect
 
+import numpy as np
 import pytest
 import torch
 
@@ -60,3 +61,23 @@ def test_public_signatures_keep_their_defaults():
     p = inspect.signature(rcp.quant_w2a4_gemv).parameters
     assert list(p)[:6] == ["packed", "codebook", "N", "K", "x", "clip_ratio"] and p["out_dtype"].default is torch.float16
     assert inspect.signature(rcp.kv4_append).parameters["clip_ratio"].default == 0.95
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("as_position", [float, np.int64, np.float32, lambda n: torch.tensor(n)])
+def test_positions_are_whatever_int_takes(as_position):
+    S, H = 3, 2
+    x = torch.randn((S, H, 128), generator=torch.Generator().manual_seed(1)).cuda()
+    a, b = (rcp.kv4_new_cache(H, S + 2, "cuda") + rcp.kv4_new_cache(H, S + 2, "cuda") for _ in range(2))
+    rcp.kv4_append(x, 2, a[0], a[1])
+    rcp.kv4_append_kv(x, x, 1, *a)
+    want = rcp.kv4_attn_decode(x[0], S, *a, 0.1)
+    rcp.kv4_append(x, as_position(2), b[0], b[1])
+    rcp.kv4_append_kv(x, x, as_position(1), *b)
+    got = rcp.kv4_attn_decode(x[0], as_position(S), *b, 0.1)
+    assert all(torch.equal(u, v) for u, v in zip(a, b)) and torch.equal(want, got)
+    rcp.kv4_append_batched(x[:1], [as_position(0)], a[0], a[1])
+    many = rcp.kv4_attn_decode_batched(x[:1], [as_position(S)], *a, 0.1)
+    assert torch.equal(many[0], rcp.kv4_attn_decode(x[0], S, *a, 0.1))
+    with pytest.raises((TypeError, ValueError)):
+        rcp.kv4_append(x, "two", a[0], a[1])
