@@ -9,6 +9,7 @@
 #include <Python.h>
 
 #include <ATen/ops/empty.h>
+#include <c10/core/DefaultDtype.h>
 #include <c10/hip/HIPStream.h>
 #include <torch/csrc/Dtype.h>
 #include <torch/csrc/autograd/python_variable.h>
@@ -134,6 +135,7 @@ inline int64_t nbytes(const Tensor& t) { return static_cast<int64_t>(t.nbytes())
 
 inline at::ScalarType scalar_type(PyObject* o)
 {
+    if (none(o)) return c10::get_default_dtype_as_scalartype();  // as torch.empty has it
     if (!THPDtype_Check(o)) throw Bad{"out_dtype must be a torch.dtype"};
     return reinterpret_cast<THPDtype*>(o)->scalar_type;
 }

@@ -63,6 +63,19 @@ def test_public_signatures_keep_their_defaults():
     assert inspect.signature(rcp.kv4_append).parameters["clip_ratio"].default == 0.95
 
 
+def test_an_output_type_left_to_torch():
+    """out_dtype=None is torch's default type: float32 is an output type (the next check is the one that fires), float64 is not."""
+    call = lambda: rcp.quant_w2a4_gemv(P, C, N, K, X, out_dtype=None)
+    with pytest.raises(ValueError, match="must be a contiguous CUDA tensor"):
+        call()
+    torch.set_default_dtype(torch.float64)
+    try:
+        with pytest.raises(ValueError, match="out must be float16 or float32"):
+            call()
+    finally:
+        torch.set_default_dtype(torch.float32)
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("as_position", [float, np.int64, np.float32, lambda n: torch.tensor(n)])
 def test_positions_are_whatever_int_takes(as_position):
