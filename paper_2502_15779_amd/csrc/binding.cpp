@@ -672,6 +672,7 @@ PyObject* kv4_attn_decode(Args a)
 
 inline std::vector<int> integers(PyObject* o)
 {
+    if (PyObject_Size(o) < 0) throw Raised{};  // (an iterator has no length)
     PyObject* s = PySequence_Fast(o, "a sequence of integers is wanted");
     if (s == nullptr) throw Raised{};
     const Py_ssize_t n = PySequence_Fast_GET_SIZE(s);
@@ -712,9 +713,11 @@ PyObject* kv4_attn_decode_batched(Args a)
     const Tensor& q = tensor(a[0], "q");
     heads_of(q, "q must be contiguous [B, H_q, 128]");
     const int B = narrow(q.size(0)), H_q = narrow(q.size(1));
+    const char* const each = "one length per sequence, and a pooled cache of B * H_kv heads";
     const std::vector<int> lens = integers(a[1]);
+    require(static_cast<int>(lens.size()) == B && B > 0, each);
     const Cache k = cache(a[2], a[3], -1, -1, "k_codes", "k_params", kPool);
-    require(static_cast<int>(lens.size()) == B && B > 0 && k.heads % B == 0, "one length per sequence, and a pooled cache of B * H_kv heads");
+    require(k.heads % B == 0, each);
     const Cache v = cache(a[4], a[5], k.heads, k.S_max, "v_codes", "v_params", kPool);
     const float scale = real(a[6]);
     const int64_t values = static_cast<int64_t>(B) * H_q * D;

@@ -29,7 +29,8 @@ OUT = torch.zeros((1, N), dtype=torch.float16)
     (lambda: rcp.kv4_append(X.view(1, 1, K)[..., :64], 0, P, P), "x must be contiguous"),
     (lambda: rcp.kv4_append(X.view(1, 1, K), 0, P, P), "codes must be uint8"),
     (lambda: rcp.kv4_attn_decode_batched(X.view(1, 1, K), [1, 2], *[torch.zeros((2, 4, n), dtype=torch.uint8) for n in (64, 4, 64, 4)],
-                                         1.0), "must be a contiguous CUDA tensor|one length per sequence"),
+                                         1.0), "one length per sequence"),
+    (lambda: rcp.kv4_append_batched(X.view(1, 1, K), [1, 2], P, P), "one position per sequence"),
 ])
 def test_arguments_that_do_not_fit_are_value_errors(call, message):
     with pytest.raises(ValueError, match=message):
@@ -55,6 +56,11 @@ Q, CODES, PARAMS = torch.zeros((1, 1, K)), torch.zeros((1, 4, 64), dtype=torch.u
 def test_numbers_beyond_32_bits_are_not_cut(call):
     with pytest.raises(ValueError, match="32-bit"):
         call()
+
+
+def test_lengths_have_a_length():
+    with pytest.raises(TypeError):
+        rcp.kv4_append_batched(Q, iter([1]), CODES, PARAMS)
 
 
 def test_public_signatures_keep_their_defaults():
