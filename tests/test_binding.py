@@ -100,3 +100,70 @@ def test_positions_are_whatever_int_takes(as_position):
     assert torch.equal(many[0], rcp.kv4_attn_decode(x[0], S, *a, 0.1))
     with pytest.raises((TypeError, ValueError)):
         rcp.kv4_append(x, "two", a[0], a[1])
+
+
+def _layer(seed):
+    """Weights of one small layer (two calls with its output in between) and a key / value cache with some tokens."""
+    g = torch.Generator().manual_seed(seed)
+    n, k, h = 512, 512, 4
+    part = torch.full((n, 3), 1 / 3).cuda()
+    packed, codebook = rcp.pack_weights((torch.randn((n, k), generator=g) * 0.02).cuda().half(), torch.full((n,), -0.04).cuda(),
+                                        torch.full((n,), 0.04).cuda(), part)
+    caches = rcp.kv4_new_cache(h, 40, "cuda") + rcp.kv4_new_cache(h, 40, "cuda")
+    for i in (0, 2):
+        rcp.kv4_append(torch.randn((30, h, 128), generator=g).cuda(), 0, caches[i], caches[i + 1])
+    return packed, codebook, n, k, caches
+
+
+def _step(layer, x, out):
+    """x -> product -> as key, value and query of one more token -> attention output, all on the current stream."""
+    packed, codebook, n, k, caches = layer
+    rcp.quant_w2a4_gemv(packed, codebook, n, k, x, 0.9, out=out[0])
+    token = out[0].view(1, 4, 128)
+    rcp.kv4_append_kv(token, token, 30, *caches, rotate_k=True)
+    rcp.kv4_rotate_attn_decode(token[0], 31, *caches, 0.1, out=out[1], workspace=out[2])
+
+
+def _buffers():
+    return [torch.zeros((1, 512), dtype=torch.float16, device="cuda"), torch.zeros((4, 128), device="cuda"),
+            torch.zeros(rcp.kv4_workspace_bytes(4, 40), dtype=torch.uint8, device="cuda")]
+
+
+@pytest.mark.gpu
+def test_calls_run_on_the_current_stream():
+    """On a side stream that first keeps the GPU busy and then writes the input: a call on any other stream would read the
+    old input (the default stream is idle meanwhile)."""
+    layer, x, new = _layer(3), torch.zeros(512, device="cuda"), torch.randn(512, generator=torch.Generator().manual_seed(4)).cuda()
+    want, got = _buffers(), _buffers()
+    _step(layer, new, want)
+    torch.cuda.synchronize()
+    side = torch.cuda.Stream()
+    with torch.cuda.stream(side):
+        torch.cuda._sleep(20_000_000)   # some 10 ms
+        x.copy_(new)
+        _step(layer, x, got)
+    side.synchronize()
+    assert torch.equal(want[0], got[0]) and torch.equal(want[1], got[1]) and got[1].abs().max() > 0
+
+
+@pytest.mark.gpu
+def test_calls_can_be_captured():
+    """One captured step, replayed on new inputs with eager work between the replays."""
+    layer, x, out = _layer(5), torch.zeros(512, device="cuda"), _buffers()
+    side = torch.cuda.Stream()
+    with torch.cuda.stream(side):
+        _step(layer, x, out)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=side):
+        _step(layer, x, out)
+    g = torch.Generator().manual_seed(6)
+    for _ in range(4):
+        new, want = torch.randn(512, generator=g).cuda(), _buffers()
+        x.copy_(new)
+        graph.replay()
+        torch.cuda.synchronize()
+        got = [t.clone() for t in out[:2]]
+        _step(layer, new, want)
+        torch.cuda.synchronize()
+        assert torch.equal(want[0], got[0]) and torch.equal(want[1], got[1]) and got[1].abs().max() > 0

@@ -240,6 +240,33 @@ def test_grouped_products_of_several_row_blocks(N, K, M):
     assert np.linalg.norm(out - ref.reshape(M, N)) <= 1e-5 * np.linalg.norm(ref)
 
 
+@pytest.mark.parametrize("N,K,M", [
+    (16388, 1024, 16), (16388, 2176, 5),                    # five row blocks per workgroup: single groups, batches of four
+    (24580, 4096, 3), (24580, 4096, 7),                     # seven, B operands of four and of eight tokens
+    (28676, 2176, 2), (28676, 4096, 8), (28676, 2176, 16),  # eight, the last workgroup with one row group
+    (33028, 8192, 16),                                      # the cap of eight: more workgroups than compute units, sixteen
+])                                                          # wavefronts, the largest LDS
+def test_grouped_products_of_many_row_blocks(N, K, M):
+    print(f"grouped gemm N={N} K={K} M={M}", flush=True)
+    NG, rng = K // 128, np.random.default_rng(47)
+    rows = np.unique(np.r_[0:64, rng.integers(0, N, 512), N - 160:N])
+    idx = rcp_synth.random_indices(47, f"mb{N}x{K}", N, K)
+    q = rcp_synth.random_int4(47 + M, f"mb{K}", M, K)
+    cb = np.sort(rng.standard_normal((N // 4, NG, 4, 4), dtype=np.float32) * 0.03, axis=3).astype(np.float16)
+    sc = (np.abs(rng.standard_normal(M)) * 0.2 + 0.05).astype(np.float16)
+    xq = ((q[:, 0::2].astype(np.uint8) & 0xF) | ((q[:, 1::2].astype(np.uint8) & 0xF) << 4)).astype(np.uint8)
+    dev = [torch.from_numpy(a).to(DEV) for a in (oracle.pack_indices_grouped(idx), cb, xq, sc)]
+    out = rcp.w2a4_gemm_grouped(dev[0], dev[1], N, K, dev[2], dev[3], M, out_dtype=torch.float32)[:, rows].cpu().numpy()
+    lut = cb.astype(np.float64)[rows // 4, :, rows % 4]
+    w = np.take_along_axis(lut, idx[rows].reshape(-1, NG, 128).astype(np.int64), axis=2).reshape(-1, K)
+    ref = (q.astype(np.float64) @ w.T) * sc.astype(np.float64)[:, None]
+    # as in test_grouped_products_of_several_row_blocks, with the sums of |q| for those of each level
+    cond = (np.abs(q).astype(np.float64) @ np.abs(w).T) * sc.astype(np.float64)[:, None]
+    spread = sc.astype(np.float64)[:, None] * (8 * 128 * np.abs(lut).max(axis=2).sum(axis=1))[None]
+    assert np.all(np.abs(out - ref) <= (4 * NG + 20) * 2.0 ** -24 * (2 * cond + spread))
+    assert np.linalg.norm(out - ref) <= 1e-5 * np.linalg.norm(ref)
+
+
 @pytest.mark.parametrize("K", [512, 2176, 4096])   # groups one at a time, batches of four with a rest, whole batches
 @pytest.mark.parametrize("M", [3, 8, 16])
 def test_the_four_rows_of_a_nibble_are_computed_alike(K, M):
