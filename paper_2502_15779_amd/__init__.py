@@ -139,7 +139,8 @@ def build():
 
 
 def lib():
-    """The loaded shared library; raises if it has not been built."""
+    """The loaded shared library with the prototypes of its whole C ABI, for callers that hand over addresses themselves (the
+    calls below go through csrc/binding.cpp); raises if it has not been built."""
     global _lib
     if _lib is None:
         if not os.path.exists(LIB_PATH):

@@ -40,6 +40,16 @@ def test_every_declared_function_is_exported(lib):
         assert hasattr(lib, n), n
 
 
+def test_the_python_handle_carries_every_prototype():
+    """rcp.lib() is what a caller with addresses of its own goes through: without its prototypes, ctypes would cut a 64-bit
+    address given as a number to 32 bits."""
+    import paper_2502_15779_amd as rcp
+    handle = rcp.lib()
+    for name in _declared_functions():
+        f = getattr(handle, name)
+        assert name in ("rcp_version", "rcp_last_error") or f.argtypes, name
+
+
 def test_size_queries(lib):
     lib.rcp_packed_bytes.restype = ctypes.c_size_t
     assert lib.rcp_packed_bytes(4096, 4096) == 4096 * 4096 // 4
