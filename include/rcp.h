@@ -161,7 +161,8 @@ int rcp_version(void);
  *                  gives every compute unit the same number of workgroups.  With group-wise tables: rounded up to blocks
  *                  of sixteen rows; automatic = as many blocks as one workgroup per compute unit takes, at most eight
  *   "kv_tokens"    cached tokens per workgroup of rcp_kv4_attn_decode: 64, 128, 256 (all loads of a workgroup
- *                  issued at once), 512, 1024, 2048 (the matrix-core kernel for long contexts, batches and grouped heads)
+ *                  issued at once), 512, 1024, 2048 (the matrix-core kernel for long contexts, batches and grouped heads);
+ *                  automatic calls with one query head per cache head and middle sizes take a third, streaming kernel
  *   "gemv_waves"   wavefronts per workgroup of the fused one-token GEMV (rcp_quant_w2a4_gemv): 4, 8
  *                  (8 needs K >= 2048 and "gemv_lanes" left automatic; otherwise 4 is used)
  *   "gemv_oneshot" one-token kernel that issues every weight load of a workgroup up front (one group of four rows
@@ -500,7 +501,10 @@ int rcp_quant_w3a4_gemv(const void* packed, const void* codebook, int N, int K,
  * rcp_kv4_attn_decode: one query token against cache positions 0 .. S-1 (1 <= S <= S_max):
  *     out[h] = sum_t softmax_t(softmax_scale * q[h] . K[g][t]) * V[g][t],   g = h / (H_q / H_kv)
  *   q: [H_q][128] of `q_dtype`; out: [H_q][128] of `out_dtype` (RCP_F16 or RCP_F32); H_q a multiple of
- *   H_kv.  Sums are binary32.  workspace: rcp_kv4_workspace_bytes(H_q, S) bytes of device memory
+ *   H_kv.  Sums are binary32.  Long contexts, batches and grouped heads multiply the query and the softmax weights (times the
+ *   value steps) as pairs of binary16 numbers: 22 bits and more of every value down to 2^-12 of its head's largest, an
+ *   absolute 2^-34 of the largest below that.  A head's result depends on no other head, to the last bit.
+ *   workspace: rcp_kv4_workspace_bytes(H_q, S) bytes of device memory
  *   (RCP_ERR_WORKSPACE when missing or smaller; the size covers every "kv_tokens" setting), overwritten by every call.  S above
  *   RCP_KV_MAX_S returns RCP_ERR_UNSUPPORTED.
  */

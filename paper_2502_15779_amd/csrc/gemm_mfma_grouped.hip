@@ -264,17 +264,17 @@ int launch_gemm_mfma_grouped(const void* packed, const void* codebook, int N, in
     const int NG = K / RCP_GROUP;
     // One workgroup per compute unit, of as many sixteen-row blocks as that takes ("gemm_rows" sets the rows): the converted
     // activations serve all of them, and no unit carries more than its share.  At 6 tokens, blocks per workgroup 1 / 2 / 3 /
-    // 4 / 7 / 8: 12288 x 4096 8.3 / 7.3 / 6.6 / 7.3 / 10.1 / 11.0 us, 28672 x 4096 15.3 / 12.5 / 12.7 / 11.1 / 10.6 / 11.3;
-    // the first form of this kernel (64 or 16 rows, one group at a time): 9.2 and 15.0.
+    // 4: 12288 x 4096 8.0 / 7.2 / 6.4 / 7.0 us, 28672 x 4096 15.7 / 12.6 / 12.8 / 11.2, and 10.6 with seven; the first form
+    // of this kernel (64 or 16 rows, one group at a time): 7.7 and 15.3.
     const int total = (N + 15) / 16, cus = num_compute_units();
     int nb = (total + cus - 1) / cus;
     if (nb > MG_MAX_BLOCKS) nb = MG_MAX_BLOCKS;
     if (options().gemm_rows != 0) nb = (options().gemm_rows + 15) / 16;
     // One group at a time up to K = 2048, where batches of four would leave most of the wavefronts without work (256 x 512 at
-    // 16 tokens 3.8 against 2.5 us, 8192 x 2048 4.8 against 4.3; at K = 4096 4.65 against 4.8), else four.
+    // 16 tokens 3.8 against 2.5 us, 8192 x 2048 4.8 against 4.3), else four (4096 x 4096 at 16 tokens 5.0 against 5.2).
     const int batch = NG <= 16 ? 1 : 4;
     // As few wavefronts as take the batches in the same number of rounds as the most would: sixteen (4096 x 14336, 6 tokens:
-    // 10.1 us with at most eight, 9.1 with fourteen).
+    // 9.9 us with at most eight, 9.0 with fourteen).
     const int batches = (NG + batch - 1) / batch;
     int waves = options().gemm_waves != 0 ? options().gemm_waves : MG_WAVES;
     const int rounds = (batches + waves - 1) / waves;

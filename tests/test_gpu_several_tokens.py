@@ -55,8 +55,9 @@ def test_kronecker_rotation_of_several_tokens_is_as_precise_as_of_one(M, n, m):
 ])
 @pytest.mark.parametrize("q_dtype", [torch.float16, torch.float32, torch.bfloat16])
 def test_attention_of_grouped_heads_on_the_matrix_cores(H_q, H_kv, S, tokens, q_dtype):
-    """Codes, query and weights enter the matrix cores as exact binary16 pieces: the result is held to a few binary32
-    roundings of the terms (2^-20 of what a row of the sum holds), far inside the stated 1e-3."""
+    """Query and weights enter the matrix cores as pairs of binary16 numbers, codes exactly: the result is held to a few
+    binary32 roundings of the largest term a row of the sum can hold (2^-20), far inside the stated 1e-3.  (What a large value
+    without attention leaves of the small ones: test_a_large_value_without_attention_leaves_the_rest_precise.)"""
     print(f"kv4 mfma H_q={H_q} H_kv={H_kv} S={S} tokens={tokens} {q_dtype}", flush=True)
     cache = []
     for name, rotate in (("k", True), ("v", False)):
