@@ -795,8 +795,8 @@ __global__ __launch_bounds__(KV_THREADS) void kv4_attn_stream_kernel(const void*
 //   score = s_t (q . c_t - z_t sum q),   out = sum_t (p_t s_t) (c_t - 8) - sum_t p_t s_t (z_t - 8).
 // Value codes enter less 8: the two sums of `out` grow with the tokens and cancel, and their binary32 roundings with them
 // (60000 tokens of 32 heads, error against 64 bits: 4.6e-7 with 0 .. 15, 1.2e-7 with -8 .. 7; the vector form 2.5e-7).  That
-// costs nine operations for the eight codes of a dword instead of seven: 1 to 4 % of the call where several query heads share
-// a cache head (16 sequences of up to 6000 tokens 23.1 -> 23.9 us, 40000 tokens of 32 over 16 heads 24.1 -> 25.0).  (The same for the keys costs as much again and gains only
+// costs nine operations for the eight codes of a dword instead of seven: 1 to 3 % of the call where several query heads share
+// a cache head (16 sequences of up to 6000 tokens 23.5 -> 23.6 us, 40000 tokens of 32 over 16 heads 24.4 -> 25.0).  (The same for the keys costs as much again and gains only
 // where the elements of a query share an offset.)
 //   scores   rows = query heads, columns = 16 tokens, k = the 128 elements: the codes go from memory to registers in
 //            operand order (lane = token l % 16, 16 bytes l / 16 of it)
@@ -1110,7 +1110,9 @@ __global__ __launch_bounds__(KV_THREADS, RP <= 2 ? 4 : 3) void kv4_attn_mfma_ker
             const float ls = __builtin_amdgcn_logf(__builtin_amdgcn_fmed3f(fabsf(sv[s]), 0x1p-24f, 65504.0f));
 #pragma unroll
             for (int v = 0; v < HV; ++v) {
-                sc[s][v] = valid[s] ? fmaf(-kz[s], qc[v].x, sc[s][v]) * (ks[s] * qc[v].y) : -INFINITY;
+                float x = fmaf(-kz[s], qc[v].x, sc[s][v]) * (ks[s] * qc[v].y);
+                asm("" : "+v"(x));  // a select: the branch that the compiler makes of it costs 2 % of a call
+                sc[s][v] = valid[s] ? x : -INFINITY;
                 top[v] = s == 0 ? sc[s][v] + ls : fmaxf(top[v], sc[s][v] + ls);
             }
         }
@@ -1349,7 +1351,7 @@ int launch_kv4_attn(const void* q, rcp_dtype q_dt, int B, int H_q, int H_kv, int
     // 2048 x 32 pairs on.  Beyond, the matrix-core form, whose work is counted in (token, cache head) pairs: splits of 256
     // tokens below 90000 (up to 351 workgroups and the ends of the sequences), 512 up to 8192 x 32, 1024 above (sweeps of
     // all three lengths and the other forms; launches of both kernels, cold caches).  Grouped heads against the vector
-    // forms, 32 over 8: 16 sequences of 300 to 6000 tokens 45.7 -> 24.0 us, 65536 tokens 47.0 -> 21.9, 16384 tokens
+    // forms, 32 over 8: 16 sequences of 300 to 6000 tokens 45.7 -> 23.7 us, 65536 tokens 47.0 -> 21.9, 16384 tokens
     // 17.5 -> 12.2, 4100 tokens 11.7 -> 9.8; 64 over 4 heads at 8192 tokens 17.3 -> 11.7; 32 over 16 at 8192 tokens
     // 12.4 -> 10.8, at 4200 and 5000 level.
     // With one query head per cache head the streaming form up to 20480 x 32 pairs, on splits of 512 tokens up to
