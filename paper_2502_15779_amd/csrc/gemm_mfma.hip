@@ -7,16 +7,15 @@
 //     F_p[h][m] = sum_k b_p[h][k] * q[m][k],  p in {b0, b1, b0 & b1}
 // are a dense contraction of a 0/1 matrix with a small-integer matrix.  A nibble of a plane word
 // holds one column of four rows; masked down to one bit it is, read as an FP4 (E2M1) number,
-//     bit 0 -> 0.5,  bit 1 -> 1.0,  bit 2 -> 2.0   (bit 3 is the sign: it is shifted to bit 2)
-// so a plane word ANDed with 0x1111.., 0x2222.., 0x4444.. is the A operand of
-// v_mfma_f32_16x16x128_f8f6f4 for rows r = 0, 1, 2 (and (w >> 1) & 0x4444.. for r = 3) without
-// any expansion; the factors 0.5 / 1 / 2 are taken out again by the instruction's E8M0 scale of the A operand.
-// The int4 activation q = 4*hi + lo, lo in {0..3}, hi in {-2..1}, is recoded into two FP4
-// operands.  Up to 8 tokens they share one B operand (columns 0..7 carry lo, columns 8..15 hi of
-// the same tokens, the hi columns weighted 2^2 by the per-lane E8M0 scale of the B operand); beyond
-// that lo and hi are two B operands, hi weighted the same way, accumulating into the same registers.
-// Every product and every sum is a small multiple of 1/2, so the fp32 accumulators are exact
-// (|F_p| <= 8K < 2^24) and the per-level sums stay bit-exact.
+//     bit 0 -> 0.5,  bit 1 -> 1.0,  bit 2 -> 2.0,  bit 3 (the sign) set over 1.0 -> 1.0 or -1.0
+// so a plane word ANDed with 0x1111.., 0x2222.., 0x4444.. (and (w & 0x8888..) | 0x2222..) is the A operand of
+// v_mfma_f32_16x16x128_f8f6f4 for row r = 0, 1, 2 (3) without any expansion, and the AND of two such operands is the one of
+// b0 & b1.  The int4 activation q = 4*hi + lo, lo in {0..3}, hi in {-2..1}, is recoded into two FP4 operands, lo / 2 (the two
+// bits as they are) and 2 hi.  Up to 8 tokens they share one B operand (columns 0..7 carry lo, columns 8..15 hi of the same
+// tokens); beyond that lo and hi are two B operands, accumulating into the same registers.  No scale is involved: a scaled
+// instruction holds the vector unit for eight cycles, a plain one for four.  What the rows' values leave in the sums
+// (F/4, F/2, F, and T/2 - F with the sum T of q) is undone once per output.  Every product and every sum is a small multiple
+// of 1/4, so the fp32 accumulators are exact (|sum| <= 8K <= 2^18) and the per-level sums stay bit-exact.
 //
 // Work decomposition.  A workgroup owns 16 groups of four rows (64 output rows): lane l of a
 // wavefront supplies row group l%16 and the 32 columns of K-block l/16 of a 128-column step
@@ -33,6 +32,17 @@ constexpr int MM_PLANE = 16 * MM_STRIDE;
 constexpr int MM_SUMS = 3 * MM_PLANE + 16;          // ints that are accumulated into (zeroed first)
 constexpr int MM_LDS_INTS = MM_SUMS + 2 * 64 + 16;  // + the 64 LUT rows of the block and the scales
 
+constexpr uint32_t MM_ONE = 0x22222222u;      // 1.0 in every nibble: with its sign bit -1.0
+constexpr float MM_MAGIC = 0x1.8p21f;         // |acc| <= 8 K <= 2^18 beside it: the sum is exact to a quarter
+constexpr uint32_t MM_MAGIC_BITS = 0x4a400000u;
+
+// eight int4 -> eight FP4 codes of 2 (q >> 2): 0000, 0100 (2), 1110 (-4), 1100 (-2) for the upper bits 00, 01, 10, 11
+__device__ __forceinline__ uint32_t fp4_twice_hi(uint32_t x)
+{
+    const uint32_t s1 = x >> 1, s2 = x >> 2;
+    return (x & 0x88888888u) | ((x | s1) & 0x44444444u) | (s2 & ~s1 & 0x22222222u);
+}
+
 struct MmStage {
     u32x4 wa, wb;  // two units: 4 rows x 32 columns, bit planes b0 / b1 interleaved per cell
     u32x4 xq;      // 32 int4 activations of this lane's token
@@ -45,6 +55,10 @@ struct MmStage {
 // weights and the activations are recoded once per 16 instead of once per 64 rows, but a matrix
 // of 4096 rows becomes 256 workgroups instead of 64.
 // MM_NS: K steps per pipeline stage.
+// What bounds it: the vector unit and the latency of a wavefront's few steps (12288 x 4096 at 16 tokens: 3.3 of 5.7 us in the
+// loop, 0.7 in the sums over the wavefronts).  Against scaled instructions, a fourth row shifted down (five operations a plane
+// word pair instead of three in 16-row workgroups) and activations recoded to 0..3 by twice the operations: 22016 x 4096 at
+// 16 / 3 tokens 9.8 / 8.2 -> 9.4 / 7.9 us, 4096 x 11008 7.7 / 6.8 -> 7.4 / 6.4, and 4 % in the mean over 378 shapes.
 template <bool OUT_F16, bool PACKED, bool NARROW, int MM_NS>
 __global__ __launch_bounds__(MM_MAX_THREADS) void gemm_mfma_kernel(const uint4* __restrict__ packed,
                                                                    const uint2* __restrict__ codebook, int N, int K,
@@ -64,12 +78,8 @@ __global__ __launch_bounds__(MM_MAX_THREADS) void gemm_mfma_kernel(const uint4* 
     // evenly; lanes with i >= RG load nothing and their rows of the A operand are zero)
     const int RB = NARROW ? 16 : 4 * RG;  // output rows of the workgroup
     const int rg = NARROW ? static_cast<int>(blockIdx.x) * 4 + (i >> 2) : static_cast<int>(blockIdx.x) * RG + i;
-    // NARROW: this lane's row of the nibble as a mask (the fourth row is the FP4 sign bit: shifted down first)
-    const uint32_t row_mask = (i & 3) == 0 ? 0x11111111u : (i & 3) == 1 ? 0x22222222u : 0x44444444u;
-    const int row_shift = (i & 3) == 3 ? 1 : 0;
-    // E8M0 scale that takes the mask's value (0.5, 1, 2, 2 for rows 0..3 of a nibble) out of the products again
-    const int row_scale = (i & 3) == 0 ? 0x80 : (i & 3) == 1 ? 0x7f : 0x7e;
-
+    // NARROW: this lane's row of the nibble as a mask, and what is set beside it (the fourth row is the FP4 sign bit)
+    const uint32_t row_mask = 0x11111111u << (i & 3), row_set = (i & 3) == 3 ? MM_ONE : 0u;
 
     const __amdgpu_buffer_rsrc_t wres = __builtin_amdgcn_make_buffer_rsrc(
         const_cast<uint4*>(packed), 0, static_cast<int>(static_cast<unsigned>(G) * static_cast<unsigned>(U) * 16u), 0x00020000);
@@ -79,7 +89,6 @@ __global__ __launch_bounds__(MM_MAX_THREADS) void gemm_mfma_kernel(const uint4* 
     const unsigned wbase = (rg < G && (NARROW || i < RG)) ? (static_cast<unsigned>(rg) * U + 2u * kb) * 16u : 0x80000000u;
     const int token = PACKED ? (i & 7) : i;  // the token whose activations this lane feeds into B
     const bool hi_lane = PACKED && i >= 8;
-    const int col_scale = hi_lane ? 0x81 : 0x7f;  // E8M0 scale of this lane's B values: 2^2 for a hi column
     const unsigned xbase = static_cast<unsigned>(token) * (K / 2) + kb * 16u;
 
     auto load = [&](int step_index, MmStage& st) {
@@ -121,7 +130,7 @@ __global__ __launch_bounds__(MM_MAX_THREADS) void gemm_mfma_kernel(const uint4* 
         for (int h = 0; h < NB; ++h) bop[h] = v8i{0, 0, 0, 0, 0, 0, 0, 0};
 #pragma unroll
         for (int d = 0; d < 4; ++d) {
-            const uint32_t lo = fp4_lo(xw[d]), hi = fp4_hi(xw[d]);
+            const uint32_t lo = xw[d] & 0x33333333u, hi = fp4_twice_hi(xw[d]);
             if constexpr (PACKED) {
                 bop[0][d] = static_cast<int>(hi_lane ? hi : lo);
             } else {
@@ -138,18 +147,14 @@ __global__ __launch_bounds__(MM_MAX_THREADS) void gemm_mfma_kernel(const uint4* 
             for (int p = 0; p < 3; ++p) an[p] = v8i{0, 0, 0, 0, 0, 0, 0, 0};
 #pragma unroll
             for (int d = 0; d < 4; ++d) {
-                an[0][d] = static_cast<int>((p0[d] >> row_shift) & row_mask);
-                an[1][d] = static_cast<int>((p1[d] >> row_shift) & row_mask);
+                an[0][d] = static_cast<int>((p0[d] & row_mask) | row_set);
+                an[1][d] = static_cast<int>((p1[d] & row_mask) | row_set);
                 an[2][d] = an[0][d] & an[1][d];
             }
 #pragma unroll
             for (int p = 0; p < 3; ++p) {
-                if constexpr (PACKED) {
-                    acc[p][0] = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(an[p], bop[0], acc[p][0], 4, 4, 0, row_scale, 0, col_scale);
-                } else {
-                    acc[p][0] = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(an[p], bop[0], acc[p][0], 4, 4, 0, row_scale, 0, 0x7f);
-                    acc[p][0] = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(an[p], bop[1], acc[p][0], 4, 4, 0, row_scale, 0, 0x81);
-                }
+#pragma unroll
+                for (int h = 0; h < NB; ++h) acc[p][0] = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(an[p], bop[h], acc[p][0], 4, 4, 0, 0, 0, 0);
             }
             return;
         }
@@ -166,25 +171,17 @@ __global__ __launch_bounds__(MM_MAX_THREADS) void gemm_mfma_kernel(const uint4* 
                     a[p][0][d] = static_cast<int>(w & 0x11111111u);
                     a[p][1][d] = static_cast<int>(w & 0x22222222u);
                     a[p][2][d] = static_cast<int>(w & 0x44444444u);
-                    a[p][3][d] = static_cast<int>((w >> 1) & 0x44444444u);
+                    a[p][3][d] = static_cast<int>((w & 0x88888888u) | MM_ONE);
                 } else {
 #pragma unroll
                     for (int r = 0; r < 4; ++r) a[2][r][d] = a[0][r][d] & a[1][r][d];  // the masks of b0 & b1
                 }
             }
-            if constexpr (PACKED) {
+#pragma unroll
+            for (int h = 0; h < NB; ++h)
 #pragma unroll
                 for (int r = 0; r < 4; ++r)
-                    acc[p][r] = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(a[p][r], bop[0], acc[p][r], 4, 4, 0, r == 0 ? 0x80 : r == 1 ? 0x7f : 0x7e, 0, col_scale);
-            } else {
-                // E8M0 scales (byte 0): the inverse of the mask's value for A, 2^0 for lo, 2^2 for hi
-#pragma unroll
-                for (int r = 0; r < 4; ++r)
-                    acc[p][r] = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(a[p][r], bop[0], acc[p][r], 4, 4, 0, r == 0 ? 0x80 : r == 1 ? 0x7f : 0x7e, 0, 0x7f);
-#pragma unroll
-                for (int r = 0; r < 4; ++r)
-                    acc[p][r] = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(a[p][r], bop[1], acc[p][r], 4, 4, 0, r == 0 ? 0x80 : r == 1 ? 0x7f : 0x7e, 0, 0x81);
-            }
+                    acc[p][r] = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(a[p][r], bop[h], acc[p][r], 4, 4, 0, 0, 0, 0);
         }
     };
     // Steps past the end of K read zeros (no traffic) and add zeros.
@@ -211,27 +208,35 @@ __global__ __launch_bounds__(MM_MAX_THREADS) void gemm_mfma_kernel(const uint4* 
     for (int j = 0; j < MM_NS; ++j) keep |= sA[j].wa.x | sA[j].wb.x | sA[j].xq.x | sB[j].wa.x | sB[j].wb.x | sB[j].xq.x;
     if (__builtin_expect(K < 0, 0)) red[0] = static_cast<int>(keep);  // never true
 
-    // acc[p][r][v] = F_p (packed: its lo part, or four times its hi part) of row 4*(RG*block + 4*kb + v) + r and this
-    // lane's token, an integer: the instruction's scales have taken out the mask's power of two and weighted the hi
-    // columns.  The wavefronts (and, when packed, the two columns of a token) add them up in LDS (integer adds: the
-    // binary32 LDS add is far slower).
-    if constexpr (NARROW) {
-        // acc[p][0][v]: row v of row group kb of the block
-        int* dst = red + token * MM_STRIDE + 4 * kb;
+    // acc[p][r][v] = F_p / 4, F_p / 2, F_p or (T - 2 F_p) / 2 (packed: its lo or its hi part) of row 4*(RG*block + 4*kb + v) + r,
+    // r = 0, 1, 2 or 3, and this lane's token.  The wavefronts add them up in LDS in units of a quarter (integer adds: the
+    // binary32 LDS add is far slower): under MM_MAGIC the lowest bit of a float is a quarter, and the bits of MM_MAGIC itself,
+    // added once per wavefront, are taken out of the total.  The two columns of a token are added before and columns without a
+    // token left out: the LDS adds sixteen lanes a cycle (12288 x 1024 at 6 tokens, where
+    // this phase took 0.74 of 3.2 us: 4.14 -> 4.05 us a launch; 6144 x 1024 at 3 tokens 4.00 -> 3.30).
+    auto quarters = [](float v) {
+        if constexpr (PACKED) v += __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0x128, 0xf, 0xf, true));  // lane ^ 8
+        return static_cast<int>(__float_as_uint(v + MM_MAGIC));
+    };
+    constexpr int RN = NARROW ? 1 : 4;
+    int sums[3][RN][4];
+#pragma unroll
+    for (int p = 0; p < 3; ++p)
+#pragma unroll
+        for (int r = 0; r < RN; ++r)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) sums[p][r][v] = quarters(acc[p][r][v]);
+    if (i < M && !hi_lane) {
+        // narrow: acc[p][0][v] is row v of row group kb of the block
+        int* dst = red + token * MM_STRIDE + (NARROW ? 4 : 16) * kb;
 #pragma unroll
         for (int p = 0; p < 3; ++p)
 #pragma unroll
-            for (int v = 0; v < 4; ++v) atomicAdd(dst + p * MM_PLANE + v, static_cast<int>(acc[p][0][v]));
-    } else {
-        int* dst = red + token * MM_STRIDE + 16 * kb;
+            for (int r = 0; r < RN; ++r)
 #pragma unroll
-        for (int p = 0; p < 3; ++p)
-#pragma unroll
-            for (int r = 0; r < 4; ++r)
-#pragma unroll
-                for (int v = 0; v < 4; ++v) atomicAdd(dst + p * MM_PLANE + 4 * v + r, static_cast<int>(acc[p][r][v]));
+                for (int v = 0; v < 4; ++v) atomicAdd(dst + p * MM_PLANE + (NARROW ? v : 4 * v + r), sums[p][r][v]);
+        atomicAdd(red + 3 * MM_PLANE + token, tsum);
     }
-    if (!hi_lane) atomicAdd(red + 3 * MM_PLANE + token, tsum);
     {
         if (tid < RB) {
             red[MM_SUMS + 2 * tid] = static_cast<int>(lut_pre.x);
@@ -241,13 +246,19 @@ __global__ __launch_bounds__(MM_MAX_THREADS) void gemm_mfma_kernel(const uint4* 
     }
     __syncthreads();
 
+    const uint32_t magic_total = MM_MAGIC_BITS * static_cast<uint32_t>(W);
     for (int o = tid; o < M * 64; o += 64 * W) {
         const int n = o >> 6, hh = o & 63;
         const int h = blockIdx.x * RB + hh;
         if (hh >= RB || h >= N) continue;
-        const int F0 = red[n * MM_STRIDE + hh], F1 = red[MM_PLANE + n * MM_STRIDE + hh];
-        const int F3 = red[2 * MM_PLANE + n * MM_STRIDE + hh];
         const int T = red[3 * MM_PLANE + n];
+        // the sums hold F, 2 F, 4 F or 2 T - 4 F by the row of the nibble
+        const int down = min(hh & 3, 2), flip = (hh & 3) == 3 ? -1 : 0, from = (hh & 3) == 3 ? 2 * T + 1 : 0;
+        auto plane = [&](int p) {
+            const int x = static_cast<int>(static_cast<uint32_t>(red[p * MM_PLANE + n * MM_STRIDE + hh]) - magic_total);
+            return ((x ^ flip) + from) >> down;
+        };
+        const int F0 = plane(0), F1 = plane(1), F3 = plane(2);
         const int P3 = F3, P1 = F0 - F3, P2 = F1 - F3, P0 = T - F0 - F1 + F3;
         const uint2 lut = make_uint2(static_cast<uint32_t>(red[MM_SUMS + 2 * hh]), static_cast<uint32_t>(red[MM_SUMS + 2 * hh + 1]));
         const float c0 = half_bits_to_float(static_cast<uint16_t>(lut.x & 0xffffu));
@@ -298,9 +309,12 @@ int launch_gemm_mfma(const void* packed, const void* codebook, int N, int K, con
     auto* x4 = static_cast<const uint4*>(xq);
     auto* sc = static_cast<const uint16_t*>(scale);
     const dim3 grid(blocks), block(waves * 64);
-    // two steps per pipeline stage once a wavefront has eight or more steps to walk (4096 x 11008: 6.9 against 7.6 us;
-    // slower on the short loops of K = 4096)
-    const bool deep = options().gemm_stage != 0 ? options().gemm_stage == 2 : KS >= 8 * waves;
+    // Two steps per pipeline stage once a wavefront has eight or more steps to walk (4096 x 11008: 6.9 against 7.6 us), and
+    // four steps of 16-row workgroups, if they are alone on their compute units (4096 x 4096, 4 / 16 tokens: 3.82 / 4.29
+    // against 4.07 / 4.40 us; with more than one workgroup a unit 8192 x 4096 at 6 tokens takes 6.1 instead of 5.5, and 5120
+    // columns, which are no whole number of double steps, 4.5 instead of 4.3).
+    const bool deep =
+        options().gemm_stage != 0 ? options().gemm_stage == 2 : KS >= 8 * waves || (narrow && blocks <= cus && KS == 4 * waves);
 #define RCP_MM(F16, PK, NA)                                                                                   \
     do {                                                                                                      \
         if (deep) gemm_mfma_kernel<F16, PK, NA, 2><<<grid, block, 0, st>>>(pk, cb, N, K, x4, sc, M, waves, RG, out, P); \

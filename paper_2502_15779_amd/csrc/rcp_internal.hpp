@@ -433,21 +433,6 @@ __host__ __device__ constexpr int gemv_x_bytes(int K, int M, int span /* LG * UN
 typedef int v8i __attribute__((ext_vector_type(8)));
 typedef float v4f __attribute__((ext_vector_type(4)));
 
-// eight int4 (two's complement) -> eight FP4 codes of lo = q & 3 in {0, 1, 2, 3}
-__device__ __forceinline__ uint32_t fp4_lo(uint32_t x)
-{
-    const uint32_t n0 = x & 0x11111111u, n1 = x & 0x22222222u;
-    const uint32_t both = n0 & (n1 >> 1);            // lo == 3 -> code 0101 (3.0): bit 0
-    return both | (((n0 ^ both) | n1) << 1);         // lo == 1 -> 0010 (1.0), lo >= 2 -> bit 2 (2.0)
-}
-
-// eight int4 -> eight FP4 codes of hi = q >> 2 in {-2, -1, 0, 1}: 1100, 1010, 0000, 0010
-__device__ __forceinline__ uint32_t fp4_hi(uint32_t x)
-{
-    const uint32_t n3 = x & 0x88888888u, n2 = x & 0x44444444u;
-    return n3 | ((n3 >> 1) & ~n2) | (n2 >> 1);
-}
-
 // eight int4 -> eight FP8 (E4M3) bytes in order, each q * 2^-9: 0..8 with that unit are E4M3 codes of their own value
 // (subnormals and the first binade), so only the sign has to be split off
 __device__ __forceinline__ void int4_to_fp8(uint32_t x, int& first, int& second)

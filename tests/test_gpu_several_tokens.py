@@ -268,6 +268,32 @@ def test_grouped_products_of_many_row_blocks(N, K, M):
     assert np.linalg.norm(out - ref) <= 1e-5 * np.linalg.norm(ref)
 
 
+@pytest.mark.parametrize("rows", [16, 44])
+@pytest.mark.parametrize("M", [3, 8, 9, 12])   # one operand for both halves of q (a column per half) and two, with unused columns
+def test_largest_sums_of_several_tokens_are_exact(M, rows):
+    """Every q at an end of its range over the longest input, all weights at one level per row of a nibble: the sums
+    |F| = 8 K and T / 2 - F are the largest that the accumulators, and the integers made of them, have to hold."""
+    N, K = 48, 32768
+    rcp.set_option("gemv_variant", 2)
+    rcp.set_option("gemm_rows", rows)
+    idx = np.empty((N, K), np.uint8)
+    idx[:] = ((np.arange(N) + np.arange(N) // 4) % 4)[:, None]
+    q = np.where(np.arange(M) % 2 == 0, -8, 7).astype(np.int8)[:, None] * np.ones((1, K), np.int8)
+    xq = ((q[:, 0::2].astype(np.uint8) & 0xF) | ((q[:, 1::2].astype(np.uint8) & 0xF) << 4)).astype(np.uint8)
+    cb = np.tile(np.array([-2, -1, 1, 3], np.float16), (N, 1))
+    packed = torch.from_numpy(oracle.pack_indices(idx)).to(DEV)
+    try:
+        out, P = rcp.w2a4_gemv(packed, torch.from_numpy(cb).to(DEV), N, K, torch.from_numpy(xq).to(DEV),
+                               torch.ones(M, dtype=torch.float16, device=DEV), M, out_dtype=torch.float32, want_partial_sums=True)
+    finally:
+        rcp.set_option("reset", 0)
+    want = np.zeros((M, N, 4), np.int64)
+    for l in range(4):
+        want[:, :, l] = np.where(idx[:, 0] == l, 1, 0)[None, :] * (q[:, :1].astype(np.int64) * K)
+    assert np.array_equal(P.cpu().numpy().reshape(M, N, 4), want)
+    assert np.array_equal(out.cpu().numpy(), (want * cb.astype(np.int64)[None]).sum(axis=2).astype(np.float32))
+
+
 @pytest.mark.parametrize("K", [512, 2176, 4096])   # groups one at a time, batches of four with a rest, whole batches
 @pytest.mark.parametrize("M", [3, 8, 16])
 def test_the_four_rows_of_a_nibble_are_computed_alike(K, M):
