@@ -9,11 +9,11 @@
 //     the eight 2-bit indices of the row, one per nibble (5 operations for 8 weights);
 //     (built for two rows at once, about 20 operations per 32 weights);
 //   - a byte of E_r is made the index pair of two neighbouring columns, t = lo + 4*hi;
-//   - the wavefront keeps, for its current group of four rows, the 4 x 16 pairs
+//   - the wavefronts of a row group keep, for their current four rows, the 4 x 16 pairs
 //     (LUT[r][lo], LUT[r][hi]) at dword t + 16*r of a 64-dword table: the 16 entries one
 //     instruction can touch (all lanes look up the same row r) lie in 16 different LDS banks, so
 //     the look-ups never conflict (equal addresses are broadcast); the four free top bits of
-//     every byte of E_r carry r and the wavefront's table number, so a byte times four IS the
+//     every byte of E_r carry r and the table's number, so a byte times four IS the
 //     LDS address;
 //   - one byte-select-and-shift (SDWA), one ds_read_b32 and one dot2 per two weights.
 // About 1.6 vector-ALU and 0.5 LDS operations per weight, against 0.69 for the W2A4 kernel.
@@ -28,8 +28,6 @@
 
 namespace rcp {
 
-constexpr int WO_THREADS = 256;
-constexpr int WO_WAVES = WO_THREADS / 64;
 constexpr int WO_TABLE_DWORDS = 64;
 
 typedef _Float16 half2_t __attribute__((ext_vector_type(2)));
@@ -61,20 +59,20 @@ __device__ __forceinline__ uint32_t lut_half(uint2 row, int l)
 }
 
 // XF32: activations are held in LDS as binary32 (bf16 / fp32 input), else as fp16 pairs.
-// WS wavefronts share one row group (each with a table of its own; one LDS exchange of the four
-// row totals per row group): short, wide matrices would otherwise put a single wavefront on a
-// SIMD, which issues an instruction only every ~7 cycles.  UNR: 16-byte loads per lane and stage.
+// WS wavefronts share one row group (and its table; one LDS exchange of the four row totals per row group): short, wide
+// matrices would otherwise put a single wavefront on a SIMD, which issues an instruction only every ~7 cycles.  SLOTS: row
+// groups of a workgroup, which share the staged token.  UNR: 16-byte loads per lane and stage.
 // NT: weight loads with the non-temporal hint (launches of 4 MB and more: on a sweep of its own the kernel is level with
 // and without it, inside a decode step of 32 layers the hint is worth 1.6 %, 1.094 -> 1.077 ms).
-template <bool XF32, int XDT, int WS, int UNR, bool NT = false>
-__global__ __launch_bounds__(WO_THREADS) void w2a16_kernel(const uint4* __restrict__ packed,
-                                                           const uint2* __restrict__ codebook, int N, int K,
-                                                           const void* __restrict__ x, void* __restrict__ out,
-                                                           int out_f16, int nblk)
+template <bool XF32, int XDT, int WS, int SLOTS, int UNR, bool NT>
+__global__ __launch_bounds__(64 * WS * SLOTS) void w2a16_kernel(const uint4* __restrict__ packed,
+                                                                const uint2* __restrict__ codebook, int N, int K,
+                                                                const void* __restrict__ x, void* __restrict__ out,
+                                                                int out_f16, int nblk)
 {
     constexpr int WO_UNR = UNR;
-    constexpr int SLOTS = WO_WAVES / WS;  // row groups a workgroup works on at a time
-    constexpr int LG = 64 * WS;           // lanes per row group
+    constexpr int WO_WAVES = WS * SLOTS, WO_THREADS = 64 * WO_WAVES;
+    constexpr int LG = 64 * WS;  // lanes per row group
     extern __shared__ uint32_t wo_smem[];
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -84,9 +82,9 @@ __global__ __launch_bounds__(WO_THREADS) void w2a16_kernel(const uint4* __restri
     const int nbatch = (G + SLOTS - 1) / SLOTS;
     const int nchunk = (U + LG * WO_UNR - 1) / (LG * WO_UNR);
     // (nblk, the number of workgroups, is an argument: the launch dimensions would have to be fetched from memory)
-    uint32_t* tab = wo_smem + wave * WO_TABLE_DWORDS;
-    const uint32_t wave_bits = 0x40404040u * static_cast<uint32_t>(wave);
-    uint32_t* sx = wo_smem + WO_WAVES * WO_TABLE_DWORDS;
+    uint32_t* tab = wo_smem + slot * WO_TABLE_DWORDS;
+    const uint32_t slot_bits = 0x40404040u * static_cast<uint32_t>(slot);
+    uint32_t* sx = wo_smem + SLOTS * WO_TABLE_DWORDS;
     constexpr int XD = XF32 ? 16 : 8;  // dwords of activations per unit
 
     const __amdgpu_buffer_rsrc_t wres = __builtin_amdgcn_make_buffer_rsrc(
@@ -111,7 +109,7 @@ __global__ __launch_bounds__(WO_THREADS) void w2a16_kernel(const uint4* __restri
     // memory answers loads in issue order: this thread's activations (up to WO_XG pieces of eight, K <= 12288; a longer
     // token's remaining pieces are fetched in the staging loop) go first, so that staging them does not have to wait
     // for the weights
-    constexpr int WO_XG = 6;
+    constexpr int WO_XG = (6 * 256 + WO_THREADS - 1) / WO_THREADS;
     const int xpieces = min((K / 8 + WO_THREADS - 1) / WO_THREADS, WO_XG);  // pieces held in registers
     Raw8<XDT> xr[WO_XG];
 #pragma unroll
@@ -178,15 +176,15 @@ __global__ __launch_bounds__(WO_THREADS) void w2a16_kernel(const uint4* __restri
     // Phase 1: the 16 pairs (LUT[r][idx of column 2jp], LUT[r][idx of column 2jp+1]).
     auto cell_lookup = [&](uint32_t B0, uint32_t B1, uint32_t (&pair)[4][4]) {
         // C02 / C13: per nibble the 2-bit indices of rows 0 and 2 (1 and 3) of one column.  E[r]: per
-        // byte lo | hi << 2 (the indices of two neighbouring columns) | r << 4 | wavefront << 6, which
+        // byte lo | hi << 2 (the indices of two neighbouring columns) | r << 4 | table << 6, which
         // times 4 is the byte address of the pair in LDS.
         const uint32_t C02 = (B0 & 0x55555555u) | ((B1 & 0x55555555u) << 1);
         const uint32_t C13 = ((B0 >> 1) & 0x55555555u) | (B1 & 0xaaaaaaaau);
         const uint32_t E[4] = {
-            (C02 & 0x03030303u) | ((C02 >> 2) & 0x0c0c0c0cu) | (wave_bits | 0x00000000u),
-            (C13 & 0x03030303u) | ((C13 >> 2) & 0x0c0c0c0cu) | (wave_bits | 0x10101010u),
-            ((C02 >> 2) & 0x03030303u) | ((C02 >> 4) & 0x0c0c0c0cu) | (wave_bits | 0x20202020u),
-            ((C13 >> 2) & 0x03030303u) | ((C13 >> 4) & 0x0c0c0c0cu) | (wave_bits | 0x30303030u)};
+            (C02 & 0x03030303u) | ((C02 >> 2) & 0x0c0c0c0cu) | (slot_bits | 0x00000000u),
+            (C13 & 0x03030303u) | ((C13 >> 2) & 0x0c0c0c0cu) | (slot_bits | 0x10101010u),
+            ((C02 >> 2) & 0x03030303u) | ((C02 >> 4) & 0x0c0c0c0cu) | (slot_bits | 0x20202020u),
+            ((C13 >> 2) & 0x03030303u) | ((C13 >> 4) & 0x0c0c0c0cu) | (slot_bits | 0x30303030u)};
 #pragma unroll
         for (int r = 0; r < 4; ++r)
 #pragma unroll
@@ -268,7 +266,9 @@ __global__ __launch_bounds__(WO_THREADS) void w2a16_kernel(const uint4* __restri
                 else static_cast<float*>(out)[h] = tot;
             }
             acc[0] = acc[1] = acc[2] = acc[3] = 0.0f;
-            build_table(lut_row);  // for the next row group; LDS operations of a wavefront stay in order
+            // for the next row group; LDS operations of a wavefront stay in order, and the wavefronts that share a table (WS > 1)
+            // have all met above, past their last look-up: they write the same values, each before its own next look-up
+            build_table(lut_row);
         }
         b = b2;
         ch = ch2;
@@ -282,11 +282,10 @@ __global__ __launch_bounds__(WO_THREADS) void w2a16_kernel(const uint4* __restri
     }
 }
 
-template <bool XF32, int XDT, int WS, int UNR, bool NT>
+template <bool XF32, int XDT, int WS, int SLOTS, int UNR, bool NT>
 static int launch_wo_one(const void* packed, const void* codebook, int N, int K, const void* x, void* out, rcp_dtype out_dt,
                          hipStream_t st)
 {
-    constexpr int SLOTS = WO_WAVES / WS;
     const int G = N / 4;
     const int nbatch = (G + SLOTS - 1) / SLOTS;
     const int cus = num_compute_units();
@@ -294,11 +293,11 @@ static int launch_wo_one(const void* packed, const void* codebook, int N, int K,
     if (blocks == 0) blocks = nbatch <= cus * 8 ? nbatch : cus * 4;
     if (blocks > nbatch) blocks = nbatch;
     if (blocks < 1) blocks = 1;
-    const size_t lds = (static_cast<size_t>(WO_WAVES) * WO_TABLE_DWORDS +
-                        static_cast<size_t>(wo_padded_units(K, 64 * WS * UNR)) * (XF32 ? 16 : 8) + 2 * WO_WAVES * 4) * 4;
+    const size_t lds = (static_cast<size_t>(SLOTS) * WO_TABLE_DWORDS +
+                        static_cast<size_t>(wo_padded_units(K, 64 * WS * UNR)) * (XF32 ? 16 : 8) + 2 * WS * SLOTS * 4) * 4;
     if (lds > 160 * 1024)
         return fail(RCP_ERR_UNSUPPORTED, "rcp_w2a16_gemv: K=%d needs %zu bytes of LDS for the activations", K, lds);
-    auto kernel = &w2a16_kernel<XF32, XDT, WS, UNR, NT>;
+    auto kernel = &w2a16_kernel<XF32, XDT, WS, SLOTS, UNR, NT>;
     // the look-ups address the tables by absolute LDS offset: dynamic LDS must start at 0 (checked once
     // per kernel variant; the answer is a property of the compiled code)
     static int lds_checked = 0;  // 1 once the variant is known to have no static LDS
@@ -315,42 +314,76 @@ static int launch_wo_one(const void* packed, const void* codebook, int N, int K,
                                            static_cast<int>(lds));
         if (e != hipSuccess) return fail(RCP_ERR_HIP, "rcp_w2a16_gemv: LDS opt-in failed: %s", hipGetErrorString(e));
     }
-    kernel<<<blocks, WO_THREADS, lds, st>>>(static_cast<const uint4*>(packed), static_cast<const uint2*>(codebook), N, K, x, out,
-                                            out_dt == RCP_F16 ? 1 : 0, blocks);
+    kernel<<<blocks, 64 * WS * SLOTS, lds, st>>>(static_cast<const uint4*>(packed), static_cast<const uint2*>(codebook), N, K, x, out,
+                                                 out_dt == RCP_F16 ? 1 : 0, blocks);
     return check_launch("rcp_w2a16_gemv");
 }
 
-// Shape -> (wavefronts per row group, loads per stage): enough wavefronts to give every SIMD
-// several, and no more loads per stage than a lane has units.
+// Shape -> (wavefronts per row group, row groups per workgroup, loads per stage): enough wavefronts to give every SIMD
+// several.
 template <bool XF32, int XDT>
 static int launch_wo(const void* packed, const void* codebook, int N, int K, const void* x, void* out, rcp_dtype out_dt,
                      hipStream_t st)
 {
     const int G = N / 4, U = K / 16;
     const int cus = num_compute_units();
-    int ws = G <= cus * 4 ? 4 : (G <= cus * 8 ? 2 : 1);
-    const int forced = options().gemv_lanes;  // 64, 128, 256 lanes per row group
-    if (forced == 64) ws = 1;
-    if (forced == 128) ws = 2;
-    if (forced == 256) ws = 4;
-    while (ws > 1 && U < 64 * ws) ws /= 2;
-    // loads per stage: the largest of 4, 2, 1 that pads a lane's units by at most a tenth (padding
-    // units are computed on like real ones, and the kernel is bound by instruction issue)
-    const int per_lane = (U + 64 * ws - 1) / (64 * ws);
+    // Every workgroup stages the token for itself.  While four workgroups of four wavefronts fit a compute unit's LDS beside
+    // each other that is cheap; two row groups of four wavefronts in one workgroup then pay only where they divide evenly
+    // over the units (2 and 4 row groups a unit: 2048 x 6144 binary32 4.69 -> 4.47 us, 4096 x 11008 fp16 7.22 -> 6.80,
+    // 4096 x 4096 4.28 -> 4.14; at 2.5 and 3 a unit 2560 x 8192 binary32 would go 5.76 -> 6.00, 3072 x 8192 5.93 -> 6.12).
+    // A longer token leaves the SIMDs with one or two wavefronts unless eight of them share it (4096 x 11008 binary32
+    // 10.93 -> 8.00 us, 5120 x 13824 15.17 -> 13.24, 32768 x 16384 bf16 54.5 -> 47.2): as two row groups of four wavefronts
+    // for few rows, as four of two for many (8192 x 16384 binary32 18.2 against 17.1) or where 256 lanes would compute on
+    // more padding than 128 (4096 x 14336 binary32 10.3 against 8.9).
+    const bool long_token = K * (XF32 ? 4 : 2) > 39 * 1024;
+    int ws, slots;
+    if (!long_token) {
+        ws = G <= cus * 4 ? 4 : (G <= cus * 8 ? 2 : 1);
+        slots = ws == 4 ? (((G + cus - 1) / cus) % 2 == 0 ? 2 : 1) : (ws == 2 ? 2 : 4);
+    } else {
+        const bool two = G > cus * 5 || ((U + 255) / 256) * 2 > (U + 127) / 128;
+        ws = G > cus && two ? 2 : 4;
+        slots = G <= cus ? 1 : (two ? 4 : 2);
+    }
+    const int forced = options().gemv_lanes;  // 64, 128, 256 lanes per row group, four wavefronts per workgroup
+    if (forced >= 64) {
+        ws = forced / 64;
+        slots = 4 / ws;
+    }
+    while (ws > 1 && U < 64 * ws) {
+        ws /= 2;
+        slots = 4 / ws;
+    }
+    // Loads per stage: one, which takes the fewest registers (55 to 61, eight wavefronts a SIMD; four take 83 to 88, five
+    // wavefronts): 22016 x 4096 fp16 10.86 -> 10.09 us, 12288 x 4096 7.11 -> 6.53, 8192 x 16384 binary32 17.6 -> 16.4.
+    // Where one row group or less falls on a compute unit (1000 x 16384 4.92 against 5.28 us) and in matrices that stream
+    // for long (from 64 MB on: 131072 x 4096 43.0 against 45.2, 32768 x 16384 bf16 48.8 against 50.1; 67 MB level), more
+    // loads in flight win: the largest of 4, 2, 1 that pads a lane's units by at most a tenth (padding units are computed
+    // on like real ones).
     int unr = 1;
-    for (int c = 2; c <= 4; c *= 2)
-        if (((per_lane + c - 1) / c) * c * 10 <= per_lane * 11) unr = c;
+    if (G <= cus || static_cast<long long>(N) * K / 4 >= (64LL << 20)) {
+        const int per_lane = (U + 64 * ws - 1) / (64 * ws);
+        for (int c = 2; c <= 4; c *= 2)
+            if (((per_lane + c - 1) / c) * c * 10 <= per_lane * 11) unr = c;
+    }
     // ("gemv_nt": 1 = non-temporal weight loads always, 2 = never; automatic: from 4 MB of packed weights on -- with
     // the out-projection's 4 MB left out the step takes 1.089 ms, with them in 1.077)
     const bool nt = options().gemv_nt != 0 ? options().gemv_nt == 1 : static_cast<long long>(N) * K / 4 >= (4LL << 20);
-#define RCP_WO(WS, UNR)                                                                                      \
-    return nt ? launch_wo_one<XF32, XDT, WS, UNR, true>(packed, codebook, N, K, x, out, out_dt, st)          \
-              : launch_wo_one<XF32, XDT, WS, UNR, false>(packed, codebook, N, K, x, out, out_dt, st)
-    if (ws == 1) { if (unr == 4) RCP_WO(1, 4); if (unr == 2) RCP_WO(1, 2); RCP_WO(1, 1); }
-    if (ws == 2) { if (unr == 4) RCP_WO(2, 4); if (unr == 2) RCP_WO(2, 2); RCP_WO(2, 1); }
-    if (unr == 4) RCP_WO(4, 4);
-    if (unr == 2) RCP_WO(4, 2);
-    RCP_WO(4, 1);
+#define RCP_WO(WS, SLOTS, UNR)                                                                                      \
+    return nt ? launch_wo_one<XF32, XDT, WS, SLOTS, UNR, true>(packed, codebook, N, K, x, out, out_dt, st)          \
+              : launch_wo_one<XF32, XDT, WS, SLOTS, UNR, false>(packed, codebook, N, K, x, out, out_dt, st)
+#define RCP_WU(WS, SLOTS)                   \
+    do {                                    \
+        if (unr == 4) RCP_WO(WS, SLOTS, 4); \
+        if (unr == 2) RCP_WO(WS, SLOTS, 2); \
+        RCP_WO(WS, SLOTS, 1);               \
+    } while (0)
+    if (ws == 1) RCP_WU(1, 4);
+    if (ws == 2 && slots == 2) RCP_WU(2, 2);
+    if (ws == 2) RCP_WU(2, 4);
+    if (slots == 1) RCP_WU(4, 1);
+    RCP_WU(4, 2);
+#undef RCP_WU
 #undef RCP_WO
 }
 

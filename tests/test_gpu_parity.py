@@ -137,6 +137,17 @@ def test_weight_only_gemv_close_to_oracle(N, K, dtype, blocks, lanes):
         assert np.linalg.norm(got - ref) <= 1e-3 * np.linalg.norm(ref) + 1e-30
 
 
+@pytest.mark.parametrize("dtype,N,K,blocks", [
+    ("f32", 1032, 9984, 0), ("f32", 1032, 10016, 0),      # either side of the longest token of the first rule
+    ("f32", 1036, 11008, 3), ("bf16", 1040, 16384, 0),    # two row groups of four wavefronts, 1036 rows leave one without a partner
+    ("f32", 1036, 14336, 0), ("f32", 1036, 14336, 2),     # four row groups of two wavefronts, the last workgroup not full
+    ("bf16", 5132, 10272, 0), ("f16", 5128, 20000, 5),    # the same by the number of rows
+    ("f16", 2048, 4096, 0), ("f16", 2044, 4128, 3),       # two row groups, short token
+    ("f32", 1036, 32768, 0)])                             # the longest token
+def test_weight_only_gemv_workgroup_forms_close_to_oracle(dtype, N, K, blocks):
+    test_weight_only_gemv_close_to_oracle(N, K, dtype, blocks, 0)
+
+
 def test_weight_only_gemv_equals_w2a4_on_dequantised_int4_activations():
     """x = S*q (S a power of two) is exact in fp16: the weight-only kernel must then agree with the W2A4 kernel."""
     N, K = 512, 4096
