@@ -826,7 +826,7 @@ def test_kronecker_rotation_within_tie_band(M, n, m, ratio, dtype):
 
 @pytest.mark.parametrize("kind,M,n,m", [("none", 2, 2080, 1), ("wht", 1, 64, 1), ("wht", 2, 4096, 1), ("wht", 1, 16384, 1),
                                         # one pass through LDS that repeats finished strides, then whole passes
-                                        ("wht", 2, 1024, 1), ("wht", 1, 8192, 1), ("wht", 3, 32768, 1),
+                                        ("wht", 2, 1024, 1), ("wht", 1, 8192, 1), ("wht", 3, 16384, 1),
                                         ("kron", 1, 64, 172), ("kron", 2, 512, 28), ("kron", 1, 128, 12),
                                         ("kron", 1, 1024, 8), ("kron", 1, 8, 12), ("kron", 1, 64, 7),
                                         # 64 Hadamard rows, the form with one workgroup per output column: smallest and
