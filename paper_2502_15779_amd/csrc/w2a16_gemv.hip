@@ -357,12 +357,14 @@ static int launch_wo(const void* packed, const void* codebook, int N, int K, con
     // Loads per stage: one, which takes the fewest registers (55 to 61, eight wavefronts a SIMD; four take 83 to 88, five
     // wavefronts): 22016 x 4096 fp16 10.86 -> 10.09 us, 12288 x 4096 7.11 -> 6.53, 8192 x 16384 binary32 17.6 -> 16.4.
     // Where one row group or less falls on a compute unit (1000 x 16384 4.92 against 5.28 us) and in matrices that stream
-    // for long (from 64 MB on: 131072 x 4096 43.0 against 45.2, 32768 x 16384 bf16 48.8 against 50.1; 67 MB level), more
+    // for long (from 56 MB on: 80000 x 3104 24.1 against 25.6, 131072 x 4096 43.0 against 45.2, 32768 x 16384 bf16 48.8 against 50.1), more
     // loads in flight win: the largest of 4, 2, 1 that pads a lane's units by at most a tenth (padding units are computed
     // on like real ones).
+    // Likewise two loads where they are a whole row group of one wavefront: 100000 x 1504 fp16 takes 18.1 us with one, 16.9 with
+    // two (50000 x 2048 bf16 11.3 either way; with four units a lane 40000 x 4096 12.8 with one, 14.0 with four).
     int unr = 1;
-    if (G <= cus || static_cast<long long>(N) * K / 4 >= (64LL << 20)) {
-        const int per_lane = (U + 64 * ws - 1) / (64 * ws);
+    const int per_lane = (U + 64 * ws - 1) / (64 * ws);
+    if (G <= cus || static_cast<long long>(N) * K / 4 >= (56LL << 20) || (ws == 1 && per_lane == 2)) {
         for (int c = 2; c <= 4; c *= 2)
             if (((per_lane + c - 1) / c) * c * 10 <= per_lane * 11) unr = c;
     }
