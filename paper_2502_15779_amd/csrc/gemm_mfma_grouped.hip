@@ -11,7 +11,7 @@
 // 16 rows of the A operand are (row group, row in the nibble) pairs as in gemm_mfma.hip, the mask
 // a per-lane value, the int4 activations FP8 bytes)
 // a lane holds the exact plane sums F_p of four rows for one token, times the power of two that the
-// operands' units leave in them, and adds their products with
+// operands' units leave in them (where several groups are taken at a time), and adds their products with
 // the group's levels to four running fp32 outputs.  The power of two is taken out of the levels, once
 // for all tokens and without a rounding: a scaled instruction would hold the vector unit for eight
 // cycles instead of four (eight layers of 4096 / 14336 at 6 tokens,
@@ -88,7 +88,13 @@ __global__ __launch_bounds__(64 * (WANTP && BATCH == 4 ? MG_P_WAVES : MG_WAVES))
     // this lane's row of the nibble as a mask, how far it is shifted down (the fourth row is the FP4 sign bit), and the
     // power of two that undoes the 0.5 / 1 / 2 / 2 it then stands for and the activations' unit
     const uint32_t row_mask = 0x11111111u << t, row_shift = t == 3 ? 1u : 0u;
-    const float row_unit = FP8_INT_UNIT * (t == 0 ? 2.0f : t == 1 ? 1.0f : 0.5f);
+    // (one group at a time the levels are as many as the instructions, and the scaled instruction does it: 130000 x 1536 at
+    // 2 tokens 28.2 us, 28.5 with the levels multiplied)
+    constexpr bool SCALED = BATCH == 1;
+    constexpr float INT_UNIT = SCALED ? 1.0f : FP8_INT_UNIT;
+    constexpr int SC_ONE = SCALED ? 0x7f : 0, SC_INT = SCALED ? FP8_INT_SCALE : 0;
+    const float row_unit = SCALED ? 1.0f : FP8_INT_UNIT * (t == 0 ? 2.0f : t == 1 ? 1.0f : 0.5f);
+    const int row_scale = SCALED ? (t == 0 ? 0x80 : t == 1 ? 0x7f : 0x7e) : 0;
 
     const __amdgpu_buffer_rsrc_t wres = __builtin_amdgcn_make_buffer_rsrc(
         const_cast<uint4*>(packed), 0, static_cast<int>(static_cast<unsigned>(G) * static_cast<unsigned>(U) * 16u), 0x00020000);
@@ -144,7 +150,7 @@ __global__ __launch_bounds__(64 * (WANTP && BATCH == 4 ? MG_P_WAVES : MG_WAVES))
 #pragma unroll
                 for (int d = 0; d < 8; ++d) bop[s][d] = __builtin_amdgcn_mov_dpp(bop[s - 1][d], 0x120 + 16 - TK, 0xf, 0xf, true);
             }
-            tq[s] = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(ones, bop[s], zero, 4, 0, 0, 0, 0, 0)[0];
+            tq[s] = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(ones, bop[s], zero, 4, 0, 0, SC_ONE, 0, SC_INT)[0];
         }
     };
     // rows 4 * kb + v of the block, this lane's token
@@ -154,8 +160,10 @@ __global__ __launch_bounds__(64 * (WANTP && BATCH == 4 ? MG_P_WAVES : MG_WAVES))
             const float c1 = half_bits_to_float(static_cast<uint16_t>(cur.lut.x >> 16));
             const float c2 = half_bits_to_float(static_cast<uint16_t>(cur.lut.y & 0xffffu));
             const float c3 = half_bits_to_float(static_cast<uint16_t>(cur.lut.y >> 16));
-            const float4 c = make_float4(FP8_INT_UNIT * c0, row_unit * (c1 - c0), row_unit * (c2 - c0),
-                                         row_unit * (((c3 - c2) - c1) + c0));
+            // (row_unit times L0, L1-L0, .. with the same roundings: it is a power of two)
+            const float u0 = row_unit * c0;
+            const float4 c = make_float4(INT_UNIT * c0, fmaf(row_unit, c1, -u0), fmaf(row_unit, c2, -u0),
+                                         fmaf(row_unit, (c3 - c2) - c1, u0));
             coef[16 * lg + 4 * kb + t] = c;
         }
         int4 sums[4][BATCH];
@@ -175,7 +183,9 @@ __global__ __launch_bounds__(64 * (WANTP && BATCH == 4 ? MG_P_WAVES : MG_WAVES))
             v4f F[3];
 #pragma unroll
             for (int p = 0; p < 3; ++p)
-                F[p] = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(an[p], bop[s], zero, 4, 0, 0, 0, 0, 0);
+                if constexpr (SCALED)
+                    F[p] = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(an[p], bop[s], zero, 4, 0, 0, row_scale, 0, SC_INT);
+                else F[p] = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(an[p], bop[s], zero, 4, 0, 0, 0, 0, 0);
 #pragma unroll
             for (int v = 0; v < 4; ++v) {
                 const float4 c = coef[16 * s + 4 * kb + v];
@@ -184,8 +194,8 @@ __global__ __launch_bounds__(64 * (WANTP && BATCH == 4 ? MG_P_WAVES : MG_WAVES))
                 val = fmaf(c.z, F[1][v], val);
                 o[v] = fmaf(c.w, F[2][v], val);
                 if constexpr (WANTP) {
-                    const float unit = FP8_INT_UNIT * (v == 0 ? 2.0f : v == 1 ? 1.0f : 0.5f);
-                    const float T = FP8_INT_UNIT * tq[s], F0 = unit * F[0][v], F1 = unit * F[1][v], F3 = unit * F[2][v];
+                    const float unit = SCALED ? 1.0f : FP8_INT_UNIT * (v == 0 ? 2.0f : v == 1 ? 1.0f : 0.5f);
+                    const float T = INT_UNIT * tq[s], F0 = unit * F[0][v], F1 = unit * F[1][v], F3 = unit * F[2][v];
                     sums[v][s] = make_int4(static_cast<int>(T - F0 - F1 + F3), static_cast<int>(F0 - F3), static_cast<int>(F1 - F3),
                                            static_cast<int>(F3));
                 }

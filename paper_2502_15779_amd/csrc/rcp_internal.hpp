@@ -449,7 +449,8 @@ __device__ __forceinline__ void int4_to_fp8(uint32_t x, int& first, int& second)
 // takes 32 consecutive columns (16-column units 2 kb and 2 kb + 1) therefore meets A lanes that take the units
 // a4b8_unit(kb) and a4b8_unit(kb) + 2.
 __device__ __forceinline__ int a4b8_unit(int kb) { return 4 * (kb & 1) + (kb >> 1); }
-constexpr float FP8_INT_UNIT = 512.0f;  // takes the 2^-9 out again
+constexpr float FP8_INT_UNIT = 512.0f;  // takes the 2^-9 out again,
+constexpr int FP8_INT_SCALE = 0x88;     // as an E8M0 scale
 
 // ---- the int4 quantiser (shared by the activation kernels and the fused GEMV prologue) ----
 // S = fp16((ratio * a) / 7); 1 when that is zero, capped at the largest finite half.
