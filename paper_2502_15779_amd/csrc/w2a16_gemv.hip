@@ -25,18 +25,11 @@
 // in flight while the current chunk is computed; units past K read zeros (index 0) and meet
 // zero-padded activations.
 #include "rcp_internal.hpp"
+#include "w2a16_plan.hpp"
 
 namespace rcp {
 
-constexpr int WO_TABLE_DWORDS = 64;
-
 typedef _Float16 half2_t __attribute__((ext_vector_type(2)));
-
-__host__ __device__ constexpr int wo_padded_units(int K, int span /* lanes per row group x loads per stage */)
-{
-    const int U = K / 16;
-    return ((U + span - 1) / span) * span;
-}
 
 // ((v >> 8*byte) & 0xff) << 2 in one instruction: a shift whose source operand selects a byte
 __device__ __forceinline__ uint32_t byte_times4(uint32_t v, int byte)
@@ -293,9 +286,8 @@ static int launch_wo_one(const void* packed, const void* codebook, int N, int K,
     if (blocks == 0) blocks = nbatch <= cus * 8 ? nbatch : cus * 4;
     if (blocks > nbatch) blocks = nbatch;
     if (blocks < 1) blocks = 1;
-    const size_t lds = (static_cast<size_t>(SLOTS) * WO_TABLE_DWORDS +
-                        static_cast<size_t>(wo_padded_units(K, 64 * WS * UNR)) * (XF32 ? 16 : 8) + 2 * WS * SLOTS * 4) * 4;
-    if (lds > 160 * 1024)
+    const size_t lds = wo_lds_bytes(XF32, K, WS, SLOTS, UNR);
+    if (lds > WO_LDS_BYTES)
         return fail(RCP_ERR_UNSUPPORTED, "rcp_w2a16_gemv: K=%d needs %zu bytes of LDS for the activations", K, lds);
     auto kernel = &w2a16_kernel<XF32, XDT, WS, SLOTS, UNR, NT>;
     // the look-ups address the tables by absolute LDS offset: dynamic LDS must start at 0 (checked once
@@ -319,55 +311,12 @@ static int launch_wo_one(const void* packed, const void* codebook, int N, int K,
     return check_launch("rcp_w2a16_gemv");
 }
 
-// Shape -> (wavefronts per row group, row groups per workgroup, loads per stage): enough wavefronts to give every SIMD
-// several.
 template <bool XF32, int XDT>
 static int launch_wo(const void* packed, const void* codebook, int N, int K, const void* x, void* out, rcp_dtype out_dt,
                      hipStream_t st)
 {
-    const int G = N / 4, U = K / 16;
-    const int cus = num_compute_units();
-    // Every workgroup stages the token for itself.  While four workgroups of four wavefronts fit a compute unit's LDS beside
-    // each other that is cheap; two row groups of four wavefronts in one workgroup then pay only where they divide evenly
-    // over the units (2 and 4 row groups a unit: 2048 x 6144 binary32 4.69 -> 4.47 us, 4096 x 11008 fp16 7.22 -> 6.80,
-    // 4096 x 4096 4.28 -> 4.14; at 2.5 and 3 a unit 2560 x 8192 binary32 would go 5.76 -> 6.00, 3072 x 8192 5.93 -> 6.12).
-    // A longer token leaves the SIMDs with one or two wavefronts unless eight of them share it (4096 x 11008 binary32
-    // 10.93 -> 8.00 us, 5120 x 13824 15.17 -> 13.24, 32768 x 16384 bf16 54.5 -> 47.2): as two row groups of four wavefronts
-    // for few rows, as four of two for many (8192 x 16384 binary32 18.2 against 17.1) or where 256 lanes would compute on
-    // more padding than 128 (4096 x 14336 binary32 10.3 against 8.9).
-    const bool long_token = K * (XF32 ? 4 : 2) > 39 * 1024;
-    int ws, slots;
-    if (!long_token) {
-        ws = G <= cus * 4 ? 4 : (G <= cus * 8 ? 2 : 1);
-        slots = ws == 4 ? (((G + cus - 1) / cus) % 2 == 0 ? 2 : 1) : (ws == 2 ? 2 : 4);
-    } else {
-        const bool two = G > cus * 5 || ((U + 255) / 256) * 2 > (U + 127) / 128;
-        ws = G > cus && two ? 2 : 4;
-        slots = G <= cus ? 1 : (two ? 4 : 2);
-    }
-    const int forced = options().gemv_lanes;  // 64, 128, 256 lanes per row group, four wavefronts per workgroup
-    if (forced >= 64) {
-        ws = forced / 64;
-        slots = 4 / ws;
-    }
-    while (ws > 1 && U < 64 * ws) {
-        ws /= 2;
-        slots = 4 / ws;
-    }
-    // Loads per stage: one, which takes the fewest registers (55 to 61, eight wavefronts a SIMD; four take 83 to 88, five
-    // wavefronts): 22016 x 4096 fp16 10.86 -> 10.09 us, 12288 x 4096 7.11 -> 6.53, 8192 x 16384 binary32 17.6 -> 16.4.
-    // Where one row group or less falls on a compute unit (1000 x 16384 4.92 against 5.28 us) and in matrices that stream
-    // for long (from 56 MB on: 80000 x 3104 24.1 against 25.6, 131072 x 4096 43.0 against 45.2, 32768 x 16384 bf16 48.8 against 50.1), more
-    // loads in flight win: the largest of 4, 2, 1 that pads a lane's units by at most a tenth (padding units are computed
-    // on like real ones).
-    // Likewise two loads where they are a whole row group of one wavefront: 100000 x 1504 fp16 takes 18.1 us with one, 16.9 with
-    // two (50000 x 2048 bf16 11.3 either way; with four units a lane 40000 x 4096 12.8 with one, 14.0 with four).
-    int unr = 1;
-    const int per_lane = (U + 64 * ws - 1) / (64 * ws);
-    if (G <= cus || static_cast<long long>(N) * K / 4 >= (56LL << 20) || (ws == 1 && per_lane == 2)) {
-        for (int c = 2; c <= 4; c *= 2)
-            if (((per_lane + c - 1) / c) * c * 10 <= per_lane * 11) unr = c;
-    }
+    const WoPlan plan = wo_plan(XF32, N, K, num_compute_units(), options().gemv_lanes);
+    const int ws = plan.ws, slots = plan.slots, unr = plan.unr;
     // ("gemv_nt": 1 = non-temporal weight loads always, 2 = never; automatic: from 4 MB of packed weights on -- with
     // the out-projection's 4 MB left out the step takes 1.089 ms, with them in 1.077)
     const bool nt = options().gemv_nt != 0 ? options().gemv_nt == 1 : static_cast<long long>(N) * K / 4 >= (4LL << 20);
