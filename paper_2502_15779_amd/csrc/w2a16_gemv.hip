@@ -57,7 +57,8 @@ __device__ __forceinline__ uint32_t lut_half(uint2 row, int l)
 // groups of a workgroup, which share the staged token.  UNR: 16-byte loads per lane and stage.
 // NT: weight loads with the non-temporal hint (launches of 4 MB and more: on a sweep of its own the kernel is level with
 // and without it, inside a decode step of 32 layers the hint is worth 1.6 %, 1.094 -> 1.077 ms).
-template <bool XF32, int XDT, int WS, int SLOTS, int UNR, bool NT>
+// CHAINS: running sums per lane and row, which the cells of a unit share.
+template <bool XF32, int XDT, int WS, int SLOTS, int UNR, bool NT, int CHAINS>
 __global__ __launch_bounds__(64 * WS * SLOTS) void w2a16_kernel(const uint4* __restrict__ packed,
                                                                 const uint2* __restrict__ codebook, int N, int K,
                                                                 const void* __restrict__ x, void* __restrict__ out,
@@ -161,7 +162,7 @@ __global__ __launch_bounds__(64 * WS * SLOTS) void w2a16_kernel(const uint4* __r
     build_table(lut_row);
     __syncthreads();
 
-    float acc[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+    float acc[CHAINS][4] = {};
     int ch = 0;
 
     // One cell (4 rows x 8 columns) in two phases, so that the 16 look-ups of the next cell can be
@@ -189,7 +190,7 @@ __global__ __launch_bounds__(64 * WS * SLOTS) void w2a16_kernel(const uint4* __r
             }
     };
     // Phase 2: products with the cell's 8 activations.
-    auto cell_dot = [&](const uint32_t (&pair)[4][4], const uint32_t* xs) {
+    auto cell_dot = [&](const uint32_t (&pair)[4][4], const uint32_t* xs, float (&acc)[4]) {
         uint32_t xv[XF32 ? 8 : 4];
         {
             const uint4 v = *reinterpret_cast<const uint4*>(xs);  // 16-byte aligned by construction
@@ -229,16 +230,22 @@ __global__ __launch_bounds__(64 * WS * SLOTS) void w2a16_kernel(const uint4* __r
         for (int i = 0; i < WO_UNR; ++i) {
             cell_lookup(w[i].z, w[i].w, pB);
             __builtin_amdgcn_sched_barrier(0);
-            cell_dot(pA, xrow + i * LG * XD);
+            cell_dot(pA, xrow + i * LG * XD, acc[0]);
             if (i + 1 < WO_UNR) cell_lookup(w[i + 1].x, w[i + 1].y, pA);
             __builtin_amdgcn_sched_barrier(0);
-            cell_dot(pB, xrow + i * LG * XD + XD / 2);
+            cell_dot(pB, xrow + i * LG * XD + XD / 2, acc[CHAINS - 1]);
         }
 
         if (last) {
             // row totals over the 64 lanes: 16-lane row rho ends up with output row 2*(rho&1) + (rho>>1)
-            const float s01 = fold32f(acc[0], acc[1]);
-            const float s23 = fold32f(acc[2], acc[3]);
+            float sum[4];
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                sum[r] = CHAINS == 2 ? acc[0][r] + acc[1][r] : acc[0][r];
+                acc[0][r] = acc[CHAINS - 1][r] = 0.0f;
+            }
+            const float s01 = fold32f(sum[0], sum[1]);
+            const float s23 = fold32f(sum[2], sum[3]);
             float tot = row_sum16f(fold16f(s01, s23));
             const int rho = lane >> 4;
             if constexpr (WS > 1) {
@@ -258,7 +265,6 @@ __global__ __launch_bounds__(64 * WS * SLOTS) void w2a16_kernel(const uint4* __r
                 if (out_f16) static_cast<__half*>(out)[h] = __float2half_rn(tot);
                 else static_cast<float*>(out)[h] = tot;
             }
-            acc[0] = acc[1] = acc[2] = acc[3] = 0.0f;
             // for the next row group; LDS operations of a wavefront stay in order, and the wavefronts that share a table (WS > 1)
             // have all met above, past their last look-up: they write the same values, each before its own next look-up
             build_table(lut_row);
@@ -275,7 +281,7 @@ __global__ __launch_bounds__(64 * WS * SLOTS) void w2a16_kernel(const uint4* __r
     }
 }
 
-template <bool XF32, int XDT, int WS, int SLOTS, int UNR, bool NT>
+template <bool XF32, int XDT, int WS, int SLOTS, int UNR, bool NT, int CHAINS>
 static int launch_wo_one(const void* packed, const void* codebook, int N, int K, const void* x, void* out, rcp_dtype out_dt,
                          hipStream_t st)
 {
@@ -289,7 +295,7 @@ static int launch_wo_one(const void* packed, const void* codebook, int N, int K,
     const size_t lds = wo_lds_bytes(XF32, K, WS, SLOTS, UNR);
     if (lds > WO_LDS_BYTES)
         return fail(RCP_ERR_UNSUPPORTED, "rcp_w2a16_gemv: K=%d needs %zu bytes of LDS for the activations", K, lds);
-    auto kernel = &w2a16_kernel<XF32, XDT, WS, SLOTS, UNR, NT>;
+    auto kernel = &w2a16_kernel<XF32, XDT, WS, SLOTS, UNR, NT, CHAINS>;
     // the look-ups address the tables by absolute LDS offset: dynamic LDS must start at 0 (checked once
     // per kernel variant; the answer is a property of the compiled code)
     static int lds_checked = 0;  // 1 once the variant is known to have no static LDS
@@ -320,15 +326,16 @@ static int launch_wo(const void* packed, const void* codebook, int N, int K, con
     // ("gemv_nt": 1 = non-temporal weight loads always, 2 = never; automatic: from 4 MB of packed weights on -- with
     // the out-projection's 4 MB left out the step takes 1.089 ms, with them in 1.077)
     const bool nt = options().gemv_nt != 0 ? options().gemv_nt == 1 : static_cast<long long>(N) * K / 4 >= (4LL << 20);
-#define RCP_WO(WS, SLOTS, UNR)                                                                                      \
-    return nt ? launch_wo_one<XF32, XDT, WS, SLOTS, UNR, true>(packed, codebook, N, K, x, out, out_dt, st)          \
-              : launch_wo_one<XF32, XDT, WS, SLOTS, UNR, false>(packed, codebook, N, K, x, out, out_dt, st)
-#define RCP_WU(WS, SLOTS)                   \
-    do {                                    \
-        if (unr == 4) RCP_WO(WS, SLOTS, 4); \
-        if (unr == 2) RCP_WO(WS, SLOTS, 2); \
-        RCP_WO(WS, SLOTS, 1);               \
+#define RCP_WO(WS, SLOTS, UNR, CHAINS)                                                                                      \
+    return nt ? launch_wo_one<XF32, XDT, WS, SLOTS, UNR, true, CHAINS>(packed, codebook, N, K, x, out, out_dt, st)          \
+              : launch_wo_one<XF32, XDT, WS, SLOTS, UNR, false, CHAINS>(packed, codebook, N, K, x, out, out_dt, st)
+#define RCP_WU(WS, SLOTS)                      \
+    do {                                       \
+        if (unr == 4) RCP_WO(WS, SLOTS, 4, 1); \
+        if (unr == 2) RCP_WO(WS, SLOTS, 2, 1); \
+        RCP_WO(WS, SLOTS, 1, 1);               \
     } while (0)
+    if (plan.chains == 2) RCP_WO(2, 4, 1, 2);
     if (ws == 1) RCP_WU(1, 4);
     if (ws == 2 && slots == 2) RCP_WU(2, 2);
     if (ws == 2) RCP_WU(2, 4);

@@ -12,6 +12,7 @@ struct WoPlan {
     int ws;     // wavefronts per row group of four rows
     int slots;  // row groups per workgroup, which share one staged token
     int unr;    // 16-byte loads per lane and stage
+    int chains; // running sums per lane and row
 };
 
 constexpr int wo_padded_units(int K, int span /* lanes per row group x loads per stage */)
@@ -54,7 +55,7 @@ inline WoPlan wo_plan(bool xf32, int N, int K, int cus, int forced_lanes)
         // 52.7 -> 45.4 us, 12288 x 11008 binary32 16.5 -> 15.0, 16384 x 9984 17.9 -> 16.1); single wavefronts keep their row groups
         // while four such workgroups fit and 128 lanes would pad more than 64 (16384 x 8704 binary32 15.9 against 16.7)
         const bool single = wo_padded_units(K, 64) < wo_padded_units(K, 128) && 4 * wo_lds_bytes(xf32, K, 1, 4, 1) <= WO_LDS_BYTES;
-        p = single ? WoPlan{1, 4, 1} : WoPlan{2, 4, 1};
+        p = single ? WoPlan{1, 4, 1, 1} : WoPlan{2, 4, 1, 1};
     } else {
         // Likewise for fewer rows, as two row groups of four wavefronts or four of two: whichever leaves the busiest unit the
         // fewer units to compute on, padding included (us in binary32, 4 x 2 / 2 x 4 wavefronts: 1280 x 14336 6.1 / 8.1,
@@ -67,10 +68,10 @@ inline WoPlan wo_plan(bool xf32, int N, int K, int cus, int forced_lanes)
         const int pad4 = wo_padded_units(K, 256), pad2 = wo_padded_units(K, 128);
         const int c42 = u2 * pad4, c24 = u4 * pad2;
         const bool two = c24 < c42 || (c24 == c42 && G > cus * 4);
-        p = two ? WoPlan{2, 4, 1} : WoPlan{4, 2, 1};
+        p = two ? WoPlan{2, 4, 1, 1} : WoPlan{4, 2, 1, 1};
         const int best = std::min(c42, c24);
-        if (8 * u1 * pad4 <= 7 * best && u1 * wo_lds_bytes(xf32, K, 4, 1, 1) <= WO_LDS_BYTES) p = {4, 1, 1};
-        else if (G > cus * 4 && 8 * u2 * pad2 <= 7 * best && u2 / 2 * wo_lds_bytes(xf32, K, 2, 2, 1) <= WO_LDS_BYTES) p = {2, 2, 1};
+        if (8 * u1 * pad4 <= 7 * best && u1 * wo_lds_bytes(xf32, K, 4, 1, 1) <= WO_LDS_BYTES) p = {4, 1, 1, 1};
+        else if (G > cus * 4 && 8 * u2 * pad2 <= 7 * best && u2 / 2 * wo_lds_bytes(xf32, K, 2, 2, 1) <= WO_LDS_BYTES) p = {2, 2, 1, 1};
     }
     if (forced_lanes >= 64) {  // 64, 128, 256 lanes per row group, four wavefronts per workgroup
         p.ws = forced_lanes / 64;
@@ -80,6 +81,10 @@ inline WoPlan wo_plan(bool xf32, int N, int K, int cus, int forced_lanes)
         p.ws /= 2;
         p.slots = 4 / p.ws;
     }
+    // Up to four row groups a unit a row is summed in 256 parts, whatever the form: two running sums a lane where 128 lanes share it
+    // (one would be faster by 1 %, 2560 x 14336 binary32 8.17 against 8.28 us, with 1.3 times the rounding error: 1.76e-7 and
+    // 1.36e-7 of the output in binary32 there, 1.33e-7 with 256 lanes)
+    p.chains = p.ws == 2 && p.slots == 4 && G <= cus * 4 ? 2 : 1;
     // Loads per stage: one, which takes the fewest registers (55 to 61, eight wavefronts a SIMD; four take 83 to 88, five
     // wavefronts): 22016 x 4096 fp16 10.86 -> 10.09 us, 12288 x 4096 7.11 -> 6.53, 8192 x 16384 binary32 17.6 -> 16.4.
     // Where one row group or less falls on a compute unit (1000 x 16384 4.92 against 5.28 us) and in matrices that stream

@@ -150,6 +150,27 @@ def test_weight_only_gemv_workgroup_forms_close_to_oracle(dtype, N, K, blocks):
     test_weight_only_gemv_close_to_oracle(N, K, dtype, blocks, 0)
 
 
+@pytest.mark.parametrize("dtype,N,K", [("f32", 2560, 14336), ("f32", 4096, 10240), ("bf16", 3072, 13312)])
+def test_weight_only_gemv_rounds_no_more_than_with_256_lanes_a_row(dtype, N, K):
+    """The automatic form's error against binary64 is that of 256 lanes a row.  Bound: partial sums of twice the length have a
+    rounding error of up to sqrt(2) times (1.3 in the mean, measured), equal ones differ by their order alone (0.92 to 1.08 on
+    one input); 1.15 lies between over four inputs."""
+    idx = rcp_synth.random_indices(43, f"wo{N}x{K}", N, K)
+    packed = _t(oracle.pack_indices(idx))
+    cb = np.sort(np.random.default_rng(43).standard_normal((N, 4)) * 0.03, axis=1).astype(np.float16)
+    W = torch.gather(_t(cb).double(), 1, _t(idx).long())
+    err = {0: 0.0, 256: 0.0}
+    for seed in range(4):
+        x = _t(rcp_synth.activation(seed, f"wo{K}", 1, K)).float()
+        x = x.to(torch.bfloat16) if dtype == "bf16" else x * np.float32(1.0009765)
+        ref = W.mv(x.double()[0])
+        for lanes in err:
+            rcp.set_option("gemv_lanes", lanes)
+            out = rcp.w2a16_gemv(packed, _t(cb), N, K, x, out_dtype=torch.float32).double().ravel()
+            err[lanes] += float((out - ref).square().sum() / ref.square().sum())
+    assert err[0] ** 0.5 <= 1.15 * err[256] ** 0.5
+
+
 def test_weight_only_gemv_equals_w2a4_on_dequantised_int4_activations():
     """x = S*q (S a power of two) is exact in fp16: the weight-only kernel must then agree with the W2A4 kernel."""
     N, K = 512, 4096

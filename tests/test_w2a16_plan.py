@@ -17,7 +17,7 @@ int main()
     int f32, N, K, lanes;
     while (scanf("%d %d %d %d", &f32, &N, &K, &lanes) == 4) {
         const rcp::WoPlan p = rcp::wo_plan(f32 != 0, N, K, 256, lanes);
-        printf("%d %d %d %zu\n", p.ws, p.slots, p.unr, rcp::wo_lds_bytes(f32 != 0, K, p.ws, p.slots, p.unr));
+        printf("%d %d %d %d %zu\n", p.ws, p.slots, p.unr, p.chains, rcp::wo_lds_bytes(f32 != 0, K, p.ws, p.slots, p.unr));
     }
 }
 """
@@ -31,7 +31,7 @@ def plan(tmp_path_factory):
     subprocess.run(["g++", "-O1", "-std=c++17", "-Wall", "-Werror", "-I", CSRC, str(d / "plan.cpp"), "-o", exe], check=True)
 
     def walk(shapes):
-        """[(f32, N, K, forced lanes)] -> [(wavefronts per row group, row groups per workgroup, loads a stage, LDS bytes)]"""
+        """[(f32, N, K, forced lanes)] -> [(wavefronts per row group, row groups per workgroup, loads a stage, running sums, LDS bytes)]"""
         text = "\n".join("%d %d %d %d" % s for s in shapes)
         lines = subprocess.run([exe], input=text, capture_output=True, text=True, check=True).stdout.split("\n")
         out = [tuple(int(v) for v in line.split()) for line in lines if line]
@@ -58,14 +58,14 @@ def test_a_long_token_leaves_the_busiest_unit_no_more_than_either_form_of_eight_
     most units without work and the others with four row groups."""
     shapes = [(f, n, k, 0) for f, lo in ((F32, 8224), (F16, 16416)) for n in ROWS if n <= 8192
               for k in list(range(lo, 32768, 352)) + [11008, 14336, 16384, 28672] if k >= lo]
-    for (f, n, k, _), (ws, slots, _, _) in zip(shapes, plan(shapes)):
+    for (f, n, k, _), (ws, slots, _, _, _) in zip(shapes, plan(shapes)):
         eight = min(busiest(n, 2) * padded(k, 4), busiest(n, 4) * padded(k, 2))
         assert busiest(n, slots) * padded(k, ws) <= eight, (f, n, k, ws, slots)
 
 
 def test_forms_of_four_wavefronts_are_resident_at_once_on_a_long_token(plan):
     shapes = [(f, n, k, 0) for f, lo in ((F32, 8224), (F16, 16416)) for n in ROWS if 1024 < n <= 8192 for k in range(lo, 32768, 352)]
-    for (f, n, k, _), (ws, slots, _, lds) in zip(shapes, plan(shapes)):
+    for (f, n, k, _), (ws, slots, _, _, lds) in zip(shapes, plan(shapes)):
         if ws * slots == 4:
             assert busiest(n, slots) // slots * lds <= 160 * 1024, (f, n, k, ws, slots)
 
@@ -82,7 +82,15 @@ def test_every_form_that_is_chosen_is_built_and_fits(plan):
     built = {(1, 4), (2, 2), (2, 4), (4, 1), (4, 2)}
     shapes = [(f, n, k, lanes) for f in (F16, F32) for n in ROWS + [8196, 12288, 65536, 131072]
               for k in list(range(32, 1056, 32)) + list(range(1056, 32769, 992)) + [32768] for lanes in (0, 16, 64, 128, 256)]
-    for s, (ws, slots, unr, lds) in zip(shapes, plan(shapes)):
+    for s, (ws, slots, unr, chains, lds) in zip(shapes, plan(shapes)):
         assert (ws, slots) in built and unr in (1, 2, 4) and lds <= 160 * 1024, s
+        assert chains == 1 or (chains, ws, slots, unr) == (2, 2, 4, 1), s
         if s[3] >= 64 and s[2] // 16 >= s[3]:
             assert ws * 64 == s[3] and ws * slots == 4, s
+
+
+def test_a_row_of_few_is_summed_in_as_many_parts_as_by_four_wavefronts(plan):
+    """256 partial sums a row up to four row groups a unit: half as many are twice as long, and their rounding errors larger."""
+    shapes = [(f, n, k, 0) for f in (F16, F32) for n in ROWS if n <= 4096 for k in range(4096, 32769, 352)]
+    for s, (ws, _, _, chains, _) in zip(shapes, plan(shapes)):
+        assert ws * chains >= 4, s
