@@ -91,11 +91,14 @@ inline WoPlan wo_plan(bool xf32, int N, int K, int cus, int forced_lanes)
     // for long (from 56 MB on: 80000 x 3104 24.1 against 25.6, 131072 x 4096 43.0 against 45.2, 32768 x 16384 bf16 48.8 against 50.1), more
     // loads in flight win: the largest of 4, 2, 1 that pads a lane's units by at most a tenth (padding units are computed
     // on like real ones).
-    // Likewise two loads where they are a whole row group of one wavefront: 100000 x 1504 fp16 takes 18.1 us with one, 16.9 with
-    // two (50000 x 2048 bf16 11.3 either way; with four units a lane 40000 x 4096 12.8 with one, 14.0 with four).
+    // Likewise two loads where they are all that a lane has: a whole row group of one wavefront (100000 x 1504 fp16 takes 18.1 us
+    // with one, 16.9 with two, 40000 x 1504 bf16 9.0 / 9.3, 50000 x 2048 bf16 11.3 either way; with four units a lane 40000 x 4096
+    // 12.8 with one, 14.0 with four), and of two wavefronts up to four row groups a unit (1028 x 2080 fp16 3.09 / 2.97, 2392 x 2080
+    // bf16 4.10 / 3.96, 4096 x 2400 binary32 4.24 / 4.14, 4096 x 3904 level; 5120 x 3904 binary32 4.87 / 5.02).
     p.unr = 1;
     const int per_lane = (U + 64 * p.ws - 1) / (64 * p.ws);
-    if (G <= cus || (one_each && p.ws == 4) || static_cast<long long>(N) * K / 4 >= (56LL << 20) || (p.ws == 1 && per_lane == 2)) {
+    const bool both = per_lane == 2 && (p.ws == 1 || (p.ws == 2 && p.slots == 2 && G <= cus * 4));
+    if (G <= cus || (one_each && p.ws == 4) || static_cast<long long>(N) * K / 4 >= (56LL << 20) || both) {
         for (int c = 2; c <= 4; c *= 2)
             if (((per_lane + c - 1) / c) * c * 10 <= per_lane * 11) p.unr = c;
     }

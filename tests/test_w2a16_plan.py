@@ -94,3 +94,10 @@ def test_a_row_of_few_is_summed_in_as_many_parts_as_by_four_wavefronts(plan):
     shapes = [(f, n, k, 0) for f in (F16, F32) for n in ROWS if n <= 4096 for k in range(4096, 32769, 352)]
     for s, (ws, _, _, chains, _) in zip(shapes, plan(shapes)):
         assert ws * chains >= 4, s
+
+
+@pytest.mark.parametrize("k", [2080, 2976, 4064])
+def test_two_units_a_lane_are_one_stage_while_few_rows_fall_on_a_unit(plan, k):
+    for f in (F16, F32):
+        for n, unr in ((1028, 2), (2048, 2), (4096, 2), (8192, 1)):
+            assert plan([(f, n, k, 0)])[0][:3] == (2, 2, unr), (f, n, k)
