@@ -340,7 +340,7 @@ static int launch_wo(const void* packed, const void* codebook, int N, int K, con
     if (ws == 2 && slots == 2) RCP_WU(2, 2);
     if (ws == 2) RCP_WU(2, 4);
     if (slots == 1) RCP_WU(4, 1);
-    RCP_WU(4, 2);
+    RCP_WO(4, 2, 1, 1);  // at most 6144 rows: never a matrix of 56 MB, which alone would ask it for more loads
 #undef RCP_WU
 #undef RCP_WO
 }

@@ -150,6 +150,32 @@ def test_weight_only_gemv_workgroup_forms_close_to_oracle(dtype, N, K, blocks):
     test_weight_only_gemv_close_to_oracle(N, K, dtype, blocks, 0)
 
 
+@pytest.mark.parametrize("dtype,N,K", [
+    ("f16", 12292, 20000), ("f32", 12804, 18464),         # two loads a stage
+    ("f16", 10708, 22016), ("bf16", 16388, 14368)])       # four; one row group or two in the last workgroup
+def test_weight_only_gemv_several_loads_of_eight_wavefronts(dtype, N, K):
+    """Matrices of 56 MB and more with a long token, four row groups of two wavefronts a workgroup: every output against single
+    wavefronts, the first, middle and last rows against the oracle."""
+    _say(f"weight-only gemv N={N} K={K} {dtype}")
+    g = torch.Generator(device=DEV).manual_seed(44)
+    packed = torch.randint(-2 ** 31, 2 ** 31 - 1, (N * K // 16,), generator=g, device=DEV, dtype=torch.int32)
+    cb = np.sort(np.random.default_rng(44).standard_normal((N, 4)) * 0.03, axis=1).astype(np.float16)
+    x = _t(rcp_synth.activation(44, f"wo{K}", 1, K))
+    x = x if dtype == "f16" else x.float().to(torch.bfloat16) if dtype == "bf16" else x.float() * np.float32(1.0009765)
+    out = rcp.w2a16_gemv(packed, _t(cb), N, K, x, out_dtype=torch.float32).cpu().numpy().ravel().astype(np.float64)
+    rcp.set_option("gemv_lanes", 64)
+    single = rcp.w2a16_gemv(packed, _t(cb), N, K, x, out_dtype=torch.float32).cpu().numpy().ravel()
+    x64 = x.double().cpu().numpy()
+    # binary32 sums of K terms in any order: within K * 2^-24 of the sum of their magnitudes, of which 2^-24 * sqrt(K) is usual
+    bound = 4 * 2.0 ** -24 * K ** 0.5 * np.abs(cb.astype(np.float64)).max(axis=1) * np.abs(x64).sum()
+    assert np.all(np.abs(out - single) <= bound)
+    for r in (0, N // 8 * 4, N - 20):
+        rows = packed[r * K // 16:(r + 20) * K // 16].cpu().numpy().view(np.uint8)
+        ref = oracle.w2a16_gemv(rows, cb[r:r + 20].view(np.uint16), 20, K, x64)[0]
+        assert np.all(np.abs(out[r:r + 20] - ref) <= bound[r:r + 20])
+        assert np.linalg.norm(out[r:r + 20] - ref) <= 1e-5 * np.linalg.norm(ref)
+
+
 @pytest.mark.parametrize("dtype,N,K", [("f32", 2560, 14336), ("f32", 4096, 10240), ("bf16", 3072, 13312)])
 def test_weight_only_gemv_rounds_no_more_than_with_256_lanes_a_row(dtype, N, K):
     """The automatic form's error against binary64 is that of 256 lanes a row.  Bound: partial sums of twice the length have a

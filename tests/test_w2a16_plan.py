@@ -80,10 +80,11 @@ def test_a_handful_of_second_row_groups_does_not_halve_the_workgroups(plan, k):
 def test_every_form_that_is_chosen_is_built_and_fits(plan):
     """Every accepted size has a kernel whose tables, token and exchange slots fit the LDS."""
     built = {(1, 4), (2, 2), (2, 4), (4, 1), (4, 2)}
-    shapes = [(f, n, k, lanes) for f in (F16, F32) for n in ROWS + [8196, 12288, 65536, 131072]
+    shapes = [(f, n, k, lanes) for f in (F16, F32) for n in ROWS + [5632, 6144, 6148, 8196, 12288, 65536, 131072]
               for k in list(range(32, 1056, 32)) + list(range(1056, 32769, 992)) + [32768] for lanes in (0, 16, 64, 128, 256)]
     for s, (ws, slots, unr, chains, lds) in zip(shapes, plan(shapes)):
         assert (ws, slots) in built and unr in (1, 2, 4) and lds <= 160 * 1024, s
+        assert unr == 1 or (ws, slots) != (4, 2), s   # the one form that is built with one load a stage only
         assert chains == 1 or (chains, ws, slots, unr) == (2, 2, 4, 1), s
         if s[3] >= 64 and s[2] // 16 >= s[3]:
             assert ws * 64 == s[3] and ws * slots == 4, s
