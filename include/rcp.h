@@ -155,7 +155,7 @@ int rcp_version(void);
  *                  from 8 MB of packed weights on; the 3-bit kernel (from 16 MB on) and the kernel for
  *                  group-wise tables (from 4 MB on) and the weight-only kernel (from 4 MB on) likewise
  *   "gemm_stage"   128-column steps per pipeline stage of the matrix-core kernel: 1, 2 (automatic: 2 from eight steps
- *                  per wavefront on, and for four steps of 16-row workgroups that are alone on their compute units)
+ *                  per wavefront on)
  *   "gemm_rows"    output rows per workgroup of the matrix-core kernel: 16 (four lanes per group of four rows), or
  *                  20, 24 .. 64 (one lane per group); automatic = 16 up to 8192 rows, else the smallest count that
  *                  gives every compute unit the same number of workgroups.  With group-wise tables: rounded up to blocks

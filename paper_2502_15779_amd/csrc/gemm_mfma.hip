@@ -309,12 +309,11 @@ int launch_gemm_mfma(const void* packed, const void* codebook, int N, int K, con
     auto* x4 = static_cast<const uint4*>(xq);
     auto* sc = static_cast<const uint16_t*>(scale);
     const dim3 grid(blocks), block(waves * 64);
-    // Two steps per pipeline stage once a wavefront has eight or more steps to walk (4096 x 11008: 6.9 against 7.6 us), and
-    // four steps of 16-row workgroups, if they are alone on their compute units (4096 x 4096, 4 / 16 tokens: 3.82 / 4.29
-    // against 4.07 / 4.40 us; with more than one workgroup a unit 8192 x 4096 at 6 tokens takes 6.1 instead of 5.5, and 5120
-    // columns, which are no whole number of double steps, 4.5 instead of 4.3).
-    const bool deep =
-        options().gemm_stage != 0 ? options().gemm_stage == 2 : KS >= 8 * waves || (narrow && blocks <= cus && KS == 4 * waves);
+    // Two steps per pipeline stage once a wavefront has eight or more steps to walk (4096 x 11008: 6.9 against 7.6 us).  Below, the
+    // better of the two depends on where the weights are: 4096 x 4096 at 4 / 16 tokens takes 3.90 / 4.25 us with two and
+    // 4.33 / 4.55 with one from memory, 4.02 / 4.23 and 3.89 / 4.23 out of the caches (1024 x 5120: 4.33 / 4.74 and 4.41 / 4.74,
+    // 4.39 / 4.79 and 3.91 / 4.24; 6144 columns gain 11 % and lose 5, 3072 lose 3 and 15).
+    const bool deep = options().gemm_stage != 0 ? options().gemm_stage == 2 : KS >= 8 * waves;
 #define RCP_MM(F16, PK, NA)                                                                                   \
     do {                                                                                                      \
         if (deep) gemm_mfma_kernel<F16, PK, NA, 2><<<grid, block, 0, st>>>(pk, cb, N, K, x4, sc, M, waves, RG, out, P); \
