@@ -14,7 +14,7 @@
 // bits as they are) and 2 hi.  Up to 8 tokens they share one B operand (columns 0..7 carry lo, columns 8..15 hi of the same
 // tokens); beyond that lo and hi are two B operands, accumulating into the same registers.  No scale is involved: a scaled
 // instruction holds the vector unit for eight cycles, a plain one for four.  What the rows' values leave in the sums
-// (F/4, F/2, F, and T/2 - F with the sum T of q) is undone once per output.  Every product and every sum is a small multiple
+// (F/4, F/2, F, and T/2 - F with the sum T of q) is undone where they are added up, the T of the fourth row once per output.  Every product and every sum is a small multiple
 // of 1/4, so the fp32 accumulators are exact (|sum| <= 8K <= 2^18) and the per-level sums stay bit-exact.
 //
 // Work decomposition.  A workgroup owns 16 groups of four rows (64 output rows): lane l of a
@@ -33,8 +33,10 @@ constexpr int MM_SUMS = 3 * MM_PLANE + 16;          // ints that are accumulated
 constexpr int MM_LDS_INTS = MM_SUMS + 2 * 64 + 16;  // + the 64 LUT rows of the block and the scales
 
 constexpr uint32_t MM_ONE = 0x22222222u;      // 1.0 in every nibble: with its sign bit -1.0
-constexpr float MM_MAGIC = 0x1.8p21f;         // |acc| <= 8 K <= 2^18 beside it: the sum is exact to a quarter
-constexpr uint32_t MM_MAGIC_BITS = 0x4a400000u;
+// the lowest bit of a float next to it is the unit of the sums of row r of a nibble (1/4, 1/2, 1, 1/2); |sum| <= 8 K <= 2^18, in
+// that unit 2^19 at most, keeps the sum exact, and the 22 low bits of the number itself are zero
+constexpr int MM_SUM_BITS = 22;
+constexpr float mm_magic(int r) { return r == 0 ? 0x1.8p21f : r == 2 ? 0x1.8p23f : 0x1.8p22f; }
 
 // eight int4 -> eight FP4 codes of 2 (q >> 2): 0000, 0100 (2), 1110 (-4), 1100 (-2) for the upper bits 00, 01, 10, 11
 __device__ __forceinline__ uint32_t fp4_twice_hi(uint32_t x)
@@ -209,14 +211,17 @@ __global__ __launch_bounds__(MM_MAX_THREADS) void gemm_mfma_kernel(const uint4* 
     if (__builtin_expect(K < 0, 0)) red[0] = static_cast<int>(keep);  // never true
 
     // acc[p][r][v] = F_p / 4, F_p / 2, F_p or (T - 2 F_p) / 2 (packed: its lo or its hi part) of row 4*(RG*block + 4*kb + v) + r,
-    // r = 0, 1, 2 or 3, and this lane's token.  The wavefronts add them up in LDS in units of a quarter (integer adds: the
-    // binary32 LDS add is far slower): under MM_MAGIC the lowest bit of a float is a quarter, and the bits of MM_MAGIC itself,
-    // added once per wavefront, are taken out of the total.  The two columns of a token are added before and columns without a
+    // r = 0, 1, 2 or 3, and this lane's token.  The wavefronts add them up in LDS as integers (the binary32 LDS add is far
+    // slower): beside mm_magic the lowest bits of a float are F_p, and for r = 3 2 F_p - T; what the upper bits of the magic
+    // numbers add up to stays above bit 22.  The two columns of a token are added before and columns without a
     // token left out: the LDS adds sixteen lanes a cycle (12288 x 1024 at 6 tokens, where
     // this phase took 0.74 of 3.2 us: 4.14 -> 4.05 us a launch; 6144 x 1024 at 3 tokens 4.00 -> 3.30).
-    auto quarters = [](float v) {
-        if constexpr (PACKED) v += __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0x128, 0xf, 0xf, true));  // lane ^ 8
-        return static_cast<int>(__float_as_uint(v + MM_MAGIC));
+    auto aligned = [](float v, int r) {
+        if constexpr (PACKED) {
+            v += __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0x128, 0xf, 0xf, true));  // lane ^ 8
+            asm("" : "+v"(v));  // the addition stays beside the exchange (and becomes one instruction with it)
+        }
+        return static_cast<int>(__float_as_uint(r == 3 ? mm_magic(3) - v : mm_magic(r) + v));
     };
     constexpr int RN = NARROW ? 1 : 4;
     int sums[3][RN][4];
@@ -225,8 +230,8 @@ __global__ __launch_bounds__(MM_MAX_THREADS) void gemm_mfma_kernel(const uint4* 
 #pragma unroll
         for (int r = 0; r < RN; ++r)
 #pragma unroll
-            for (int v = 0; v < 4; ++v) sums[p][r][v] = quarters(acc[p][r][v]);
-    if (i < M && !hi_lane) {
+            for (int v = 0; v < 4; ++v) sums[p][r][v] = aligned(acc[p][r][v], NARROW ? v : r);
+    if (__builtin_expect(i < M && !hi_lane, 1)) {  // (in place: the jump to a block behind the kernel's end and back costs a fetch)
         // narrow: acc[p][0][v] is row v of row group kb of the block
         int* dst = red + token * MM_STRIDE + (NARROW ? 4 : 16) * kb;
 #pragma unroll
@@ -246,21 +251,23 @@ __global__ __launch_bounds__(MM_MAX_THREADS) void gemm_mfma_kernel(const uint4* 
     }
     __syncthreads();
 
-    const uint32_t magic_total = MM_MAGIC_BITS * static_cast<uint32_t>(W);
-    for (int o = tid; o < M * 64; o += 64 * W) {
-        const int n = o >> 6, hh = o & 63;
-        const int h = blockIdx.x * RB + hh;
-        if (hh >= RB || h >= N) continue;
+    // A thread keeps its output row (and the row's levels) and walks the tokens; a wavefront covers a token's 64 rows, or four
+    // tokens of the 16 rows of the narrow form.  The wavefronts are few where K is short, and this phase then most of what they
+    // do.  Against the fourth row and the units undone plane by plane (8 operations more a token), rows of 16 in a quarter of the
+    // lanes, and the exchange above as two instructions: 12872 x 512 at 2 / 8 tokens 3.62 / 3.45 -> 3.13 / 3.29 us, 131072 x 512
+    // at 16 10.84 -> 10.40, 4096 x 512 at 16 3.09 -> 2.58, 4 % in the mean over 308 shapes (but 131072 x 384 at 2 5.60 -> 5.93).
+    const int hh = NARROW ? lane & 15 : lane, h = static_cast<int>(blockIdx.x) * RB + hh;
+    if (hh >= RB || h >= N) return;
+    // the low bits of the sums are F_p, in the fourth row of a nibble 2 F_p - T
+    const int fourth = (hh & 3) == 3 ? 1 : 0;
+    auto low_bits = [&](int x) { return __builtin_amdgcn_sbfe(x, fourth, MM_SUM_BITS - fourth); };
+    for (int n = NARROW ? 4 * wave + (lane >> 4) : wave; n < M; n += NARROW ? 4 * W : W) {
+        asm volatile("" ::: "memory");  // the levels are read beside the sums, not waited for ahead of the loop
         const int T = red[3 * MM_PLANE + n];
-        // the sums hold F, 2 F, 4 F or 2 T - 4 F by the row of the nibble
-        const int down = min(hh & 3, 2), flip = (hh & 3) == 3 ? -1 : 0, from = (hh & 3) == 3 ? 2 * T + 1 : 0;
-        auto plane = [&](int p) {
-            const int x = static_cast<int>(static_cast<uint32_t>(red[p * MM_PLANE + n * MM_STRIDE + hh]) - magic_total);
-            return ((x ^ flip) + from) >> down;
-        };
-        const int F0 = plane(0), F1 = plane(1), F3 = plane(2);
-        const int P3 = F3, P1 = F0 - F3, P2 = F1 - F3, P0 = T - F0 - F1 + F3;
+        const int* row = red + n * MM_STRIDE + hh;
+        const int x0 = row[0], x1 = row[MM_PLANE], x3 = row[2 * MM_PLANE];
         const uint2 lut = make_uint2(static_cast<uint32_t>(red[MM_SUMS + 2 * hh]), static_cast<uint32_t>(red[MM_SUMS + 2 * hh + 1]));
+        const int P1 = low_bits(x0 - x3), P2 = low_bits(x1 - x3), P3 = low_bits(x3 + (fourth ? T : 0)), P0 = T - P1 - P2 - P3;
         const float c0 = half_bits_to_float(static_cast<uint16_t>(lut.x & 0xffffu));
         const float c1 = half_bits_to_float(static_cast<uint16_t>(lut.x >> 16));
         const float c2 = half_bits_to_float(static_cast<uint16_t>(lut.y & 0xffffu));
