@@ -151,11 +151,12 @@ def test_weight_only_gemv_workgroup_forms_close_to_oracle(dtype, N, K, blocks):
 
 
 @pytest.mark.parametrize("dtype,N,K", [
-    ("f16", 12292, 20000), ("f32", 12804, 18464),         # two loads a stage
-    ("f16", 10708, 22016), ("bf16", 16388, 14368)])       # four; one row group or two in the last workgroup
-def test_weight_only_gemv_several_loads_of_eight_wavefronts(dtype, N, K):
-    """Matrices of 56 MB and more with a long token, four row groups of two wavefronts a workgroup: every output against single
-    wavefronts, the first, middle and last rows against the oracle."""
+    # a long token, four row groups of two wavefronts, one row group or two in the last workgroup: a load a stage, two, four
+    ("f32", 8204, 9984), ("f16", 12292, 20000), ("f32", 12804, 18464), ("f16", 10708, 22016), ("bf16", 16388, 14368),
+    # row groups of single wavefronts: two units a lane, a whole row group a stage; two and four loads from 56 MB on; a long token
+    ("f16", 8196, 1056), ("bf16", 8204, 2048), ("f16", 22940, 10240), ("f16", 14404, 16384), ("bf16", 8204, 8704)])
+def test_weight_only_gemv_of_many_rows(dtype, N, K):
+    """Every output against four single wavefronts a workgroup, the first, middle and last rows against the oracle."""
     _say(f"weight-only gemv N={N} K={K} {dtype}")
     g = torch.Generator(device=DEV).manual_seed(44)
     packed = torch.randint(-2 ** 31, 2 ** 31 - 1, (N * K // 16,), generator=g, device=DEV, dtype=torch.int32)
