@@ -13,9 +13,10 @@
 // b0 & b1.  The int4 activation q = 4*hi + lo, lo in {0..3}, hi in {-2..1}, is recoded into two FP4 operands, lo / 2 (the two
 // bits as they are) and 2 hi.  Up to 8 tokens they share one B operand (columns 0..7 carry lo, columns 8..15 hi of the same
 // tokens); beyond that lo and hi are two B operands, accumulating into the same registers.  No scale is involved: a scaled
-// instruction holds the vector unit for eight cycles, a plain one for four.  What the rows' values leave in the sums
-// (F/4, F/2, F, and T/2 - F with the sum T of q) is undone where they are added up, the T of the fourth row once per output.  Every product and every sum is a small multiple
-// of 1/4, so the fp32 accumulators are exact (|sum| <= 8K <= 2^18) and the per-level sums stay bit-exact.
+// instruction takes the vector unit four cycles longer than a plain one.  What the rows' values leave in the sums (F/4, F/2, F, and
+// T/2 - F with the sum T of q) is undone where they are added up, the T of the fourth row once per output.  Every product and
+// every sum is a small multiple of 1/4, so the fp32 accumulators are exact (|sum| <= 8K <= 2^18) and the per-level sums stay
+// bit-exact.
 //
 // Work decomposition.  A workgroup owns 16 groups of four rows (64 output rows): lane l of a
 // wavefront supplies row group l%16 and the 32 columns of K-block l/16 of a 128-column step

@@ -13,8 +13,8 @@
 // a lane holds the exact plane sums F_p of four rows for one token, times the power of two that the
 // operands' units leave in them (where several groups are taken at a time), and adds their products with
 // the group's levels to four running fp32 outputs.  The power of two is taken out of the levels, once
-// for all tokens and without a rounding: a scaled instruction would hold the vector unit for eight
-// cycles instead of four (eight layers of 4096 / 14336 at 6 tokens,
+// for all tokens and without a rounding: a scaled instruction would take the vector unit four
+// cycles longer (eight layers of 4096 / 14336 at 6 tokens,
 // quantisers and rotations included, 359.2 -> 356.6 us).  The per-group sum T of q that level 0 needs comes
 // from one more instruction with an all-ones A operand.  The fourth row of a nibble is the FP4 sign
 // bit; its lanes shift it down by one.

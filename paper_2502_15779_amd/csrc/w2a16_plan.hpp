@@ -88,9 +88,9 @@ inline WoPlan wo_plan(bool xf32, int N, int K, int cus, int forced_lanes)
     // Loads per stage: one, which takes the fewest registers (55 to 61, eight wavefronts a SIMD; four take 83 to 88, five
     // wavefronts): 22016 x 4096 fp16 10.86 -> 10.09 us, 12288 x 4096 7.11 -> 6.53, 8192 x 16384 binary32 17.6 -> 16.4.
     // Where one row group or less falls on a compute unit (1000 x 16384 4.92 against 5.28 us) and in matrices that stream
-    // for long (from 56 MB on: 80000 x 3104 24.1 against 25.6, 131072 x 4096 43.0 against 45.2, 32768 x 16384 bf16 48.8 against 50.1), more
-    // loads in flight win: the largest of 4, 2, 1 that pads a lane's units by at most a tenth (padding units are computed
-    // on like real ones).
+    // for long (from 56 MB on: 80000 x 3104 24.1 against 25.6, 131072 x 4096 43.0 against 45.2, 32768 x 16384 bf16 45.2 against 47.2;
+    // but 14336 x 22016 fp16 29.5 against 25.7), more loads in flight win: the largest of 4, 2, 1 that pads a lane's units by at
+    // most a tenth (padding units are computed on like real ones).
     // Likewise two loads where they are all that a lane has: a whole row group of one wavefront (100000 x 1504 fp16 takes 18.1 us
     // with one, 16.9 with two, 40000 x 1504 bf16 9.0 / 9.3, 50000 x 2048 bf16 11.3 either way; with four units a lane 40000 x 4096
     // 12.8 with one, 14.0 with four), and of two wavefronts up to four row groups a unit (1028 x 2080 fp16 3.09 / 2.97, 2392 x 2080
