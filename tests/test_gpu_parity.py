@@ -139,7 +139,9 @@ def test_weight_only_gemv_close_to_oracle(N, K, dtype, blocks, lanes):
 
 @pytest.mark.parametrize("dtype,N,K,blocks", [
     ("f32", 1040, 8192, 0), ("f32", 1040, 8224, 0),       # either side of the shortest long token
-    ("f32", 1036, 11008, 3), ("bf16", 1044, 16384, 0),    # two row groups of four wavefronts, one left without a partner
+    ("f32", 1036, 11008, 3), ("bf16", 1040, 16384, 0), ("bf16", 1044, 16384, 0),   # two row groups of four wavefronts, one left
+    ("f32", 1032, 9984, 0), ("f32", 1032, 10016, 0), ("f32", 1036, 14336, 0), ("f32", 1036, 14336, 2),   # without a partner
+    ("bf16", 5132, 10272, 0), ("f16", 5128, 20000, 5),    # the same, six row groups on a unit
     ("f32", 2308, 14336, 0), ("f32", 2308, 14336, 2),     # four row groups of two wavefronts, the last workgroup not full
     ("f32", 2308, 11008, 0), ("f16", 2308, 22016, 5),     # one row group of four wavefronts, three on a unit
     ("bf16", 5132, 10240, 0),                             # two of two wavefronts, one left without a partner
