@@ -544,7 +544,7 @@ int rcp_kv4_rotate_attn_decode(const void* q, rcp_dtype q_dtype, int H_q, int H_
  *   pos_host[b] (0 <= pos_host[b] < S_max, else RCP_ERR_SHAPE).  Arithmetic as rcp_kv4_append.
  * rcp_kv4_attn_decode_batched: q and out are [B][H_q][128]; sequence b attends to its first S_host[b] tokens
  *   (1 <= S_host[b] <= S_max).  Each row equals what rcp_kv4_attn_decode gives for that sequence alone
- *   up to the order of its binary32 sums: the automatic split length is chosen from the total number of
+ *   up to the order of its binary32 sums: the automatic split length is chosen from the numbers of
  *   cached tokens of the call, so a batched row and the single call agree bit for bit only when the
  *   "kv_tokens" option fixes the split length, and within the stated tolerance otherwise.  workspace: B * rcp_kv4_workspace_bytes(H_q, max_b S_host[b])
  *   bytes.  H_q <= 4095. */

@@ -11,6 +11,7 @@
 
 #include <type_traits>
 
+#include "kv4_plan.hpp"
 #include "rcp_internal.hpp"
 
 namespace rcp {
@@ -21,6 +22,8 @@ constexpr int KV_D = 128;
 struct KvBatch {
     int v[RCP_MAX_M];
     int H_q, H_kv;
+    int n;                 // sequences,
+    int first[RCP_MAX_M];  // and in a compact grid the first workgroup of each (beyond the last one: the number of all)
 };
 
 // ---------------------------------------------------------------------------------------
@@ -219,7 +222,7 @@ constexpr int KV_THREADS = 256;
 constexpr int KV_MAX_L = 256;          // tokens per workgroup at most: four per lane group, all loads in flight at once
 constexpr int KV_PART = KV_D + 4;      // floats per partial result: acc[128], m, l, 2 unused
 constexpr float KV_LAZY = 30.0f;       // how far a score may exceed the streaming kernel's reference before it is raised
-constexpr int KV_LONG_L = 1024;        // tokens per workgroup of the streaming and the matrix-core kernel for large calls
+constexpr int KV_LONG_L = 1024;        // tokens per workgroup of the streaming kernel for large calls
 
 // The four low nibbles and the four high nibbles of a dword as bytes.  The empty asm keeps the
 // compiler from folding the mask into each later byte extraction (a 4-bit field extract plus a
@@ -905,7 +908,7 @@ struct KvMfmaLds {
     };
 };
 
-template <int RP>
+template <int RP, bool COMPACT>
 __global__ __launch_bounds__(KV_THREADS, RP <= 2 ? 4 : 3) void kv4_attn_mfma_kernel(const void* __restrict__ q, int q_dt, int rotate, int S_max, int rep,
                                                                    int splits, float softmax_scale, const u32x4* __restrict__ k_codes,
                                                                    const uint32_t* __restrict__ k_params,
@@ -916,11 +919,35 @@ __global__ __launch_bounds__(KV_THREADS, RP <= 2 ? 4 : 3) void kv4_attn_mfma_ker
     constexpr int HV = RP < 4 ? RP : 4;                       // heads a lane holds scores of
     constexpr int SETS = RP <= 4 ? 1 : RP == 8 ? 2 : 4;       // tokens a lane holds scores of
     __shared__ KvMfmaLds<RP> lds;
-    const int seq = blockIdx.z;
-    const int S = batch.v[seq];
-    const int split = static_cast<int>(blockIdx.x) % splits, hk0 = static_cast<int>(blockIdx.x) / splits;
+    int seq = 0, S = batch.v[0];
+    // plain grid (splits of the longest sequence, cache heads [, sequences]): from arguments that arrive with the wavefront
+    int hk0 = static_cast<int>(blockIdx.x) / splits, split = static_cast<int>(blockIdx.x) - hk0 * splits;
+    if constexpr (COMPACT) {
+        // Only splits that hold tokens have a workgroup: among those of a plain grid the early leavers upset the order in which the
+        // compute units are filled (16 sequences of up to 6000 tokens, 44000 in all, 360 of 768 workgroups at work on 256
+        // units: 24.0 -> 19.4 us at the same split length).
+        int start = 0;
+        auto look = [&](int lo, int hi) {  // selects on arguments that are all fetched together
+#pragma unroll
+            for (int b = lo; b < hi; ++b) {
+                const bool from = static_cast<int>(blockIdx.x) >= batch.first[b];
+                seq = from ? b : seq;
+                start = from ? batch.first[b] : start;
+                S = from ? batch.v[b] : S;
+            }
+        };
+        look(1, 4);
+        if (batch.n > 4) look(4, 8);  // uniform
+        if (batch.n > 8) look(8, RCP_MAX_M);
+        const int within = static_cast<int>(blockIdx.x) - start;
+        split = within / batch.H_kv;
+        hk0 = within - split * batch.H_kv;
+    } else {
+        seq = blockIdx.z;
+        S = batch.v[seq];
+        if (split * L >= S) return;  // the whole workgroup: this sequence has fewer splits
+    }
     const int t0 = split * L;
-    if (t0 >= S) return;  // the whole workgroup: this sequence has fewer splits
     const int t_end = min(S, t0 + L);
     const int hk = hk0 + seq * batch.H_kv;
     const int R = min(RP, rep - static_cast<int>(blockIdx.y) * RP);  // query heads of this workgroup
@@ -1344,52 +1371,61 @@ int launch_kv4_attn(const void* q, rcp_dtype q_dt, int B, int H_q, int H_kv, int
             S = lengths[b] > S ? lengths[b] : S;  // the longest sequence sizes the grid
             total += lengths[b];
         }
-        batch.H_q = H_q;
-        batch.H_kv = H_kv;
     }
     // Below 4096 x 32 (token, query head) pairs the form that issues all loads at once: 128 tokens per workgroup, 256 from
-    // 2048 x 32 pairs on.  Beyond, the matrix-core form, whose work is counted in (token, cache head) pairs: splits of 256
-    // tokens below 90000 (up to 351 workgroups and the ends of the sequences), 512 up to 8192 x 32, 1024 above (sweeps of
-    // all three lengths and the other forms; launches of both kernels, cold caches).  Grouped heads against the vector
-    // forms, 32 over 8: 16 sequences of 300 to 6000 tokens 45.7 -> 23.7 us, 65536 tokens 47.0 -> 21.9, 16384 tokens
-    // 17.5 -> 12.2, 4100 tokens 11.7 -> 9.8; 64 over 4 heads at 8192 tokens 17.3 -> 11.7; 32 over 16 at 8192 tokens
-    // 12.4 -> 10.8, at 4200 and 5000 level.
+    // 2048 x 32 pairs on.  Beyond, the matrix-core form, on splits of the length that kv_split_tokens finds.  Grouped heads against
+    // the vector forms, 32 over 8: 16 sequences of 300 to 6000 tokens 45.7 -> 23.7 us (1024-token splits), 65536 tokens
+    // 47.0 -> 21.9, 16384 tokens 17.5 -> 12.2, 4100 tokens 11.7 -> 9.8; 64 over 4 heads at 8192 tokens 17.3 -> 11.7; 32 over 16 at
+    // 8192 tokens 12.4 -> 10.8, at 4200 and 5000 level.
     // With one query head per cache head the streaming form up to 20480 x 32 pairs, on splits of 512 tokens up to
     // 8192 x 32, of 1024 beyond (streaming against matrix form, 32 heads: 5000 tokens 12.4 / 13.6 us, 8192 tokens
     // 12.6 / 13.9, 16384 tokens 17.7 / 18.7, 8 x 1024 tokens 11.5 / 12.3; 24000 tokens 23.1 / 23.1, 16 sequences of up to
     // 2000 tokens 26.1 / 24.7, of 4096 46.5 / 42.8).  The option asks for the matrix-core form at every size.
-    const int rep = H_q / H_kv;
+    batch.H_q = H_q;
+    batch.H_kv = H_kv;
+    if (!batched) batch.v[0] = S;
+    const unsigned nseq = static_cast<unsigned>(batched ? B : 1);
+    batch.n = static_cast<int>(nseq);
+    const int rep = H_q / H_kv, per = (rep + 15) / 16;  // sixteen query heads at most per workgroup of the matrix-core form
     const long long pairs = total * H_kv;
     int L = options().kv_tokens;
     const bool stream = L == 0 && rep == 1 && pairs >= 131072 && pairs < 655360;
     const bool matrix = !stream && (L == 0 ? total * H_q >= 131072 : L > KV_MAX_L);
     if (stream) L = pairs <= 262144 ? 512 : KV_LONG_L;
     else if (L == 0) {
-        if (matrix) L = pairs < 90000 ? 256 : pairs <= 262144 ? 512 : KV_LONG_L;
+        if (matrix) L = kv_split_tokens(batch.v, static_cast<int>(nseq), H_kv * per, num_compute_units());
         else L = total * H_q < 65536 ? 128 : KV_MAX_L;
     }
     const int splits = (S + L - 1) / L;
-    batch.H_q = H_q;
-    batch.H_kv = H_kv;
-    if (!batched) batch.v[0] = S;
-    const unsigned nseq = static_cast<unsigned>(batched ? B : 1);
     auto* kc = static_cast<const u32x4*>(k_codes);
     auto* vc = static_cast<const u32x4*>(v_codes);
     auto* kp = static_cast<const uint32_t*>(k_params);
     auto* vp = static_cast<const uint32_t*>(v_params);
     auto* part = static_cast<float*>(workspace);
     if (matrix) {
-        const unsigned per = rep < 16 ? 1u : static_cast<unsigned>((rep + 15) / 16);  // sixteen query heads at most per workgroup
-        const dim3 grid(static_cast<unsigned>(splits) * static_cast<unsigned>(H_kv), per, nseq);
+        // the plain grid for one sequence and while it has no more workgroups than there are units (finding the sequence costs 0.1 to
+        // 0.3 us: 11 sequences of 2500 tokens in all, 64 over 8 heads, 9.7 against 10.0)
+        const bool compact = nseq > 1 && static_cast<long long>(splits) * H_kv * per * nseq > num_compute_units();
+        int groups = 0;
+        for (int b = 0; b < RCP_MAX_M; ++b) {
+            batch.first[b] = groups;
+            if (b < static_cast<int>(nseq)) groups += (batch.v[b] + L - 1) / L * H_kv;
+        }
+        const dim3 grid(static_cast<unsigned>(compact ? groups : splits * H_kv), static_cast<unsigned>(per), compact ? 1u : nseq);
         auto launch = [&](auto kernel) {
             kernel<<<grid, KV_THREADS, 0, st>>>(q, static_cast<int>(q_dt), fused ? 1 : 0, S_max, rep, splits, softmax_scale, kc, kp, vc, vp, L,
                                                 part, batch);
         };
-        if (rep == 1) launch(&kv4_attn_mfma_kernel<1>);
-        else if (rep == 2) launch(&kv4_attn_mfma_kernel<2>);
-        else if (rep <= 4) launch(&kv4_attn_mfma_kernel<4>);
-        else if (rep <= 8) launch(&kv4_attn_mfma_kernel<8>);
-        else launch(&kv4_attn_mfma_kernel<16>);
+        auto form = [&](auto gapless) {
+            constexpr bool COMPACT = decltype(gapless)::value;
+            if (rep == 1) launch(&kv4_attn_mfma_kernel<1, COMPACT>);
+            else if (rep == 2) launch(&kv4_attn_mfma_kernel<2, COMPACT>);
+            else if (rep <= 4) launch(&kv4_attn_mfma_kernel<4, COMPACT>);
+            else if (rep <= 8) launch(&kv4_attn_mfma_kernel<8, COMPACT>);
+            else launch(&kv4_attn_mfma_kernel<16, COMPACT>);
+        };
+        if (compact) form(std::true_type{});
+        else form(std::false_type{});
     } else {
         // one index per (split, query head), padded to whole groups of 8 * rep (see kv_place)
         const unsigned units = static_cast<unsigned>(splits) * static_cast<unsigned>(H_kv);

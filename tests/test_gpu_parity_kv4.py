@@ -311,6 +311,57 @@ def test_batched_attention_matches_the_oracle_sequence_by_sequence(lengths, H_q,
             assert torch.equal(single, out[b])
 
 
+def _random_pool(seed, heads, S_max):
+    """Caches of arbitrary codes, steps 2^-4 .. 2^-2 and zero points 4 .. 11: (k codes, k params, v codes, v params)."""
+    g = torch.Generator(device=DEV).manual_seed(seed)
+    pool = []
+    for _ in range(2):
+        pool.append(torch.randint(0, 256, (heads, S_max, 64), generator=g, device=DEV, dtype=torch.uint8))
+        step = torch.exp2(-4 + 2 * torch.rand((heads, S_max), generator=g, device=DEV)).half()
+        z = torch.randint(4, 12, (heads, S_max), generator=g, device=DEV, dtype=torch.int16)
+        pool.append(torch.stack((step.view(torch.int16), z), dim=-1).view(torch.uint8))
+    return pool
+
+
+# more workgroups than compute units in a grid for the longest sequence: only splits with tokens have one, found from the lengths
+@pytest.mark.parametrize("H_q,H_kv,lengths", [
+    (32, 32, [1300, 1, 512, 513]), (40, 10, [3000, 1, 2, 511, 1024, 700, 5, 1536, 2999]), (32, 32, [2049, 256]),
+    (20, 20, [600] * 7 + [1]), (160, 8, [1, 1025, 2500, 40, 40, 40, 512, 512]), (64, 32, [1, 2600, 1]),
+    (32, 8, [97 * i + 1 for i in range(16)][::-1]), (64, 16, [3000] + [1] * 14 + [2999])])
+def test_a_row_of_a_ragged_batch_is_the_single_call(H_q, H_kv, lengths):
+    """At a fixed split length, bit for bit: the single calls take the plain grid."""
+    _say(f"kv4 ragged batch H_q={H_q} H_kv={H_kv} lengths={lengths}")
+    B = len(lengths)
+    pool = _random_pool(H_q + B, B * H_kv, max(lengths) // 4 * 4 + 8)  # (each sequence's share of it aligned)
+    q = torch.randn((B, H_q, D), generator=torch.Generator(device=DEV).manual_seed(B), device=DEV)
+    rcp.set_option("kv_tokens", 512)
+    assert -(-max(lengths) // 512) * H_kv * B > 256
+    out = rcp.kv4_attn_decode_batched(q, lengths, *pool, 0.0625)
+    for b, S in enumerate(lengths):
+        assert torch.equal(out[b], rcp.kv4_attn_decode(q[b], S, *[a[b * H_kv:(b + 1) * H_kv] for a in pool], 0.0625)), (b, S)
+
+
+@pytest.mark.parametrize("H_q,H_kv,lengths", [(32, 8, [4100, 300, 1, 2048, 5000]), (64, 32, [1700, 900]), (32, 4, [5000]), (32, 8, [9000]),
+                                              (64, 16, [1000] * 15 + [17])])
+def test_attention_on_automatic_splits(H_q, H_kv, lengths):
+    """The split length that the lengths ask for, against the oracle on the first and the last sequence's first and last heads."""
+    _say(f"kv4 automatic splits H_q={H_q} H_kv={H_kv} lengths={lengths[:5]}")
+    B = len(lengths)
+    assert sum(lengths) * H_q >= 131072
+    pool = _random_pool(7 * H_q + B, B * H_kv, max(lengths) + 3)
+    q = torch.randn((B, H_q, D), generator=torch.Generator(device=DEV).manual_seed(H_kv), device=DEV)
+    if B == 1:
+        out = rcp.kv4_attn_decode(q[0], lengths[0], *pool, 0.0625).unsqueeze(0)
+    else:
+        out = rcp.kv4_attn_decode_batched(q, lengths, *pool, 0.0625)
+    got, q64, rep = out.cpu().numpy().astype(np.float64), q.cpu().numpy().astype(np.float64), H_q // H_kv
+    for b in sorted({0, B - 1}):
+        for h in (0, H_q - 1):
+            k = b * H_kv + h // rep
+            ref = oracle.kv4_attn_decode(q64[b, h:h + 1], lengths[b], *[np.ascontiguousarray(a[k:k + 1].cpu().numpy()) for a in pool], 0.0625)
+            assert np.all(np.abs(got[b, h] - ref[0]) <= TOL * (1.0 + np.abs(ref[0]))), (b, h)
+
+
 def test_batched_append_equals_single_appends():
     _say("kv4 batched append")
     B, H, S_max = 5, 8, 40
