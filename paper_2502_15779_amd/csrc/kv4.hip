@@ -221,8 +221,6 @@ __global__ __launch_bounds__(256) void kv4_append_kv_kernel(const void* __restri
 constexpr int KV_THREADS = 256;
 constexpr int KV_MAX_L = 256;          // tokens per workgroup at most: four per lane group, all loads in flight at once
 constexpr int KV_PART = KV_D + 4;      // floats per partial result: acc[128], m, l, 2 unused
-constexpr float KV_LAZY = 30.0f;       // how far a score may exceed the streaming kernel's reference before it is raised
-constexpr int KV_LONG_L = 1024;        // tokens per workgroup of the streaming kernel for large calls
 
 // The four low nibbles and the four high nibbles of a dword as bytes.  The empty asm keeps the
 // compiler from folding the mask into each later byte extraction (a 4-bit field extract plus a
@@ -481,7 +479,7 @@ __global__ __launch_bounds__(KV_THREADS) void kv4_attn_kernel(const void* __rest
         valid[it] = t < t_end;
         const size_t at = head_base + (valid[it] ? t : t_end - 1);
         // the cache is read once per call: loads with the non-temporal hint (6.6 -> 6.0 us at 1024 tokens, 13.2 -> 12.5 at
-        // 8192, 57 -> 51 us for 16 sequences of 4096 in the streaming kernel)
+        // 8192, 57 -> 51 us for 16 sequences of 4096)
         kw[it] = __builtin_nontemporal_load(k_codes + (at * 4 + piece));
         kp[it] = __builtin_nontemporal_load(k_params + at);
     }
@@ -597,187 +595,6 @@ __global__ __launch_bounds__(KV_THREADS) void kv4_attn_kernel(const void* __rest
             for (int r = 0; r < 4; ++r) ls += lrow[w][r];
         dst[KV_D] = m;
         dst[KV_D + 1] = ls;
-    }
-}
-
-// ---------------------------------------------------------------------------------------
-// The streaming form for one query head per cache head at middle sizes, where the device is refilled a few times: a
-// workgroup that loads, waits, computes and leaves keeps too few bytes in flight, and a matrix product with one row of
-// sixteen in use is a longer chain behind each load.  Workgroup = (split of L tokens, head [, sequence]), L = 512 or 1024.
-// The split is cut into chunks of 16 tokens; wavefront w takes chunks w, w + 4, ... and walks them on its own: no workgroup
-// barrier inside the loop, the loads of its next two chunks in flight while it computes one.  Each wavefront keeps a
-// reference m (uniform over the wavefront; the running maximum, raised lazily) and rescales its sums when a chunk raises
-// it:  acc <- acc * e^(m_old - m_new);  p_t = e^(score_t - m_new).
-// At the end the four wavefronts merge in LDS with the same rule and (m, l, acc) of the split goes to the workspace for
-// kv4_combine_kernel.
-// ---------------------------------------------------------------------------------------
-struct KvChunk {
-    u32x4 kw, vw;
-    uint32_t kp, vp;
-    bool valid;
-};
-
-template <int QDT, bool BATCHED, bool QROT = false>
-__global__ __launch_bounds__(KV_THREADS) void kv4_attn_stream_kernel(const void* __restrict__ q, int S, int S_max, int rep,
-                                                                     int splits, float softmax_scale,
-                                                                     const u32x4* __restrict__ k_codes,
-                                                                     const uint32_t* __restrict__ k_params,
-                                                                     const u32x4* __restrict__ v_codes,
-                                                                     const uint32_t* __restrict__ v_params, int L,
-                                                                     float* __restrict__ part, KvBatch batch)
-{
-    __shared__ float red[4][KV_D];
-    __shared__ float wm[4], lrow[4][4], zrow[4][4];
-    int split, h, hk;
-    if (!kv_place(blockIdx.x, splits, rep, batch.H_kv, split, h, hk)) return;  // padding of the grid
-    const int tid = threadIdx.x, lane = tid & 63, slot = lane >> 2, piece = tid & 3;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int t0 = split * L;
-    if constexpr (BATCHED) {
-        const int seq = blockIdx.z;
-        S = batch.v[seq];
-        if (t0 >= S) return;  // the whole workgroup: this sequence has fewer splits
-        h += seq * batch.H_q;
-        hk += seq * batch.H_kv;
-    }
-    const int t_end = min(S, t0 + L);
-    const size_t head_base = static_cast<size_t>(hk) * S_max;
-    // chunks of this wavefront that hold at least one cached token
-    const int span = t_end - t0 - 16 * wave;
-    const int nchunks = span > 0 ? (span + 63) >> 6 : 0;
-
-    auto load = [&](int c, KvChunk& r) {  // chunk c of this wavefront: tokens t0 + 16 (4 c + wave) ...; past the end: the last token, weight 0
-        const int t = t0 + 16 * (4 * c + wave) + slot;
-        r.valid = t < t_end;
-        const size_t at = head_base + (r.valid ? t : t_end - 1);
-        // read once per call: non-temporal loads, as in kv4_attn_kernel
-        r.kw = __builtin_nontemporal_load(k_codes + (at * 4 + piece));
-        r.kp = __builtin_nontemporal_load(k_params + at);
-        r.vw = __builtin_nontemporal_load(v_codes + (at * 4 + piece));
-        r.vp = __builtin_nontemporal_load(v_params + at);
-    };
-
-    Raw8<QDT> qraw[4];
-#pragma unroll
-    for (int d = 0; d < 4; ++d) qraw[d] = load8_raw<QDT>(q, static_cast<size_t>(h) * KV_D + 32 * piece + 8 * d);
-    KvChunk cA, cB;
-    load(0, cA);
-    load(1, cB);
-
-    float qr[32];
-    const float qsum = kv_query_registers<QDT>(qraw, QROT, piece, qr);
-    const float unit = kv_fp8_unit(), inv_unit = 1.0f / unit;
-    const float scale_by_unit = softmax_scale * inv_unit, qsum_unit = qsum * unit;
-
-    float acc[32];
-#pragma unroll
-    for (int r = 0; r < 32; ++r) acc[r] = 0.0f;
-    float lsum = 0.0f, zacc = 0.0f;
-    float m = -INFINITY;  // uniform over the wavefront
-    int chunk = 0;
-
-    auto step = [&](KvChunk& cur) {
-        float dot[4] = {0.0f, 0.0f, 0.0f, 0.0f};
-#pragma unroll
-        for (int d = 0; d < 4; ++d) {
-            uint32_t lo, hi;
-            nibble_bytes(cur.kw[d], lo, hi);
-            float fl[4], fh[4];
-            bytes_to_floats(lo, fl);
-            bytes_to_floats(hi, fh);
-#pragma unroll
-            for (int b = 0; b < 4; ++b) {
-                dot[d] = fmaf(qr[8 * d + b], fl[b], dot[d]);
-                dot[d] = fmaf(qr[8 * d + 4 + b], fh[b], dot[d]);
-            }
-        }
-        const float s = half_bits_to_float(static_cast<uint16_t>(cur.kp & 0xffffu)) * scale_by_unit;
-        const float z = static_cast<float>(static_cast<int>(cur.kp) >> 16);
-        float sc = quad_sum(s * (((dot[0] + dot[1]) + (dot[2] + dot[3])) - z * qsum_unit));
-        sc = cur.valid ? sc : -INFINITY;
-        // The reference m only has to keep the exponentials in range, so it is raised lazily: when some score
-        // of the chunk exceeds it by more than KV_LAZY (always on the first chunk, where m = -inf; every chunk
-        // that is stepped holds a cached token, so the new maximum is finite).  Weights then stay below
-        // e^KV_LAZY and the sums of a split far inside the binary32 range.
-        if (__builtin_amdgcn_ballot_w64(sc > m + KV_LAZY) != 0) {  // uniform
-            const float m_new = fmaxf(m, wave_max(sc));
-            const float alpha = __expf(m - m_new);  // 0 on the first chunk
-#pragma unroll
-            for (int r = 0; r < 32; ++r) acc[r] *= alpha;
-            lsum *= alpha;
-            zacc *= alpha;
-            m = m_new;
-        }
-        const float p = __expf(sc - m);
-        const float w0 = p * half_bits_to_float(static_cast<uint16_t>(cur.vp & 0xffffu));
-        const float w = w0 * inv_unit;
-        lsum += p;
-        zacc = fmaf(w0, static_cast<float>(static_cast<int>(cur.vp) >> 16), zacc);
-#pragma unroll
-        for (int d = 0; d < 4; ++d) {
-            uint32_t lo, hi;
-            nibble_bytes(cur.vw[d], lo, hi);
-            float fl[4], fh[4];
-            bytes_to_floats(lo, fl);
-            bytes_to_floats(hi, fh);
-#pragma unroll
-            for (int b = 0; b < 4; ++b) {
-                acc[8 * d + b] = fmaf(w, fl[b], acc[8 * d + b]);
-                acc[8 * d + 4 + b] = fmaf(w, fh[b], acc[8 * d + 4 + b]);
-            }
-        }
-        __builtin_amdgcn_sched_barrier(0);
-        load(chunk + 2, cur);  // refill with the chunk two steps ahead (past the end: a harmless repeat of the last token)
-        __builtin_amdgcn_sched_barrier(0);
-        ++chunk;
-    };
-    // steps counted up front and run in pairs: one loop body, one exit (four chunks in flight instead of
-    // two: 130 registers and no gain)
-    for (int i = 0; i < nchunks / 2; ++i) {
-        step(cA);
-        step(cB);
-    }
-    if (nchunks & 1) step(cA);
-
-    // ---- the 16 tokens of a wavefront's chunks are summed as in kv4_attn_kernel; the four wavefronts
-    // merge through LDS, each weighted by e^(its m - the largest m) ----
-#pragma unroll
-    for (int r = 0; r < 32; ++r) acc[r] = row_tokens_sum(acc[r]);
-    lsum = row_tokens_sum(lsum);
-    zacc = row_tokens_sum(zacc);
-    float f16v[16], f32v[8];
-#pragma unroll
-    for (int k = 0; k < 16; ++k) f16v[k] = fold16f(acc[2 * k], acc[2 * k + 1]);
-#pragma unroll
-    for (int k = 0; k < 8; ++k) f32v[k] = fold32f(f16v[2 * k], f16v[2 * k + 1]);
-    const int rw = (tid >> 4) & 3;
-    if ((tid & 12) == 0) {
-#pragma unroll
-        for (int k = 0; k < 8; ++k) red[wave][32 * piece + kv_elem_of_reg(4 * k + rw)] = f32v[k];
-        if (piece == 0) {
-            lrow[wave][rw] = lsum;
-            zrow[wave][rw] = zacc;
-        }
-    }
-    if (lane == 0) wm[wave] = m;
-    __syncthreads();
-    float* dst = part + (static_cast<size_t>(h) * splits + split) * KV_PART;
-    if (tid <= KV_D) {
-        const float M = fmaxf(fmaxf(wm[0], wm[1]), fmaxf(wm[2], wm[3]));  // wavefront 0 always has a token: finite
-        float total = 0.0f;
-#pragma unroll
-        for (int w = 0; w < 4; ++w) {
-            const float e = __expf(wm[w] - M);  // 0 for a wavefront without tokens
-            float v;
-            if (tid < KV_D) v = red[w][tid] - ((zrow[w][0] + zrow[w][1]) + (zrow[w][2] + zrow[w][3]));
-            else v = (lrow[w][0] + lrow[w][1]) + (lrow[w][2] + lrow[w][3]);
-            total = fmaf(e, v, total);
-        }
-        if (tid < KV_D) dst[tid] = total;
-        else {
-            dst[KV_D] = M;
-            dst[KV_D + 1] = total;
-        }
     }
 }
 
@@ -1372,30 +1189,26 @@ int launch_kv4_attn(const void* q, rcp_dtype q_dt, int B, int H_q, int H_kv, int
             total += lengths[b];
         }
     }
-    // Below 4096 x 32 (token, query head) pairs the form that issues all loads at once: 128 tokens per workgroup, 256 from
-    // 2048 x 32 pairs on.  Beyond, the matrix-core form, on splits of the length that kv_split_tokens finds.  Grouped heads against
-    // the vector forms, 32 over 8: 16 sequences of 300 to 6000 tokens 45.7 -> 23.7 us (1024-token splits), 65536 tokens
-    // 47.0 -> 21.9, 16384 tokens 17.5 -> 12.2, 4100 tokens 11.7 -> 9.8; 64 over 4 heads at 8192 tokens 17.3 -> 11.7; 32 over 16 at
-    // 8192 tokens 12.4 -> 10.8, at 4200 and 5000 level.
-    // With one query head per cache head the streaming form up to 20480 x 32 pairs, on splits of 512 tokens up to
-    // 8192 x 32, of 1024 beyond (streaming against matrix form, 32 heads: 5000 tokens 12.4 / 13.6 us, 8192 tokens
-    // 12.6 / 13.9, 16384 tokens 17.7 / 18.7, 8 x 1024 tokens 11.5 / 12.3; 24000 tokens 23.1 / 23.1, 16 sequences of up to
-    // 2000 tokens 26.1 / 24.7, of 4096 46.5 / 42.8).  The option asks for the matrix-core form at every size.
+    // The form that issues all loads at once for small calls, 128 tokens per workgroup and from 2048 x 32 (token, query head) pairs on
+    // 256, else the matrix-core form on splits of the length that kv_split_tokens finds.  Where they meet (us, all at once / matrix):
+    // a batch at 40960 pairs, ragged ones gain most because workgroups without tokens delay the first form (16 sequences, 1661 tokens
+    // of 64 over 16 heads 13.1 / 9.0, 8 of 2250 of 32 over 8 9.5 / 8.9; below, 8 of 1183 8.5 / 8.6); one sequence with two to four
+    // query heads a cache head at 65536 (3000 tokens of 32 over 16 9.7 / 9.1, of 32 over 8 9.4 / 9.4; below, 929 of 64 over 16
+    // 8.4 / 8.6), with more or one at 131072 (3000 of 32 over 4 9.5 / 9.7, 4001 of 32 with the query's rotation 10.4 / 10.5 and
+    // 5 % more of a decode step).
+    // One query head a cache head had a third, streaming form up to 20480 x 32 pairs (streaming / matrix: 5000 tokens of 32
+    // heads 12.8 / 12.0, 12000 18.4 / 16.5, 9 sequences of 11368 in all 22.0 / 18.2; 6500 to 8200 tokens, the one stretch where it was
+    // ahead, 13.2 / 13.6).  The option asks for the matrix-core form at every size.
     batch.H_q = H_q;
     batch.H_kv = H_kv;
     if (!batched) batch.v[0] = S;
     const unsigned nseq = static_cast<unsigned>(batched ? B : 1);
     batch.n = static_cast<int>(nseq);
     const int rep = H_q / H_kv, per = (rep + 15) / 16;  // sixteen query heads at most per workgroup of the matrix-core form
-    const long long pairs = total * H_kv;
     int L = options().kv_tokens;
-    const bool stream = L == 0 && rep == 1 && pairs >= 131072 && pairs < 655360;
-    const bool matrix = !stream && (L == 0 ? total * H_q >= 131072 : L > KV_MAX_L);
-    if (stream) L = pairs <= 262144 ? 512 : KV_LONG_L;
-    else if (L == 0) {
-        if (matrix) L = kv_split_tokens(batch.v, static_cast<int>(nseq), H_kv * per, num_compute_units());
-        else L = total * H_q < 65536 ? 128 : KV_MAX_L;
-    }
+    const bool matrix = L == 0 ? total * H_q >= (batched ? 40960 : rep == 1 || rep > 4 ? 131072 : 65536) : L > KV_MAX_L;
+    if (matrix && L == 0) L = kv_split_tokens(batch.v, static_cast<int>(nseq), H_kv * per, num_compute_units());
+    if (L == 0) L = total * H_q < 65536 ? 128 : KV_MAX_L;
     const int splits = (S + L - 1) / L;
     auto* kc = static_cast<const u32x4*>(k_codes);
     auto* vc = static_cast<const u32x4*>(v_codes);
@@ -1439,16 +1252,9 @@ int launch_kv4_attn(const void* q, rcp_dtype q_dt, int B, int H_q, int H_kv, int
         else if (fused) launch(&kv4_attn_kernel<QDT, ITERS, false, true>); \
         else launch(&kv4_attn_kernel<QDT, ITERS, false>);                \
     } while (0)
-        auto launch_stream = [&](auto kernel) {
-            kernel<<<grid, KV_THREADS, 0, st>>>(q, S, S_max, rep, splits, softmax_scale, kc, kp, vc, vp, L, part, batch);
-        };
 #define RCP_KV_DISPATCH(QDT)                                                          \
     do {                                                                              \
-        if (stream) {                                                                 \
-            if (batched) launch_stream(&kv4_attn_stream_kernel<QDT, true>);           \
-            else if (fused) launch_stream(&kv4_attn_stream_kernel<QDT, false, true>); \
-            else launch_stream(&kv4_attn_stream_kernel<QDT, false>);                  \
-        } else if (L == 64) RCP_KV_LAUNCH(QDT, 1);                                    \
+        if (L == 64) RCP_KV_LAUNCH(QDT, 1);                                           \
         else if (L == 128) RCP_KV_LAUNCH(QDT, 2);                                     \
         else RCP_KV_LAUNCH(QDT, 4);                                                   \
     } while (0)
