@@ -570,7 +570,7 @@ template <int DT, int RPL>
 static int launch_kron_split(const void* x, int M, const rcp_rotation* rot, float* y, float norm, hipStream_t st)
 {
     dim3 grid((rot->m + 7) / 8 * 8, M);
-    kron_split_kernel<DT, RPL><<<grid, KRON_THREADS, 0, st>>>(x, rot->m, rot->Q, norm, y);
+    enqueue(&kron_split_kernel<DT, RPL>, grid, KRON_THREADS, 0, st, x, rot->m, rot->Q, norm, y);
     return check_launch("rcp_rotate_quant_act(kron)");
 }
 
@@ -666,9 +666,9 @@ static int launch_quant(const void* x, int M, int K, float clip_ratio, void* xq,
     const int iters = (units + threads - 1) / threads;
     auto* q = static_cast<uint32_t*>(xq);
     auto* s = static_cast<uint16_t*>(scale);
-    if (iters == 1) quant_kernel<DT, 1><<<M, threads, 0, st>>>(x, K, clip_ratio, threads, q, s);
-    else if (iters == 2) quant_kernel<DT, 2><<<M, threads, 0, st>>>(x, K, clip_ratio, threads, q, s);
-    else if (iters <= 4) quant_kernel<DT, 4><<<M, threads, 0, st>>>(x, K, clip_ratio, threads, q, s);
+    if (iters == 1) enqueue(&quant_kernel<DT, 1>, M, threads, 0, st, x, K, clip_ratio, threads, q, s);
+    else if (iters == 2) enqueue(&quant_kernel<DT, 2>, M, threads, 0, st, x, K, clip_ratio, threads, q, s);
+    else if (iters <= 4) enqueue(&quant_kernel<DT, 4>, M, threads, 0, st, x, K, clip_ratio, threads, q, s);
     else return fail(RCP_ERR_UNSUPPORTED, "rcp_rotate_quant_act: K=%d too large for the quantiser", K);
     return check_launch("rcp_rotate_quant_act(quantise)");
 }
@@ -686,7 +686,7 @@ static int launch_wht(const void* x, int M, int n, float clip_ratio, void* xq, v
     // 5.15 -> 4.87 us; at 4096 and 2048 points 16 per thread are 20-30 % slower)
     if (n < 8192) {
         const int threads = ((n / 8 + 63) / 64) * 64;
-        wht_quant_kernel<DT, 3, QUANT><<<M, threads, lds, st>>>(x, n, log2n, norm, clip_ratio, threads / 64, q, s, y);
+        enqueue(&wht_quant_kernel<DT, 3, QUANT>, M, threads, lds, st, x, n, log2n, norm, clip_ratio, threads / 64, q, s, y);
     } else {
         if (lds + 64 > 65536) {  // 64 KiB of dynamic LDS plus the static reduction slots: above the default limit
             hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&wht_quant_kernel<DT, 4, QUANT>),
@@ -694,7 +694,7 @@ static int launch_wht(const void* x, int M, int n, float clip_ratio, void* xq, v
             if (e != hipSuccess) return fail(RCP_ERR_HIP, "rcp_rotate_quant_act: LDS opt-in failed: %s", hipGetErrorString(e));
         }
         const int threads = ((n / 16 + 63) / 64) * 64;
-        wht_quant_kernel<DT, 4, QUANT><<<M, threads, lds, st>>>(x, n, log2n, norm, clip_ratio, threads / 64, q, s, y);
+        enqueue(&wht_quant_kernel<DT, 4, QUANT>, M, threads, lds, st, x, n, log2n, norm, clip_ratio, threads / 64, q, s, y);
     }
     return check_launch("rcp_rotate_quant_act(wht)");
 }
@@ -710,7 +710,7 @@ static int launch_kron_wave(const void* x, int M, int K, const rcp_rotation* rot
         if (e != hipSuccess) return fail(RCP_ERR_HIP, "rcp_rotate_quant_act: LDS opt-in failed: %s", hipGetErrorString(e));
     }
     dim3 grid((m + 3) / 4, M);
-    kron_wave_kernel<DT, RPL><<<grid, KRON_THREADS, lds, st>>>(x, n, m, rot->Q, norm, y);
+    enqueue(&kron_wave_kernel<DT, RPL>, grid, KRON_THREADS, lds, st, x, n, m, rot->Q, norm, y);
     return check_launch("rcp_rotate_quant_act(kron)");
 }
 
@@ -726,8 +726,8 @@ static int launch_kron(const void* x, int M, int K, const rcp_rotation* rot, flo
     // sequence kernel reproduces.
     if (M > 1 && m % 4 == 0 && (n == 64 || n == 128) && static_cast<size_t>(M) * m * xbytes >= (12u << 20)) {
         const dim3 grid((m + 15) / 16, M);
-        if (n == 64) kron_mfma_kernel<DT, 1><<<grid, KRON_THREADS, 0, st>>>(x, m, rot->Q, norm, y);
-        else kron_mfma_kernel<DT, 2><<<grid, KRON_THREADS, 0, st>>>(x, m, rot->Q, norm, y);
+        if (n == 64) enqueue(&kron_mfma_kernel<DT, 1>, grid, KRON_THREADS, 0, st, x, m, rot->Q, norm, y);
+        else enqueue(&kron_mfma_kernel<DT, 2>, grid, KRON_THREADS, 0, st, x, m, rot->Q, norm, y);
         return check_launch("rcp_rotate_quant_act(kron)");
     }
     // one workgroup per output column when a wavefront's share of the columns fits in registers:
@@ -758,7 +758,7 @@ static int launch_kron(const void* x, int M, int K, const rcp_rotation* rot, flo
         if (e != hipSuccess) return fail(RCP_ERR_HIP, "rcp_rotate_quant_act: LDS opt-in failed: %s", hipGetErrorString(e));
     }
     dim3 grid((m + KRON_JB - 1) / KRON_JB, M);
-    kron_rotate_kernel<DT><<<grid, KRON_THREADS, lds, st>>>(x, n, m, rot->Q, norm, y);
+    enqueue(&kron_rotate_kernel<DT>, grid, KRON_THREADS, lds, st, x, n, m, rot->Q, norm, y);
     return check_launch("rcp_rotate_quant_act(kron)");
 }
 
@@ -780,7 +780,7 @@ static int launch_heads(const void* x, int M, int K, const rcp_rotation* rot, fl
             if (e != hipSuccess)                                                                                   \
                 return fail(RCP_ERR_HIP, "rcp_rotate_quant_act: LDS opt-in failed: %s", hipGetErrorString(e));     \
         }                                                                                                          \
-        kernel<<<M, HEADS_THREADS, lds, st>>>(x, m, norm, clip_ratio, q, s, y);                                    \
+        enqueue(kernel, M, HEADS_THREADS, lds, st, x, m, norm, clip_ratio, q, s, y);                                    \
         break;                                                                                                     \
     }
     switch (n) {
@@ -872,7 +872,7 @@ static int launch_rotate_typed(const void* x, int M, int K, const rcp_rotation* 
     if (kind == RCP_ROT_KRON) return launch_kron<DT>(x, M, K, rot, y, st);
     if (kind == RCP_ROT_HEADS) return launch_heads<DT, false>(x, M, K, rot, 1.0f, nullptr, nullptr, y, st);
     const size_t groups = static_cast<size_t>(M) * K / 8;
-    widen_kernel<DT><<<static_cast<unsigned>((groups + 255) / 256), 256, 0, st>>>(x, groups, y);
+    enqueue(&widen_kernel<DT>, static_cast<unsigned>((groups + 255) / 256), 256, 0, st, x, groups, y);
     return check_launch("rcp_rotate_act");
 }
 

@@ -324,8 +324,8 @@ int launch_gemm_mfma(const void* packed, const void* codebook, int N, int K, con
     const bool deep = options().gemm_stage != 0 ? options().gemm_stage == 2 : KS >= 8 * waves;
 #define RCP_MM(F16, PK, NA)                                                                                   \
     do {                                                                                                      \
-        if (deep) gemm_mfma_kernel<F16, PK, NA, 2><<<grid, block, 0, st>>>(pk, cb, N, K, x4, sc, M, waves, RG, out, P); \
-        else gemm_mfma_kernel<F16, PK, NA, 1><<<grid, block, 0, st>>>(pk, cb, N, K, x4, sc, M, waves, RG, out, P);      \
+        if (deep) enqueue(&gemm_mfma_kernel<F16, PK, NA, 2>, grid, block, 0, st, pk, cb, N, K, x4, sc, M, waves, RG, out, P); \
+        else enqueue(&gemm_mfma_kernel<F16, PK, NA, 1>, grid, block, 0, st, pk, cb, N, K, x4, sc, M, waves, RG, out, P);      \
     } while (0)
     const bool f16 = out_dt == RCP_F16, pkd = M <= 8;
     if (narrow) {

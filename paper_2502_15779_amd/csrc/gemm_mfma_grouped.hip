@@ -311,7 +311,7 @@ int launch_gemm_mfma_grouped(const void* packed, const void* codebook, int N, in
                                                      hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(lds));        \
             if (e != hipSuccess) return fail(RCP_ERR_HIP, "rcp_w2a4_gemm_grouped: LDS opt-in failed: %s", hipGetErrorString(e)); \
         }                                                                                                                       \
-        gemm_mfma_grouped_kernel<F16, P_, B_, TK><<<blocks, resident * 64, lds, st>>>(pk, cb, N, K, x4, sc, M, waves, nb, out, P); \
+        enqueue(&gemm_mfma_grouped_kernel<F16, P_, B_, TK>, blocks, resident * 64, lds, st, pk, cb, N, K, x4, sc, M, waves, nb, out, P); \
     } while (0)
 #define RCP_MG_TK(F16)                               \
     do {                                             \

@@ -553,7 +553,7 @@ static int launch_one(const GemvArgs& a, int blocks, hipStream_t st)
                                            hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(lds));
         if (e != hipSuccess) return fail(RCP_ERR_HIP, "rcp_w2a4_gemv: LDS opt-in failed: %s", hipGetErrorString(e));
     }
-    kernel<<<blocks, NW * 64, lds, st>>>(
+    enqueue(kernel, blocks, NW * 64, lds, st, 
         static_cast<const uint4*>(a.packed), static_cast<const uint2*>(a.codebook), a.N, a.K,
         a.xraw != nullptr ? a.xraw : a.xq, static_cast<const uint16_t*>(a.scale), a.M, a.clip_ratio, blocks,
         a.rot_n > 0 ? (a.rot_wht ? a.rot_m : (a.rot_n | (a.rot_m << 8))) : 0, a.out, a.P,
@@ -706,7 +706,7 @@ static int dispatch_gemv(const GemvArgs& a, hipStream_t st)
     const int want_waves = options().gemv_waves;
     const bool wide_ok = a.xraw != nullptr && a.rot_n == 0 && a.K / 16 >= 128 && options().gemv_lanes == 0;
     // (with fp32 activations the two forms are within 2 % of each other: left on four wavefronts)
-    const bool wide_pays = (a.N / 4 + 3) / 4 <= num_compute_units() && a.K >= 8192 && a.x_dt != RCP_F32;
+    const bool wide_pays = a.K >= 8192 && a.x_dt != RCP_F32 && (a.N / 4 + 3) / 4 <= num_compute_units();
     if (wide_ok && (want_waves == 8 || (want_waves == 0 && wide_pays))) {
         const int nbatch = (a.N / 4 + 3) / 4;  // four row groups per workgroup, as with four wavefronts
         int blocks = options().gemv_blocks;

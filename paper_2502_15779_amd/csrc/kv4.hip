@@ -1127,7 +1127,7 @@ int launch_kv4_append(const void* x, rcp_dtype dt, int n_tokens, int H, int S_ma
     const bool by_tokens = !batched && kv4_by_tokens(n_tokens) && H <= 65535;
     const dim3 grid = kv4_append_grid(n_tokens, H, by_tokens, 1u);
     auto launch = [&](auto kernel) {
-        kernel<<<grid, 256, 0, st>>>(x, by_tokens ? n_tokens : n_tokens * H, H, S_max, pos, clip_ratio, c, p, batch);
+        enqueue(kernel, grid, 256, 0, st, x, by_tokens ? n_tokens : n_tokens * H, H, S_max, pos, clip_ratio, c, p, batch);
     };
 #define RCP_KV_APPEND(DT)                                                          \
     do {                                                                           \
@@ -1157,7 +1157,7 @@ int launch_kv4_append_kv(const void* k, const void* v, rcp_dtype dt, int n_token
     const bool by_tokens = kv4_by_tokens(n_tokens) && H <= 65535;
     const dim3 grid = kv4_append_grid(n_tokens, H, by_tokens, 2u);
     auto launch = [&](auto kernel) {
-        kernel<<<grid, 256, 0, st>>>(k, v, by_tokens ? n_tokens : n_tokens * H, H, S_max, pos, rotate_k ? 1 : 0, clip_ratio,
+        enqueue(kernel, grid, 256, 0, st, k, v, by_tokens ? n_tokens : n_tokens * H, H, S_max, pos, rotate_k ? 1 : 0, clip_ratio,
                                      static_cast<uint32_t*>(k_codes), static_cast<uint32_t*>(k_params),
                                      static_cast<uint32_t*>(v_codes), static_cast<uint32_t*>(v_params));
     };
@@ -1226,7 +1226,7 @@ int launch_kv4_attn(const void* q, rcp_dtype q_dt, int B, int H_q, int H_kv, int
         }
         const dim3 grid(static_cast<unsigned>(compact ? groups : splits * H_kv), static_cast<unsigned>(per), compact ? 1u : nseq);
         auto launch = [&](auto kernel) {
-            kernel<<<grid, KV_THREADS, 0, st>>>(q, static_cast<int>(q_dt), fused ? 1 : 0, S_max, rep, splits, softmax_scale, kc, kp, vc, vp, L,
+            enqueue(kernel, grid, KV_THREADS, 0, st, q, static_cast<int>(q_dt), fused ? 1 : 0, S_max, rep, splits, softmax_scale, kc, kp, vc, vp, L,
                                                 part, batch);
         };
         auto form = [&](auto gapless) {
@@ -1244,7 +1244,7 @@ int launch_kv4_attn(const void* q, rcp_dtype q_dt, int B, int H_q, int H_kv, int
         const unsigned units = static_cast<unsigned>(splits) * static_cast<unsigned>(H_kv);
         const dim3 grid(8u * static_cast<unsigned>(rep) * ((units + 7u) / 8u), 1u, nseq);
         auto launch = [&](auto kernel) {
-            kernel<<<grid, KV_THREADS, 0, st>>>(q, S, S_max, rep, splits, softmax_scale, kc, kp, vc, vp, part, batch);
+            enqueue(kernel, grid, KV_THREADS, 0, st, q, S, S_max, rep, splits, softmax_scale, kc, kp, vc, vp, part, batch);
         };
 #define RCP_KV_LAUNCH(QDT, ITERS)                                        \
     do {                                                                 \
@@ -1269,7 +1269,7 @@ int launch_kv4_attn(const void* q, rcp_dtype q_dt, int B, int H_q, int H_kv, int
     int groups = (splits + 3) / 4;
     if (groups > KV_CT / KV_D) groups = KV_CT / KV_D;
     const unsigned cgrid = static_cast<unsigned>(H_q) * (batched ? B : 1);
-    auto combine = [&](auto kernel) { kernel<<<cgrid, groups * KV_D, 0, st>>>(part, splits, groups, out, L, matrix ? 1.0f : 1.44269504088896340736f, batch); };
+    auto combine = [&](auto kernel) { enqueue(kernel, cgrid, groups * KV_D, 0, st, part, splits, groups, out, L, matrix ? 1.0f : 1.44269504088896340736f, batch); };
     if (batched) {
         if (out_dt == RCP_F16) combine(&kv4_combine_kernel<true, true>);
         else combine(&kv4_combine_kernel<false, true>);

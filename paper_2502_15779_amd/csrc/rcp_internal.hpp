@@ -7,6 +7,8 @@
 #include <stddef.h>
 #include <stdint.h>
 
+#include <tuple>
+
 #include "rcp.h"
 
 namespace rcp {
@@ -14,6 +16,20 @@ namespace rcp {
 // ---- error plumbing (api.hip) -------------------------------------------------
 int fail(int code, const char* fmt, ...);
 int check_launch(const char* what);  // hipGetLastError() -> RCP_ERR_HIP / RCP_OK
+
+// kernel<<<grid, block, lds, st>>>(args...) without the pair of calls that carry the four of them to the kernel's host stub:
+// 3.55 instead of 3.74 us a launch (torch's HIP library, one host thread); its error is found by check_launch as before.
+template <class... P, class... A>
+inline void enqueue(void (*kernel)(P...), dim3 grid, dim3 block, size_t lds, hipStream_t st, const A&... args)
+{
+    std::tuple<P...> values(static_cast<P>(args)...);
+    std::apply(
+        [&](auto&... value) {
+            void* pointers[] = {const_cast<void*>(static_cast<const void*>(&value))...};
+            (void)hipLaunchKernel(reinterpret_cast<const void*>(kernel), grid, block, pointers, lds, st);
+        },
+        values);
+}
 
 // ---- tuning knobs (api.hip), 0 = automatic --------------------------------------
 struct Options {

@@ -312,7 +312,7 @@ static int launch_wo_one(const void* packed, const void* codebook, int N, int K,
                                            static_cast<int>(lds));
         if (e != hipSuccess) return fail(RCP_ERR_HIP, "rcp_w2a16_gemv: LDS opt-in failed: %s", hipGetErrorString(e));
     }
-    kernel<<<blocks, 64 * WS * SLOTS, lds, st>>>(static_cast<const uint4*>(packed), static_cast<const uint2*>(codebook), N, K, x, out,
+    enqueue(kernel, blocks, 64 * WS * SLOTS, lds, st, static_cast<const uint4*>(packed), static_cast<const uint2*>(codebook), N, K, x, out,
                                                  out_dt == RCP_F16 ? 1 : 0, blocks);
     return check_launch("rcp_w2a16_gemv");
 }

@@ -379,7 +379,7 @@ static int launch_w3_ws(const W3Args& a, hipStream_t st)
     if (blocks == 0) blocks = nbatch >= cus * 16 ? cus * 8 : (nbatch <= cus * 2 ? nbatch : cus * 2);
     if (blocks > nbatch) blocks = nbatch;
     auto launch = [&](auto kernel) {
-        kernel<<<blocks, W3_THREADS, lds, st>>>(static_cast<const uint8_t*>(a.packed), static_cast<const uint4*>(a.codebook), a.N,
+        enqueue(kernel, blocks, W3_THREADS, lds, st, static_cast<const uint8_t*>(a.packed), static_cast<const uint4*>(a.codebook), a.N,
                                                 a.K, a.x, static_cast<const uint16_t*>(a.scale), a.clip_ratio, blocks, a.out, a.P,
                                                 static_cast<uint2*>(a.xq_out), static_cast<uint16_t*>(a.scale_out));
     };
