@@ -553,7 +553,7 @@ static int launch_one(const GemvArgs& a, int blocks, hipStream_t st)
                                            hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(lds));
         if (e != hipSuccess) return fail(RCP_ERR_HIP, "rcp_w2a4_gemv: LDS opt-in failed: %s", hipGetErrorString(e));
     }
-    enqueue(kernel, blocks, NW * 64, lds, st, 
+    enqueue(kernel, blocks, NW * 64, lds, st,
         static_cast<const uint4*>(a.packed), static_cast<const uint2*>(a.codebook), a.N, a.K,
         a.xraw != nullptr ? a.xraw : a.xq, static_cast<const uint16_t*>(a.scale), a.M, a.clip_ratio, blocks,
         a.rot_n > 0 ? (a.rot_wht ? a.rot_m : (a.rot_n | (a.rot_m << 8))) : 0, a.out, a.P,

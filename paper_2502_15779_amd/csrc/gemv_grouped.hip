@@ -372,7 +372,7 @@ template <bool OUT_F16, int XDT, bool NT, int LG = 32>
 static int launch_grouped_nt(const GroupedArgs& a, int blocks, size_t lds, hipStream_t st)
 {
     auto launch = [&](auto kernel) {
-        enqueue(kernel, blocks, GG_THREADS, lds, st, 
+        enqueue(kernel, blocks, GG_THREADS, lds, st,
             static_cast<const uint4*>(a.packed), static_cast<const uint4*>(a.codebook), a.N, a.K, a.xraw,
             static_cast<const uint4*>(a.xq), static_cast<const uint16_t*>(a.scale), a.clip_ratio, blocks, a.out, a.P,
             static_cast<uint32_t*>(a.xq_out), static_cast<uint16_t*>(a.scale_out));

@@ -263,7 +263,7 @@ static int launch_oneshot_one(const void* packed, const void* codebook, int N, i
     const size_t lds = static_cast<size_t>(UPL) * 64 * 8 + 2 * ONE_WAVES * sizeof(int);
     const int blocks = (N / 4 + ONE_WAVES - 1) / ONE_WAVES;
     auto launch = [&](auto kernel) {
-        enqueue(kernel, blocks, ONE_WAVES * 64, lds, st, 
+        enqueue(kernel, blocks, ONE_WAVES * 64, lds, st,
             static_cast<const uint4*>(packed), static_cast<const uint2*>(codebook), N, K, x, static_cast<const uint16_t*>(scale),
             out_dt == RCP_F16 ? 1 : 0, clip_ratio, out, P, static_cast<uint32_t*>(xq_out), static_cast<uint16_t*>(scale_out));
     };
