@@ -469,10 +469,15 @@ constexpr float FP8_INT_UNIT = 512.0f;  // takes the 2^-9 out again,
 constexpr int FP8_INT_SCALE = 0x88;     // as an E8M0 scale
 
 // ---- the int4 quantiser (shared by the activation kernels and the fused GEMV prologue) ----
-// S = fp16((ratio * a) / 7); 1 when that is zero, capped at the largest finite half.
+// S = fp16((ratio * a) / 7); 1 when that is zero, capped at the largest finite half.  The quotient by 7 is the correctly rounded
+// one without a division (a chain of ten instructions that every wavefront waits for): the residual p - 7 q0 of q0 = p RN(1/7) is
+// exact, and q0 plus its seventh misses p / 7 by less than 2^-21 units in the last place, while no quotient by 7 comes nearer than
+// 2^-4 units to the midpoint of two floats.  An infinite p leaves NaN, which is capped like an infinity; below 2^-120 the half is 0.
 __device__ __forceinline__ uint16_t scale_bits_from_amax(float a, float clip_ratio)
 {
-    const float raw = __fdiv_rn(__fmul_rn(clip_ratio, a), 7.0f);
+    const float p = __fmul_rn(clip_ratio, a), seventh = 0.142857149243354797363f;
+    const float q0 = __fmul_rn(p, seventh);
+    const float raw = __fmaf_rn(__fmaf_rn(-q0, 7.0f, p), seventh, q0);
     uint16_t b = __half_as_ushort(__float2half_rn(raw));
     if ((b & 0x7fffu) == 0) b = 0x3c00u;
     if ((b & 0x7fffu) >= 0x7c00u) b = 0x7bffu;
@@ -481,9 +486,10 @@ __device__ __forceinline__ uint16_t scale_bits_from_amax(float a, float clip_rat
 
 // Eight values -> one dword of int4: nibble j = clamp(rint(y[j] / s), -8, 7), where y/s is
 // the correctly rounded binary32 quotient.  t = y * (1/s) carries two roundings, the quotient
-// one: for |t| <= 16.5 the two differ by less than 3e-6, so rint(t) is already the answer
-// unless t sits within 1e-5 of a rounding boundary n + 1/2 (beyond 16 both clamp to the same
-// end); in that rare case the eight values are redone with the IEEE division.
+// one, and 1/s may be off by a unit in the last place: for |t| <= 16.5 the two differ by less
+// than 5e-6, so rint(t) is already the answer unless t sits within 1e-5 of a rounding boundary
+// n + 1/2 (beyond 16 both clamp to the same end); in that rare case the eight values are redone
+// with the IEEE division.
 // The clamped integers r_j are packed four at a time in binary32, where
 // sum_j (r_j + 8) * 16^j < 2^16 is exact, and the offset-binary nibbles become two's
 // complement by flipping each nibble's top bit.
@@ -515,24 +521,31 @@ __device__ __forceinline__ uint32_t quantize8_fast(const float (&y)[8], float rs
     return pack8_int4(n);
 }
 
+// 1 / s up to a unit in the last place, which is all that the forms below need (the correctly rounded one is ten instructions)
+__device__ __forceinline__ float quant_reciprocal(float s) { return __builtin_amdgcn_rcpf(s); }
+
 // For y that holds fp16 or bf16 numbers as they came from memory (no rotation in between): no second pass at all.  With
 // at most 11 significant bits in y and in the fp16 scale, the exact quotient y/s is either exactly a half-integer k + 1/2
 // or at least 2^-13 away from every one of them up to 16.5 ((2 m_y 2^e - (2k+1) m_s) / (2 m_s) with integers m < 2^11 is
-// zero or at least that large).  One Newton step on the quotient, q1 = q0 + (y - q0 s) (1/s) with the residual taken
-// exactly by a fused multiply-add, lands on k + 1/2 itself in the first case (the residual's share of the error of 1/s is
-// far below half a unit in the last place), where rint breaks the tie to even exactly like the correctly rounded
-// quotient would; in the second case q1 and the correctly rounded quotient are both within 2e-6 of the exact one and on
-// the same side of every boundary.  Beyond 16.5 both clamp to the same end.
-__device__ __forceinline__ uint32_t quantize8_short(const float (&y)[8], float s, float rs)
+// zero or at least that large).  y (1/s) + 1536, rounded once, is a multiple of 2^-13: it misses the exact quotient by less than
+// 2^-18 before that rounding, so a half-integer quotient lands on itself and any other one stays on its side of every
+// half-integer.  The second addition rounds that to an integer, ties to even as the correctly rounded quotient would, and leaves
+// n + 8 in the low bits of the float (beyond 16.5 both clamp to the same end; NaN takes the lower one), which are put together as
+// integers.  32 vector instructions for eight values instead of 52 with a Newton step on the quotient and the codes packed in
+// binary32: what a token costs a SIMD before its first product.
+__device__ __forceinline__ uint32_t quantize8_short(const float (&y)[8], float rs)
 {
-    float n[8];
+    uint32_t w[8];
 #pragma unroll
     for (int j = 0; j < 8; ++j) {
-        const float q0 = __fmul_rn(y[j], rs);
-        const float q1 = __fmaf_rn(__fmaf_rn(-q0, s, y[j]), rs, q0);
-        n[j] = rintf(q1);
+        const float snapped = __fmaf_rn(y[j], rs, 1536.0f);
+        const float code = __fadd_rn(snapped, 12582912.0f - 1536.0f + 8.0f);
+        w[j] = __float_as_uint(__builtin_amdgcn_fmed3f(code, 12582912.0f, 12582912.0f + 15.0f));
     }
-    return pack8_int4(n);
+    // the upper bits of the floats end up above bit 15 of the sums of four codes
+    const uint32_t lo = (((w[3] << 4) + w[2]) << 8) + ((w[1] << 4) + w[0]);
+    const uint32_t hi = (((w[7] << 4) + w[6]) << 8) + ((w[5] << 4) + w[4]);
+    return __builtin_amdgcn_perm(hi, lo, 0x05040100u) ^ 0x88888888u;
 }
 
 __device__ __forceinline__ uint32_t quantize8_exact(const float (&y)[8], float s)
@@ -545,7 +558,7 @@ __device__ __forceinline__ uint32_t quantize8_exact(const float (&y)[8], float s
 
 __device__ __forceinline__ uint32_t quantize8(const float (&y)[8], float s)
 {
-    const float rs = __frcp_rn(s);
+    const float rs = quant_reciprocal(s);
     float n[8];
     float far = 0.0f;  // largest distance of a t from its rounded value (one maximum instead of eight tests)
 #pragma unroll

@@ -1253,3 +1253,28 @@ def test_full_size_grouped_and_weight_only_as_benchmarked():
     ref = oracle.w2a16_gemv(rp, rc, N, K, x.astype(np.float64))[0]
     g16 = o16.cpu().numpy().astype(np.float64).ravel()
     assert np.linalg.norm(g16 - ref) <= 1e-3 * np.linalg.norm(ref)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("dtype", [torch.float16, torch.bfloat16])
+def test_codes_of_16_bit_values_round_like_the_quotient(dtype):
+    """rint(y / S) clamped, S the rounded seventh of the maximum: arbitrary mantissas of the exponents that matter, ties among them."""
+    M, K = 16, 8192
+    g = torch.Generator().manual_seed(13)
+    top = torch.exp2(torch.linspace(-10, 9, M)).unsqueeze(1)
+    mantissa = 1 + torch.randint(0, 1024 if dtype == torch.float16 else 128, (M, K), generator=g) / (1024 if dtype == torch.float16 else 128)
+    x = (top * mantissa * torch.exp2(-torch.randint(1, 6, (M, K), generator=g).float()) * (2 * torch.randint(0, 2, (M, K), generator=g) - 1)).to(dtype)
+    x[:, 5] = (2 * top[:, 0]).to(dtype)                                        # the maximum
+    half = (torch.arange(-16, 17) / 2).repeat(K // 32)[:K // 2]
+    S = np.float16(np.float32(x[:, 5].float().numpy()) / np.float32(7.0)).astype(np.float32)
+    x[:, K // 2:] = (torch.from_numpy(S).unsqueeze(1) * half).to(dtype)        # half-integer quotients as near as the type has them
+    x[:, 5] = (2 * top[:, 0]).to(dtype)
+    xq, scale = rcp.rotate_quant_act(x.cuda(), None, 1.0)
+    x32 = x.float().numpy()
+    S = np.float16(np.abs(x32).max(axis=1) / np.float32(7.0)).astype(np.float32)
+    assert np.array_equal(scale.float().cpu().numpy(), S)
+    want = np.clip(np.rint((x32 / S[:, None]).astype(np.float32)), -8, 7).astype(np.int32)
+    byte = xq.cpu().numpy().reshape(M, K // 2).astype(np.int32)
+    got = np.stack([byte & 15, byte >> 4], axis=2).reshape(M, K)
+    assert np.array_equal((got + 8) % 16 - 8, want)
+    assert np.count_nonzero(np.abs(x32.astype(np.float64) / S[:, None] % 1) == 0.5) > 100

@@ -80,3 +80,46 @@ def test_plain_reciprocal_product_does_not_round_like_the_division():
         plain = np.clip(np.rint((y * rs).astype(np.float32)), -8, 7).astype(np.int32)
         wrong += int(np.count_nonzero(plain != _definition(y, s)))
     assert wrong > 0
+
+
+# ---- the form without the Newton step: y (1/S) + 1536 snaps to a multiple of 2^-13, a second addition rounds it to an integer ----
+def _snapped(y, rs):
+    v = _fma32(y, np.float32(rs), np.float32(1536.0))
+    code = (v + np.float32(12582912.0 - 1536.0 + 8.0)).astype(np.float32)
+    return (np.clip(code, np.float32(12582912.0), np.float32(12582927.0)) - np.float32(12582920.0)).astype(np.int32)
+
+
+def _reciprocals(s):
+    rs = np.float32(1.0) / np.float32(s)
+    return rs, np.nextafter(rs, np.float32(0.0), dtype=np.float32), np.nextafter(rs, np.float32(np.inf), dtype=np.float32)
+
+
+def test_snapped_quotient_rounds_like_the_division_for_every_fp16_input():
+    y_all = np.arange(0x10000, dtype=np.uint32).astype(np.uint16).view(np.float16)
+    y = y_all[np.isfinite(y_all)].astype(np.float32)
+    for s in _scales():
+        for rs in _reciprocals(s):
+            got, want = _snapped(y, rs), _definition(y, s)
+            assert np.array_equal(got, want), (float(s), y[got != want][:4])
+
+
+def test_snapped_quotient_rounds_like_the_division_for_bf16_inputs():
+    hi = np.arange(0x3000, 0x4A00, dtype=np.uint32)
+    y = (np.concatenate([hi, hi | 0x8000]) << 16).view(np.float32)
+    for s in _scales():
+        for rs in _reciprocals(s):
+            got, want = _snapped(y, rs), _definition(y, s)
+            assert np.array_equal(got, want), (float(s), y[got != want][:4])
+
+
+def test_the_scale_is_the_rounded_quotient_by_seven():
+    rng = np.random.default_rng(3)
+    p = np.concatenate([rng.integers(0x00800000, 0x7F800000, size=400000), np.arange(0x3F800000, 0x40800000, 37),
+                        np.array([0x7F7FFFFF, 0x477FE000, 0x33800000, 0x00800000])]).astype(np.uint32).view(np.float32)
+    with np.errstate(under="ignore"):
+        seventh = np.float32(0.142857149243354797363)
+        q0 = (p * seventh).astype(np.float32)
+        raw = _fma32(_fma32(-q0, np.float32(7.0), p), seventh, q0)
+        want = (p / np.float32(7.0)).astype(np.float32)
+    big = p >= np.float32(2.0 ** -110)
+    assert np.array_equal(raw[big], want[big]) and np.all(np.abs(raw[~big]) < 2.0 ** -100)
