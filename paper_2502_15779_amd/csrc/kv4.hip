@@ -624,10 +624,10 @@ __global__ __launch_bounds__(KV_THREADS) void kv4_attn_kernel(const void* __rest
 //            come back transposed by ds_read_b64_tr_b4 (16 tokens of one element per lane); the 16-byte pieces of a
 //            token are permuted by the token's position so that sixteen rows fall into different banks
 // Between the two a lane holds the scores of its token(s) for up to four heads; the weights pass through LDS.
-// What bounds it, by the counters of 16 sequences of 300 to 6000 tokens, 32 over 8 heads (22.7 us for 9.6 us of bytes): no
-// unit.  A SIMD holds 1.1 wavefronts on average, its vector unit issues in 34 % of the cycles and its matrix unit is busy in
-// 12 %; a wavefront spends a third of its life waiting for memory or LDS and 28 % for its own previous instructions.  The
-// workgroups are too few and too unequal to hide the chain of one chunk.
+// What bounds it, by the counters of 16 sequences of 300 to 6000 tokens, 32 over 8 heads (18.4 us by the trace for 9.6 us of bytes,
+// 22.5 with fixed splits and workgroups without tokens): no unit.  A SIMD holds 1.3 wavefronts on average, its vector unit issues
+// in 41 % of the cycles and its matrix unit is busy in 15 %; a wavefront spends a third of its life waiting for memory or
+// LDS and 27 % for its own previous instructions: the chain of one chunk, which too few wavefronts hide.
 // RP: query heads per cache head, rounded up to a power of two.
 // Registers: four wavefronts a SIMD for one and two heads (124 and 128 registers; left at 130, 120000 tokens of 16 over 8
 // heads take 34.3 us instead of 31.6), three for the others.

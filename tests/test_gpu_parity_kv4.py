@@ -196,7 +196,7 @@ def test_attention_matches_oracle(H_q, H_kv, S, S_max, q_dtype):
 @pytest.mark.parametrize("H_q,H_kv,S", [(4, 4, 1), (4, 2, 130), (8, 8, 1000), (2, 1, 3333), (2, 2, 17), (1, 1, 2049), (2, 1, 5000)])
 @pytest.mark.parametrize("q_dtype", ["f16", "f32", "bf16"])
 def test_attention_every_split_length(tokens, H_q, H_kv, S, q_dtype):
-    # every (query type, tokens per workgroup) instantiation of the per-split and of the streaming kernel
+    # every (query type, tokens per workgroup) instantiation of the per-split kernel, and the matrix-core form on longer splits
     _say(f"kv4 attn tokens/workgroup={tokens} H_q={H_q} H_kv={H_kv} S={S} {q_dtype}")
     cache = _build_cache(11, S, H_kv, S + 3)
     qd, q32 = _as_dtype(rcp_synth.query_vectors(11, f"q{H_q}", H_q), q_dtype)

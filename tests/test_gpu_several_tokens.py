@@ -153,9 +153,9 @@ def _attention_of_heads(q64, lengths, host, scale, heads, B, H_kv):
 
 
 @pytest.mark.parametrize("H,lengths", [
-    (32, [4095]), (32, [4097]),      # all loads at once up to here, the streaming form from here on
-    (32, [8192]), (5, [52500]),      # splits of 512 and of 1024 tokens
-    (8, [81900]), (8, [81920]),      # the last of the streaming form and the first of the matrix-core form
+    (32, [4095]), (32, [4097]),      # all loads at once up to here, the matrix-core form from here on
+    (32, [8192]), (5, [52500]),      # a power of two of tokens; an odd number of heads
+    (8, [81900]), (8, [81920]),      # splits of the most tokens, the last one not full and full
     (16, [600, 4000, 1, 2900, 1500]),
 ])
 @pytest.mark.parametrize("q_dtype", [torch.float16, torch.float32, torch.bfloat16])
