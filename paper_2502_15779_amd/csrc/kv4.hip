@@ -1197,8 +1197,9 @@ int launch_kv4_attn(const void* q, rcp_dtype q_dt, int B, int H_q, int H_kv, int
     // 8.4 / 8.6), with more or one at 131072 (3000 of 32 over 4 9.5 / 9.7, 4001 of 32 with the query's rotation 10.4 / 10.5 and
     // 5 % more of a decode step).
     // One query head a cache head had a third, streaming form up to 20480 x 32 pairs (streaming / matrix: 5000 tokens of 32
-    // heads 12.8 / 12.0, 12000 18.4 / 16.5, 9 sequences of 11368 in all 22.0 / 18.2; 6500 to 8200 tokens, the one stretch where it was
-    // ahead, 13.2 / 13.6).  The option asks for the matrix-core form at every size.
+    // heads 12.8 / 12.0, 12000 18.4 / 16.5, 9 sequences of 11368 in all 22.0 / 18.2, 16 of 1024 19.6 / 18.7).  It was ahead only where its 512
+    // tokens a split filled every unit once or twice: 6500 to 8200 tokens 12.5 / 12.8, 8 sequences of 1024 12.3 / 12.7, 4 of 2048 12.5 / 13.1;
+    // its error is 7.6e-7 to 1.2e-6 there, the matrix form's 3e-7.  The option asks for the matrix-core form at every size.
     batch.H_q = H_q;
     batch.H_kv = H_kv;
     if (!batched) batch.v[0] = S;
