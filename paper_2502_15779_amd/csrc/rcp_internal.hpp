@@ -469,16 +469,19 @@ constexpr float FP8_INT_UNIT = 512.0f;  // takes the 2^-9 out again,
 constexpr int FP8_INT_SCALE = 0x88;     // as an E8M0 scale
 
 // ---- the int4 quantiser (shared by the activation kernels and the fused GEMV prologue) ----
-// S = fp16((ratio * a) / 7); 1 when that is zero, capped at the largest finite half.  The quotient by 7 is the correctly rounded
-// one without a division (a chain of ten instructions that every wavefront waits for): the residual p - 7 q0 of q0 = p RN(1/7) is
-// exact, and q0 plus its seventh misses p / 7 by less than 2^-21 units in the last place, while no quotient by 7 comes nearer than
-// 2^-4 units to the midpoint of two floats.  An infinite p leaves NaN, which is capped like an infinity; below 2^-120 the half is 0.
+// S = fp16((ratio * a) / 7), product and quotient rounded to binary32 first; 1 when that is zero, capped at the largest finite half.
+// The quotient by 7 is the correctly rounded one without a division (a chain of ten instructions that every wavefront waits for), by
+// the textbook correction with an exact residual: p - 7 q0 of q0 = p RN(1/7) is exact, and q0 plus its seventh misses p / 7 by less
+// than 2^-21 units in the last place, while no quotient by 7 comes nearer than 2^-4 units to the midpoint of two floats.  It is a
+// number of its own before it becomes a half (round_to_half): converted by the multiply-add itself it would be rounded once, and
+// quotients that binary32 puts on the midpoint of two halves would go to the other one.  An infinite p leaves NaN, which is capped
+// like an infinity; below 2^-120 the half is 0.
 __device__ __forceinline__ uint16_t scale_bits_from_amax(float a, float clip_ratio)
 {
     const float p = __fmul_rn(clip_ratio, a), seventh = 0.142857149243354797363f;
     const float q0 = __fmul_rn(p, seventh);
     const float raw = __fmaf_rn(__fmaf_rn(-q0, 7.0f, p), seventh, q0);
-    uint16_t b = __half_as_ushort(__float2half_rn(raw));
+    uint16_t b = __half_as_ushort(round_to_half(raw));
     if ((b & 0x7fffu) == 0) b = 0x3c00u;
     if ((b & 0x7fffu) >= 0x7c00u) b = 0x7bffu;
     return b;

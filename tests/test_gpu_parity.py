@@ -1278,3 +1278,76 @@ def test_codes_of_16_bit_values_round_like_the_quotient(dtype):
     got = np.stack([byte & 15, byte >> 4], axis=2).reshape(M, K)
     assert np.array_equal((got + 8) % 16 - 8, want)
     assert np.count_nonzero(np.abs(x32.astype(np.float64) / S[:, None] % 1) == 0.5) > 100
+
+
+def _maxima_beside_midpoints_of_halves():
+    """(clip ratio, binary32 maxima): the binary32 quotient of the product by 7 is the midpoint of two halves.  Of the fp16 maxima those
+    with a subnormal scale."""
+    ties = (7.0 * np.arange(2049, 4096, 2) / 2048.0).astype(np.float32)
+    known = np.array([0x3FC34A00], np.uint32).view(np.float32)
+    halves = np.arange(1, 0x7C00, dtype=np.uint16).view(np.float16).astype(np.float32)
+    raw = ((np.float32(0.9) * halves).astype(np.float32) / np.float32(7.0)).astype(np.float64)
+    small = halves[(raw < 2.0 ** -14) & (raw * 2.0 ** 24 % 1.0 == 0.5)]
+    assert small.size > 10
+    return [(1.0, np.concatenate([known, ties])), (0.9, np.concatenate([np.array([0x3FDD5CE4], np.uint32).view(np.float32), small]))]
+
+
+@pytest.mark.parametrize("rotation", ["none", "wht", "wht_large", "heads"])
+def test_scales_whose_quotient_is_a_midpoint_of_two_halves(rotation):
+    """Every quantiser with a launch of its own: S is the half of the binary32 quotient, with the ties that this brings."""
+    _say(f"scales on midpoints of halves, rotation={rotation}")
+    K, rot, gain = {"none": (64, None, 1.0), "wht": (256, rcp.Rotation.wht(256), 16.0), "wht_large": (16384, rcp.Rotation.wht(16384), 128.0),
+                    "heads": (1024, rcp.Rotation.heads(16, 64), 4.0)}[rotation]
+    for clip, maxima in _maxima_beside_midpoints_of_halves():
+        if K > 1024:
+            maxima = maxima[::8]
+        for at in range(0, maxima.size, 16):
+            a = maxima[at:at + 16]
+            x = np.zeros((a.size, K), np.float32)
+            x[:, 0] = gain * a                       # the rotation spreads it evenly, a power of two smaller
+            xq, scale = rcp.rotate_quant_act(_t(x), rot, clip)
+            y = x if rot is None else np.repeat(a[:, None], K, axis=1)
+            if rotation == "heads":
+                y[:, np.arange(K) % 64 != 0] = 0.0   # across the heads only
+            ref_xq, ref_scale, _ = oracle.quantize_act(y, clip)
+            assert np.array_equal(scale.cpu().numpy().view(np.uint16), ref_scale), (clip, at)
+            assert np.array_equal(xq.cpu().numpy(), ref_xq), (clip, at)
+
+
+@pytest.mark.parametrize("path", ["general", "oneshot", "eight", "wht", "grouped", "w3", "sequence"])
+def test_fused_scales_whose_quotient_is_a_midpoint_of_two_halves(path):
+    """The same in the prologue of every fused call."""
+    N, K = 64, 2048
+    _say(f"fused scales on midpoints of halves, {path}")
+    rcp.set_option("gemv_oneshot", 1 if path == "oneshot" else 2)
+    rcp.set_option("gemv_waves", 8 if path == "eight" else 0)
+    pk = torch.randint(0, 256, ((3 * N * K // 8) if path == "w3" else N * K // 4,), dtype=torch.uint8, device=DEV)
+    levels = {"w3": (N, 8), "grouped": (N // 4, K // 128, 4, 4)}.get(path, (N, 4))
+    cb = _t(np.sort(np.random.default_rng(5).standard_normal(levels) * 0.03, axis=-1).astype(np.float16))
+    xq = torch.zeros((1, K // 2), dtype=torch.uint8, device=DEV)
+    sc = torch.zeros((1,), dtype=torch.float16, device=DEV)
+    for clip, maxima in _maxima_beside_midpoints_of_halves():
+        for a in maxima[::32] if clip == 1.0 else maxima:
+            x = np.zeros((1, K), np.float32)
+            x[0, 3:9] = a * np.array([0.25, -0.5, 1.0, -1.0, 0.75, 0.1], np.float32)
+            y = x
+            if path == "wht":
+                x = np.zeros((1, 1024), np.float32)
+                x[0, 0], y = 32.0 * a, np.full((1, 1024), a, np.float32)
+            xd = _t(x)
+            if path in ("general", "oneshot", "eight"):
+                rcp.quant_w2a4_gemv(pk, cb, N, K, xd, clip, xq_out=xq, scale_out=sc)
+            elif path == "wht":
+                xq = torch.zeros((1, 512), dtype=torch.uint8, device=DEV)
+                rcp.rotate_quant_w2a4_gemv(pk[:N * 256], cb, N, 1024, xd, rcp.Rotation.wht(1024), clip, xq_out=xq, scale_out=sc)
+            elif path == "grouped":
+                rcp.quant_w2a4_gemv_grouped(pk, cb, N, K, xd, clip, xq_out=xq, scale_out=sc)
+            elif path == "w3":
+                rcp.quant_w3a4_gemv(pk, cb, N, K, xd, clip, xq_out=xq, scale_out=sc)
+            else:
+                steps = [rcp.GemvStep(pk, cb, N, K, xd, torch.empty((1, N), dtype=torch.float16, device=DEV), clip_ratio=clip, xq_out=xq,
+                                      scale_out=sc)]
+                rcp.quant_w2a4_gemv_sequence(steps, rcp.gemv_sequence_workspace(steps))
+            ref_xq, ref_scale, _ = oracle.quantize_act(y, clip)
+            assert np.array_equal(sc.cpu().numpy().view(np.uint16), ref_scale), (clip, a)
+            assert np.array_equal(xq.cpu().numpy().ravel(), ref_xq.ravel()), (clip, a)

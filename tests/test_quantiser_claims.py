@@ -8,8 +8,14 @@ a reciprocal that is off by one unit in the last place does not change that.  Th
 numpy on every finite fp16 input (and a dense sample of bf16 inputs) for several hundred scales.  The fused multiply-adds
 are evaluated in binary64, where the products and the first sum are exact.
 """
+import os
+import subprocess
+
 import numpy as np
 import pytest
+
+import oracle
+from paper_2502_15779_amd import _build
 
 
 def _fma32(a, b, c):
@@ -123,3 +129,36 @@ def test_the_scale_is_the_rounded_quotient_by_seven():
         want = (p / np.float32(7.0)).astype(np.float32)
     big = p >= np.float32(2.0 ** -110)
     assert np.array_equal(raw[big], want[big]) and np.all(np.abs(raw[~big]) < 2.0 ** -100)
+
+
+def _quotients_on_midpoints_of_halves():
+    """Binary32 maxima 7 m / 2048, m odd: their seventh is exactly half way between two halves (eleven bits and one)."""
+    return (7.0 * np.arange(2049, 4096, 2) / 2048.0).astype(np.float32)
+
+
+def test_the_scale_is_the_half_of_the_binary32_quotient():
+    """Product, quotient and half are rounded one after the other, as the oracle does; rounding the quotient to a half in one step
+    gives other scales, so a compiled kernel must not merge the two."""
+    known = [(1.0, 0x3FC34A00, 0x32FA), (0.9, 0x3FDD5CE4, 0x331E)]
+    for clip, bits, half in known:
+        a = np.array([bits], np.uint32).view(np.float32)
+        assert oracle.quantize_act(np.repeat(a, 32).reshape(1, 32), clip)[1][0] == half
+    a = _quotients_on_midpoints_of_halves()
+    scale = oracle.quantize_act(np.repeat(a[:, None], 32, axis=1), 1.0)[1]
+    assert np.array_equal(scale, (a / np.float32(7.0)).astype(np.float32).astype(np.float16).view(np.uint16))
+    seventh = np.float32(0.142857149243354797363)
+    q0 = (a * seventh).astype(np.float32)
+    once = (_fma32(-q0, np.float32(7.0), a).astype(np.float64) * np.float64(seventh) + q0).astype(np.float16).view(np.uint16)
+    assert np.count_nonzero(once != scale) > 100
+
+
+def test_the_compiled_scale_is_rounded_to_binary32_before_the_half(tmp_path):
+    src = tmp_path / "scale.hip"
+    src.write_text('#include "rcp_internal.hpp"\n'
+                   "__global__ void scale(const float* a, float clip, uint16_t* s)\n"
+                   "{ s[threadIdx.x] = rcp::scale_bits_from_amax(a[threadIdx.x], clip); }\n")
+    cmd = [os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")] + _build.COMPILE_FLAGS
+    cmd += ["-I", os.path.join(_build.ROOT, "include"), "-I", _build.CSRC, "--cuda-device-only", "-S", str(src), "-o", str(tmp_path / "scale.s")]
+    subprocess.run(cmd, check=True, capture_output=True)
+    text = (tmp_path / "scale.s").read_text()
+    assert "v_cvt_f16_f32" in text and "mixlo" not in text and "mixhi" not in text
