@@ -219,7 +219,6 @@ __global__ __launch_bounds__(256) void kv4_append_kv_kernel(const void* __restri
 // the 16 bytes, byte b, nibble e): the order in which the nibbles come out of two masks.
 // ---------------------------------------------------------------------------------------
 constexpr int KV_THREADS = 256;
-constexpr int KV_MAX_L = 256;          // tokens per workgroup at most: four per lane group, all loads in flight at once
 constexpr int KV_PART = KV_D + 4;      // floats per partial result: acc[128], m, l, 2 unused
 
 // The four low nibbles and the four high nibbles of a dword as bytes.  The empty asm keeps the
@@ -1179,37 +1178,26 @@ int launch_kv4_attn(const void* q, rcp_dtype q_dt, int B, int H_q, int H_kv, int
     const bool batched = lengths != nullptr;
     const bool fused = !batched && rotate_q;
     KvBatch batch = {};
-    long long total = S;
     if (batched) {
         S = 0;
-        total = 0;
         for (int b = 0; b < B; ++b) {
             batch.v[b] = lengths[b];
             S = lengths[b] > S ? lengths[b] : S;  // the longest sequence sizes the grid
-            total += lengths[b];
         }
     }
-    // The form that issues all loads at once for small calls, 128 tokens per workgroup and from 2048 x 32 (token, query head) pairs on
-    // 256, else the matrix-core form on splits of the length that kv_split_tokens finds.  Where they meet (us, all at once / matrix):
-    // a batch at 40960 pairs, ragged ones gain most because workgroups without tokens delay the first form (16 sequences, 1661 tokens
-    // of 64 over 16 heads 13.1 / 9.0, 8 of 2250 of 32 over 8 9.5 / 8.9; below, 8 of 1183 8.5 / 8.6); one sequence with two to four
-    // query heads a cache head at 65536 (3000 tokens of 32 over 16 9.7 / 9.1, of 32 over 8 9.4 / 9.4; below, 929 of 64 over 16
-    // 8.4 / 8.6), with more or one at 131072 (3000 of 32 over 4 9.5 / 9.7, 4001 of 32 with the query's rotation 10.4 / 10.5 and
-    // 5 % more of a decode step).
     // One query head a cache head had a third, streaming form up to 20480 x 32 pairs (streaming / matrix: 5000 tokens of 32
     // heads 12.8 / 12.0, 12000 18.4 / 16.5, 9 sequences of 11368 in all 22.0 / 18.2, 16 of 1024 19.6 / 18.7).  It was ahead only where its 512
     // tokens a split filled every unit once or twice: 6500 to 8200 tokens 12.5 / 12.8, 8 sequences of 1024 12.3 / 12.7, 4 of 2048 12.5 / 13.1;
-    // its error is 7.6e-7 to 1.2e-6 there, the matrix form's 3e-7.  The option asks for the matrix-core form at every size.
+    // its error is 7.6e-7 to 1.2e-6 there, the matrix form's 3e-7.
     batch.H_q = H_q;
     batch.H_kv = H_kv;
     if (!batched) batch.v[0] = S;
     const unsigned nseq = static_cast<unsigned>(batched ? B : 1);
     batch.n = static_cast<int>(nseq);
     const int rep = H_q / H_kv, per = (rep + 15) / 16;  // sixteen query heads at most per workgroup of the matrix-core form
-    int L = options().kv_tokens;
-    const bool matrix = L == 0 ? total * H_q >= (batched ? 40960 : rep == 1 || rep > 4 ? 131072 : 65536) : L > KV_MAX_L;
-    if (matrix && L == 0) L = kv_split_tokens(batch.v, static_cast<int>(nseq), H_kv * per, num_compute_units());
-    if (L == 0) L = total * H_q < 65536 ? 128 : KV_MAX_L;
+    const KvPlan plan = kv_plan(batch.v, static_cast<int>(nseq), batched, H_q, H_kv, num_compute_units(), options().kv_tokens);
+    const bool matrix = plan.form == KvForm::matrix;
+    const int L = plan.tokens;
     const int splits = (S + L - 1) / L;
     auto* kc = static_cast<const u32x4*>(k_codes);
     auto* vc = static_cast<const u32x4*>(v_codes);
@@ -1241,9 +1229,7 @@ int launch_kv4_attn(const void* q, rcp_dtype q_dt, int B, int H_q, int H_kv, int
         if (compact) form(std::true_type{});
         else form(std::false_type{});
     } else {
-        // one index per (split, query head), padded to whole groups of 8 * rep (see kv_place)
-        const unsigned units = static_cast<unsigned>(splits) * static_cast<unsigned>(H_kv);
-        const dim3 grid(8u * static_cast<unsigned>(rep) * ((units + 7u) / 8u), 1u, nseq);
+        const dim3 grid(static_cast<unsigned>(kv_at_once_groups(splits, rep, H_kv)), 1u, nseq);
         auto launch = [&](auto kernel) {
             enqueue(kernel, grid, KV_THREADS, 0, st, q, S, S_max, rep, splits, softmax_scale, kc, kp, vc, vp, part, batch);
         };

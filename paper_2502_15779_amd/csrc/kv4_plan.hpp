@@ -1,4 +1,5 @@
-// The matrix-core attention's rule from the lengths of a call to the split length.  Plain C++, no HIP: a host program can walk it.
+// The attention's rules from the lengths and heads of a call to the form of the kernel and its split length.  Plain C++, no HIP: a
+// host program can walk them.
 #pragma once
 
 namespace rcp {
@@ -42,6 +43,58 @@ inline int kv_split_tokens(const int* lengths, int n, int heads, int cus)
         if (c * KV_BLOCK >= longest) break;
     }
     return best * KV_BLOCK;
+}
+
+enum class KvForm { at_once, matrix };
+struct KvPlan {
+    KvForm form;
+    int tokens;  // of a workgroup
+};
+constexpr int KV_MAX_L = 256;  // tokens of a workgroup of the form that issues all loads at once, at most: four per lane group
+
+// workgroups of that form for one sequence: an index per (split, query head), padded to whole groups of 8 * rep (kv_place)
+inline long long kv_at_once_groups(int splits, int rep, int H_kv) { return 8LL * rep * ((static_cast<long long>(splits) * H_kv + 7) / 8); }
+
+// forced: the "kv_tokens" option, 0 = automatic; more than KV_MAX_L asks for the matrix-core form.
+// The form that issues all loads at once for small calls, 128 tokens per workgroup and from 2048 x 32 (token, query head) pairs on
+// 256, else the matrix-core form on splits of the length that kv_split_tokens finds.  Where they meet (us, all at once / matrix):
+//   one sequence   with two to four query heads a cache head at 65536 pairs (3000 tokens of 32 over 16 9.7 / 9.1, of 32 over 8 9.4 /
+//                  9.4; below, 929 of 64 over 16 8.4 / 8.6), with more or one at 131072 (3000 of 32 over 4 9.5 / 9.7, 4001 of 32 with
+//                  the query's rotation 10.4 / 10.5 and 5 % more of a decode step)
+//   a batch        from 40960 pairs on (below, 8 sequences of 1183 tokens in all, 32 over 8 heads, 8.5 / 8.6), as soon as the first form has more
+//                  than two workgroups a unit, those without tokens and the padding of its grid among them, which ragged and short
+//                  sequences have most of (16 sequences of 1618 tokens, 32 over 4 heads, 11.4 / 8.8; of 1489, 32 heads, 11.5 / 9.5; 12 of 1248, 48
+//                  over 8, 10.1 / 8.6).  Up to two it depends on the query heads a cache head (230 drawn batches):
+//                  more than eight: all at once up to 131072 pairs (2 of 936 tokens, 64 over 4 heads, 8.3 / 10.2; of 1406 9.2 / 10.3)
+//                  five to eight:   all at once up to 65536 (4 of 1872, 32 over 4, 8.4 / 9.2; of 2812 9.5 / 9.1)
+//                  three or four:   all at once up to 65536 where a sequence is longer than a workgroup of the matrix-core form
+//                                   (4 of 1872, 32 over 8, 8.6 / 8.8; 16 of 1664 8.7 / 8.4)
+//                  two:             matrix-core form (2 of 1874, 32 over 16, 8.8 / 8.1)
+//                  one:             all at once up to 65536 where the matrix-core form, a workgroup for every head, has more than one a
+//                                   unit (16 of 1872, 32 heads, 9.1 / 9.6; 8 of 1872 8.9 / 8.5)
+inline KvPlan kv_plan(const int* lengths, int n, bool batched, int H_q, int H_kv, int cus, int forced)
+{
+    if (forced != 0) return {forced > KV_MAX_L ? KvForm::matrix : KvForm::at_once, forced};
+    const int rep = H_q / H_kv, heads = H_kv * ((rep + 15) / 16);  // sixteen query heads at most per workgroup of the matrix-core form
+    long long total = 0;
+    int longest = 0;
+    for (int b = 0; b < n; ++b) {
+        total += lengths[b];
+        longest = lengths[b] > longest ? lengths[b] : longest;
+    }
+    const long long pairs = total * H_q;
+    const int few = pairs < 65536 ? 128 : KV_MAX_L;
+    bool matrix;
+    if (pairs >= 131072) matrix = true;
+    else if (!batched) matrix = rep >= 2 && rep <= 4 && pairs >= 65536;
+    else if (pairs < 40960) matrix = false;
+    else if (n * kv_at_once_groups((longest + few - 1) / few, rep, H_kv) > 2 * cus) matrix = true;
+    else if (rep > 8) matrix = false;
+    else if (rep == 2 || pairs >= 65536) matrix = true;
+    else if (rep == 1) matrix = kv_workgroups(lengths, n, heads, KV_BLOCK) <= cus;
+    else matrix = rep <= 4 && longest <= KV_BLOCK;
+    if (!matrix) return {KvForm::at_once, few};
+    return {KvForm::matrix, kv_split_tokens(lengths, n, heads, cus)};
 }
 
 }  // namespace rcp

@@ -341,17 +341,22 @@ def test_a_row_of_a_ragged_batch_is_the_single_call(H_q, H_kv, lengths):
         assert torch.equal(out[b], rcp.kv4_attn_decode(q[b], S, *[a[b * H_kv:(b + 1) * H_kv] for a in pool], 0.0625)), (b, S)
 
 
-@pytest.mark.parametrize("H_q,H_kv,lengths", [(32, 8, [4100, 300, 1, 2048, 5000]), (64, 32, [1700, 900]), (32, 4, [5000]), (32, 8, [9000]),
-                                              (64, 16, [1000] * 15 + [17])])
+@pytest.mark.parametrize("H_q,H_kv,lengths", [
+    (32, 8, [4100, 300, 1, 2048, 5000]), (64, 32, [1700, 900]), (32, 4, [5000]), (32, 8, [9000]), (64, 16, [1000] * 15 + [17]),
+    (32, 8, [319] * 4), (32, 8, [340, 320, 310, 310]), (32, 32, [300] + [65] * 15), (32, 32, [117] * 16), (32, 32, [117] * 15 + [130]),
+    (64, 4, [480, 200]), (64, 4, [703, 1]), (64, 4, [1407, 1300]), (32, 4, [511, 512, 500, 500]), (32, 4, [512, 512, 512, 513]),   # around the
+    (8, 1, [1747, 1600, 1700, 1726]), (20, 10, [1200, 1100]), (32, 16, [2047]), (32, 16, [2049]), (16, 4, [4095]), (16, 4, [4097]),   # forms' meeting
+    (64, 8, [2047]), (64, 8, [2049])])                                                                                              # points
 def test_attention_on_automatic_splits(H_q, H_kv, lengths):
     """The split length that the lengths ask for, against the oracle on the first and the last sequence's first and last heads."""
     _say(f"kv4 automatic splits H_q={H_q} H_kv={H_kv} lengths={lengths[:5]}")
     B = len(lengths)
-    assert sum(lengths) * H_q >= 131072
     pool = _random_pool(7 * H_q + B, B * H_kv, max(lengths) + 3)
     q = torch.randn((B, H_q, D), generator=torch.Generator(device=DEV).manual_seed(H_kv), device=DEV)
     if B == 1:
         out = rcp.kv4_attn_decode(q[0], lengths[0], *pool, 0.0625).unsqueeze(0)
+        apart = rcp.kv4_attn_decode(rcp.rotate_act(q[0], rcp.Rotation.wht(D)), lengths[0], *pool, 0.0625)
+        assert torch.equal(rcp.kv4_rotate_attn_decode(q[0], lengths[0], *pool, 0.0625), apart)
     else:
         out = rcp.kv4_attn_decode_batched(q, lengths, *pool, 0.0625)
     got, q64, rep = out.cpu().numpy().astype(np.float64), q.cpu().numpy().astype(np.float64), H_q // H_kv

@@ -1,4 +1,5 @@
-"""The matrix-core attention's rule from the lengths of a call to the split length (csrc/kv4_plan.hpp), walked on the host."""
+"""The attention's rules from the lengths and heads of a call to the kernel's form and split length (csrc/kv4_plan.hpp), walked on the
+host."""
 import os
 import random
 import subprocess
@@ -24,17 +25,37 @@ int main()
 """
 
 
-@pytest.fixture(scope="module")
-def plan(tmp_path_factory):
-    d = tmp_path_factory.mktemp("plan")
-    (d / "plan.cpp").write_text(SOURCE)
+FORMS = r"""
+#include "kv4_plan.hpp"
+#include <cstdio>
+int main()
+{
+    int batched, H_q, H_kv, forced, n, lengths[16];
+    const char* names[] = {"at_once", "matrix"};
+    while (scanf("%d %d %d %d %d", &batched, &H_q, &H_kv, &forced, &n) == 5) {
+        for (int b = 0; b < n; ++b)
+            if (scanf("%d", lengths + b) != 1) return 1;
+        const rcp::KvPlan plan = rcp::kv_plan(lengths, n, batched != 0, H_q, H_kv, 256, forced);
+        printf("%s %d\n", names[static_cast<int>(plan.form)], plan.tokens);
+    }
+}
+"""
+
+
+def _compiled(d, source):
+    (d / "plan.cpp").write_text(source)
     exe = str(d / "plan")
     subprocess.run(["g++", "-O1", "-std=c++17", "-Wall", "-Werror", "-I", CSRC, str(d / "plan.cpp"), "-o", exe], check=True)
+    return lambda text: subprocess.run([exe], input=text, capture_output=True, text=True, check=True).stdout.split("\n")
+
+
+@pytest.fixture(scope="module")
+def plan(tmp_path_factory):
+    run = _compiled(tmp_path_factory.mktemp("plan"), SOURCE)
 
     def walk(calls):
         """[(heads, lengths)] -> [(tokens of a split, workgroups)]"""
-        text = "\n".join(" ".join(map(str, (heads, len(lengths)) + tuple(lengths))) for heads, lengths in calls)
-        lines = subprocess.run([exe], input=text, capture_output=True, text=True, check=True).stdout.split("\n")
+        lines = run("\n".join(" ".join(map(str, (heads, len(lengths)) + tuple(lengths))) for heads, lengths in calls))
         out = [tuple(int(v) for v in line.split()) for line in lines if line]
         assert len(out) == len(calls)
         return out
@@ -65,3 +86,45 @@ def test_no_other_split_leaves_the_fullest_unit_less(plan):
         for shorter in range(256, tokens, 256):
             if fullest(heads, lengths, shorter) > 1:
                 assert fullest(heads, lengths, shorter) > fullest(heads, lengths, tokens) or heads * splits(lengths, tokens) <= CUS + CUS // 32
+
+
+@pytest.fixture(scope="module")
+def form(tmp_path_factory):
+    run = _compiled(tmp_path_factory.mktemp("form"), FORMS)
+
+    def walk(H_q, H_kv, lengths, batched=None, forced=0):
+        """(form, tokens of a workgroup)"""
+        batched = len(lengths) > 1 if batched is None else batched
+        name, tokens = run(" ".join(map(str, [int(batched), H_q, H_kv, forced, len(lengths)] + list(lengths))))[0].split()
+        return name, int(tokens)
+    return walk
+
+
+# (query heads, cache heads, lengths, form): the faster one on the card, both timed
+@pytest.mark.parametrize("H_q,H_kv,lengths,want", [
+    (64, 4, [468] * 2, "at_once"), (64, 4, [117] * 8, "matrix"), (64, 4, [703] * 2, "at_once"), (128, 8, [423] * 2, "at_once"),
+    (96, 8, [353] * 3, "matrix"), (64, 2, [162] * 4, "matrix"), (16, 1, [1281, 1280, 1200, 1205], "at_once"),          # more than eight query heads
+    (32, 4, [468] * 4, "at_once"), (64, 8, [324] * 2, "at_once"), (32, 4, [703] * 4, "matrix"), (32, 4, [168] * 5 + [70] * 11, "matrix"),
+    (48, 8, [312] * 4, "matrix"),                                                                                     # five to eight
+    (32, 8, [468] * 4, "at_once"), (32, 8, [104] * 16, "matrix"), (32, 8, [440] * 9, "matrix"),                       # three or four
+    (32, 16, [648] * 2, "matrix"), (64, 32, [428] * 3, "matrix"),                                                     # two
+    (32, 32, [117] * 16, "at_once"), (32, 32, [234] * 8, "matrix"), (32, 32, [168] * 4 + [68] * 12, "matrix"),
+    (32, 32, [378, 300, 300, 300, 294], "at_once"), (64, 64, [68] * 13, "matrix"),                                    # one
+    (32, 32, [160] * 8, "matrix"), (32, 8, [319] * 4, "at_once"), (32, 32, [159] * 8, "at_once"),                     # 40960 pairs
+    (32, 4, [511] * 4, "at_once"), (32, 4, [512] * 4, "matrix")])                                                     # 65536 pairs
+def test_a_batch_takes_the_form_that_is_faster_for_it(form, H_q, H_kv, lengths, want):
+    assert form(H_q, H_kv, lengths)[0] == want
+
+
+@pytest.mark.parametrize("H_q,H_kv,S,want", [
+    (32, 32, 4095, "at_once"), (32, 4, 4095, "at_once"), (32, 4, 4096, "matrix"), (64, 4, 2047, "at_once"), (64, 4, 2048, "matrix"),
+    (32, 8, 2047, "at_once"), (32, 8, 2048, "matrix"), (32, 16, 2047, "at_once"), (32, 16, 2048, "matrix"), (32, 32, 9000, "matrix")])
+def test_the_form_for_one_sequence(form, H_q, H_kv, S, want):
+    name, tokens = form(H_q, H_kv, [S])
+    assert name == want and (want == "matrix" or tokens == (128 if S * H_q < 65536 else 256))
+
+
+def test_the_option_asks_for_a_form(form):
+    for tokens in (64, 128, 256, 512, 1024, 2048):
+        for lengths in ([7], [9000], [100] * 16):
+            assert form(32, 8, lengths, forced=tokens) == ("at_once" if tokens <= 256 else "matrix", tokens)
