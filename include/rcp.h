@@ -161,7 +161,8 @@ int rcp_version(void);
  *                  gives every compute unit the same number of workgroups.  With group-wise tables: rounded up to blocks
  *                  of sixteen rows; automatic = as many blocks as one workgroup per compute unit takes, at most eight
  *   "kv_tokens"    cached tokens per workgroup of rcp_kv4_attn_decode: 64, 128, 256 (all loads of a workgroup
- *                  issued at once), 512, 1024, 2048 (the matrix-core kernel for long contexts, batches and grouped heads)
+ *                  issued at once), 512, 1024, 2048 (the matrix-core kernel for long contexts, batches and grouped heads);
+ *                  automatic calls with one query head per cache head and some middle sizes take a third, streaming kernel
  *   "gemv_waves"   wavefronts per workgroup of the fused one-token GEMV (rcp_quant_w2a4_gemv): 4, 8
  *                  (8 needs K >= 2048 and "gemv_lanes" left automatic; otherwise 4 is used)
  *   "gemv_oneshot" one-token kernel that issues every weight load of a workgroup up front (one group of four rows

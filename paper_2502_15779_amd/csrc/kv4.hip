@@ -598,6 +598,189 @@ __global__ __launch_bounds__(KV_THREADS) void kv4_attn_kernel(const void* __rest
 }
 
 // ---------------------------------------------------------------------------------------
+// The streaming form for one query head per cache head where splits of 512 tokens give every compute unit one workgroup or a few
+// (kv_streams has its figures): a matrix product with one row of sixteen in use is a longer chain behind each load.  Workgroup = (split, head
+// [, sequence]).  The split is cut into chunks of 16 tokens; wavefront w takes chunks w, w + 4, ... and walks them on its own: no
+// workgroup barrier inside the loop, the loads of its next two chunks in flight while it computes one.  Each wavefront keeps a
+// reference m (uniform over the wavefront; the running maximum, raised lazily) and rescales its sums when a chunk raises
+// it:  acc <- acc * 2^(m_old - m_new);  p_t = 2^(score_t - m_new), scores in units of log 2.
+// At the end the four wavefronts merge in LDS with the same rule and (m, l, acc) of the split goes to the workspace for
+// kv4_combine_kernel.  The sums of a lane (eight tokens) are centred before they are added up over lanes, wavefronts and splits, as
+// the value codes of the matrix-core form are: left as they are, they grow with the tokens and cancel (24 drawn calls, error against 64
+// bits: 2.2e-7 on average without, 1.4e-7 with, 1.5e-7 in the matrix-core form; the time is the same).
+// ---------------------------------------------------------------------------------------
+constexpr float KV_LAZY = 40.0f;  // how far a score may exceed the reference before it is raised
+struct KvChunk {
+    u32x4 kw, vw;
+    uint32_t kp, vp;
+    bool valid;
+};
+
+template <int QDT, bool BATCHED, bool QROT>
+__global__ __launch_bounds__(KV_THREADS) void kv4_attn_stream_kernel(const void* __restrict__ q, int S, int S_max, int splits,
+                                                                     float softmax_scale, const u32x4* __restrict__ k_codes,
+                                                                     const uint32_t* __restrict__ k_params,
+                                                                     const u32x4* __restrict__ v_codes,
+                                                                     const uint32_t* __restrict__ v_params, int L,
+                                                                     float* __restrict__ part, KvBatch batch)
+{
+    __shared__ float red[4][KV_D];
+    __shared__ float wm[4], lrow[4][4], zrow[4][4];
+    int h = static_cast<int>(blockIdx.x) / splits;
+    const int split = static_cast<int>(blockIdx.x) - h * splits;
+    const int tid = threadIdx.x, lane = tid & 63, slot = lane >> 2, piece = tid & 3;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int t0 = split * L;
+    if constexpr (BATCHED) {
+        const int seq = blockIdx.z;
+        S = batch.v[seq];
+        if (t0 >= S) return;  // the whole workgroup: this sequence has fewer splits
+        h += seq * batch.H_q;
+    }
+    const int t_end = min(S, t0 + L);
+    const size_t head_base = static_cast<size_t>(h) * S_max;
+    // chunks of this wavefront that hold at least one cached token
+    const int span = t_end - t0 - 16 * wave;
+    const int nchunks = span > 0 ? (span + 63) >> 6 : 0;
+
+    auto load = [&](int c, KvChunk& r) {  // chunk c of this wavefront: tokens t0 + 16 (4 c + wave) ...; past the end: the last token, weight 0
+        const int t = t0 + 16 * (4 * c + wave) + slot;
+        r.valid = t < t_end;
+        const size_t at = head_base + (r.valid ? t : t_end - 1);
+        // read once per call: non-temporal loads, as in kv4_attn_kernel
+        r.kw = __builtin_nontemporal_load(k_codes + (at * 4 + piece));
+        r.kp = __builtin_nontemporal_load(k_params + at);
+        r.vw = __builtin_nontemporal_load(v_codes + (at * 4 + piece));
+        r.vp = __builtin_nontemporal_load(v_params + at);
+    };
+
+    Raw8<QDT> qraw[4];
+#pragma unroll
+    for (int d = 0; d < 4; ++d) qraw[d] = load8_raw<QDT>(q, static_cast<size_t>(h) * KV_D + 32 * piece + 8 * d);
+    KvChunk cA, cB;
+    load(0, cA);
+    load(1, cB);
+
+    float qr[32];
+    const float qsum = kv_query_registers<QDT>(qraw, QROT, piece, qr);
+    const float unit = kv_fp8_unit(), inv_unit = 1.0f / unit;
+    const float scale_by_unit = softmax_scale * 1.44269504088896340736f * inv_unit, qsum_unit = qsum * unit;
+
+    float acc[32];
+#pragma unroll
+    for (int r = 0; r < 32; ++r) acc[r] = 0.0f;
+    float lsum = 0.0f, zacc = 0.0f, wsum = 0.0f;
+    float m = -INFINITY;  // uniform over the wavefront
+    int chunk = 0;
+
+    auto step = [&](KvChunk& cur) {
+        float dot[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+        for (int d = 0; d < 4; ++d) {
+            uint32_t lo, hi;
+            nibble_bytes(cur.kw[d], lo, hi);
+            float fl[4], fh[4];
+            bytes_to_floats(lo, fl);
+            bytes_to_floats(hi, fh);
+#pragma unroll
+            for (int b = 0; b < 4; ++b) {
+                dot[d] = fmaf(qr[8 * d + b], fl[b], dot[d]);
+                dot[d] = fmaf(qr[8 * d + 4 + b], fh[b], dot[d]);
+            }
+        }
+        const float s = half_bits_to_float(static_cast<uint16_t>(cur.kp & 0xffffu)) * scale_by_unit;
+        const float z = static_cast<float>(static_cast<int>(cur.kp) >> 16);
+        float sc = quad_sum(s * (((dot[0] + dot[1]) + (dot[2] + dot[3])) - z * qsum_unit));
+        sc = cur.valid ? sc : -INFINITY;
+        // The reference m only has to keep the powers in range, so it is raised lazily: when some score
+        // of the chunk exceeds it by more than KV_LAZY (always on the first chunk, where m = -inf; every chunk
+        // that is stepped holds a cached token, so the new maximum is finite).  Weights then stay below
+        // 2^KV_LAZY and the sums of a split far inside the binary32 range.
+        if (__builtin_amdgcn_ballot_w64(sc > m + KV_LAZY) != 0) {  // uniform
+            const float m_new = fmaxf(m, wave_max(sc));
+            const float alpha = __builtin_amdgcn_exp2f(m - m_new);  // 0 on the first chunk
+#pragma unroll
+            for (int r = 0; r < 32; ++r) acc[r] *= alpha;
+            lsum *= alpha;
+            zacc *= alpha;
+            wsum *= alpha;
+            m = m_new;
+        }
+        const float p = __builtin_amdgcn_exp2f(sc - m);
+        const float w0 = p * half_bits_to_float(static_cast<uint16_t>(cur.vp & 0xffffu));
+        const float w = w0 * inv_unit;
+        lsum += p;
+        wsum += w0;
+        zacc = fmaf(w0, static_cast<float>((static_cast<int>(cur.vp) >> 16) - 8), zacc);
+#pragma unroll
+        for (int d = 0; d < 4; ++d) {
+            uint32_t lo, hi;
+            nibble_bytes(cur.vw[d], lo, hi);
+            float fl[4], fh[4];
+            bytes_to_floats(lo, fl);
+            bytes_to_floats(hi, fh);
+#pragma unroll
+            for (int b = 0; b < 4; ++b) {
+                acc[8 * d + b] = fmaf(w, fl[b], acc[8 * d + b]);
+                acc[8 * d + 4 + b] = fmaf(w, fh[b], acc[8 * d + 4 + b]);
+            }
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        load(chunk + 2, cur);  // refill with the chunk two steps ahead (past the end: a harmless repeat of the last token)
+        __builtin_amdgcn_sched_barrier(0);
+        ++chunk;
+    };
+    // steps counted up front and run in pairs: one loop body, one exit (four chunks in flight instead of
+    // two: 130 registers and no gain)
+    for (int i = 0; i < nchunks / 2; ++i) {
+        step(cA);
+        step(cB);
+    }
+    if (nchunks & 1) step(cA);
+
+    // ---- the 16 tokens of a wavefront's chunks are summed as in kv4_attn_kernel; the four wavefronts
+    // merge through LDS, each weighted by 2^(its m - the largest m) ----
+#pragma unroll
+    for (int r = 0; r < 32; ++r) acc[r] = row_tokens_sum(fmaf(-8.0f, wsum, acc[r]));
+    lsum = row_tokens_sum(lsum);
+    zacc = row_tokens_sum(zacc);
+    float f16v[16], f32v[8];
+#pragma unroll
+    for (int k = 0; k < 16; ++k) f16v[k] = fold16f(acc[2 * k], acc[2 * k + 1]);
+#pragma unroll
+    for (int k = 0; k < 8; ++k) f32v[k] = fold32f(f16v[2 * k], f16v[2 * k + 1]);
+    const int rw = (tid >> 4) & 3;
+    if ((tid & 12) == 0) {
+#pragma unroll
+        for (int k = 0; k < 8; ++k) red[wave][32 * piece + kv_elem_of_reg(4 * k + rw)] = f32v[k];
+        if (piece == 0) {
+            lrow[wave][rw] = lsum;
+            zrow[wave][rw] = zacc;
+        }
+    }
+    if (lane == 0) wm[wave] = m;
+    __syncthreads();
+    float* dst = part + (static_cast<size_t>(h) * splits + split) * KV_PART;
+    if (tid <= KV_D) {
+        const float M = fmaxf(fmaxf(wm[0], wm[1]), fmaxf(wm[2], wm[3]));  // wavefront 0 always has a token: finite
+        float total = 0.0f;
+#pragma unroll
+        for (int w = 0; w < 4; ++w) {
+            const float e = __builtin_amdgcn_exp2f(wm[w] - M);  // 0 for a wavefront without tokens
+            float v;
+            if (tid < KV_D) v = red[w][tid] - ((zrow[w][0] + zrow[w][1]) + (zrow[w][2] + zrow[w][3]));
+            else v = (lrow[w][0] + lrow[w][1]) + (lrow[w][2] + lrow[w][3]);
+            total = fmaf(e, v, total);
+        }
+        if (tid < KV_D) dst[tid] = total;
+        else {
+            dst[KV_D] = M;
+            dst[KV_D + 1] = total;
+        }
+    }
+}
+
+// ---------------------------------------------------------------------------------------
 // The matrix-core form for long contexts, batches and grouped query heads.  Workgroup = (split of L tokens, cache head
 // [, sixteen of its query heads] [, sequence]); all query heads that read the cache head are rows of one matrix
 // product, so the codes are fetched and unpacked once for all of them.  Wavefront w of the four walks the chunks
@@ -1185,10 +1368,6 @@ int launch_kv4_attn(const void* q, rcp_dtype q_dt, int B, int H_q, int H_kv, int
             S = lengths[b] > S ? lengths[b] : S;  // the longest sequence sizes the grid
         }
     }
-    // One query head a cache head had a third, streaming form up to 20480 x 32 pairs (streaming / matrix: 5000 tokens of 32
-    // heads 12.8 / 12.0, 12000 18.4 / 16.5, 9 sequences of 11368 in all 22.0 / 18.2, 16 of 1024 19.6 / 18.7).  It was ahead only where its 512
-    // tokens a split filled every unit once or twice: 6500 to 8200 tokens 12.5 / 12.8, 8 sequences of 1024 12.3 / 12.7, 4 of 2048 12.5 / 13.1;
-    // its error is 7.6e-7 to 1.2e-6 there, the matrix form's 3e-7.
     batch.H_q = H_q;
     batch.H_kv = H_kv;
     if (!batched) batch.v[0] = S;
@@ -1228,6 +1407,20 @@ int launch_kv4_attn(const void* q, rcp_dtype q_dt, int B, int H_q, int H_kv, int
         };
         if (compact) form(std::true_type{});
         else form(std::false_type{});
+    } else if (plan.form == KvForm::stream) {
+        const dim3 grid(static_cast<unsigned>(splits) * static_cast<unsigned>(H_kv), 1u, nseq);
+        auto launch = [&](auto kernel) {
+            enqueue(kernel, grid, KV_THREADS, 0, st, q, S, S_max, splits, softmax_scale, kc, kp, vc, vp, L, part, batch);
+        };
+        auto form = [&](auto dt) {
+            constexpr int QDT = decltype(dt)::value;
+            if (batched) launch(&kv4_attn_stream_kernel<QDT, true, false>);
+            else if (fused) launch(&kv4_attn_stream_kernel<QDT, false, true>);
+            else launch(&kv4_attn_stream_kernel<QDT, false, false>);
+        };
+        if (q_dt == RCP_F32) form(std::integral_constant<int, RCP_F32>{});
+        else if (q_dt == RCP_F16) form(std::integral_constant<int, RCP_F16>{});
+        else form(std::integral_constant<int, RCP_BF16>{});
     } else {
         const dim3 grid(static_cast<unsigned>(kv_at_once_groups(splits, rep, H_kv)), 1u, nseq);
         auto launch = [&](auto kernel) {
@@ -1256,7 +1449,7 @@ int launch_kv4_attn(const void* q, rcp_dtype q_dt, int B, int H_q, int H_kv, int
     int groups = (splits + 3) / 4;
     if (groups > KV_CT / KV_D) groups = KV_CT / KV_D;
     const unsigned cgrid = static_cast<unsigned>(H_q) * (batched ? B : 1);
-    auto combine = [&](auto kernel) { enqueue(kernel, cgrid, groups * KV_D, 0, st, part, splits, groups, out, L, matrix ? 1.0f : 1.44269504088896340736f, batch); };
+    auto combine = [&](auto kernel) { enqueue(kernel, cgrid, groups * KV_D, 0, st, part, splits, groups, out, L, plan.form == KvForm::at_once ? 1.44269504088896340736f : 1.0f, batch); };
     if (batched) {
         if (out_dt == RCP_F16) combine(&kv4_combine_kernel<true, true>);
         else combine(&kv4_combine_kernel<false, true>);

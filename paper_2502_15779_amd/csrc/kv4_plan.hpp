@@ -45,7 +45,34 @@ inline int kv_split_tokens(const int* lengths, int n, int heads, int cus)
     return best * KV_BLOCK;
 }
 
-enum class KvForm { at_once, matrix };
+constexpr int KV_STREAM_L = 512;  // tokens of a workgroup of the streaming form
+
+// Whether one query head a cache head and 131072 to 262144 pairs go to the streaming form instead of the matrix-core form on splits of
+// `tokens`.  Its grid has a slot for every split of the longest sequence, and all have to hold tokens (those without delay it: 16
+// sequences of up to 600 tokens, 5318 in all, 32 heads, 17.0 us instead of 14.2).  It is the faster one (us, streaming / matrix)
+//   with one workgroup a unit                     4 sequences of 2048 tokens, 16 heads, 9.8 / 10.5
+// and, where the matrix-core form has more than one,
+//   with one split a sequence, 192 tokens of it   16 of 293 tokens, 32 heads, 10.4 / 11.9; of 196, 64 heads, 13.0 / 13.4; of 147 12.0 / 11.9
+//   with two, up to two workgroups a unit         16 of 782, 16 heads, 12.1 / 12.6; 8 of 1024, 32 heads, 12.5 / 12.7
+//   with three or four, nearly full ones          4 of 2048, 32 heads, 12.6 / 13.3; of 1563 (a last split of 27 tokens) 12.3 / 12.0
+//   for a single sequence                         7500 tokens of 32 heads 12.4 / 12.8, 30625 of 8 13.5 / 13.8
+// Elsewhere the matrix-core form: one workgroup a unit of 768 tokens against one and a half of 512, 18750 tokens of 8 heads 12.8 / 12.1; batches of
+// longer sequences level, 4 of 8192, 8 heads, 13.1 / 12.9.  Both err by 1 to 3e-7 there.
+inline bool kv_streams(const int* lengths, int n, int heads, int longest, long long total, int cus, int tokens)
+{
+    const long long pairs = total * heads;
+    if (pairs < 131072 || pairs > 262144) return false;
+    const int splits = (longest + KV_STREAM_L - 1) / KV_STREAM_L;
+    const long long groups = kv_workgroups(lengths, n, heads, KV_STREAM_L);
+    if (groups != static_cast<long long>(splits) * n * heads) return false;
+    if (groups <= cus + cus / 32) return true;
+    if (kv_workgroups(lengths, n, heads, tokens) <= cus + cus / 32) return false;
+    if (splits == 1) return pairs >= 192 * groups;
+    if (groups > 2 * cus) return false;
+    return n == 1 || splits == 2 || (splits <= 4 && pairs * 8 >= groups * KV_STREAM_L * 7);
+}
+
+enum class KvForm { at_once, stream, matrix };
 struct KvPlan {
     KvForm form;
     int tokens;  // of a workgroup
@@ -57,7 +84,8 @@ inline long long kv_at_once_groups(int splits, int rep, int H_kv) { return 8LL *
 
 // forced: the "kv_tokens" option, 0 = automatic; more than KV_MAX_L asks for the matrix-core form.
 // The form that issues all loads at once for small calls, 128 tokens per workgroup and from 2048 x 32 (token, query head) pairs on
-// 256, else the matrix-core form on splits of the length that kv_split_tokens finds.  Where they meet (us, all at once / matrix):
+// 256, else the matrix-core form on splits of the length that kv_split_tokens finds, or the streaming form (kv_streams).  Where the first
+// two meet (us, all at once / matrix):
 //   one sequence   with two to four query heads a cache head at 65536 pairs (3000 tokens of 32 over 16 9.7 / 9.1, of 32 over 8 9.4 /
 //                  9.4; below, 929 of 64 over 16 8.4 / 8.6), with more or one at 131072 (3000 of 32 over 4 9.5 / 9.7, 4001 of 32 with
 //                  the query's rotation 10.4 / 10.5 and 5 % more of a decode step)
@@ -94,7 +122,9 @@ inline KvPlan kv_plan(const int* lengths, int n, bool batched, int H_q, int H_kv
     else if (rep == 1) matrix = kv_workgroups(lengths, n, heads, KV_BLOCK) <= cus;
     else matrix = rep <= 4 && longest <= KV_BLOCK;
     if (!matrix) return {KvForm::at_once, few};
-    return {KvForm::matrix, kv_split_tokens(lengths, n, heads, cus)};
+    const int tokens = kv_split_tokens(lengths, n, heads, cus);
+    if (rep == 1 && kv_streams(lengths, n, heads, longest, total, cus, tokens)) return {KvForm::stream, KV_STREAM_L};
+    return {KvForm::matrix, tokens};
 }
 
 }  // namespace rcp

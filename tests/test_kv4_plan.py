@@ -31,7 +31,7 @@ FORMS = r"""
 int main()
 {
     int batched, H_q, H_kv, forced, n, lengths[16];
-    const char* names[] = {"at_once", "matrix"};
+    const char* names[] = {"at_once", "stream", "matrix"};
     while (scanf("%d %d %d %d %d", &batched, &H_q, &H_kv, &forced, &n) == 5) {
         for (int b = 0; b < n; ++b)
             if (scanf("%d", lengths + b) != 1) return 1;
@@ -118,11 +118,41 @@ def test_a_batch_takes_the_form_that_is_faster_for_it(form, H_q, H_kv, lengths, 
 
 @pytest.mark.parametrize("H_q,H_kv,S,want", [
     (32, 32, 4095, "at_once"), (32, 4, 4095, "at_once"), (32, 4, 4096, "matrix"), (64, 4, 2047, "at_once"), (64, 4, 2048, "matrix"),
-    (32, 8, 2047, "at_once"), (32, 8, 2048, "matrix"), (32, 16, 2047, "at_once"), (32, 16, 2048, "matrix"), (32, 32, 9000, "matrix")])
+    (32, 8, 2047, "at_once"), (32, 8, 2048, "matrix"), (32, 16, 2047, "at_once"), (32, 16, 2048, "matrix"), (32, 32, 9000, "matrix"),
+    (32, 32, 4096, "stream"), (32, 32, 4097, "matrix"), (32, 32, 6144, "matrix"), (32, 32, 7500, "stream"),
+    (32, 32, 8192, "stream"), (32, 32, 8193, "matrix"), (8, 8, 30625, "stream"), (64, 64, 4096, "stream"), (32, 16, 7500, "matrix")])
 def test_the_form_for_one_sequence(form, H_q, H_kv, S, want):
     name, tokens = form(H_q, H_kv, [S])
-    assert name == want and (want == "matrix" or tokens == (128 if S * H_q < 65536 else 256))
+    assert name == want and (want == "matrix" or tokens == (512 if want == "stream" else 128 if S * H_q < 65536 else 256))
 
+
+@pytest.mark.parametrize("H,lengths,want", [
+    (16, [2048] * 4, "stream"), (8, [1024] * 16, "stream"), (16, [2048] * 3 + [2000], "matrix"),                  # one workgroup a unit
+    (32, [293] * 16, "stream"), (32, [430] * 8 + [300] * 8, "stream"), (64, [196] * 16, "stream"), (64, [180] * 16, "matrix"),   # one split a sequence
+    (32, [512] * 16, "stream"), (32, [513] + [505] * 15, "matrix"), (32, [600] + [300] * 15, "matrix"),
+    (16, [782] * 16, "stream"), (32, [1024] * 8, "stream"), (32, [1024] * 7 + [512], "matrix"),                   # two
+    (32, [2048] * 4, "stream"), (8, [1797] * 16, "stream"), (32, [1563] * 4, "matrix"),                           # four
+    (8, [4096] * 8, "matrix"), (16, [3438] * 4, "matrix"), (8, [18750], "matrix"), (32, [4000, 2120], "matrix")])
+def test_one_query_head_streams_where_that_is_faster(form, H, lengths, want):
+    assert form(H, H, lengths) == (want, 512 if want == "stream" else form(H, H, lengths)[1])
+
+
+def test_streaming_splits_leave_no_workgroup_without_tokens_and_fit_the_scratch(form):
+    rng = random.Random(3)
+    seen = 0
+    for _ in range(4000):
+        H, n = rng.choice([4, 8, 16, 32, 40, 64]), rng.randint(1, 16)
+        S = int(2 ** rng.uniform(17, 18) / H / n) + 1
+        lengths = [S] + [max(1, int(S * (1 - rng.choice([0, 0.02, 0.3]) * rng.random()))) for _ in range(n - 1)]
+        if rng.random() < 0.9 and len({-(-v // 512) for v in lengths}) > 1:
+            continue
+        name, tokens = form(H, H, lengths)
+        if name == "stream":
+            seen += 1
+            assert tokens == 512 and len({-(-v // 512) for v in lengths}) == 1 and 131072 <= H * sum(lengths) <= 262144
+        if seen == 60:
+            return
+    assert seen == 60
 
 def test_the_option_asks_for_a_form(form):
     for tokens in (64, 128, 256, 512, 1024, 2048):
