@@ -22,8 +22,11 @@ inline long long kv_workgroups(const int* lengths, int n, int heads, int tokens)
 // for the query, the merge of its wavefronts and the wait for its first tokens.  Measured over 20 calls (32 over 8, 64 over 8, 32
 // over 16 and 64 over 4 heads; one sequence of 5000 to 131072 tokens, ragged batches of 16000 to 65000) with 1 to 16 blocks a split:
 // with C blocks a split and k workgroups on the fullest unit a call takes 8.6 + 1.73 C us for k = 1, where every wait shows, and
-// 6.4 + k (2.05 + 1.22 C) beyond; that a few units have a second one goes unnoticed up to a thirty-second
-// of them (12483 tokens of 32 over 16 heads as 272 workgroups of 768 tokens 14.7 us, as 400 of 512 13.5).  The split of least cost against
+// 6.4 + k (2.05 + 1.22 C) beyond.  That a few units, a thirty-second at most, have a second one goes unnoticed with splits of 512 tokens
+// (260 workgroups: 12.5 us, 13.1 as 130 of 1024), and of 768 where all of those are the short end of a batch's last sequence, which come last in its
+// grid (an end of 35 tokens, 264 workgroups: 11.9, as 512 a split 12.5; of 565 tokens, 258: 13.6 and 12.2); not with others: a single
+// sequence of 2951 tokens of 66 heads 13.8 as 264 of 768 and 12.1 as 396 of 512, 4 of 19187 in all of 13 heads 14.5 as 260 of 1024 and
+// 13.2 of 512, 2 of 16482 of 32 over 4 13.4 as 260 of 256 and 12.0 of 512.  The split of least cost against
 // fixed ones of 256, 512 or 1024 tokens: 40000 tokens of 32 over 8 heads 20.1 -> 18.1 us, 16 sequences of
 // up to 6000 (44000 in all) 24.0 -> 17.8, of up to 4000 of 32 heads 40.1 -> 30.5; 65536 tokens 21.3 either way.
 inline int kv_split_tokens(const int* lengths, int n, int heads, int cus)
@@ -34,7 +37,9 @@ inline int kv_split_tokens(const int* lengths, int n, int heads, int cus)
     long long least = 0;
     for (int c = 1; c <= KV_MOST_BLOCKS; ++c) {
         const long long groups = kv_workgroups(lengths, n, heads, c * KV_BLOCK);
-        const long long k = groups <= cus + cus / 32 ? 1 : (groups + cus - 1) / cus;
+        const int end = (lengths[n - 1] - 1) % (c * KV_BLOCK) + 1;
+        const bool spare = c == 2 || (c == 3 && n > 1 && end <= KV_BLOCK && groups <= cus + heads);
+        const long long k = groups <= cus + (spare ? cus / 32 : 0) ? 1 : (groups + cus - 1) / cus;
         const long long cost = k == 1 ? 860 + 173 * c : 640 + k * (205 + 122 * c);
         if (c == 1 || cost < least) {
             least = cost;

@@ -88,6 +88,16 @@ def test_no_other_split_leaves_the_fullest_unit_less(plan):
                 assert fullest(heads, lengths, shorter) > fullest(heads, lengths, tokens) or heads * splits(lengths, tokens) <= CUS + CUS // 32
 
 
+@pytest.mark.parametrize("heads,lengths,want", [
+    (66, [2951], 512), (65, [2447], 512), (10, [19286], 512), (4, [8837, 7645], 512),
+    (33, [1188, 951, 814, 803], 768), (43, [1424, 940, 1333], 512), (4, [9997, 9939, 9300, 9583, 9873], 512),
+    (2, [24780] * 4, 512), (10, [12847], 512)])
+def test_a_few_units_with_a_second_workgroup(plan, heads, lengths, want):
+    """Just over one workgroup a unit: whole second ones are not free."""
+    assert any(CUS < heads * splits(lengths, t) <= CUS + CUS // 32 for t in (256, 512, 768, 1024))
+    assert plan([(heads, lengths)])[0][0] == want
+
+
 @pytest.fixture(scope="module")
 def form(tmp_path_factory):
     run = _compiled(tmp_path_factory.mktemp("form"), FORMS)
