@@ -8,6 +8,7 @@
 #include <stdint.h>
 
 #include <tuple>
+#include <type_traits>
 
 #include "rcp.h"
 
@@ -18,11 +19,13 @@ int fail(int code, const char* fmt, ...);
 int check_launch(const char* what);  // hipGetLastError() -> RCP_ERR_HIP / RCP_OK
 
 // kernel<<<grid, block, lds, st>>>(args...) without the pair of calls that carry the four of them to the kernel's host stub:
-// 3.55 instead of 3.74 us a launch (torch's HIP library, one host thread); its error is found by check_launch as before.
+// 3.55 instead of 3.74 us a launch (torch's HIP library, one host thread); its error is found by check_launch as before.  Arguments
+// are converted as there: a void* does not become a typed pointer.
 template <class... P, class... A>
 inline void enqueue(void (*kernel)(P...), dim3 grid, dim3 block, size_t lds, hipStream_t st, const A&... args)
 {
-    std::tuple<P...> values(static_cast<P>(args)...);
+    static_assert((std::is_convertible_v<const A&, P> && ...), "an argument does not convert to its parameter by itself");
+    std::tuple<P...> values(args...);
     std::apply(
         [&](auto&... value) {
             void* pointers[] = {const_cast<void*>(static_cast<const void*>(&value))...};
@@ -42,7 +45,7 @@ struct Options {
     int gemv_nt;         // non-temporal weight loads in the general one-token kernel: 1 = always, 2 = never
     int gemv_waves;      // wavefronts per workgroup of the fused one-token GEMV: 4 or 8
     int gemm_rows;       // output rows per workgroup of the matrix-core kernel: 16 or 64
-    int kv_tokens;       // cached tokens per workgroup of the KV4 attention kernel: 64, 128 or 256
+    int kv_tokens;       // cached tokens per workgroup of the KV4 attention: 64, 128, 256, and on the matrix cores 512, 1024, 2048
     int seq_blocks;      // workgroups of the GEMV sequence kernel
     int gemv_oneshot;    // one-token GEMV with all loads issued up front: 0 automatic, 1 whenever the shape fits, 2 never
 };
