@@ -88,6 +88,35 @@ def test_no_other_split_leaves_the_fullest_unit_less(plan):
                 assert fullest(heads, lengths, shorter) > fullest(heads, lengths, tokens) or heads * splits(lengths, tokens) <= CUS + CUS // 32
 
 
+def _microseconds(heads, lengths, blocks):
+    """The model in hundredths: a workgroup's share of the fullest unit; whether the units over one workgroup each count."""
+    tokens = 256 * blocks
+    groups, end = heads * splits(lengths, tokens), (lengths[-1] - 1) % tokens + 1
+    spare = 8 if blocks == 2 or (blocks == 3 and len(lengths) > 1 and end <= 256 and groups <= CUS + heads) else 0
+    if groups <= CUS + spare:
+        return 860 + 173 * blocks
+    return 640 + -(-groups // CUS) * (205 + 122 * blocks)
+
+
+def test_the_split_is_the_one_of_least_cost(plan):
+    """The shortest of those of least cost, none longer than the longest sequence needs, at most four blocks."""
+    rng = random.Random(5)
+    calls = [(rng.choice([1, 2, 4, 8, 10, 16, 24, 32, 65]), [int(2 ** rng.uniform(4, 15)) for _ in range(rng.choice([1, 1, 2, 5, 16]))]) for _ in range(1500)]
+    taken = set()
+    for (heads, lengths), (tokens, _) in zip(calls, plan(calls)):
+        blocks = range(1, min(4, -(-max(lengths) // 256)) + 1)
+        assert tokens == 256 * min(blocks, key=lambda c: (_microseconds(heads, lengths, c), c)), (heads, lengths)
+        taken.add(tokens)
+    assert taken == {256, 512, 768, 1024}
+
+
+@pytest.mark.parametrize("heads,lengths,want", [
+    (8, [40000], 768), (8, [65536], 1024), (16, [12483], 512), (8, [131072], 1024), (8, [4096], 256),
+    (32, [4096], 512), (1, [300], 256), (1, [256 * 256], 256), (1, [256 * 256 + 1], 512), (1, [264 * 512], 512), (1, [264 * 512 + 1], 768)])
+def test_split_lengths_of_some_calls(plan, heads, lengths, want):
+    assert plan([(heads, lengths)])[0][0] == want
+
+
 @pytest.mark.parametrize("heads,lengths,want", [
     (66, [2951], 512), (65, [2447], 512), (10, [19286], 512), (4, [8837, 7645], 512),
     (33, [1188, 951, 814, 803], 768), (43, [1424, 940, 1333], 512), (4, [9997, 9939, 9300, 9583, 9873], 512),
