@@ -598,14 +598,14 @@ __global__ __launch_bounds__(KV_THREADS) void kv4_attn_kernel(const void* __rest
 }
 
 // ---------------------------------------------------------------------------------------
-// The streaming form for one query head per cache head where splits of 512 tokens give every compute unit one workgroup or a few
-// (kv_streams has its figures): a matrix product with one row of sixteen in use is a longer chain behind each load.  Workgroup = (split, head
+// The streaming form for one query head per cache head where splits of 512 tokens, or of 1024, give every compute unit one workgroup or a few
+// (kv_stream_tokens has its figures): a matrix product with one row of sixteen in use is a longer chain behind each load.  Workgroup = (split, head
 // [, sequence]).  The split is cut into chunks of 16 tokens; wavefront w takes chunks w, w + 4, ... and walks them on its own: no
 // workgroup barrier inside the loop, the loads of its next two chunks in flight while it computes one.  Each wavefront keeps a
 // reference m (uniform over the wavefront; the running maximum, raised lazily) and rescales its sums when a chunk raises
 // it:  acc <- acc * 2^(m_old - m_new);  p_t = 2^(score_t - m_new), scores in units of log 2.
 // At the end the four wavefronts merge in LDS with the same rule and (m, l, acc) of the split goes to the workspace for
-// kv4_combine_kernel.  The sums of a lane (eight tokens) are centred before they are added up over lanes, wavefronts and splits, as
+// kv4_combine_kernel.  The sums of a lane (eight or sixteen tokens) are centred before they are added up over lanes, wavefronts and splits, as
 // the value codes of the matrix-core form are: left as they are, they grow with the tokens and cancel (24 drawn calls, error against 64
 // bits: 2.2e-7 on average without, 1.4e-7 with, 1.5e-7 in the matrix-core form; the time is the same).
 // ---------------------------------------------------------------------------------------

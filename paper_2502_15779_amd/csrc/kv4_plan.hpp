@@ -51,31 +51,39 @@ inline int kv_split_tokens(const int* lengths, int n, int heads, int cus)
     return best * KV_BLOCK;
 }
 
-constexpr int KV_STREAM_L = 512;  // tokens of a workgroup of the streaming form
+constexpr int KV_STREAM_L = 512;  // tokens of a workgroup of the streaming form, 1024 for large calls
 
-// Whether one query head a cache head and 131072 to 262144 pairs go to the streaming form instead of the matrix-core form on splits of
-// `tokens`.  Its grid has a slot for every split of the longest sequence, and all have to hold tokens (those without delay it: 16
-// sequences of up to 600 tokens, 5318 in all, 32 heads, 17.0 us instead of 14.2).  It is the faster one (us, streaming / matrix)
+// Whether one query head a cache head and 131072 to 655360 pairs go to the streaming form instead of the matrix-core form on splits of
+// `tokens`, and on how many tokens a workgroup (0: the matrix-core form).  Its grid has a slot for every split of the longest sequence, and
+// all have to hold tokens (those without delay it: 16 sequences of up to 600 tokens, 5318 in all, 32 heads, 17.0 us instead of 14.2).  It is
+// the faster one (us, streaming / matrix) up to 262144 pairs
 //   with one workgroup a unit                     4 sequences of 2048 tokens, 16 heads, 9.8 / 10.5
 // and, where the matrix-core form has more than one,
 //   with one split a sequence, 192 tokens of it   16 of 293 tokens, 32 heads, 10.4 / 11.9; of 196, 64 heads, 13.0 / 13.4; of 147 12.0 / 11.9
 //   with two, up to two workgroups a unit         16 of 782, 16 heads, 12.1 / 12.6; 8 of 1024, 32 heads, 12.5 / 12.7
+//   with three, 2 to 2.7 a unit, not full ones    7 of 1098, 32 heads, 13.4 / 14.2; but 3 of 1489, 64 heads, 14.9 / 14.2
 //   with three or four, nearly full ones          4 of 2048, 32 heads, 12.6 / 13.3; of 1563 (a last split of 27 tokens) 12.3 / 12.0
 //   for a single sequence                         7500 tokens of 32 heads 12.4 / 12.8, 30625 of 8 13.5 / 13.8
+// and beyond with one split of up to 1024 tokens a sequence, 1.6 to 4 workgroups a unit: 10 of 887, 48 heads, 16.3 / 17.3, 15 of 10371 in all, 32
+// heads, 15.1 / 16.4, 13 of 5661, 64 heads, 17.5 / 19.5 (85 drawn calls 0.97 of the matrix-core form; the worst 14 of 10766, 40 heads, 19.4 / 18.9); with
+// 1.5 workgroups a unit 8 of 7462, 48 heads, 16.9 / 15.9.
 // Elsewhere the matrix-core form: one workgroup a unit of 768 tokens against one and a half of 512, 18750 tokens of 8 heads 12.8 / 12.1; batches of
-// longer sequences level, 4 of 8192, 8 heads, 13.1 / 12.9.  Both err by 1 to 3e-7 there.
-inline bool kv_streams(const int* lengths, int n, int heads, int longest, long long total, int cus, int tokens)
+// longer sequences level, 4 of 8192, 8 heads, 13.1 / 12.9.  Both err by 1 to 4e-7 there.
+inline int kv_stream_tokens(const int* lengths, int n, int heads, int longest, long long total, int cus, int tokens)
 {
     const long long pairs = total * heads;
-    if (pairs < 131072 || pairs > 262144) return false;
+    if (pairs < 131072 || pairs >= 655360) return 0;
+    if (pairs > 262144) return longest <= 2 * KV_STREAM_L && 16 * n * heads >= 25 * cus && n * heads <= 4 * cus ? 2 * KV_STREAM_L : 0;
     const int splits = (longest + KV_STREAM_L - 1) / KV_STREAM_L;
-    const long long groups = kv_workgroups(lengths, n, heads, KV_STREAM_L);
-    if (groups != static_cast<long long>(splits) * n * heads) return false;
-    if (groups <= cus + cus / 32) return true;
-    if (kv_workgroups(lengths, n, heads, tokens) <= cus + cus / 32) return false;
-    if (splits == 1) return pairs >= 192 * groups;
-    if (groups > 2 * cus) return false;
-    return n == 1 || splits == 2 || (splits <= 4 && pairs * 8 >= groups * KV_STREAM_L * 7);
+    const long long groups = kv_workgroups(lengths, n, heads, KV_STREAM_L), slots = groups * KV_STREAM_L;
+    if (groups != static_cast<long long>(splits) * n * heads) return 0;
+    if (groups <= cus + cus / 32) return KV_STREAM_L;
+    if (kv_workgroups(lengths, n, heads, tokens) <= cus + cus / 32) return 0;
+    bool faster = false;
+    if (splits == 1) faster = pairs >= 192 * groups;
+    else if (groups <= 2 * cus) faster = n == 1 || splits == 2 || (splits <= 4 && 8 * pairs >= 7 * slots);
+    else if (splits == 3) faster = 10 * groups <= 27 * cus && 20 * pairs <= 17 * slots;
+    return faster ? KV_STREAM_L : 0;
 }
 
 enum class KvForm { at_once, stream, matrix };
@@ -90,7 +98,7 @@ inline long long kv_at_once_groups(int splits, int rep, int H_kv) { return 8LL *
 
 // forced: the "kv_tokens" option, 0 = automatic; more than KV_MAX_L asks for the matrix-core form.
 // The form that issues all loads at once for small calls, 128 tokens per workgroup and from 2048 x 32 (token, query head) pairs on
-// 256, else the matrix-core form on splits of the length that kv_split_tokens finds, or the streaming form (kv_streams).  Where the first
+// 256, else the matrix-core form on splits of the length that kv_split_tokens finds, or the streaming form (kv_stream_tokens).  Where the first
 // two meet (us, all at once / matrix):
 //   one sequence   with two to four query heads a cache head at 65536 pairs (3000 tokens of 32 over 16 9.7 / 9.1, of 32 over 8 9.4 /
 //                  9.4; below, 929 of 64 over 16 8.4 / 8.6), with more or one at 131072 (3000 of 32 over 4 9.5 / 9.7, 4001 of 32 with
@@ -130,7 +138,8 @@ inline KvPlan kv_plan(const int* lengths, int n, bool batched, int H_q, int H_kv
     else matrix = rep <= 4 && longest <= KV_BLOCK;
     if (!matrix) return {KvForm::at_once, few};
     const int tokens = kv_split_tokens(lengths, n, heads, cus);
-    if (rep == 1 && kv_streams(lengths, n, heads, longest, total, cus, tokens)) return {KvForm::stream, KV_STREAM_L};
+    const int stream = rep == 1 ? kv_stream_tokens(lengths, n, heads, longest, total, cus, tokens) : 0;
+    if (stream != 0) return {KvForm::stream, stream};
     return {KvForm::matrix, tokens};
 }
 

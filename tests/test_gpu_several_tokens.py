@@ -157,6 +157,7 @@ def _attention_of_heads(q64, lengths, host, scale, heads, B, H_kv):
     (32, [7500]), (32, [8192]), (16, [15361]),       # streaming: an odd number, all and one token of the last split
     (32, [430] * 8 + [257, 512, 300, 299, 64 * 6 + 1, 64 * 6 + 16, 64 * 6 + 17, 400]),   # its wavefronts with and without a last chunk
     (8, [1024] * 16), (32, [2048, 2047, 1985, 2033]), (64, [1797, 1900]),
+    (48, [887, 1024, 513, 961, 1, 16, 17, 960, 1009, 1000]), (32, [1098] * 7),       # on 1024 tokens, in three splits
     (5, [52500]),                    # an odd number of heads
     (8, [81900]), (8, [81920]),      # splits of the most tokens, the last one not full and full
     (16, [600, 4000, 1, 2900, 1500]),

@@ -170,10 +170,14 @@ def test_the_form_for_one_sequence(form, H_q, H_kv, S, want):
     (32, [293] * 16, "stream"), (32, [430] * 8 + [300] * 8, "stream"), (64, [196] * 16, "stream"), (64, [180] * 16, "matrix"),   # one split a sequence
     (32, [512] * 16, "stream"), (32, [513] + [505] * 15, "matrix"), (32, [600] + [300] * 15, "matrix"),
     (16, [782] * 16, "stream"), (32, [1024] * 8, "stream"), (32, [1024] * 7 + [512], "matrix"),                   # two
+    (32, [1098] * 7, "stream"), (16, [1101] * 13, "stream"), (64, [1489, 1300, 1224], "matrix"), (32, [1098] * 8, "matrix"),   # three
     (32, [2048] * 4, "stream"), (8, [1797] * 16, "stream"), (32, [1563] * 4, "matrix"),                           # four
+    (48, [887] * 10, "stream"), (32, [809] * 10 + [456] * 5, "stream"), (40, [827] * 10, "stream"), (48, [978] * 8, "matrix"),   # 1024 tokens
+    (48, [1025] + [887] * 9, "matrix"), (40, [940] * 13, "stream"), (64, [640] * 16, "matrix"), (96, [400] * 11, "matrix"),
     (8, [4096] * 8, "matrix"), (16, [3438] * 4, "matrix"), (8, [18750], "matrix"), (32, [4000, 2120], "matrix")])
 def test_one_query_head_streams_where_that_is_faster(form, H, lengths, want):
-    assert form(H, H, lengths) == (want, 512 if want == "stream" else form(H, H, lengths)[1])
+    tokens = 512 if H * sum(lengths) <= 262144 else 1024
+    assert form(H, H, lengths) == (want, tokens if want == "stream" else form(H, H, lengths)[1])
 
 
 def test_streaming_splits_leave_no_workgroup_without_tokens_and_fit_the_scratch(form):
@@ -181,14 +185,16 @@ def test_streaming_splits_leave_no_workgroup_without_tokens_and_fit_the_scratch(
     seen = 0
     for _ in range(4000):
         H, n = rng.choice([4, 8, 16, 32, 40, 64]), rng.randint(1, 16)
-        S = int(2 ** rng.uniform(17, 18) / H / n) + 1
+        S = int(2 ** rng.uniform(17, 19.4) / H / n) + 1
         lengths = [S] + [max(1, int(S * (1 - rng.choice([0, 0.02, 0.3]) * rng.random()))) for _ in range(n - 1)]
         if rng.random() < 0.9 and len({-(-v // 512) for v in lengths}) > 1:
             continue
         name, tokens = form(H, H, lengths)
         if name == "stream":
             seen += 1
-            assert tokens == 512 and len({-(-v // 512) for v in lengths}) == 1 and 131072 <= H * sum(lengths) <= 262144
+            pairs = H * sum(lengths)
+            assert tokens == (512 if pairs <= 262144 else 1024) and 131072 <= pairs < 655360
+            assert len({-(-v // tokens) for v in lengths}) == 1
         if seen == 60:
             return
     assert seen == 60
