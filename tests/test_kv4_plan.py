@@ -180,7 +180,7 @@ def test_one_query_head_streams_where_that_is_faster(form, H, lengths, want):
     assert form(H, H, lengths) == (want, tokens if want == "stream" else form(H, H, lengths)[1])
 
 
-def test_streaming_splits_leave_no_workgroup_without_tokens_and_fit_the_scratch(form):
+def test_streaming_splits_leave_no_workgroup_without_tokens(form):
     rng = random.Random(3)
     seen = 0
     for _ in range(4000):
